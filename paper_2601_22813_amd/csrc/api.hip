@@ -610,10 +610,10 @@ qii_status qii_linear_fwd_amax(const void *X, const void *W, qii_dtype dt, int64
         hipError_t e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 2, slot_words, s);
         if (e != hipSuccess) return hip_fail(e, "fill");
     }
-    // When the GEMM will take its main kernel (d_in a multiple of 256) the two quantizers also write
+    // When the GEMM will take its main kernel the two quantizers also write
     // their scale bytes straight into the GEMM workspace in that kernel's tiled layout: no re-tiling launch.
     uint8_t *gws = p + 2 * kSlot;
-    const bool tile = d_in % 256 == 0 && T * d_out > 0 && qii::rows_kernels_apply(sx, T, d_in) && qii::rows_kernels_apply(sw, d_out, d_in);
+    const bool tile = qii::gemm_reads_tiled_scales(T, d_out, d_in) && qii::rows_kernels_apply(sx, T, d_in) && qii::rows_kernels_apply(sw, d_out, d_in);
     uint8_t *x_tiled = tile ? gws : nullptr, *w_tiled = tile ? gws + (T + 255) / 256 * 256 * (d_in / 16) : nullptr;
     st = quantize_source(sx, T, d_in, mode, 0, 0, 0, amax_x, Xq, slots, nullptr, s, true, false, x_tiled);
     if (st != QII_OK) return st;

@@ -9,12 +9,12 @@
 // v_mfma_f32_32x32x16_f16; every product and the f32 accumulation are those of the
 // dequantized operands.  The two tensor scales are applied once in the epilogue.
 //
-// Three kernels share this scheme (launch_gemm picks one): gemm_kernel_v4, the main one
+// Three families of kernels share this scheme (choose_route picks one): gemm_kernel_v4, the main one
 // (K a multiple of 256, scale bytes re-tiled into a workspace, LDS-direct loads, explicit
-// software pipeline); gemm_kernel_v2 (K a multiple of 128, no workspace); gemm_kernel (any
-// K that is a multiple of 16, NVFP4's own rule; ragged everything).
+// software pipeline); gemm_kernel_v2 (K a multiple of 128, no workspace); the small-tile kernels
+// of gemm_small.hip (any K that is a multiple of 16, NVFP4's own rule, no workspace).
 //
-// Tiling: 256 x 256 block tile, K tile 128 or 256, 4 waves (2 x 2) each owning 128 x 128 =
+// Tiling of the two kernels here: 256 x 256 block tile, K tile 128 or 256, 4 waves (2 x 2) each owning 128 x 128 =
 // 4 x 4 MFMA tiles (256 accumulator registers).  One 32x32x16 MFMA consumes exactly
 // one scale group per lane: lanes 0..31 supply k 0..31 of a 64-element K slice and
 // lanes 32..63 supply k 32..63, four MFMAs walk the four dwords of a lane's 16 bytes
@@ -28,79 +28,6 @@ namespace qii {
 namespace {
 
 constexpr int BM = 256, BN = 256, BK = 128;
-constexpr int kPitch = 80;   // bytes per LDS row of codes: 64 data + 16 pad (bank spread)
-constexpr int kSPitch = 8;   // scale bytes per row per K tile
-constexpr int kStageBytes = BM * kPitch + BN * kPitch + BM * kSPitch + BN * kSPitch;
-
-struct StagePtr {
-    uint8_t *a, *b, *as, *bs;
-};
-__device__ __forceinline__ StagePtr stage_ptr(uint8_t *smem, int s)
-{
-    uint8_t *base = smem + s * kStageBytes;
-    return StagePtr{base, base + BM * kPitch, base + (BM + BN) * kPitch,
-                    base + (BM + BN) * kPitch + BM * kSPitch};
-}
-
-// raw global -> register staging of one K tile (per thread: 4+4 code vectors, 1+1 scale vectors)
-struct Staged {
-    uint4 a[4], b[4];
-    uint2 as, bs;
-};
-
-// scale bytes of one row for the K tile at k0 (8 groups); groups beyond K read as 0
-__device__ __forceinline__ uint2 load_scales(const uint8_t *scales, int64_t row, int64_t nrows,
-                                             int64_t K, int64_t k0)
-{
-    uint2 r = make_uint2(0u, 0u);
-    if (row >= nrows) return r;
-    const uint8_t *p = scales + row * (K / 16) + k0 / 16;
-    uint32_t w[2] = {0u, 0u};
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        if (k0 + 16 * i < K) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
-    return make_uint2(w[0], w[1]);
-}
-
-// A 16-byte piece of a code row holds two scale groups.  K is any multiple of 16 here: when it is
-// an odd multiple the last piece of a row is half valid and rows are only 8-byte aligned, so the
-// tile is moved in 8-byte halves; everything beyond M, N or K is zero (code 0, scale 0).
-__device__ __forceinline__ void load_tile(Staged &st, const uint8_t *a_codes, const uint8_t *a_scales,
-                                          const uint8_t *b_codes, const uint8_t *b_scales, int64_t M,
-                                          int64_t N, int64_t K, int64_t m0, int64_t n0, int64_t k0)
-{
-    const int t = threadIdx.x;
-    const int seg = t & 3, r = t >> 2;
-    const int64_t kbyte = k0 / 2 + 16 * seg;
-    const bool lo_ok = k0 + 32 * seg < K, hi_ok = k0 + 32 * seg + 16 < K;
-    const uint2 z = make_uint2(0u, 0u);
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int64_t ra = m0 + p * 64 + r, rb = n0 + p * 64 + r;
-        const uint8_t *pa = a_codes + ra * (K / 2) + kbyte, *pb = b_codes + rb * (K / 2) + kbyte;
-        const uint2 al = (lo_ok && ra < M) ? *reinterpret_cast<const uint2 *>(pa) : z;
-        const uint2 ah = (hi_ok && ra < M) ? *reinterpret_cast<const uint2 *>(pa + 8) : z;
-        const uint2 bl = (lo_ok && rb < N) ? *reinterpret_cast<const uint2 *>(pb) : z;
-        const uint2 bh = (hi_ok && rb < N) ? *reinterpret_cast<const uint2 *>(pb + 8) : z;
-        st.a[p] = make_uint4(al.x, al.y, ah.x, ah.y);
-        st.b[p] = make_uint4(bl.x, bl.y, bh.x, bh.y);
-    }
-    st.as = load_scales(a_scales, m0 + t, M, K, k0);
-    st.bs = load_scales(b_scales, n0 + t, N, K, k0);
-}
-
-__device__ __forceinline__ void store_tile(const Staged &st, const StagePtr &sp)
-{
-    const int t = threadIdx.x;
-    const int seg = t & 3, r = t >> 2;
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        *reinterpret_cast<uint4 *>(sp.a + (p * 64 + r) * kPitch + 16 * seg) = st.a[p];
-        *reinterpret_cast<uint4 *>(sp.b + (p * 64 + r) * kPitch + 16 * seg) = st.b[p];
-    }
-    *reinterpret_cast<uint2 *>(sp.as + t * kSPitch) = st.as;
-    *reinterpret_cast<uint2 *>(sp.bs + t * kSPitch) = st.bs;
-}
 
 // 8 FP4 codes (one dword) times one E4M3 scale -> 8 exact f16 values.
 // scale16x2 holds the scale byte shifted to f16 position in both halves: as f16 that is
@@ -124,107 +51,8 @@ __device__ __forceinline__ uint32_t scale_pair(uint32_t two_bytes, int which)
     return (b << 7) | (b << 23);
 }
 
-template <bool kBf16Out>
-__global__ __launch_bounds__(256, 1) void gemm_kernel(const uint8_t *__restrict__ a_codes,
-                                                      const uint8_t *__restrict__ a_scales,
-                                                      const float *__restrict__ a_ts,
-                                                      const uint8_t *__restrict__ b_codes,
-                                                      const uint8_t *__restrict__ b_scales,
-                                                      const float *__restrict__ b_ts, int64_t M,
-                                                      int64_t N, int64_t K, void *__restrict__ Cout,
-                                                      int64_t ldc, int tiles_n, uint32_t *amax_out)
-{
-    extern __shared__ __align__(16) uint8_t smem[];
-    const int tile = blockIdx.x;
-    const int64_t m0 = (int64_t)(tile / tiles_n) * BM, n0 = (int64_t)(tile % tiles_n) * BN;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int li = lane & 31, kb = lane >> 5;
-
-    floatx16 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int64_t ktiles = (K + BK - 1) / BK;
-    Staged st;
-    load_tile(st, a_codes, a_scales, b_codes, b_scales, M, N, K, m0, n0, 0);
-    store_tile(st, stage_ptr(smem, 0));
-    __syncthreads();
-
-    for (int64_t kt = 0; kt < ktiles; ++kt) {
-        const StagePtr sp = stage_ptr(smem, (int)(kt & 1));
-        if (kt + 1 < ktiles)
-            load_tile(st, a_codes, a_scales, b_codes, b_scales, M, N, K, m0, n0, (kt + 1) * BK);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            uint4 ra[4], rb[4];
-            uint32_t sa[4], sb[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int rowa = wm * 128 + t * 32 + li, rowb = wn * 128 + t * 32 + li;
-                ra[t] = *reinterpret_cast<const uint4 *>(sp.a + rowa * kPitch + 32 * j + 16 * kb);
-                rb[t] = *reinterpret_cast<const uint4 *>(sp.b + rowb * kPitch + 32 * j + 16 * kb);
-                sa[t] = *reinterpret_cast<const uint16_t *>(sp.as + rowa * kSPitch + 4 * j + 2 * kb);
-                sb[t] = *reinterpret_cast<const uint16_t *>(sp.bs + rowb * kSPitch + 4 * j + 2 * kb);
-            }
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                half8_t fa[4], fb[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const uint32_t wa = d == 0 ? ra[t].x : d == 1 ? ra[t].y : d == 2 ? ra[t].z : ra[t].w;
-                    const uint32_t wb = d == 0 ? rb[t].x : d == 1 ? rb[t].y : d == 2 ? rb[t].z : rb[t].w;
-                    fa[t] = dequant8(wa, scale_pair(sa[t], d >> 1));
-                    fb[t] = dequant8(wb, scale_pair(sb[t], d >> 1));
-                }
-#pragma unroll
-                for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj)
-                        acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[ti], fb[tj], acc[ti][tj], 0, 0, 0);
-            }
-        }
-        if (kt + 1 < ktiles) {
-            store_tile(st, stage_ptr(smem, (int)((kt + 1) & 1)));
-            __syncthreads();
-        }
-    }
-
-    // epilogue: C = acc * (x32_A * x32_B).  acc[r] of a 32x32 tile is row
-    // 8*(r/4) + 4*(lane/32) + r%4, column lane%32.
-    const float ts = (*a_ts) * (*b_ts);
-    float cmax = 0.0f;   // max |C| as stored, over this lane's entries inside the matrix
-#pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 4; ++tj) {
-            const int64_t col = n0 + wn * 128 + tj * 32 + li;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t row = m0 + wm * 128 + ti * 32 + 8 * (r >> 2) + 4 * kb + (r & 3);
-                if (row < M && col < N) {
-                    const float v = acc[ti][tj][r] * ts;
-                    if (kBf16Out) {
-                        const uint32_t bits = f32_to_bf16_bits(v);
-                        reinterpret_cast<uint16_t *>(Cout)[row * ldc + col] = (uint16_t)bits;
-                        cmax = fmaxf(cmax, fabsf(u2f(bits << 16)));
-                    } else {
-                        reinterpret_cast<float *>(Cout)[row * ldc + col] = v;
-                        cmax = fmaxf(cmax, fabsf(v));
-                    }
-                }
-            }
-        }
-    emit_tile_max(cmax, amax_out);
-}
-
-
 // ------------------------------------------------------------------------------------------
-// Main kernel (K a multiple of 128).  Differences from gemm_kernel above:
+// Kernel without a workspace (K a multiple of 128).
 //  * global -> LDS with global_load_lds (no staging registers, no VALU, no ds_write): each
 //    lane fetches one 16-byte piece of a code row (or one dword of scale bytes) and the wave's
 //    64 pieces land contiguously in LDS.  The piece a lane fetches is chosen so that the LDS
@@ -478,33 +306,6 @@ __device__ __forceinline__ void frag_read_wait(RawFrag4 &f)
                    "+v"(f.sb[0]), "+v"(f.sb[1]), "+v"(f.sb[2]), "+v"(f.sb[3]));
 }
 
-// The two scale bytes of a lane's 32 elements of K, as two f16 numbers in one register: byte b in
-// f16 position (b << 7) is e4m3 * 2^-8, subnormals included.  v_perm_b32 spreads the bytes to the
-// two halves, one shift moves them to f16 position.
-__device__ __forceinline__ uint32_t scale_halves(uint32_t two_bytes)
-{
-    return __builtin_amdgcn_perm(0u, two_bytes, 0x0C010C00u) << 7;
-}
-
-// half of one fragment (4 of its 8 values): two conversions and two packed multiplies by the f16
-// scale in the low (kHi = 0) or high half of `scales`, taken for both lanes of the packed multiply
-// through the instruction's operand selectors
-template <int H, int kHi>
-__device__ __forceinline__ void dequant_half(half8_t &dst, uint32_t codes, uint32_t scales)
-{
-    const half2_t c0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 256.0f, 2 * H);
-    const half2_t c1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 256.0f, 2 * H + 1);
-    half2_t h0, h1;
-    if (kHi) {
-        asm("v_pk_mul_f16 %0, %1, %2 op_sel:[0,1] op_sel_hi:[1,1]" : "=v"(h0) : "v"(c0), "v"(scales));
-        asm("v_pk_mul_f16 %0, %1, %2 op_sel:[0,1] op_sel_hi:[1,1]" : "=v"(h1) : "v"(c1), "v"(scales));
-    } else {
-        asm("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[1,0]" : "=v"(h0) : "v"(c0), "v"(scales));
-        asm("v_pk_mul_f16 %0, %1, %2 op_sel_hi:[1,0]" : "=v"(h1) : "v"(c1), "v"(scales));
-    }
-    dst[4 * H] = h0[0]; dst[4 * H + 1] = h0[1]; dst[4 * H + 2] = h1[0]; dst[4 * H + 3] = h1[1];
-}
-
 struct Frags {
     half8_t a[4], b[4];
 };
@@ -541,21 +342,14 @@ __device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu,
 #undef QII_MMA
 }
 
-// Launch position -> origin of the output tile.  XCD-aware order: consecutive block ids land on
-// different XCDs (8 of them, each with its own L2), so every XCD gets a contiguous run of tiles;
-// within the run, tiles are walked in groups of 4 tile rows, column by column, so that the ~32
-// tiles an XCD works on at once share 4 A panels and 8 B panels (about 3.5 MiB at K = 2048)
-// instead of 1 + 32.
+// Launch position -> origin of the output tile (about 32 tiles an XCD works on at once share 4 A panels and
+// 8 B panels, 3.5 MiB at K = 2048, instead of 1 + 32).
 __device__ __forceinline__ void tile_origin(int pos, int tiles_m, int tiles_n, int64_t &m0, int64_t &n0)
 {
-    int tile = pos;
-    const int ntiles = tiles_m * tiles_n;
-    if ((ntiles & 7) == 0) tile = (tile & 7) * (ntiles >> 3) + (tile >> 3);
-    constexpr int kGroupM = 4;
-    const int width = kGroupM * tiles_n, first_m = (tile / width) * kGroupM;
-    const int gm = tiles_m - first_m < kGroupM ? tiles_m - first_m : kGroupM;
-    m0 = (int64_t)(first_m + (tile % width) % gm) * BM;
-    n0 = (int64_t)((tile % width) / gm) * BN;
+    int tm, tn;
+    tile_coords(pos, tiles_m, tiles_n, tm, tn);
+    m0 = (int64_t)tm * BM;
+    n0 = (int64_t)tn * BN;
 }
 
 // kStream = false: one block per output tile (launch position blockIdx.x).
@@ -775,22 +569,22 @@ struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
     int grid;   // blocks that share them
+    double us;  // modelled time of the main kernel (and the second one), without the re-tiling launch
 };
 
 static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
 {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), ktiles = K / BK4;
-    StreamPlan plan{(int)tiles, 0, 0};
-    if (K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8) return plan;
     const int64_t rounds = tiles / 256, rem = tiles % 256;
-    if (rem == 0) return plan;
+    const double full_us = (double)rounds * (5.8 * (double)ktiles + 5.0);
+    const double kt_us = 4.6 + (rem > 176 ? 1.2 * (double)(rem - 176) / 80.0 : 0.0);
+    const double plain_us = full_us + (rem ? kt_us * (double)ktiles + 5.0 : 0.0);
+    StreamPlan plan{(int)tiles, 0, 0, plain_us};
+    if (K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8 || rem == 0) return plan;
     const int64_t units = rem * ktiles;
     int64_t grid = units / 4 < 256 ? units / 4 : 256;
     if (grid >= 8) grid &= ~(int64_t)7;
     if (grid <= rem) return plan;
-    const double full_us = (double)rounds * (5.8 * (double)ktiles + 5.0);
-    const double kt_us = 4.6 + (rem > 176 ? 1.2 * (double)(rem - 176) / 80.0 : 0.0);
-    const double plain_us = full_us + kt_us * (double)ktiles + 5.0;
     const int64_t per = (units + grid - 1) / grid;
     const bool one_segment = ktiles % per == 0 && units % grid == 0;
     const double shared_us = full_us + 5.8 * (double)per + (one_segment ? 26.0 : 38.0) + 0.05 * (double)(grid + rem);
@@ -798,6 +592,7 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
     plan.full = (int)(rounds * 256);
     plan.rem = (int)rem;
     plan.grid = (int)grid;
+    plan.us = shared_us;
     return plan;
 }
 
@@ -851,9 +646,9 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
                                      float *partial, hipStream_t s)
 {
     const int64_t M = A.rows, N = B.rows, K = A.cols;
-    hipError_t e = allow_dynamic_lds(gemm_kernel_v4<kBf16Out, false>, kSmem4);
+    hipError_t e = allow_dynamic_lds<gemm_kernel_v4<kBf16Out, false>>(kSmem4);
     if (e != hipSuccess) return e;
-    e = allow_dynamic_lds(gemm_kernel_v4<kBf16Out, true>, kSmem4);
+    e = allow_dynamic_lds<gemm_kernel_v4<kBf16Out, true>>(kSmem4);
     if (e != hipSuccess) return e;
     if (plan.full > 0)
         hipLaunchKernelGGL((gemm_kernel_v4<kBf16Out, false>), dim3((unsigned)plan.full), dim3(256), kSmem4, s, A.codes, a_tiled,
@@ -870,6 +665,54 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
     return hipGetLastError();
 }
 
+// Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to
+// event timings of every kernel over M x N = 64 x 64 .. 16384 x 2048 and K = 256 .. 16384 (bf16 results;
+// kt = K / 256, b = blocks / 256 compute units), for instance:
+//                         64 x 64   128 x 128 KG 2   128 x 128 (4, 4)   256 x 256 (with re-tiling)
+//    512 x  512 x   512       5.4              8.9              11.6     21.5
+//   1024 x 1024 x  4096      17.6             36.3              28.7     53.0 (shared last round)
+//   2048 x 2048 x  2048      24.5             22.8              21.6     47.6
+//   2048 x 2048 x 16384     150.4            135.0             110.8    135.8 (shared)
+//   4096 x 2048 x  2048      42.7             35.0              39.4     47.7
+//   4096 x 4096 x  4096     150.8            123.5             127.8    102.7
+// 64 x 64 tiles: up to three blocks run on a unit and their time adds up from one block per unit on.
+// 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is.
+// 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
+// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan;
+// 3 us of launch and first loads, 4.5 of re-tiling where the scale bytes are not tiled yet.
+enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide };
+
+static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool retile)
+{
+    auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
+    const bool any = K % BK4 != 0;
+    const double kt = (double)((K + BK4 - 1) / BK4), n64 = count(64), n128 = count(128), n256 = count(256);
+    const double b64 = n64 > 256.0 ? n64 / 256.0 : 1.0, b = n128 > 256.0 ? n128 / 256.0 : 1.0;
+    const double us64 = 3.3 + 0.85 * b64 + (0.15 + 0.54 * b64) * kt * (any ? 1.3 : 1.0);
+    const double pairs = (double)(int64_t)(b / 2.0), last = b - 2.0 * pairs;
+    const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.4 + 0.55 * last : 2.6 + 0.53 * last);
+    const double us128 = 4.0 + 1.7 * b + slope * kt * (any ? 1.25 : 1.0);
+    const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
+    const double us_wide = rounds * (8.3 + (1.15 + 0.45 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.17 : 1.0));
+    const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full;
+    const double us_v2 = 8.0 + (full + (rem > 0.0 ? 1.0 : 0.0)) * 5.0 + (7.0 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.7 : 0.0)) * kt;
+    Route best = kRoute64;
+    double us = us64;
+    auto offer = [&](Route r, double t) {
+        if (t < us) { us = t; best = r; }
+    };
+    offer(kRoute128, us128);
+    offer(kRoute128Wide, us_wide);
+    if (main_ok) offer(kRouteMain, stream_plan(M, N, K).us + 3.0 + (retile ? 4.5 : 0.0));
+    else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
+    return best;
+}
+
+bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
+{
+    return K % BK4 == 0 && M > 0 && N > 0 && choose_route(M, N, K, true, false) == kRouteMain;
+}
+
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
                        float *amax_c, void *ws, size_t ws_bytes, hipStream_t s, int pretiled)
 {
@@ -882,21 +725,23 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     }
     if (M == 0 || N == 0) return hipSuccess;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
     const size_t need = K % BK4 == 0 ? scales_workspace_bytes(M, N, K) : 0;
     // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
-    const bool a_ok = (pretiled & 4) || (reinterpret_cast<uintptr_t>(A.scales) & 15) == 0;
-    const bool b_ok = (pretiled & 8) || (reinterpret_cast<uintptr_t>(B.scales) & 15) == 0;
-    if (K % BK4 == 0 && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok) {
-        uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
-        uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
+    const bool a_ok = (pretiled & 5) || (reinterpret_cast<uintptr_t>(A.scales) & 15) == 0;
+    const bool b_ok = (pretiled & 10) || (reinterpret_cast<uintptr_t>(B.scales) & 15) == 0;
+    const bool main_ok = K % BK4 == 0 && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
+    const bool retile = !(pretiled & 5) || !(pretiled & 10);
+    Route route = choose_route(M, N, K, main_ok, retile);
+    uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
+    uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
+    if (route == kRouteMain) {
         const uint8_t *a_tiled = (pretiled & 1) ? A.scales : a_ws;   // (bits 2, 3: a_ws / b_ws are already filled)
         const uint8_t *b_tiled = (pretiled & 2) ? B.scales : b_ws;
         // the tiles of an incomplete last round are shared between blocks when the caller's workspace
         // has room for their partial tiles (behind the scales, 256-byte aligned)
         StreamPlan plan = stream_plan(M, N, K);
         const size_t poff = (need + 255) / 256 * 256;
-        if (plan.rem && ws_bytes < poff + (size_t)(plan.grid + plan.rem) * BM * BN * 4) plan = StreamPlan{(int)(tiles_m * tiles_n), 0, 0};
+        if (plan.rem && ws_bytes < poff + (size_t)(plan.grid + plan.rem) * BM * BN * 4) plan = StreamPlan{(int)(tiles_m * tiles_n), 0, 0, 0.0};
         float *partial = plan.rem ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(ws) + poff) : nullptr;
         // (an operand whose scales arrive tiled takes no part: zero rows)
         const int64_t ma = (pretiled & 5) ? 0 : M, nb_rows = (pretiled & 10) ? 0 : N;
@@ -907,37 +752,21 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
         return c_is_bf16 ? launch_main_kernel<true>(A, a_tiled, B, b_tiled, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, plan, partial, s)
                          : launch_main_kernel<false>(A, a_tiled, B, b_tiled, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, plan, partial, s);
     }
-    if (pretiled) return hipErrorInvalidValue;   // only the main kernel reads tiled scales
-    if ((K % 128) == 0) {
-        hipError_t e;
-        if (c_is_bf16) {
-            e = allow_dynamic_lds(gemm_kernel_v2<true>, kSmem2);
-            if (e != hipSuccess) return e;
+    if (route == kRouteNoWorkspace && !pretiled) {
+        const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
+        const hipError_t e = c_is_bf16 ? allow_dynamic_lds<gemm_kernel_v2<true>>(kSmem2) : allow_dynamic_lds<gemm_kernel_v2<false>>(kSmem2);
+        if (e != hipSuccess) return e;
+        if (c_is_bf16)
             hipLaunchKernelGGL(gemm_kernel_v2<true>, grid, block, kSmem2, s, A.codes, A.scales, A.tensor_scale,
                                B.codes, B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n, amax_out);
-        } else {
-            e = allow_dynamic_lds(gemm_kernel_v2<false>, kSmem2);
-            if (e != hipSuccess) return e;
+        else
             hipLaunchKernelGGL(gemm_kernel_v2<false>, grid, block, kSmem2, s, A.codes, A.scales, A.tensor_scale,
                                B.codes, B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n, amax_out);
-        }
         return hipGetLastError();
     }
-    // any K that is a multiple of 16: the ragged kernel (8-byte pieces, predicated tails)
-    constexpr int smem = 2 * kStageBytes;
-    hipError_t e;
-    if (c_is_bf16) {
-        e = allow_dynamic_lds(gemm_kernel<true>, smem);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(gemm_kernel<true>, grid, block, smem, s, A.codes, A.scales, A.tensor_scale, B.codes,
-                           B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_n, amax_out);
-    } else {
-        e = allow_dynamic_lds(gemm_kernel<false>, smem);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(gemm_kernel<false>, grid, block, smem, s, A.codes, A.scales, A.tensor_scale, B.codes,
-                           B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_n, amax_out);
-    }
-    return hipGetLastError();
+    // an operand that is tiled only (bits 0, 1) is read tiled, any other row-major
+    const SmallTile tile = route == kRoute64 ? kTile64 : route == kRoute128Wide ? kTile128Wide : kTile128;
+    return launch_gemm_small(A, (pretiled & 1) != 0, B, (pretiled & 2) != 0, C, c_is_bf16, ldc, amax_out, tile, s);
 }
 
 }  // namespace qii

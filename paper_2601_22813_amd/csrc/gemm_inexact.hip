@@ -382,12 +382,12 @@ static hipError_t launch_inexact(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C
     const dim3 grid((unsigned)(tiles_m * tiles_n)), block(512);
     hipError_t e;
     if (c_is_bf16) {
-        e = allow_dynamic_lds(gemm_inexact_kernel<kFmt, true>, kSmemI);
+        e = allow_dynamic_lds<gemm_inexact_kernel<kFmt, true>>(kSmemI);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((gemm_inexact_kernel<kFmt, true>), grid, block, kSmemI, s, a_img, A.tensor_scale, b_img,
                            B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n);
     } else {
-        e = allow_dynamic_lds(gemm_inexact_kernel<kFmt, false>, kSmemI);
+        e = allow_dynamic_lds<gemm_inexact_kernel<kFmt, false>>(kSmemI);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((gemm_inexact_kernel<kFmt, false>), grid, block, kSmemI, s, a_img, A.tensor_scale, b_img,
                            B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n);

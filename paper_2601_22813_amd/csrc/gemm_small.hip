@@ -1,0 +1,491 @@
+// Small-tile kernels of the block-scaled NVFP4 GEMM (same scheme as gemm.hip: raw codes and scale
+// bytes in LDS, fragments dequantized to exact f16 products in registers, f16 matrix instruction):
+// for products whose 256 x 256 tiles leave most compute units idle, and for any K that is a multiple
+// of 16 (NVFP4's own rule).
+//
+// A wave dequantizes MT + NT fragments per MT * NT matrix instructions (2 conversions + 2 packed products
+// each per matrix instruction at 4 x 4, the main kernel's tile; 3 + 3 at 2 x 4, 4 + 4 at 2 x 2, 8 + 8 at
+// 1 x 1, against 32 cycles of the matrix pipe), so a wave's tile must stay as large as its registers
+// allow even where the block's tile is small.  The waves of a block therefore share K, not M and N: the
+// four 64-wide slices of a 256-wide K tile go to KG groups of waves, and the groups' accumulators are added
+// through LDS at the end, in a fixed order.
+//   128 x 128 block tile: 2 waves of 64 x 128 (MT, NT = 2, 4) per group, 2 groups (4 waves, two blocks
+//                         per compute unit) or 4 groups (8 waves, when there is one block per unit);
+//   64 x 64 block tile:   one wave of 64 x 64 (2, 2) per group, 4 groups.
+//
+// Operands are staged through registers (global -> VGPR -> LDS): a tile is small enough for that (at
+// most 36 registers), the next tile's loads then stay in flight for a whole tile's time, and a ragged K
+// needs no padding of the operands: codes and scales beyond K are staged as zeros.  The scale bytes are
+// read row-major or in the tiled layout, whichever the operand has: no re-tiling launch, no workspace.
+#include "gemm_common.h"
+#include "qii_device.h"
+#include "qii_internal.h"
+
+namespace qii {
+namespace {
+
+constexpr int BK = 256;
+
+// where an operand's scale bytes are: 16 bytes per row and K tile at s + row_term(row) + kt * kt_stride
+struct ScaleView {
+    const uint8_t *s;
+    int64_t row_pitch;    // row-major: bytes per row; tiled: bytes per 256 rows
+    int64_t kt_stride;    // row-major: 16; tiled: 4096
+    int tiled;
+};
+
+struct SmallArgs {
+    const uint8_t *a_codes, *b_codes;
+    ScaleView as, bs;
+    const float *a_ts, *b_ts;
+    int64_t M, N, K;
+    void *C;
+    int64_t ldc;
+    int tiles_m, tiles_n;
+    uint32_t *amax_out;
+};
+
+__device__ __forceinline__ const uint8_t *scale_row(const ScaleView &v, int64_t row)
+{
+    return v.tiled ? v.s + (row >> 8) * v.row_pitch + (row & 255) * 16 : v.s + row * v.row_pitch;
+}
+
+// Block of WM * KG waves: tile BM x BN, wave tile 32 MT x 32 NT (the waves of a group sit below one another)
+template <int MT_, int NT_, int WM_, int KG_>
+struct Geo {
+    static constexpr int MT = MT_, NT = NT_, WM = WM_, KG = KG_;
+    static constexpr int BM = 32 * MT * WM, BN = 32 * NT, kThreads = 64 * WM * KG;
+    static constexpr int kRowsPerPass = kThreads / 8;         // 8 pieces of 16 bytes per code row
+    static constexpr int kPassA = BM / kRowsPerPass, kPassB = BN / kRowsPerPass;
+    static constexpr int kSlices = 4 / KG;                    // of a K tile per group
+    static constexpr int kStage = (BM + BN) * (128 + 16);     // LDS bytes of one K tile
+    static constexpr int kUnits = MT * NT;                    // 32 x 32 accumulator tiles of a wave
+    // LDS: two stages; the reduction's first round (half of every wave's accumulators)
+    static constexpr int kReduce = WM * KG * (kUnits / 2) * 4096;
+    static constexpr int kLds = 2 * kStage > kReduce ? 2 * kStage : kReduce;
+};
+
+// One thread's share of a K tile on its way to LDS: 16-byte pieces of code rows and, for threads below
+// the row count, one row's 16 scale bytes
+template <class G>
+struct Staged {
+    uint4 a[G::kPassA], b[G::kPassB], s;
+};
+
+// Rows are 8-byte (codes) and byte (scales) aligned when K is an odd multiple of 16; then a K tile may
+// also end at K, half way through a 16-byte piece: what lies beyond is staged as zeros.
+template <bool kAnyK>
+__device__ __forceinline__ uint4 load_codes16(const uint8_t *p)
+{
+    if (!kAnyK) return *reinterpret_cast<const uint4 *>(p);
+    const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 8);
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+__device__ __forceinline__ uint4 load_codes16_tail(const uint8_t *p, int64_t left)   // left: elements up to K
+{
+    uint2 lo = make_uint2(0u, 0u), hi = make_uint2(0u, 0u);
+    if (left > 0) lo = *reinterpret_cast<const uint2 *>(p);
+    if (left > 16) hi = *reinterpret_cast<const uint2 *>(p + 8);
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+template <bool kAnyK>
+__device__ __forceinline__ uint4 load_scales16(const uint8_t *p)
+{
+    if (kAnyK) {
+        uint4 v;
+        __builtin_memcpy(&v, p, 16);
+        return v;
+    }
+    const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 8);   // (8-byte aligned)
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+
+__device__ __forceinline__ uint4 load_scales16_tail(const uint8_t *p, int64_t left)
+{
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (16 * i < left) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// this thread's source addresses (K tile 0), rows beyond the matrix replaced by its last row (their
+// results land in accumulator rows or columns that are never stored)
+template <class G>
+struct Sources {
+    const uint8_t *a[G::kPassA], *b[G::kPassB], *s;
+    int64_t kt_stride;
+};
+
+template <class G, bool kAnyK>
+__device__ __forceinline__ void load_tile(Staged<G> &st, const Sources<G> &src, int kt, int64_t K)
+{
+    const int64_t k0 = (int64_t)kt * BK;
+    const bool scales = (int)threadIdx.x < G::BM + G::BN;
+    if (kAnyK && k0 + BK > K) {   // uniform: the last, partial tile
+        const int64_t left = K - k0 - 32 * (threadIdx.x & 7);
+#pragma unroll
+        for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16_tail(src.a[p] + k0 / 2, left);
+#pragma unroll
+        for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16_tail(src.b[p] + k0 / 2, left);
+        if (scales) st.s = load_scales16_tail(src.s + kt * src.kt_stride, K - k0);
+        return;
+    }
+#pragma unroll
+    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<kAnyK>(src.a[p] + k0 / 2);
+#pragma unroll
+    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<kAnyK>(src.b[p] + k0 / 2);
+    if (scales) st.s = load_scales16<kAnyK>(src.s + kt * src.kt_stride);
+}
+
+// LDS stage: A codes, B codes (128 bytes per row; row r keeps its 16-byte piece s in slot s ^ (r & 7), so
+// that the 128-bit reads of 8 consecutive rows hit different banks), then the rows' 16 scale bytes
+template <class G>
+__device__ __forceinline__ void store_tile(const Staged<G> &st, uint8_t *stage)
+{
+    const int t = threadIdx.x, slot = ((t & 7) ^ ((t >> 3) & 7)) * 16;   // (rows of a thread differ by multiples of 8)
+    uint8_t *dst = stage + (t >> 3) * 128 + slot;
+#pragma unroll
+    for (int p = 0; p < G::kPassA; ++p) *reinterpret_cast<uint4 *>(dst + p * G::kRowsPerPass * 128) = st.a[p];
+#pragma unroll
+    for (int p = 0; p < G::kPassB; ++p) *reinterpret_cast<uint4 *>(dst + (G::BM + p * G::kRowsPerPass) * 128) = st.b[p];
+    if (t < G::BM + G::BN) *reinterpret_cast<uint4 *>(stage + (G::BM + G::BN) * 128 + t * 16) = st.s;
+}
+
+// raw fragments of one 64-wide K slice: 32 codes and two scale bytes per lane and 32-row block
+template <class G>
+struct RawFrags {
+    u32x4 a[G::MT], b[G::NT];
+    uint32_t sa[G::MT], sb[G::NT];
+};
+
+template <class G>
+__device__ __forceinline__ void read_slice(RawFrags<G> &f, const uint8_t *stage, int j, int wm, int li, int kb)
+{
+    const int slot = ((2 * j + kb) ^ (li & 7)) * 16, sc = 4 * j + 2 * kb;
+    const uint8_t *codes = stage, *scales = stage + (G::BM + G::BN) * 128;
+#pragma unroll
+    for (int t = 0; t < G::MT; ++t) {
+        const int row = (wm * G::MT + t) * 32 + li;
+        f.a[t] = *reinterpret_cast<const u32x4 *>(codes + row * 128 + slot);
+        f.sa[t] = *reinterpret_cast<const uint16_t *>(scales + row * 16 + sc);
+    }
+#pragma unroll
+    for (int t = 0; t < G::NT; ++t) {
+        const int row = G::BM + t * 32 + li;
+        f.b[t] = *reinterpret_cast<const u32x4 *>(codes + row * 128 + slot);
+        f.sb[t] = *reinterpret_cast<const uint16_t *>(scales + row * 16 + sc);
+    }
+}
+
+// Dword D of a fragment's codes -> 8 exact f16 values.  The products are written in plain C++ (they compile
+// to one packed multiply with operand selectors each), not as the inline assembly of dequant_half: here a
+// matrix instruction may follow at once, and only the compiler knows how far it must stay behind.
+template <int D>
+__device__ __forceinline__ half8_t dequant_dword(const u32x4 &codes, uint32_t scales)
+{
+    const half2_t both = __builtin_bit_cast(half2_t, scales), s = {both[D >> 1], both[D >> 1]};
+    const half2_t h0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes[D], 256.0f, 0) * s;
+    const half2_t h1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes[D], 256.0f, 1) * s;
+    const half2_t h2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes[D], 256.0f, 2) * s;
+    const half2_t h3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes[D], 256.0f, 3) * s;
+    half8_t r;
+    r[0] = h0[0]; r[1] = h0[1]; r[2] = h1[0]; r[3] = h1[1];
+    r[4] = h2[0]; r[5] = h2[1]; r[6] = h3[0]; r[7] = h3[1];
+    return r;
+}
+
+template <class G, int D>
+__device__ __forceinline__ void mma_dword(floatx16 (&acc)[G::kUnits], const RawFrags<G> &f)
+{
+    half8_t fa[G::MT], fb[G::NT];
+#pragma unroll
+    for (int t = 0; t < G::MT; ++t) fa[t] = dequant_dword<D>(f.a[t], f.sa[t]);
+#pragma unroll
+    for (int t = 0; t < G::NT; ++t) fb[t] = dequant_dword<D>(f.b[t], f.sb[t]);
+#pragma unroll
+    for (int j = 0; j < G::NT; ++j)
+#pragma unroll
+        for (int i = 0; i < G::MT; ++i)
+            acc[j * G::MT + i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i], fb[j], acc[j * G::MT + i], 0, 0, 0);
+}
+
+// first and second half of the 64-wide K slice held in f
+template <class G>
+__device__ __forceinline__ void mma_first(floatx16 (&acc)[G::kUnits], RawFrags<G> &f)
+{
+#pragma unroll
+    for (int t = 0; t < G::MT; ++t) f.sa[t] = scale_halves(f.sa[t]);
+#pragma unroll
+    for (int t = 0; t < G::NT; ++t) f.sb[t] = scale_halves(f.sb[t]);
+    mma_dword<G, 0>(acc, f);
+    mma_dword<G, 1>(acc, f);
+}
+
+template <class G>
+__device__ __forceinline__ void mma_second(floatx16 (&acc)[G::kUnits], const RawFrags<G> &f)
+{
+    mma_dword<G, 2>(acc, f);
+    mma_dword<G, 3>(acc, f);
+}
+
+// ---- explicit pipeline of the one-wave-per-SIMD form (4 x 4 tiles) -----------------------------
+// While a step's 16 matrix instructions run on the fragments in cu, the next step's fragments (dword D of
+// f) are dequantized into nx, half a fragment after each matrix instruction; the scheduling barriers keep
+// that order.  A fragment is complete several matrix instructions before the first one that reads it.
+template <class G>
+struct Frags {
+    half8_t a[G::MT], b[G::NT];
+};
+
+template <class G, int D>
+__device__ __forceinline__ void dequant_chunk(Frags<G> &nx, RawFrags<G> &f, int i)
+{
+    const int t = (i >> 1) & 3;
+    if (i < 8) {
+        if (D == 0 && (i & 1) == 0) f.sa[t] = scale_halves(f.sa[t]);
+        if ((i & 1) == 0) dequant_half<0, (D >> 1)>(nx.a[t], f.a[t][D], f.sa[t]);
+        else dequant_half<1, (D >> 1)>(nx.a[t], f.a[t][D], f.sa[t]);
+    } else {
+        if (D == 0 && (i & 1) == 0) f.sb[t] = scale_halves(f.sb[t]);
+        if ((i & 1) == 0) dequant_half<0, (D >> 1)>(nx.b[t], f.b[t][D], f.sb[t]);
+        else dequant_half<1, (D >> 1)>(nx.b[t], f.b[t][D], f.sb[t]);
+    }
+}
+
+// side(i): further work of the caller after matrix instruction i (memory operations, spread out)
+template <class G, int D, class Side>
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[G::kUnits], const Frags<G> &cu, Frags<G> &nx, RawFrags<G> &f, Side &&side)
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = i >> 2, col = i & 3;
+        acc[col * G::MT + row] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.a[row], cu.b[col], acc[col * G::MT + row], 0, 0, 0);
+        side(i);
+        dequant_chunk<G, D>(nx, f, i);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// One round of the reduction over the K groups: groups kg and kg ^ D exchange halves of their N accumulator
+// tiles through LDS; the group with bit D clear keeps and completes the first half, the other the second.
+template <class G, int N, int D>
+__device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&out)[N / 2], uint8_t *smem, int wave, int kg, int lane)
+{
+    const bool hi = (kg & D) != 0;   // wave-uniform
+    float4 *own = reinterpret_cast<float4 *>(smem) + wave * (N / 2) * 256 + lane;
+    const float4 *other = reinterpret_cast<const float4 *>(smem) + (wave ^ (D * G::WM)) * (N / 2) * 256 + lane;
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const floatx16 &give = hi ? u[k] : u[N / 2 + k];
+            own[(k * 4 + r) * 64] = make_float4(give[4 * r], give[4 * r + 1], give[4 * r + 2], give[4 * r + 3]);
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < N / 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float4 v = other[(k * 4 + r) * 64];
+            const floatx16 &keep = hi ? u[N / 2 + k] : u[k];
+            out[k][4 * r] = keep[4 * r] + v.x;
+            out[k][4 * r + 1] = keep[4 * r + 1] + v.y;
+            out[k][4 * r + 2] = keep[4 * r + 2] + v.z;
+            out[k][4 * r + 3] = keep[4 * r + 3] + v.w;
+        }
+    __syncthreads();   // the area is written again by the next round or the epilogue
+}
+
+template <bool kBf16Out, class G, bool kAnyK>
+__global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_kernel(SmallArgs g)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave % G::WM, kg = wave / G::WM;
+    const int li = lane & 31, kb = lane >> 5;
+    int tm, tn;
+    tile_coords((int)blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * G::BM, n0 = (int64_t)tn * G::BN;
+
+    Sources<G> src;
+    {
+        const int64_t pitch = g.K / 2, off = 16 * (t & 7);
+#pragma unroll
+        for (int p = 0; p < G::kPassA; ++p) {
+            const int64_t r = m0 + p * G::kRowsPerPass + (t >> 3);
+            src.a[p] = g.a_codes + (r < g.M ? r : g.M - 1) * pitch + off;
+        }
+#pragma unroll
+        for (int p = 0; p < G::kPassB; ++p) {
+            const int64_t r = n0 + p * G::kRowsPerPass + (t >> 3);
+            src.b[p] = g.b_codes + (r < g.N ? r : g.N - 1) * pitch + off;
+        }
+        const bool of_a = t < G::BM;   // (threads beyond BM + BN load no scales)
+        const int64_t ra = m0 + t, rb = n0 + t - G::BM;
+        src.s = of_a ? scale_row(g.as, ra < g.M ? ra : g.M - 1) : scale_row(g.bs, rb < g.N ? rb : g.N - 1);
+        src.kt_stride = of_a ? g.as.kt_stride : g.bs.kt_stride;
+    }
+
+    floatx16 acc[G::kUnits];   // tile (i, j) of the wave at j MT + i
+#pragma unroll
+    for (int u = 0; u < G::kUnits; ++u)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][r] = 0.0f;
+
+    // While tile kt is multiplied, tile kt + 1 goes from registers to the other LDS stage, tile kt + 2 takes
+    // its place in the registers, and the barrier sits in the middle of the wave's last slice, whose
+    // fragments are in registers by then: all reads of this tile's stage are done, and the first slice of
+    // the next tile is read while the rest is multiplied.
+    const int ktiles = (int)((g.K + BK - 1) / BK);
+    Staged<G> st;
+    load_tile<G, kAnyK>(st, src, 0, g.K);
+    store_tile<G>(st, smem);
+    if (ktiles > 1) load_tile<G, kAnyK>(st, src, 1, g.K);
+    __syncthreads();
+    const int j0 = kg * G::kSlices;
+    RawFrags<G> f0, f1;
+    read_slice<G>(f0, smem, j0, wm, li, kb);
+    if constexpr (G::MT == 4) {
+        Frags<G> x, y;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dequant_chunk<G, 0>(x, f0, i);
+        // one tile: fc holds its raw slice, x its first fragments; fn takes the next tile's slice
+        auto one_tile = [&](int kt, RawFrags<G> &fc, RawFrags<G> &fn) {
+            uint8_t *nxt = smem + ((kt + 1) & 1) * G::kStage;
+            const bool whole = !kAnyK || (int64_t)(kt + 3) * BK <= g.K;   // tile kt + 2 is not the partial one (uniform)
+            const int64_t k2 = (int64_t)(kt + 2) * BK;
+            const bool more = kt + 2 < ktiles;
+            uint8_t *dst = nxt + (t >> 3) * 128 + ((t & 7) ^ ((t >> 3) & 7)) * 16;
+            auto no_side = [](int) {};
+            auto move = [&](int i) {   // piece i of tile kt + 1 to LDS, its register takes tile kt + 2's piece
+                if (i < G::kPassA) {
+                    *reinterpret_cast<uint4 *>(dst + i * G::kRowsPerPass * 128) = st.a[i];
+                    if (more && whole) st.a[i] = load_codes16<kAnyK>(src.a[i] + k2 / 2);
+                } else if (i < G::kPassA + G::kPassB) {
+                    const int p = i - G::kPassA;
+                    *reinterpret_cast<uint4 *>(dst + (G::BM + p * G::kRowsPerPass) * 128) = st.b[p];
+                    if (more && whole) st.b[p] = load_codes16<kAnyK>(src.b[p] + k2 / 2);
+                } else if (i == G::kPassA + G::kPassB) {   // (256 threads, 256 rows)
+                    *reinterpret_cast<uint4 *>(nxt + (G::BM + G::BN) * 128 + t * 16) = st.s;
+                    if (more && whole) st.s = load_scales16<kAnyK>(src.s + (kt + 2) * src.kt_stride);
+                }
+            };
+            const int slot = ((2 * j0 + kb) ^ (li & 7)) * 16, sc = 4 * j0 + 2 * kb;
+            const uint8_t *codes = nxt + li * 128 + slot, *scales = nxt + (G::BM + G::BN) * 128 + li * 16 + sc;
+            auto fetch = [&](int i) {   // (after the last tile: a stale stage, never multiplied)
+                if (i < 4) {
+                    fn.a[i] = *reinterpret_cast<const u32x4 *>(codes + i * 32 * 128);
+                    fn.sa[i] = *reinterpret_cast<const uint16_t *>(scales + i * 32 * 16);
+                } else if (i < 8) {
+                    fn.b[i - 4] = *reinterpret_cast<const u32x4 *>(codes + (G::BM + (i - 4) * 32) * 128);
+                    fn.sb[i - 4] = *reinterpret_cast<const uint16_t *>(scales + (G::BM + (i - 4) * 32) * 16);
+                }
+            };
+            mma_step<G, 1>(acc, x, y, fc, move);
+            if (kAnyK && more && !whole) load_tile<G, kAnyK>(st, src, kt + 2, g.K);
+            __syncthreads();
+            mma_step<G, 2>(acc, y, x, fc, fetch);
+            mma_step<G, 3>(acc, x, y, fc, no_side);
+            mma_step<G, 0>(acc, y, x, fn, no_side);
+        };
+        // (an odd tile first: a way out in the middle of the loop makes the compiler spill the accumulators)
+        int kt = 0;
+        if (ktiles & 1) {
+            one_tile(0, f0, f1);
+            f0 = f1;
+            kt = 1;
+        }
+        for (; kt < ktiles; kt += 2) {
+            one_tile(kt, f0, f1);
+            one_tile(kt + 1, f1, f0);
+        }
+    } else
+    for (int kt = 0; kt < ktiles; ++kt) {
+        uint8_t *cur = smem + (kt & 1) * G::kStage, *nxt = smem + ((kt + 1) & 1) * G::kStage;
+        if (kt + 1 < ktiles) {
+            store_tile<G>(st, nxt);
+            if (kt + 2 < ktiles) load_tile<G, kAnyK>(st, src, kt + 2, g.K);
+        }
+        if (G::kSlices == 2) {
+            // (one set of raw fragments: the other block on the compute unit covers their latency)
+            mma_first<G>(acc, f0);
+            mma_second<G>(acc, f0);
+            read_slice<G>(f0, cur, j0 + 1, wm, li, kb);
+            mma_first<G>(acc, f0);
+            __syncthreads();
+            mma_second<G>(acc, f0);
+            if (kt + 1 < ktiles) read_slice<G>(f0, nxt, j0, wm, li, kb);
+        } else {
+            mma_first<G>(acc, f0);
+            __syncthreads();
+            if (kt + 1 < ktiles) read_slice<G>(f1, nxt, j0, wm, li, kb);
+            mma_second<G>(acc, f0);
+            f0 = f1;
+        }
+    }
+    __syncthreads();   // the reduction overlays the stages
+
+    const float ts = (*g.a_ts) * (*g.b_ts);
+    if (G::KG == 2) {   // groups finish columns 32 NT / 2 kg and on
+        floatx16 h[G::kUnits / 2];
+        reduce_round<G, G::kUnits, 1>(acc, h, smem, wave, kg, lane);
+        floatx16 c[G::MT][G::NT / 2];
+#pragma unroll
+        for (int i = 0; i < G::MT; ++i)
+#pragma unroll
+            for (int j = 0; j < G::NT / 2; ++j) c[i][j] = h[j * G::MT + i];
+        store_tile_through_lds<kBf16Out, true, G::MT, G::NT / 2>(c, smem, ts, g.C, g.ldc, g.M, g.N, m0 + wm * 32 * G::MT,
+                                                                n0 + kg * 16 * G::NT, wave, 0, 0, lane, li, kb, g.amax_out);
+    } else {
+        floatx16 h[G::kUnits / 2], q[G::kUnits / 4];
+        reduce_round<G, G::kUnits, 2>(acc, h, smem, wave, kg, lane);
+        reduce_round<G, G::kUnits / 2, 1>(h, q, smem, wave, kg, lane);
+        constexpr int kRows = G::kUnits / 4 >= G::MT ? G::MT : 1;   // a whole column of tiles, or one tile
+        floatx16 c[kRows][1];
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) c[i][0] = q[i];
+        const int row = kRows == G::MT ? 0 : (kg & 1) * 32, col = kRows == G::MT ? kg * 32 : (kg >> 1) * 32;
+        store_tile_through_lds<kBf16Out, true, kRows, 1>(c, smem, ts, g.C, g.ldc, g.M, g.N, m0 + wm * 32 * G::MT + row, n0 + col, wave, 0, 0,
+                                                         lane, li, kb, g.amax_out);
+    }
+}
+
+template <bool kBf16Out, class G>
+hipError_t launch(SmallArgs g, hipStream_t s)
+{
+    g.tiles_m = (int)((g.M + G::BM - 1) / G::BM);
+    g.tiles_n = (int)((g.N + G::BN - 1) / G::BN);
+    const auto kern = g.K % BK != 0 ? gemm_small_kernel<kBf16Out, G, true> : gemm_small_kernel<kBf16Out, G, false>;
+    const hipError_t e = g.K % BK != 0 ? allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, true>>(G::kLds)
+                                       : allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, false>>(G::kLds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(G::kThreads), G::kLds, s, g);
+    return hipGetLastError();
+}
+
+ScaleView view(const qii_nvfp4 &t, bool tiled)
+{
+    return tiled ? ScaleView{t.scales, t.cols * 16, 4096, 1} : ScaleView{t.scales, t.cols / 16, 16, 0};
+}
+
+}  // namespace
+
+hipError_t launch_gemm_small(const qii_nvfp4 &A, bool a_tiled, const qii_nvfp4 &B, bool b_tiled, void *C, int c_is_bf16, int64_t ldc,
+                             uint32_t *amax_out, SmallTile tile, hipStream_t s)
+{
+    SmallArgs g;
+    g.a_codes = A.codes; g.b_codes = B.codes;
+    g.as = view(A, a_tiled); g.bs = view(B, b_tiled);
+    g.a_ts = A.tensor_scale; g.b_ts = B.tensor_scale;
+    g.M = A.rows; g.N = B.rows; g.K = A.cols;
+    g.C = C; g.ldc = ldc; g.amax_out = amax_out;
+    g.tiles_m = g.tiles_n = 0;   // (launch fills them in)
+    if (tile == kTile64) return c_is_bf16 ? launch<true, Geo<2, 2, 1, 4>>(g, s) : launch<false, Geo<2, 2, 1, 4>>(g, s);
+    if (tile == kTile128Wide) return c_is_bf16 ? launch<true, Geo<4, 4, 1, 4>>(g, s) : launch<false, Geo<4, 4, 1, 4>>(g, s);
+    return c_is_bf16 ? launch<true, Geo<2, 4, 2, 2>>(g, s) : launch<false, Geo<2, 4, 2, 2>>(g, s);
+}
+
+}  // namespace qii

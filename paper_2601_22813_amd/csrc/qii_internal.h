@@ -100,6 +100,15 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
                        float *amax_c, void *ws, size_t ws_bytes, hipStream_t s, int pretiled = 0);
 
+// whether launch_gemm, given a workspace and tiled scale bytes, would run the main kernel: only then is
+// it worth a quantizer's while to write the tiled copy
+bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K);
+// the same product by the small-tile kernels (gemm_small.hip): any K; each operand's scale bytes row-major
+// or, K a multiple of 256, tiled
+enum SmallTile { kTile64, kTile128, kTile128Wide };
+hipError_t launch_gemm_small(const qii_nvfp4 &A, bool a_tiled, const qii_nvfp4 &B, bool b_tiled, void *C, int c_is_bf16, int64_t ldc,
+                             uint32_t *amax_out, SmallTile tile, hipStream_t s);
+
 // host-only test aids for the shared last round of the main GEMM kernel (gemm_sharing_map.h):
 // plan = {positions run one block per tile, shared tiles, sharing blocks}; the segments of a
 // hardware block id as {block number, shared tile, first K tile, K tiles, slot} (returns their

@@ -1,0 +1,70 @@
+"""The GEMM's small-tile kernels (64 x 64 and 128 x 128 blocks, K split between groups of waves) at the sizes where
+they can go wrong, and the kernels that larger products take, against the oracle.  Tolerance: as in test_gpu_gemm_linear.py, 1e-5 of the sum of |products| (f32
+accumulation of exact products, at most K = 8192 terms, plus the additions of the K groups) and half a unit in the
+last place of a bf16 result.  Operands hold every FP4 code and every E4M3 scale byte the library writes (0 .. 126)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_22813_amd import binding as qii
+
+from gpu_util import nv_to_dev, ws
+
+pytestmark = pytest.mark.gpu
+
+
+def operand(oracle, rng, rows, K):
+    return oracle.NVFP4(rng.integers(0, 256, (rows, K // 2)).astype(np.uint8), rng.integers(0, 127, (rows, K // 16)).astype(np.uint8),
+                        np.array([0.0625], np.float32))
+
+
+def check_product(oracle, M, N, K, use_ws):
+    rng = np.random.default_rng(M + 3 * N + 7 * K)
+    qa, qb = operand(oracle, rng, M, K), operand(oracle, rng, N, K)
+    # every corner and edge of the matrix and of its 64- and 128-wide tiles, and random entries
+    rows = sorted({r for b in range(0, M + 64, 64) for r in (b - 1, b, b + 31, b + 32) if 0 <= r < M})
+    cols = sorted({c for b in range(0, N + 64, 64) for c in (b - 1, b, b + 31, b + 32) if 0 <= c < N})
+    ms = np.concatenate([rng.choice(rows, 3000), rng.integers(0, M, 3000), [0, 0, M - 1, M - 1]])
+    ns = np.concatenate([rng.choice(cols, 3000), rng.integers(0, N, 3000), [0, N - 1, 0, N - 1]])
+    ref, absum = oracle.gemm_sampled(qa, qb, ms, ns)
+    A, B = nv_to_dev(qa), nv_to_dev(qb)
+    for dtype, ldc in ((torch.float32, N + 4), (torch.bfloat16, N), (torch.bfloat16, N + 3)):
+        print(f"gemm {M}x{N}x{K} {dtype} ldc {ldc}", flush=True)
+        C = torch.full((M, ldc), float("nan"), dtype=dtype, device="cuda")
+        amax = torch.full((1,), float("nan"), device="cuda")
+        w = ws(qii.qii_gemm_workspace_bytes(M, N, K)) if use_ws else None
+        if w is not None:
+            w.fill_(0x7F)   # a stale workspace must not leak in
+        qii.qii_gemm_nvfp4_amax(A, B, C[:, :N], amax, w)
+        torch.cuda.synchronize()
+        got = C[:, :N].float()
+        assert torch.isfinite(got).all()
+        assert ldc == N or torch.isnan(C[:, N:]).all(), "columns beyond N were written"
+        assert amax.item() == got.abs().max().item()
+        err = np.abs(got.cpu().numpy().astype(np.float64)[ms, ns] - ref)
+        tol = 1e-5 * absum + (2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else 0.0) + 1e-30
+        worst = int(np.argmax(err - tol))
+        assert np.all(err <= tol), f"worst at ({ms[worst]}, {ns[worst]}): error {err[worst]}, tolerance {tol[worst]}"
+
+
+@pytest.mark.parametrize("M,N,K", [
+    # 64 x 64 tiles: one element; one row of tiles; one past a tile; K shorter than, equal to and one group beyond a
+    # K tile; an odd multiple of 16 (rows 8-byte aligned, the last 16-byte piece half valid); three whole K tiles
+    (1, 1, 16), (63, 65, 256), (64, 64, 272), (65, 130, 240), (129, 127, 528), (200, 72, 768), (7, 300, 1040),
+    # 128 x 128 tiles, two K groups: ragged edges with one, two and three K tiles, K ragged and whole
+    (2040, 1990, 256), (2047, 1921, 512), (2040, 1990, 528),
+    # 128 x 128 tiles, four waves of 4 x 4: odd and even numbers of K tiles, K ragged and whole
+    (2000, 1930, 2064), (2000, 1921, 2304), (1930, 2040, 2560), (2041, 1928, 2320),
+])
+def test_small_tile_kernels_match_the_oracle(oracle, M, N, K):
+    check_product(oracle, M, N, K, use_ws=True)
+
+
+@pytest.mark.parametrize("M,N,K,use_ws", [
+    (8190, 4090, 1152, True),    # K a multiple of 128: the kernel without a workspace
+    (8190, 4090, 2048, False),   # no workspace given: the same kernel
+    (4090, 4080, 2048, True),    # the main kernel, ragged edges
+    (4200, 4200, 8192, True),    # 289 tiles: a full round, then 33 tiles shared between blocks
+])
+def test_large_products_match_the_oracle(oracle, M, N, K, use_ws):
+    check_product(oracle, M, N, K, use_ws)
