@@ -1,6 +1,6 @@
 // Pieces shared by the GEMM kernels of libqii: vector types, the in-register dequantization of a
-// fragment, the epilogue that stages a wave's accumulator tile through LDS and stores full rows (optionally emitting max |C|), and the
-// host helper that raises a kernel's dynamic LDS limit once per device.
+// fragment, and the epilogue that stages a wave's accumulator tile through LDS and stores full rows
+// (optionally emitting max |C|).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -142,23 +142,6 @@ __device__ __forceinline__ void store_tile_through_lds(floatx16 (&acc)[MT][NT], 
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next band overwrites
     }
     emit_tile_max(cmax, amax_out);
-}
-
-// The kernels need more dynamic LDS than the default limit; the attribute is set once per kernel
-// (the kernel is the template argument: kernels of one signature each have their own flags) and device, not
-// per launch (a launch may sit inside a stream capture).
-template <auto kKernel>
-hipError_t allow_dynamic_lds(int bytes)
-{
-    constexpr int kMaxDevices = 64;
-    static bool done[kMaxDevices] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev >= 0 && dev < kMaxDevices && done[dev]) return hipSuccess;
-    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess && dev >= 0 && dev < kMaxDevices) done[dev] = true;
-    return e;
 }
 
 }  // namespace

@@ -7,6 +7,23 @@
 
 namespace qii {
 
+// Some kernels need more dynamic LDS than the default limit; the attribute is set once per kernel
+// (the kernel is the template argument: kernels of one signature each have their own flags) and device, not
+// per launch (a launch may sit inside a stream capture).
+template <auto kKernel>
+hipError_t allow_dynamic_lds(int bytes)
+{
+    constexpr int kMaxDevices = 64;
+    static bool done[kMaxDevices] = {};
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev >= 0 && dev < kMaxDevices && done[dev]) return hipSuccess;
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(kKernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess && dev >= 0 && dev < kMaxDevices) done[dev] = true;
+    return e;
+}
+
 // Where the quantizer reads its logical R x C matrix from.
 //   kind F32 / BF16: element (r, c) = x[r*ld + c]            (transpose == 0)
 //                                     x[c*ld + r]            (transpose == 1)
@@ -90,6 +107,10 @@ bool cols_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s);
 hipError_t launch_quantize_cols(const QuantizeArgs &a, hipStream_t s);
+// a saved NVFP4 tensor quantized along its columns (quantize_requant.hip)
+bool requant_kernels_apply(const Source &src, int64_t R, int64_t C);
+hipError_t launch_absmax_requant(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht, float *amax, hipStream_t s);
+hipError_t launch_quantize_requant(const QuantizeArgs &a, hipStream_t s);
 // ws (nullable): gemm_workspace_bytes(M, N, K) bytes, 16-byte aligned, for the re-tiled scale
 // bytes of the fast kernel; without it a slower kernel reads the row-major scales directly
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);

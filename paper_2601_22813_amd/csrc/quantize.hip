@@ -396,6 +396,7 @@ hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint6
 {
     if (R == 0 || C == 0) return hipSuccess;
     if (rows_kernels_apply(src, R, C)) return launch_absmax_rows(src, R, C, rht, seed_rht, amax, s);
+    if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(src, R, C, rht, seed_rht, amax, s);
     if (cols_kernels_apply(src, R, C)) return launch_absmax_cols(src, R, C, rht, seed_rht, amax, s);
     const dim3 grid((unsigned)grid_for(R, C, 256)), block(256);
     return with_loader(src, [&](auto load) {
@@ -423,6 +424,7 @@ hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s)
     if (a.R == 0 || a.C == 0) return hipSuccess;
     if (rows_kernels_apply(a.src, a.R, a.C)) return launch_quantize_rows(a, s);
     if (a.scales_tiled) return hipErrorInvalidValue;   // only the rows kernels write the tiled copy
+    if (requant_kernels_apply(a.src, a.R, a.C)) return launch_quantize_requant(a, s);
     if (cols_kernels_apply(a.src, a.R, a.C)) return launch_quantize_cols(a, s);
     const dim3 grid((unsigned)grid_for(a.R, a.C, 256)), block(256);
     return with_loader(a.src, [&](auto load) {

@@ -1,8 +1,6 @@
 // Tuned quantizer / abs-max kernels for dense row-major sources quantized along their
 // COLUMNS (the transposed case: Q(E^T), whose scale groups and rotation chunks run down the
-// rows of x while memory is contiguous along its columns), and for the backward pass's
-// re-quantization of a saved NVFP4 tensor with transposition (Q(W^T), Q(X^T)), where the
-// source element is dequantized on load: (e2m1 * e4m3) * tensor_scale.
+// rows of x while memory is contiguous along its columns).
 //
 // Layout of the work: the 4 lanes of a quad own two adjacent columns of x (= two output rows)
 // and one 128-chunk of them, 32 rows each (lane q holds rows 32q .. 32q+31 of the chunk, for
@@ -17,8 +15,7 @@
 // bytes of a (column, chunk) are gathered with DPP into one store.  The scale-rounding draws
 // follow the library-wide rule (one Philox call feeds rows 4j..4j+3 of one column group): the
 // 8 lanes that own columns 4j..4j+3 compute one call each (column groups 0..7 of the chunk)
-// and fetch the words they need with ds_bpermute.  An NVFP4 source (re-quantization with
-// transposition) is dequantized on load; there one byte holds a row's two columns.
+// and fetch the words they need with ds_bpermute.
 #include "qii_device.h"
 #include "qii_internal.h"
 #include "quantize_core.h"
@@ -28,10 +25,8 @@ namespace qii {
 namespace {
 
 struct ColsArgs {
-    const void *x;       // f32 / bf16 data, or the FP4 codes of an NVFP4 source
-    const uint8_t *in_scales;  // NVFP4 source only
-    const float *in_ts;        // NVFP4 source only
-    int64_t ld;          // elements (stored columns for an NVFP4 source)
+    const void *x;       // f32 / bf16 data
+    int64_t ld;          // elements
     int64_t R, C;        // logical shape: R = columns of x (output rows), C = rows of x
     uint32_t sign[4];
     uint64_t seed_sr;
@@ -55,11 +50,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const void *base, i
 }
 
 // Raw words of this lane's 32 rows (rows 32q .. 32q+31 of the chunk) of columns j0 and j0+1
-// (j0 even): one word per row (two bf16, or two FP4 codes plus their scale byte), two for f32.
+// (j0 even): one word per row (two bf16), two for f32.
 template <int kSrc>
 struct RawCols {
     uint32_t a[32];
-    uint32_t b[kSrc == kSrcBF16 ? 1 : 32];   // f32: second column; NVFP4: scale bytes
+    uint32_t b[kSrc == kSrcBF16 ? 1 : 32];   // f32: second column
 };
 
 // issue the loads; `chunk` is wave-uniform, j0 is clamped into the tensor by the caller, so every
@@ -67,18 +62,7 @@ struct RawCols {
 template <int kSrc>
 __device__ __forceinline__ void load_quarter_chunk_raw(RawCols<kSrc> &r, const ColsArgs &a, int64_t chunk, uint32_t j0, int q)
 {
-    if (kSrc == kSrcNVFP4) {
-        // buffer loads: wave-uniform base and row offset in scalar registers, 32-bit lane offset
-        const int64_t cstride = a.ld / 2, sstride = a.ld / 16;
-        const __amdgpu_buffer_rsrc_t rc_rsrc = chunk_rsrc((const uint8_t *)a.x + chunk * 128 * cstride, 127 * cstride + a.R / 2);
-        const __amdgpu_buffer_rsrc_t rs_rsrc = chunk_rsrc(a.in_scales + chunk * 128 * sstride, 127 * sstride + a.R / 16);
-        const int oc = (int)(32 * q * cstride + j0 / 2), os = (int)(32 * q * sstride + j0 / 16);
-#pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            r.a[i] = __builtin_amdgcn_raw_buffer_load_b8(rc_rsrc, oc, (int)(i * cstride), 0);
-            r.b[i] = __builtin_amdgcn_raw_buffer_load_b8(rs_rsrc, os, (int)(i * sstride), 0);
-        }
-    } else if (kSrc == kSrcBF16) {
+    if (kSrc == kSrcBF16) {
         const __amdgpu_buffer_rsrc_t rsrc = chunk_rsrc((const char *)a.x + chunk * 128 * a.ld * 2, (127 * a.ld + a.R) * 2);
         const int off = (int)((32 * q * a.ld + j0) * 2);
 #pragma unroll
@@ -95,22 +79,15 @@ __device__ __forceinline__ void load_quarter_chunk_raw(RawCols<kSrc> &r, const C
     }
 }
 
-// widen to f32 (an NVFP4 source is dequantized: (e2m1 * e4m3) * tensor scale, first product exact)
-// and apply the rotation signs
+// widen to f32 and apply the rotation signs
 template <int kSrc, bool kRht>
 __device__ __forceinline__ void unpack_quarter_chunk(float v[2][32], const RawCols<kSrc> &r, const ColsArgs &a, int q)
 {
     const uint32_t sw = q == 0 ? a.sign[0] : q == 1 ? a.sign[1] : q == 2 ? a.sign[2] : a.sign[3];
-    const float x32 = kSrc == kSrcNVFP4 ? *a.in_ts : 0.0f;
 #pragma unroll
     for (int i = 0; i < 32; ++i) {
         const uint32_t flip = kRht ? (((sw >> i) & 1u) << 31) : 0u;
-        if (kSrc == kSrcNVFP4) {
-            const float2_t c = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(r.a[i], 1.0f, 0);
-            const float x8 = e4m3_decode(r.b[i]);
-            v[0][i] = u2f(f2u((c[0] * x8) * x32) ^ flip);
-            v[1][i] = u2f(f2u((c[1] * x8) * x32) ^ flip);
-        } else if (kSrc == kSrcBF16) {
+        if (kSrc == kSrcBF16) {
             v[0][i] = u2f((r.a[i] << 16) ^ flip);
             v[1][i] = u2f((r.a[i] & 0xFFFF0000u) ^ flip);
         } else {
@@ -317,7 +294,7 @@ __global__ __launch_bounds__(256) void absmax_cols_kernel(ColsArgs a, int64_t ti
 ColsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, uint64_t seed_sr)
 {
     ColsArgs a;
-    a.x = src.x; a.in_scales = src.scales; a.in_ts = src.ts; a.ld = src.ld; a.R = R; a.C = C;
+    a.x = src.x; a.ld = src.ld; a.R = R; a.C = C;
     const U4 w = philox_seeded(seed_rht, 0, 0, 0, kStreamRht);
     a.sign[0] = w.x; a.sign[1] = w.y; a.sign[2] = w.z; a.sign[3] = w.w;
     a.seed_sr = seed_sr;
@@ -341,8 +318,7 @@ bool cols_kernels_apply(const Source &src, int64_t R, int64_t C)
     if (src.ld > (int64_t)1 << 21) return false;   // offsets within a chunk (128 rows, in bytes) stay below 2^31
     const uintptr_t p = reinterpret_cast<uintptr_t>(src.x);
     if (src.kind == kSrcBF16) return src.ld % 2 == 0 && p % 4 == 0;
-    if (src.kind == kSrcF32) return src.ld % 2 == 0 && p % 8 == 0;
-    return true;   // NVFP4: stored columns are a multiple of 16
+    return src.kind == kSrcF32 && src.ld % 2 == 0 && p % 8 == 0;
 }
 
 hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
@@ -359,8 +335,7 @@ hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, 
         else hipLaunchKernelGGL((absmax_cols_kernel<SRC, false>), grid, block, 0, s, a, tiles_x, tiles);     \
     } while (0)
     if (src.kind == kSrcBF16) QII_AMAX(kSrcBF16);
-    else if (src.kind == kSrcF32) QII_AMAX(kSrcF32);
-    else QII_AMAX(kSrcNVFP4);
+    else QII_AMAX(kSrcF32);
 #undef QII_AMAX
     return hipGetLastError();
 }
@@ -386,8 +361,7 @@ hipError_t launch_quantize_cols(const QuantizeArgs &q, hipStream_t s)
         else QII_COLS_MODE(SRC, false);                           \
     } while (0)
     if (q.src.kind == kSrcBF16) QII_COLS_SRC(kSrcBF16);
-    else if (q.src.kind == kSrcF32) QII_COLS_SRC(kSrcF32);
-    else QII_COLS_SRC(kSrcNVFP4);
+    else QII_COLS_SRC(kSrcF32);
 #undef QII_COLS_SRC
 #undef QII_COLS_MODE
 #undef QII_COLS
