@@ -29,6 +29,7 @@ qii_status hip_fail(hipError_t e, const char *what)
 
 constexpr size_t kSlot = 256;  // bytes reserved per device scalar in a workspace
 constexpr size_t kRegion = qii::kAmaxRegionBytes;   // the spread running maximum of the post hoc scheme (16 KiB)
+constexpr size_t kForwardWords = 2 * (size_t)qii::kForwardMaxWords * 4;   // forward pass: block maxima of X and of W
 size_t align_up(size_t v) { return (v + kSlot - 1) / kSlot * kSlot; }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
@@ -374,7 +375,7 @@ size_t qii_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) { return align_
 
 size_t qii_linear_fwd_workspace_bytes(int64_t T, int64_t d_in, int64_t d_out)
 {
-    return 2 * kSlot + qii_gemm_workspace_bytes(T, d_out, d_in);
+    return kForwardWords + qii_gemm_workspace_bytes(T, d_out, d_in);
 }
 
 size_t qii_linear_bwd_mode_workspace_bytes(int64_t T, int64_t d_in, int64_t d_out, qii_mode mode)
@@ -604,23 +605,36 @@ qii_status qii_linear_fwd_amax(const void *X, const void *W, qii_dtype dt, int64
                     qii_linear_fwd_workspace_bytes(T, d_in, d_out));
     uint8_t *p = reinterpret_cast<uint8_t *>(ws);
     hipStream_t s = (hipStream_t)stream;
-    float *slots = reinterpret_cast<float *>(p);
-    const int slot_words = (int)(kSlot / 4);
-    if ((!amax_x || !amax_w) && (T * d_in > 0 || d_out * d_in > 0)) {
-        hipError_t e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 2, slot_words, s);
-        if (e != hipSuccess) return hip_fail(e, "fill");
-    }
-    // When the GEMM will take its main kernel the two quantizers also write
-    // their scale bytes straight into the GEMM workspace in that kernel's tiled layout: no re-tiling launch.
-    uint8_t *gws = p + 2 * kSlot;
+    float *words = reinterpret_cast<float *>(p);
+    // When the GEMM will take its main kernel the two quantizers also write their scale bytes straight
+    // into the GEMM workspace in that kernel's tiled layout: no re-tiling launch.
+    uint8_t *gws = p + kForwardWords;
     const bool tile = qii::gemm_reads_tiled_scales(T, d_out, d_in) && qii::rows_kernels_apply(sx, T, d_in) && qii::rows_kernels_apply(sw, d_out, d_in);
     uint8_t *x_tiled = tile ? gws : nullptr, *w_tiled = tile ? gws + (T + 255) / 256 * 256 * (d_in / 16) : nullptr;
-    st = quantize_source(sx, T, d_in, mode, 0, 0, 0, amax_x, Xq, slots, nullptr, s, true, false, x_tiled);
-    if (st != QII_OK) return st;
-    st = quantize_source(sw, d_out, d_in, mode, 0, 0, 0, amax_w, Wq, slots + slot_words, nullptr, s, true, false, w_tiled);
-    if (st != QII_OK) return st;
+    if (qii::forward_quantize_applies(sx, T, sw, d_out, d_in)) {
+        qii::QuantizeArgs q[2] = {};
+        q[0].src = sx; q[0].R = T; q[0].amax = amax_x; q[0].scales_tiled = x_tiled;
+        q[1].src = sw; q[1].R = d_out; q[1].amax = amax_w; q[1].scales_tiled = w_tiled;
+        for (int i = 0; i < 2; ++i) {
+            const qii_nvfp4 *out = i == 0 ? Xq : Wq;
+            q[i].C = d_in; q[i].mode = (int)mode;
+            q[i].codes = out->codes; q[i].scales = out->scales; q[i].tensor_scale = out->tensor_scale;
+        }
+        const hipError_t eq = qii::launch_forward_quantize(q, words, s);
+        if (eq != hipSuccess) return hip_fail(eq, "quantize");
+    } else {   // an empty tensor, or rows too long for the kernels above
+        const int slot_words = (int)(kSlot / 4);
+        if ((!amax_x || !amax_w) && (T * d_in > 0 || d_out * d_in > 0)) {
+            const hipError_t ef = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(words), 0u, 2, slot_words, s);
+            if (ef != hipSuccess) return hip_fail(ef, "fill");
+        }
+        st = quantize_source(sx, T, d_in, mode, 0, 0, 0, amax_x, Xq, words, nullptr, s, true, false, x_tiled);
+        if (st != QII_OK) return st;
+        st = quantize_source(sw, d_out, d_in, mode, 0, 0, 0, amax_w, Wq, words + slot_words, nullptr, s, true, false, w_tiled);
+        if (st != QII_OK) return st;
+    }
     // (the GEMM's arguments were checked above, before the first launch)
-    hipError_t e = qii::launch_gemm(*Xq, *Wq, Y, y_dt == QII_BF16, d_out, amax_y, gws, ws_bytes - 2 * kSlot, s, tile ? 12 : 0);
+    hipError_t e = qii::launch_gemm(*Xq, *Wq, Y, y_dt == QII_BF16, d_out, amax_y, gws, ws_bytes - kForwardWords, s, tile ? 12 : 0);
     if (e != hipSuccess) return hip_fail(e, "gemm");
     return QII_OK;
 }

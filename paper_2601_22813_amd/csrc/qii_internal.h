@@ -102,6 +102,11 @@ bool rows_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s);
 hipError_t launch_quantize_rows(const QuantizeArgs &a, hipStream_t s);
+// Q(X) and Q(W) of a forward pass (no rotation, QII_RTN or QII_RTN_46) in one launch, after one that measures the
+// maxima that are not supplied (amax null); words: room for 2 * kForwardMaxWords floats
+constexpr int kForwardMaxWords = 1024;
+bool forward_quantize_applies(const Source &x, int64_t T, const Source &w, int64_t d_out, int64_t d_in);
+hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStream_t s);
 // tuned kernels for dense sources quantized along their columns (quantize_cols.hip)
 bool cols_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,

@@ -26,10 +26,11 @@ struct RowsArgs {
     uint32_t sign[4];    // the 128 rotation signs (host-side Philox), bit j of word j/32
     uint64_t seed_sr;
     const float *amax;
+    int n_amax;          // words at amax whose maximum is the tensor's: 1, or one per block of the pass that measured it
     uint8_t *codes;
     uint8_t *scales;
     float *tensor_scale;
-    uint32_t *amax_out;  // abs-max kernel (one word), and the heavy pass of the post hoc scheme
+    uint32_t *amax_out;  // abs-max kernel (one word, or one per block), and the heavy pass of the post hoc scheme
                          // (kAmaxSpread words, nullable there)
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
     uint8_t *tiled;      // nullable: a second copy of the scale bytes, [row / 256][C / 256][row % 256][16]
@@ -45,7 +46,7 @@ struct LaneSetup : OctetLane {
 
 // kQuadsPerWave: row quads a wave takes (the quantizers: 1; the abs-max pass: 2)
 template <int kQuadsPerWave>
-__device__ __forceinline__ LaneSetup lane_setup(const RowsArgs &a, int64_t G)
+__device__ __forceinline__ LaneSetup lane_setup(const RowsArgs &a, int64_t G, int block)
 {
     LaneSetup L;
     const int lane = threadIdx.x & 63;
@@ -55,7 +56,7 @@ __device__ __forceinline__ LaneSetup lane_setup(const RowsArgs &a, int64_t G)
     const int wcol = wave & (a.wpr - 1), wq = wave / a.wpr, qpb = 4 / a.wpr;
     // consecutive blocks walk along a row first, then down the rows: blocks that run at the same
     // time read one contiguous region of the tensor
-    const int bx = (int)blockIdx.x / a.gy, by = (int)blockIdx.x - bx * a.gy;
+    const int bx = block / a.gy, by = block - bx * a.gy;
     L.quad = (bx * qpb + wq) * kQuadsPerWave;
     const int64_t chunk = ((int64_t)by * a.wpr + wcol) * 8 + (lane >> 3);
     L.g = chunk * 8 + L.blk;
@@ -182,24 +183,40 @@ __device__ __forceinline__ void quantize_quad(const RowsArgs &a, const LaneSetup
     }
 }
 
+// The tensor's maximum: one word, or (forward pass) the maximum of the words that the blocks of the abs-max
+// pass left, reduced by every block.  All threads of the block must call it.
+template <bool kRht>
+__device__ __forceinline__ float tensor_max(const RowsArgs &a, float *wave_m)
+{
+    if (kRht || a.n_amax == 1) return *a.amax;   // uniform
+    float m = 0.0f;
+    for (int i = threadIdx.x; i < a.n_amax; i += 256) m = fmaxf(m, a.amax[i]);
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    return fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3]));
+}
+
 // One wave = one quad of rows x 1024 columns, one block = 4 such pieces; the grid covers the tensor.
 // Blocks are short-lived on purpose: many independent blocks that start and finish at different
 // times keep the memory traffic of the chip smooth, where long-lived waves marching in step (a
 // grid-stride loop with prefetch was measured) load and compute in bursts and ran 10 % slower.
 template <bool kBf16, int kMode, bool kRht>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
+__device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
 {
+    __shared__ float inv_tab[128];
+    __shared__ float wave_m[4];
     constexpr int esz = kBf16 ? 2 : 4;
     const int64_t G = a.C / 16;
-    const LaneSetup L = lane_setup<1>(a, G);
+    const LaneSetup L = lane_setup<1>(a, G, block);
     // the rows are requested before anything else: the loads do not depend on the tensor
     // constants, whose set-up (a dependent load, divisions, the table) then overlaps them
     const uint32_t voff = (uint32_t)L.g * (16u * esz);   // (beyond the row for lanes beyond the last column)
     Raw<kBf16> raw[4];
     load_quad<kBf16>(raw, a, L.quad, voff);
     // (the heavy pass of the post hoc scheme knows no tensor maximum: tc stays unused there)
-    const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{} : tensor_consts(kMode, *a.amax);
-    if (kMode != QII_MS_EDEN_PH && blockIdx.x == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
+    const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{} : tensor_consts(kMode, tensor_max<kRht>(a, wave_m));
+    if (kMode != QII_MS_EDEN_PH && block == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
     StoreOffsets so;
     so.codes = L.col_ok ? (uint32_t)L.g * 8u : kNoStore;
     so.scale8 = (L.col_ok && L.blk == 0) ? (uint32_t)L.g : kNoStore;
@@ -217,8 +234,6 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
         }
         return;
     }
-    __shared__ float inv_tab[128];
-    __shared__ float wave_m[4];
     if (kMode != QII_MS_EDEN_PH) fill_inv_table(inv_tab, tc);
     uint32_t mask[kBf16 ? 8 : 16];
     make_masks<kBf16>(L.sign16, mask);
@@ -233,8 +248,24 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
         __syncthreads();
         if (threadIdx.x == 0)
             max_to_global(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])),
-                          amax_spread_word(a.amax_out, blockIdx.x));
+                          amax_spread_word(a.amax_out, (uint32_t)block));
     }
+}
+
+template <bool kBf16, int kMode, bool kRht>
+__global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
+{
+    quantize_rows_body<kBf16, kMode, kRht>(a, (int)blockIdx.x);
+}
+
+// X and W of a forward pass in one launch: the first n0 blocks take a0
+template <bool kBf16, int kMode>
+__global__ __launch_bounds__(256) void quantize_rows2_kernel(RowsArgs a0, RowsArgs a1, int n0)
+{
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    RowsArgs a = a0;
+    if (!first) a = a1;
+    quantize_rows_body<kBf16, kMode, false>(a, (int)blockIdx.x - (first ? 0 : n0));
 }
 
 // Abs-max pass.  Its result is one word that every block has to fold its maximum into, and such
@@ -242,14 +273,14 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
 // kernel runs as few, long-lived blocks (two per compute unit) that stride over the row quads with
 // the next quad's loads in flight, and issue one atomic each at the very end.
 template <bool kBf16, bool kRht>
-__global__ __launch_bounds__(256) void absmax_rows_kernel(RowsArgs a)
+__device__ __forceinline__ float absmax_rows_body(const RowsArgs &a, int block, int blocks)
 {
     constexpr int esz = kBf16 ? 2 : 4;
     __shared__ float wave_m[4];
     const int64_t G = a.C / 16;
-    const LaneSetup L = lane_setup<1>(a, G);
+    const LaneSetup L = lane_setup<1>(a, G, block);
     const int quads = (int)((a.R + 3) / 4);
-    const int step = ((int)gridDim.x / a.gy) * (4 / a.wpr);
+    const int step = (blocks / a.gy) * (4 / a.wpr);
     const uint32_t voff = (uint32_t)L.g * (16u * esz);
     uint32_t mask[kBf16 ? 8 : 16];
     make_masks<kBf16>(L.sign16, mask);
@@ -273,8 +304,30 @@ __global__ __launch_bounds__(256) void absmax_rows_kernel(RowsArgs a)
     m = wave_max(m);
     if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) max_to_global(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])), a.amax_out);
+    return fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3]));
 }
+
+template <bool kBf16, bool kRht>
+__global__ __launch_bounds__(256) void absmax_rows_kernel(RowsArgs a)
+{
+    const float m = absmax_rows_body<kBf16, kRht>(a, (int)blockIdx.x, (int)gridDim.x);
+    if (threadIdx.x == 0) max_to_global(m, a.amax_out);
+}
+
+// X and W of a forward pass in one launch: the first n0 blocks take a0.  The result stays inside the
+// library, so every block leaves its maximum in a word of its own and the quantizer's blocks reduce
+// the words: no clearing launch before, no atomics.
+template <bool kBf16>
+__global__ __launch_bounds__(256) void absmax_rows2_kernel(RowsArgs a0, RowsArgs a1, int n0)
+{
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    RowsArgs a = a0;
+    if (!first) a = a1;
+    const int block = (int)blockIdx.x - (first ? 0 : n0), blocks = first ? n0 : (int)gridDim.x - n0;
+    const float m = absmax_rows_body<kBf16, false>(a, block, blocks);
+    if (threadIdx.x == 0) a.amax_out[block] = f2u(m);
+}
+
 
 // waves of a block side by side on a row: as many as the row needs, at most 4
 int rows_wpr(int64_t C)
@@ -306,7 +359,7 @@ RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
     const U4 w = philox_seeded(seed_rht, 0, 0, 0, kStreamRht);
     a.sign[0] = w.x; a.sign[1] = w.y; a.sign[2] = w.z; a.sign[3] = w.w;
     a.seed_sr = seed_sr;
-    a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr;
+    a.amax = nullptr; a.n_amax = 1; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr;
     a.tbuf = nullptr;
     a.tiled = nullptr;
     a.wpr = rows_wpr(C);
@@ -362,6 +415,55 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
 #undef QII_ROWS_MODE
 #undef QII_ROWS
     return hipGetLastError();
+}
+
+// Forward pass: Q(X) and Q(W), no rotation, RTN or RTN with 4/6.  Where a maximum is not supplied it is measured
+// first: at most kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each.
+hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStream_t s)
+{
+    RowsArgs a[2];
+    int64_t size[2];
+    for (int i = 0; i < 2; ++i) {
+        a[i] = make_args(q[i].src, q[i].R, q[i].C, 0, 0);
+        a[i].amax = q[i].amax;
+        a[i].codes = q[i].codes; a[i].scales = q[i].scales; a[i].tensor_scale = q[i].tensor_scale;
+        a[i].tiled = q[i].scales_tiled;
+        if (a[i].tiled && q[i].C % 256 != 0) return hipErrorInvalidValue;
+        size[i] = q[i].amax ? 0 : q[i].R * q[i].C;
+    }
+    const bool bf = q[0].src.kind == kSrcBF16;
+    const dim3 block(256);
+    if (size[0] + size[1] > 0) {
+        int n[2] = {0, 0};
+        for (int i = 0; i < 2; ++i) {
+            if (size[i] == 0) continue;
+            int64_t share = (int64_t)((double)kForwardMaxWords * (double)size[i] / (double)(size[0] + size[1])) / a[i].gy;
+            if (share * a[i].gy > kForwardMaxWords - 64) share = (kForwardMaxWords - 64) / a[i].gy;   // (the other tensor has room)
+            if (share < 1) share = 1;
+            n[i] = (int)rows_grid(q[i].R, q[i].C, share).x;
+            if (n[i] > kForwardMaxWords) return hipErrorInvalidValue;   // (see forward_quantize_applies)
+            a[i].amax_out = reinterpret_cast<uint32_t *>(words + i * kForwardMaxWords);
+            a[i].amax = words + i * kForwardMaxWords;
+            a[i].n_amax = n[i];
+        }
+        const dim3 grid((unsigned)(n[0] + n[1]));
+        if (bf) hipLaunchKernelGGL((absmax_rows2_kernel<true>), grid, block, 0, s, a[0], a[1], n[0]);
+        else hipLaunchKernelGGL((absmax_rows2_kernel<false>), grid, block, 0, s, a[0], a[1], n[0]);
+    }
+    const int n0 = (int)rows_grid(q[0].R, q[0].C, 0).x;
+    const dim3 grid((unsigned)n0 + rows_grid(q[1].R, q[1].C, 0).x);
+#define QII_FWD(BF, MODE) hipLaunchKernelGGL((quantize_rows2_kernel<BF, MODE>), grid, block, 0, s, a[0], a[1], n0)
+    if (q[0].mode == QII_RTN) { if (bf) QII_FWD(true, QII_RTN); else QII_FWD(false, QII_RTN); }
+    else { if (bf) QII_FWD(true, QII_RTN_46); else QII_FWD(false, QII_RTN_46); }
+#undef QII_FWD
+    return hipGetLastError();
+}
+
+// both tensors by the rows kernels, a row within what one row of abs-max blocks covers, grids that fit
+bool forward_quantize_applies(const Source &x, int64_t T, const Source &w, int64_t d_out, int64_t d_in)
+{
+    return T > 0 && d_out > 0 && d_in > 0 && rows_kernels_apply(x, T, d_in) && rows_kernels_apply(w, d_out, d_in) &&
+           d_in <= (int64_t)4096 * (kForwardMaxWords / 2) && ((T + d_out) / 4 + 2) * ((d_in + 4095) / 4096) < ((int64_t)1 << 30);
 }
 
 }  // namespace qii
