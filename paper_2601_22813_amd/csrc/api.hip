@@ -117,7 +117,10 @@ qii_status quantize_source(const qii::Source &src, int64_t R, int64_t C, qii_mod
     if (mode == QII_MS_EDEN_PH) {
         // Sec. 7: heavy pass (codes, corrected pseudo-scales, running maximum), then scales only
         if (!tbuf) return fail(QII_WORKSPACE_TOO_SMALL, "the post hoc scheme needs qii_quantize_posthoc_workspace_bytes of workspace");
-        if (!amax_in && !slot_zeroed) {   // the running maximum is spread over 64 words of its region
+        // the running maximum: one word per block of the heavy pass where those are few, else spread over 64
+        // words of its region, which start at 0
+        const int words = amax_in ? 0 : qii::posthoc_words(src, R, C);
+        if (!amax_in && !words && !slot_zeroed) {
             hipError_t e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_slot), 0u, (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s);
             if (e != hipSuccess) return hip_fail(e, "fill");
         }
@@ -126,10 +129,12 @@ qii_status quantize_source(const qii::Source &src, int64_t R, int64_t C, qii_mod
         a.seed_rht = seed_rht; a.seed_sr = seed_sr; a.amax = nullptr;
         a.codes = out->codes; a.scales = out->scales; a.tensor_scale = out->tensor_scale;
         a.tbuf = tbuf; a.amax_accum = amax_in ? nullptr : reinterpret_cast<uint32_t *>(amax_slot);
+        a.amax_words = words;
         hipError_t e = qii::launch_quantize(a, s);
         if (e != hipSuccess) return hip_fail(e, "quantize (heavy pass)");
-        e = qii::launch_posthoc_scales(tbuf, amax_in ? amax_in : amax_slot, amax_in ? 1 : (int)qii::kAmaxSpread, R, C, seed_sr,
-                                       out->scales, out->tensor_scale, s, tiled_scales);
+        const qii::PosthocScales p = {tbuf, amax_in ? amax_in : amax_slot, amax_in != nullptr, words, R, C, seed_sr, out->scales,
+                                      out->tensor_scale, tiled_scales};
+        e = qii::launch_posthoc_scales(&p, 1, s);
         if (e != hipSuccess) return hip_fail(e, "quantize (scales pass)");
         return QII_OK;
     }
@@ -283,7 +288,9 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
     const bool ph = mode == QII_MS_EDEN_PH;
     if ((tiled_r || tiled_c) && !ph) return fail(QII_INVALID_ARG, "tiled scales are written by the post hoc scheme only");
     hipError_t e = hipSuccess;
-    if (!slots_zeroed) {
+    const int64_t blocks = (rows / 128) * (cols / 128);
+    const int words = ph && blocks <= qii::kMaxBlockWords ? (int)blocks : 0;   // one word per block: nothing to clear
+    if (!slots_zeroed && !words) {
         e = ph ? qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s)
                : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, 1, 1, s);
         if (e != hipSuccess) return hip_fail(e, "fill");
@@ -298,7 +305,7 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
         if (e != hipSuccess) return hip_fail(e, "absmax");
     }
     qii::PairQuantizeArgs p;
-    p.src = src; p.rows = rows; p.cols = cols; p.mode = (int)mode;
+    p.src = src; p.rows = rows; p.cols = cols; p.mode = (int)mode; p.amax_words = words;
     p.r = {seed_rht_r, seed_sr_r, ph ? nullptr : slot_r, out_r->codes, out_r->scales, out_r->tensor_scale, tbuf_r,
            ph ? reinterpret_cast<uint32_t *>(slot_r) : nullptr};
     p.c = {seed_rht_c, seed_sr_c, ph ? nullptr : slot_c, out_c->codes, out_c->scales, out_c->tensor_scale, tbuf_c,
@@ -306,9 +313,10 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
     e = qii::launch_quantize_pair(p, s);
     if (e != hipSuccess) return hip_fail(e, "quantize (both orientations)");
     if (ph) {
-        e = qii::launch_posthoc_scales(tbuf_r, slot_r, (int)qii::kAmaxSpread, rows, cols, seed_sr_r, out_r->scales, out_r->tensor_scale, s, tiled_r);
-        if (e != hipSuccess) return hip_fail(e, "quantize (scales pass)");
-        e = qii::launch_posthoc_scales(tbuf_c, slot_c, (int)qii::kAmaxSpread, cols, rows, seed_sr_c, out_c->scales, out_c->tensor_scale, s, tiled_c);
+        const qii::PosthocScales sc[2] = {
+            {tbuf_r, slot_r, false, words, rows, cols, seed_sr_r, out_r->scales, out_r->tensor_scale, tiled_r},
+            {tbuf_c, slot_c, false, words, cols, rows, seed_sr_c, out_c->scales, out_c->tensor_scale, tiled_c}};
+        e = qii::launch_posthoc_scales(sc, 2, s);
         if (e != hipSuccess) return hip_fail(e, "quantize (scales pass)");
     }
     return QII_OK;
@@ -692,28 +700,78 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     const size_t gws_bytes = reinterpret_cast<uint8_t *>(ws) + ws_bytes - p;
     uint64_t sd[6];
     for (uint32_t i = 0; i < 6; ++i) sd[i] = qii_derive_seed(seed, i);
-    // (the post hoc scheme spreads each running maximum over 64 words, 256 bytes apart: the four
-    // regions are contiguous, so one launch clears all 256 words)
-    hipError_t e = ph ? qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4 * (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s)
-                      : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4, slot_words, s);
-    if (e != hipSuccess) return hip_fail(e, "fill");
-    // Q(E) and Q(E^T) from one read of dY: rotation sd[0] along d_out for the dX GEMM, sd[1] along
-    // the tokens for the dW GEMM (their abs-max areas are the first and third of the four)
     // The four quantized operands live only in this workspace.  In the post hoc scheme their scale
     // bytes come from the scales pass, which writes them straight into the layout the main GEMM
     // kernel reads when the GEMM's inner dimension allows that kernel: no re-tiling launch.
     const bool tile_dx = ph && d_out % 256 == 0, tile_dw = ph && T % 256 == 0;
+    // W and X are re-quantized by shared launches: heavy passes (post hoc scheme; both need a per-group buffer,
+    // which the two of E are by then free for, if the sizes allow) or abs-max and quantize passes.
+    qii::Source sq[2] = {};
+    int64_t Rq[2] = {}, Cq[2] = {};
+    st = nvfp4_source(Wq, 1, 128, &sq[0], &Rq[0], &Cq[0]);
+    if (st != QII_OK) return st;
+    st = nvfp4_source(Xq, 1, 128, &sq[1], &Rq[1], &Cq[1]);
+    if (st != QII_OK) return st;
+    const size_t tw = align_up((size_t)(Rq[0] * (Cq[0] / 16)) * 4), tx = align_up((size_t)(Rq[1] * (Cq[1] / 16)) * 4);
+    const bool together = d_in > 0 && qii::requant_kernels_apply(sq[0], Rq[0], Cq[0]) && qii::requant_kernels_apply(sq[1], Rq[1], Cq[1]) &&
+                          (!ph || 4 * kRegion + tw + tx <= posthoc_region_bytes(T, d_in, d_out, mode));
+    int words_q[2] = {0, 0};
+    if (ph && together)
+        for (int i = 0; i < 2; ++i) words_q[i] = qii::requant_blocks(Rq, Cq, 2, i);
+    const bool words_ok = words_q[0] > 0 && words_q[0] <= qii::kMaxBlockWords && words_q[1] > 0 && words_q[1] <= qii::kMaxBlockWords;
+    if (!words_ok) words_q[0] = words_q[1] = 0;
+    const bool words_e = ph && qii::pair_kernel_applies(se, T, d_out) && (T / 128) * (d_out / 128) <= qii::kMaxBlockWords;
+    // (the post hoc scheme spreads each running maximum over 64 words, 256 bytes apart, where its blocks are too
+    // many for a word each: the four regions are contiguous, so one launch clears all 256 words)
+    hipError_t e = hipSuccess;
+    if (!ph) e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4, slot_words, s);
+    else if (!words_ok || !words_e)
+        e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4 * (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s);
+    if (e != hipSuccess) return hip_fail(e, "fill");
+    // Q(E) and Q(E^T) from one read of dY: rotation sd[0] along d_out for the dX GEMM, sd[1] along
+    // the tokens for the dW GEMM (their abs-max areas are the first and third of the four)
     st = quantize_pair(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words, tbuf,
                        tbuf2, s, true, tile_dx, tile_dw);
     if (st != QII_OK) return st;
-    // dX = Q(E) Q(W^T)^T : inner dimension d_out
-    st = requantize_saved(Wq, 1, mode, 128, sd[0], sd[3], &WTq, slots + slot_words, tbuf, s, true, tile_dx);
-    if (st != QII_OK) return st;
+    float *slot_q[2] = {slots + slot_words, slots + 3 * slot_words};
+    if (together) {
+        const qii_nvfp4 *out[2] = {&WTq, &XTq};
+        const uint64_t rht[2] = {sd[0], sd[1]}, sr[2] = {sd[3], sd[5]};
+        float *tb[2] = {tbuf, ph ? tbuf + tw / 4 : nullptr};
+        if (!ph) {
+            e = qii::launch_absmax_requant(sq, Rq, Cq, 1, rht, slot_q, 2, s);
+            if (e != hipSuccess) return hip_fail(e, "absmax");
+        }
+        qii::QuantizeArgs q[2] = {};
+        for (int i = 0; i < 2; ++i) {
+            q[i].src = sq[i]; q[i].R = Rq[i]; q[i].C = Cq[i]; q[i].mode = (int)mode; q[i].rht = 1;
+            q[i].seed_rht = rht[i]; q[i].seed_sr = sr[i];
+            q[i].amax = ph ? nullptr : slot_q[i];
+            q[i].codes = out[i]->codes; q[i].scales = out[i]->scales; q[i].tensor_scale = out[i]->tensor_scale;
+            q[i].tbuf = tb[i]; q[i].amax_accum = ph ? reinterpret_cast<uint32_t *>(slot_q[i]) : nullptr;
+            q[i].amax_words = words_q[i];
+        }
+        e = qii::launch_quantize_requant(q, 2, s);
+        if (e != hipSuccess) return hip_fail(e, "quantize");
+        if (ph) {
+            const qii::PosthocScales sc[2] = {
+                {tb[0], slot_q[0], false, words_q[0], Rq[0], Cq[0], sr[0], WTq.scales, WTq.tensor_scale, tile_dx},
+                {tb[1], slot_q[1], false, words_q[1], Rq[1], Cq[1], sr[1], XTq.scales, XTq.tensor_scale, tile_dw}};
+            e = qii::launch_posthoc_scales(sc, 2, s);
+            if (e != hipSuccess) return hip_fail(e, "quantize (scales pass)");
+        }
+    }
+    // dX = Q(E) Q(W^T)^T : inner dimension d_out;  dW = Q(E^T) Q(X^T)^T : inner dimension T
+    if (!together) {
+        st = requantize_saved(Wq, 1, mode, 128, sd[0], sd[3], &WTq, slot_q[0], tbuf, s, true, tile_dx);
+        if (st != QII_OK) return st;
+    }
     st = gemm_internal(&Eq, &WTq, dX, g_dt, d_in, gws, gws_bytes, stream, tile_dx ? 3 : 0);
     if (st != QII_OK) return st;
-    // dW = Q(E^T) Q(X^T)^T : inner dimension T
-    st = requantize_saved(Xq, 1, mode, 128, sd[1], sd[5], &XTq, slots + 3 * slot_words, tbuf, s, true, tile_dw);
-    if (st != QII_OK) return st;
+    if (!together) {
+        st = requantize_saved(Xq, 1, mode, 128, sd[1], sd[5], &XTq, slot_q[1], tbuf, s, true, tile_dw);
+        if (st != QII_OK) return st;
+    }
     return gemm_internal(&ETq, &XTq, dW, g_dt, d_in, gws, gws_bytes, stream, tile_dw ? 3 : 0);
 }
 

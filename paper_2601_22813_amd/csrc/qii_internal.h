@@ -55,6 +55,7 @@ struct QuantizeArgs {
     // bytes apart, a region of 16 KiB) at amax_accum (nullable: the caller supplies the maximum itself); launch_posthoc_scales finishes
     float *tbuf;
     uint32_t *amax_accum;
+    int amax_words = 0;      // != 0: one word per block at amax_accum instead (posthoc_words, requant_blocks)
     // a second copy of the scale bytes in the main GEMM kernel's tiled layout (nullable; only where
     // rows_kernels_apply, no rotation, C a multiple of 256; room for R rounded up to 256 rows)
     uint8_t *scales_tiled = nullptr;
@@ -67,6 +68,7 @@ struct PairQuantizeArgs {
     Source src;
     int64_t rows, cols;
     int mode;
+    int amax_words;          // QII_MS_EDEN_PH: one word per block ((rows / 128) (cols / 128) of them) per side
     struct Side {
         uint64_t seed_rht, seed_sr;
         const float *amax;
@@ -88,13 +90,26 @@ hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint6
 hipError_t launch_rht(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, float *y,
                       float *amax /* nullable, must hold 0 */, hipStream_t s);
 hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s);
-// amax: n_amax words, 256 bytes apart (1: a maximum supplied by the caller; 64: the spread running
-// maximum of the heavy pass, whose maximum is taken).  tiled (C a multiple of 256): the scale bytes
-// go out in the layout the main GEMM kernel reads ([row / 256][C / 256][row % 256][16 bytes]; room for
-// the row count rounded up to 256) instead of row-major
-hipError_t launch_posthoc_scales(const float *tbuf, const float *amax, int n_amax, int64_t R, int64_t C,
-                                 uint64_t seed_sr, uint8_t *scales, float *tensor_scale, hipStream_t s,
-                                 bool tiled = false);
+// The scales pass of one or two tensors in one launch.  The maximum is supplied by the caller (one word), or
+// that of `words` words left by the heavy pass's blocks, or (words == 0) of its spread running maximum.  tiled (C
+// a multiple of 256): the scale bytes go out in the layout the main GEMM kernel reads ([row / 256][C / 256][row %
+// 256][16 bytes]; room for the row count rounded up to 256) instead of row-major
+struct PosthocScales {
+    const float *tbuf, *amax;
+    bool supplied;
+    int words;
+    int64_t R, C;
+    uint64_t seed_sr;
+    uint8_t *scales;
+    float *tensor_scale;
+    bool tiled;
+};
+hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t s);
+// number of blocks of the heavy pass that launch_quantize would run for this source, when it can leave one
+// word per block (at most 1024 of them, 4 KiB); else 0
+int posthoc_words(const Source &src, int64_t R, int64_t C);
+int rows_blocks(int64_t R, int64_t C);
+int cols_blocks(int64_t R, int64_t C);
 hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const float *ts,
                              int64_t rows, int64_t cols, float *y, hipStream_t s);
 // tuned kernels for dense sources quantized along their rows (quantize_rows.hip)
@@ -114,8 +129,11 @@ hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, 
 hipError_t launch_quantize_cols(const QuantizeArgs &a, hipStream_t s);
 // a saved NVFP4 tensor quantized along its columns (quantize_requant.hip)
 bool requant_kernels_apply(const Source &src, int64_t R, int64_t C);
-hipError_t launch_absmax_requant(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht, float *amax, hipStream_t s);
-hipError_t launch_quantize_requant(const QuantizeArgs &a, hipStream_t s);
+// (one or two tensors in one launch, quantized in the same mode; requant_blocks: blocks of tensor i of such a launch)
+int requant_blocks(const int64_t *R, const int64_t *C, int count, int i);
+hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int64_t *C, int rht, const uint64_t *seed_rht,
+                                 float *const *amax, int count, hipStream_t s);
+hipError_t launch_quantize_requant(const QuantizeArgs *a, int count, hipStream_t s);
 // ws (nullable): gemm_workspace_bytes(M, N, K) bytes, 16-byte aligned, for the re-tiled scale
 // bytes of the fast kernel; without it a slower kernel reads the row-major scales directly
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);

@@ -294,53 +294,102 @@ __global__ __launch_bounds__(256) void quantize_kernel(Loader load, int64_t R, i
 // Second pass of the post hoc scheme (Sec. 7): scales only.  x^FP32 = max|x| / (s * 256); the
 // byte of group (row, g) is SR_E4M3(t / x^FP32) with the 20-bit draw of (seed, row, g), the one
 // Algorithm 1 uses.  One thread takes 4 rows x 4 groups: four Philox calls (a call serves the
-// four rows of one group) and, when whole, one 16-byte load and one 4-byte store per row.
-__global__ __launch_bounds__(256) void posthoc_scales_kernel(const float *__restrict__ tbuf,
-                                                             const float *__restrict__ amax_ptr, int n_amax,
-                                                             int64_t R, int64_t G, uint64_t seed_sr,
-                                                             uint8_t *__restrict__ scales,
-                                                             float *__restrict__ tensor_scale, int64_t tiled_ksn)
+// four rows of one group) and, when whole, one 16-byte load and one 4-byte store per row.  The vector unit
+// bounds it (the Philox calls above all).  The divisions take the short exact sequence, and the roundings the
+// form without subnormals, wherever a whole wave's operands allow.  Up to two tensors in one launch: the first n0
+// blocks take a0, the others a1.
+struct ScalesArgs {
+    const float *tbuf, *amax;   // the tensor maximum is that of n_amax words, `stride` words apart
+    int n_amax, stride;
+    int64_t R, G;
+    uint64_t seed_sr;
+    uint8_t *scales;
+    float *tensor_scale;
+    int64_t tiled_ksn;          // != 0 (G a multiple of 16): K tiles of the layout the main GEMM kernel reads
+};
+
+// four scale bytes of one row
+__device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_t draw[4][4], int it, float x32, float rd, bool in_range)
 {
-    // the tensor maximum: one word supplied by the caller, or the maximum of the words the heavy
-    // pass spread its running maximum over
-    __shared__ float amax_s;
-    if (threadIdx.x < 64) {
-        const float m = wave_max((int)threadIdx.x < n_amax ? amax_ptr[threadIdx.x * kAmaxStrideWords] : 0.0f);
-        if (threadIdx.x == 0) amax_s = m;
+    float u[4];
+    bool odd = !in_range;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) odd = odd || !(t[j] == 0.0f || (t[j] > 0x1p-60f && t[j] < 0x1p60f));
+    if (__builtin_amdgcn_ballot_w64(odd) == 0ull) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = div_by_const(t[j], x32, rd, true);
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = t[j] / x32;
     }
+    uint32_t b[4];
+    bool small = false;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t bn = ((f2u(u[j]) + draw[j][it]) >> 20) - 960u;
+        b[j] = bn > 0x7Eu ? 0x7Eu : bn;
+        small = small || !(u[j] >= 0x1p-6f);
+    }
+    if (__builtin_amdgcn_ballot_w64(small) != 0ull) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b[j] = e4m3_sr(u[j], draw[j][it]);
+    }
+    return b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
+}
+
+__global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesArgs a0, ScalesArgs a1, int n0)
+{
+    __shared__ float wave_m[4];
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    ScalesArgs a = a0;
+    if (!first) a = a1;
+    const int64_t block = (int64_t)blockIdx.x - (first ? 0 : n0);
+    float amax = 0.0f;
+    for (int i = threadIdx.x; i < a.n_amax; i += 256) amax = fmaxf(amax, a.amax[(int64_t)i * a.stride]);
+    amax = wave_max(amax);
+    if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = amax;
     __syncthreads();
-    const float amax = amax_s;
+    amax = fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3]));
     const float s = (float)(96.0 / 17.0 / 0.93);
     const float x32 = amax > 0.0f ? amax / (s * 256.0f) : 1.0f;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx == 0) *tensor_scale = x32;
+    const float rd = 1.0f / x32;
+    const bool in_range = x32 > 0x1p-60f && x32 < 0x1p60f;
+    const int64_t idx = block * 256 + threadIdx.x, G = a.G;
+    if (idx == 0) *a.tensor_scale = x32;
     const int64_t gq = (G + 3) / 4;
-    if (idx >= ((R + 3) / 4) * gq) return;
-    const int64_t quad = idx / gq, g0 = (idx % gq) * 4;
+    const int64_t total = ((a.R + 3) / 4) * gq;
+    const bool live = idx < total;
+    // (a 64-bit division costs as much as a Philox call)
+    const int64_t quad = !live ? 0 : total <= 0x7FFFFFFF ? (int64_t)((uint32_t)idx / (uint32_t)gq) : idx / gq;
+    const int64_t g0 = live ? (idx - quad * gq) * 4 : 0;
+    const bool whole = (G % 4 == 0);
+    float4 t[4];
+    if (whole)   // requested before the draws are made
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int64_t row = quad * 4 + it;
+            t[it] = live && row < a.R ? *reinterpret_cast<const float4 *>(a.tbuf + row * G + g0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
     uint32_t draw[4][4];   // [group][row]
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const U4 w = philox_seeded(seed_sr, (uint32_t)(g0 + j), (uint32_t)quad, 0, kStreamScale);
+        const U4 w = philox_seeded(a.seed_sr, (uint32_t)(g0 + j), (uint32_t)quad, 0, kStreamScale);
         draw[j][0] = w.x >> 12; draw[j][1] = w.y >> 12; draw[j][2] = w.z >> 12; draw[j][3] = w.w >> 12;
     }
-    const bool whole = (G % 4 == 0);
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const int64_t row = quad * 4 + it;
-        if (row >= R) break;
+        const bool ok = live && row < a.R;
         if (whole) {
-            const float4 t = *reinterpret_cast<const float4 *>(tbuf + row * G + g0);
-            const uint32_t b = e4m3_sr(t.x / x32, draw[0][it]) | (e4m3_sr(t.y / x32, draw[1][it]) << 8) |
-                               (e4m3_sr(t.z / x32, draw[2][it]) << 16) | (e4m3_sr(t.w / x32, draw[3][it]) << 24);
-            // tiled_ksn != 0 (G a multiple of 16): the layout the main GEMM kernel reads, 16 bytes per
-            // (row, 256 columns), [row / 256][column / 256][row % 256]
-            uint8_t *dst = tiled_ksn ? scales + (((row >> 8) * tiled_ksn + (g0 >> 4)) * 256 + (row & 255)) * 16 + (g0 & 15)
-                                     : scales + row * G + g0;
-            *reinterpret_cast<uint32_t *>(dst) = b;
-        } else {
+            const float tt[4] = {t[it].x, t[it].y, t[it].z, t[it].w};
+            const uint32_t b = scale_bytes4(tt, draw, it, x32, rd, in_range);   // (all lanes: it votes)
+            uint8_t *dst = a.tiled_ksn ? a.scales + (((row >> 8) * a.tiled_ksn + (g0 >> 4)) * 256 + (row & 255)) * 16 + (g0 & 15)
+                                       : a.scales + row * G + g0;
+            if (ok) *reinterpret_cast<uint32_t *>(dst) = b;
+        } else if (ok) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (g0 + j < G) scales[row * G + g0 + j] = (uint8_t)e4m3_sr(tbuf[row * G + g0 + j] / x32, draw[j][it]);
+                if (g0 + j < G) a.scales[row * G + g0 + j] = (uint8_t)e4m3_sr(a.tbuf[row * G + g0 + j] / x32, draw[j][it]);
         }
     }
 }
@@ -396,7 +445,7 @@ hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint6
 {
     if (R == 0 || C == 0) return hipSuccess;
     if (rows_kernels_apply(src, R, C)) return launch_absmax_rows(src, R, C, rht, seed_rht, amax, s);
-    if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(src, R, C, rht, seed_rht, amax, s);
+    if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(&src, &R, &C, rht, &seed_rht, &amax, 1, s);
     if (cols_kernels_apply(src, R, C)) return launch_absmax_cols(src, R, C, rht, seed_rht, amax, s);
     const dim3 grid((unsigned)grid_for(R, C, 256)), block(256);
     return with_loader(src, [&](auto load) {
@@ -424,7 +473,7 @@ hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s)
     if (a.R == 0 || a.C == 0) return hipSuccess;
     if (rows_kernels_apply(a.src, a.R, a.C)) return launch_quantize_rows(a, s);
     if (a.scales_tiled) return hipErrorInvalidValue;   // only the rows kernels write the tiled copy
-    if (requant_kernels_apply(a.src, a.R, a.C)) return launch_quantize_requant(a, s);
+    if (requant_kernels_apply(a.src, a.R, a.C)) return launch_quantize_requant(&a, 1, s);
     if (cols_kernels_apply(a.src, a.R, a.C)) return launch_quantize_cols(a, s);
     const dim3 grid((unsigned)grid_for(a.R, a.C, 256)), block(256);
     return with_loader(a.src, [&](auto load) {
@@ -443,14 +492,29 @@ hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s)
     });
 }
 
-hipError_t launch_posthoc_scales(const float *tbuf, const float *amax, int n_amax, int64_t R, int64_t C,
-                                 uint64_t seed_sr, uint8_t *scales, float *tensor_scale, hipStream_t s, bool tiled)
+int posthoc_words(const Source &src, int64_t R, int64_t C)
 {
-    const int64_t G = C / 16, threads = ((R + 3) / 4) * ((G + 3) / 4);
-    if (threads == 0) return hipSuccess;
-    if (tiled && C % 256 != 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(posthoc_scales_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, tbuf,
-                       amax, n_amax, R, G, seed_sr, scales, tensor_scale, tiled ? C / 256 : (int64_t)0);
+    int64_t n = 0;
+    if (rows_kernels_apply(src, R, C)) n = (R + 3) / 4 > kMaxBlockWords * 4 ? 0 : rows_blocks(R, C);
+    else if (requant_kernels_apply(src, R, C)) n = requant_blocks(&R, &C, 1, 0);
+    else if (cols_kernels_apply(src, R, C)) n = cols_blocks(R, C);
+    return n <= kMaxBlockWords ? (int)n : 0;
+}
+
+hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t s)
+{
+    ScalesArgs a[2];
+    int64_t blocks[2] = {0, 0};
+    for (int i = 0; i < count; ++i) {
+        const int64_t G = p[i].C / 16;
+        if (p[i].tiled && p[i].C % 256 != 0) return hipErrorInvalidValue;
+        a[i] = ScalesArgs{p[i].tbuf, p[i].amax, p[i].words ? p[i].words : p[i].supplied ? 1 : (int)kAmaxSpread,
+                          p[i].words ? 1 : (int)kAmaxStrideWords, p[i].R, G, p[i].seed_sr, p[i].scales, p[i].tensor_scale,
+                          p[i].tiled ? p[i].C / 256 : (int64_t)0};
+        blocks[i] = (((p[i].R + 3) / 4) * ((G + 3) / 4) + 255) / 256;
+    }
+    if (blocks[0] + blocks[1] == 0) return hipSuccess;
+    hipLaunchKernelGGL(posthoc_scales_kernel, dim3((unsigned)(blocks[0] + blocks[1])), dim3(256), 0, s, a[0], a[count - 1], (int)blocks[0]);
     return hipGetLastError();
 }
 

@@ -34,7 +34,8 @@ struct ColsArgs {
     uint8_t *codes;
     uint8_t *scales;
     float *tensor_scale;
-    uint32_t *amax_out;  // abs-max kernel (one word), and the heavy pass of the post hoc scheme (kAmaxSpread words, nullable there)
+    uint32_t *amax_out;  // abs-max kernel (one word), and the heavy pass of the post hoc scheme (nullable there: the spread
+    int words;           // words, or, words != 0, one per block)
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
 };
 
@@ -193,8 +194,8 @@ __global__ __launch_bounds__(256) void quantize_cols_kernel(ColsArgs a)
             if (lane == 0) wave_m[wave] = m;
             __syncthreads();
             if (threadIdx.x == 0)
-                max_to_global(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])),
-                              amax_spread_word(a.amax_out, blockIdx.x + gridDim.x * blockIdx.y));
+                leave_block_max(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])), a.amax_out, a.words,
+                                (int)(blockIdx.x + gridDim.x * blockIdx.y));
         }
         return;
     }
@@ -300,6 +301,7 @@ ColsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
     a.seed_sr = seed_sr;
     a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr;
     a.tbuf = nullptr;
+    a.words = 0;
     return a;
 }
 
@@ -319,6 +321,12 @@ bool cols_kernels_apply(const Source &src, int64_t R, int64_t C)
     const uintptr_t p = reinterpret_cast<uintptr_t>(src.x);
     if (src.kind == kSrcBF16) return src.ld % 2 == 0 && p % 4 == 0;
     return src.kind == kSrcF32 && src.ld % 2 == 0 && p % 8 == 0;
+}
+
+int cols_blocks(int64_t R, int64_t C)
+{
+    const dim3 g = cols_grid(R, C);
+    return (int)(g.x * g.y);
 }
 
 hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
@@ -344,7 +352,7 @@ hipError_t launch_quantize_cols(const QuantizeArgs &q, hipStream_t s)
 {
     ColsArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr);
     a.amax = q.amax; a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale;
-    a.tbuf = q.tbuf; a.amax_out = q.amax_accum;
+    a.tbuf = q.tbuf; a.amax_out = q.amax_accum; a.words = q.amax_words;
     const dim3 grid = cols_grid(q.R, q.C), block(256);
 #define QII_COLS(SRC, MODE, RHT) hipLaunchKernelGGL((quantize_cols_kernel<SRC, MODE, RHT>), grid, block, 0, s, a)
 #define QII_COLS_MODE(SRC, RHT)                                   \

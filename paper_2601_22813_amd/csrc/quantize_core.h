@@ -265,6 +265,17 @@ __device__ __forceinline__ void max_to_global(float m, uint32_t *amax_bits)
     if (f2u(m) > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, f2u(m));
 }
 
+// A block's maximum at the end of a heavy pass: into a word of its own (words != 0; at most kMaxBlockWords
+// blocks, nothing has to be cleared first), else into the spread running maximum.  The scales pass reads every
+// word in every block: up to 1024 words that costs less than the clearing launch, at 4096 as much.
+constexpr int kMaxBlockWords = 1024;
+
+__device__ __forceinline__ void leave_block_max(float m, uint32_t *region, int words, int block)
+{
+    if (words) region[block] = f2u(m);   // uniform
+    else max_to_global(m, amax_spread_word(region, (uint32_t)block));
+}
+
 // Quantize one group.  y: rotated values; draw20: the 20 scale-rounding bits of this group
 // (MS-EDEN); (seed_sr, row, g): identify the element draws (SR).  Returns the scale byte and
 // fills packed[2] with the 16 codes (element 2j in the low nibble of byte j).

@@ -32,7 +32,7 @@ struct PairSide {
     uint8_t *scales;
     float *tensor_scale;
     float *tbuf;           // QII_MS_EDEN_PH: corrected pseudo-scales, one f32 per group
-    uint32_t *amax_out;    // QII_MS_EDEN_PH: spread running maximum (nullable)
+    uint32_t *amax_out;    // QII_MS_EDEN_PH: spread running maximum, or one word per block (nullable)
 };
 
 struct PairArgs {
@@ -40,6 +40,7 @@ struct PairArgs {
     int64_t ld;            // elements
     int64_t rows, cols;    // of x; both multiples of 128
     int tiles_x;           // tiles along a row of x
+    int words;             // the maxima go to one word per block
     PairSide r, c;         // r: Q(x), rows x cols;  c: Q(x^T), cols x rows
 };
 
@@ -198,8 +199,8 @@ __global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
         __syncthreads();
         if (t < 2) {
             uint32_t *out = t == 0 ? a.r.amax_out : a.c.amax_out;
-            if (out) max_to_global(fmaxf(fmaxf(wave_m[t][0], wave_m[t][1]), fmaxf(wave_m[t][2], wave_m[t][3])),
-                                   amax_spread_word(out, blockIdx.x));
+            if (out) leave_block_max(fmaxf(fmaxf(wave_m[t][0], wave_m[t][1]), fmaxf(wave_m[t][2], wave_m[t][3])), out, a.words,
+                                     (int)blockIdx.x);
         }
     }
 }
@@ -221,6 +222,7 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
     a.x = reinterpret_cast<const uint16_t *>(p.src.x);
     a.ld = p.src.ld; a.rows = p.rows; a.cols = p.cols;
     a.tiles_x = (int)(p.cols / 128);
+    a.words = p.amax_words;
     const PairQuantizeArgs::Side *in[2] = {&p.r, &p.c};
     PairSide *out[2] = {&a.r, &a.c};
     for (int i = 0; i < 2; ++i) {

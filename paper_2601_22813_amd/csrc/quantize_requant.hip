@@ -34,7 +34,8 @@ struct RequantArgs {
     uint8_t *codes;
     uint8_t *scales;
     float *tensor_scale;
-    uint32_t *amax_out;  // abs-max kernel (one word), heavy pass of the post hoc scheme (kAmaxSpread words, nullable there)
+    uint32_t *amax_out;  // abs-max kernel (one word), heavy pass of the post hoc scheme (nullable there): the spread words,
+    int words;           // or, words != 0, one word per block
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
     int tiles_x;         // tiles along a stored row
     int tiles;
@@ -155,21 +156,27 @@ __device__ __forceinline__ void finish_groups(const RequantArgs &a, float v[2][3
     }
 }
 
+// W and X of a backward pass go through one launch: the first n0 blocks take a0, the others a1 (a call for one
+// tensor gives all blocks to a0)
 template <int kMode, bool kRht, int kChunks>
-__global__ __launch_bounds__(256 * kChunks) void requantize_cols_kernel(RequantArgs a)
+__global__ __launch_bounds__(256 * kChunks) void requantize_cols_kernel(RequantArgs a0, RequantArgs a1, int n0)
 {
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    RequantArgs a = a0;
+    if (!first) a = a1;
+    const int block = (int)blockIdx.x - (first ? 0 : n0);
     extern __shared__ __align__(16) uint8_t image[];
     __shared__ float inv_tab[128], wave_m[4 * kChunks];
     const int lane = threadIdx.x & 63, q = lane & 3;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t chunk0, col0;
-    tile_origin<kChunks>(a, (int)blockIdx.x, chunk0, col0);
+    tile_origin<kChunks>(a, block, chunk0, col0);
     RawTile raw;
     load_tile<kChunks>(raw, a, chunk0, col0);
     // (the heavy pass of the post hoc scheme knows no tensor maximum: tc stays unused there)
     const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{} : tensor_consts(kMode, *a.amax);
     if (kMode != QII_MS_EDEN_PH) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
+        if (block == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
         fill_inv_table(inv_tab, tc);
     }
     store_image<kChunks>(raw, image);
@@ -211,7 +218,7 @@ __global__ __launch_bounds__(256 * kChunks) void requantize_cols_kernel(RequantA
             if (threadIdx.x == 0) {
 #pragma unroll
                 for (int i = 1; i < 4 * kChunks; ++i) m = fmaxf(m, wave_m[i]);
-                max_to_global(m, amax_spread_word(a.amax_out, blockIdx.x));
+                leave_block_max(m, a.amax_out, a.words, block);
             }
         }
         return;
@@ -226,8 +233,12 @@ __global__ __launch_bounds__(256 * kChunks) void requantize_cols_kernel(RequantA
 // Abs-max pass: at most 512 blocks (one atomic each: such atomics on one address are resolved one after the
 // other) that stride over the tiles, the next tile's loads in flight.
 template <bool kRht, int kChunks>
-__global__ __launch_bounds__(256 * kChunks) void requantize_absmax_kernel(RequantArgs a)
+__global__ __launch_bounds__(256 * kChunks) void requantize_absmax_kernel(RequantArgs a0, RequantArgs a1, int n0)
 {
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    RequantArgs a = a0;
+    if (!first) a = a1;
+    const int block = (int)blockIdx.x - (first ? 0 : n0), blocks = first ? n0 : (int)gridDim.x - n0;
     extern __shared__ __align__(16) uint8_t image[];
     __shared__ float wave_m[4 * kChunks];
     const int lane = threadIdx.x & 63, q = lane & 3;
@@ -235,14 +246,14 @@ __global__ __launch_bounds__(256 * kChunks) void requantize_absmax_kernel(Requan
     float m = 0.0f;
     RawTile raw;
     int64_t chunk0, col0;
-    tile_origin<kChunks>(a, (int)blockIdx.x, chunk0, col0);
+    tile_origin<kChunks>(a, block, chunk0, col0);
     load_tile<kChunks>(raw, a, chunk0, col0);
-    for (int id = (int)blockIdx.x; id < a.tiles; id += (int)gridDim.x) {
+    for (int id = block; id < a.tiles; id += blocks) {
         const bool live = (chunk0 + (wave >> 2)) * 128 < a.C;   // wave-uniform
         const int64_t j0 = col0 + 32 * (wave & 3) + 2 * (lane >> 2);
         store_image<kChunks>(raw, image);
-        if (id + (int)gridDim.x < a.tiles) {
-            tile_origin<kChunks>(a, id + (int)gridDim.x, chunk0, col0);
+        if (id + blocks < a.tiles) {
+            tile_origin<kChunks>(a, id + blocks, chunk0, col0);
             load_tile<kChunks>(raw, a, chunk0, col0);
         }
         __syncthreads();
@@ -277,23 +288,30 @@ RequantArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht
     const U4 w = philox_seeded(seed_rht, 0, 0, 0, kStreamRht);
     a.sign[0] = w.x; a.sign[1] = w.y; a.sign[2] = w.z; a.sign[3] = w.w;
     a.seed_sr = seed_sr;
-    a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr; a.tbuf = nullptr;
+    a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr; a.tbuf = nullptr; a.words = 0;
     a.tiles_x = (int)((R + 127) / 128);
     a.tiles = (int)((C / 128 + chunks - 1) / chunks) * a.tiles_x;
     return a;
 }
 
 template <auto kKernel>
-hipError_t launch(dim3 grid, dim3 block, int lds, hipStream_t s, const RequantArgs &a)
+hipError_t launch(dim3 grid, dim3 block, int lds, hipStream_t s, const RequantArgs *a, int count, int n0)
 {
     const hipError_t e = allow_dynamic_lds<kKernel>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kKernel, grid, block, lds, s, a);
+    hipLaunchKernelGGL(kKernel, grid, block, lds, s, a[0], a[count - 1], n0);
     return hipGetLastError();
 }
 
+int64_t tiles_of(int64_t R, int64_t C, int chunks) { return (R + 127) / 128 * ((C / 128 + chunks - 1) / chunks); }
+
 // two chunks per block when that still gives every compute unit two blocks
-int chunks_per_block(int64_t R, int64_t C) { return ((R + 127) / 128) * (C / 256) >= 512 ? 2 : 1; }
+int chunks_per_block(const int64_t *R, const int64_t *C, int count)
+{
+    int64_t tiles2 = 0;
+    for (int i = 0; i < count; ++i) tiles2 += tiles_of(R[i], C[i], 2);
+    return tiles2 >= 512 ? 2 : 1;
+}
 
 }  // namespace
 
@@ -304,38 +322,62 @@ bool requant_kernels_apply(const Source &src, int64_t R, int64_t C)
            ((R + 127) / 128) * (C / 128) < ((int64_t)1 << 31);
 }
 
-hipError_t launch_absmax_requant(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht, float *amax, hipStream_t s)
+int requant_blocks(const int64_t *R, const int64_t *C, int count, int i)
 {
-    const int ch = chunks_per_block(R, C);
-    RequantArgs a = make_args(src, R, C, seed_rht, 0, ch);
-    a.amax_out = reinterpret_cast<uint32_t *>(amax);
-    const dim3 grid((unsigned)(a.tiles < 512 ? a.tiles : 512)), block(256 * ch);
-    if (ch == 2)
-        return rht ? launch<requantize_absmax_kernel<true, 2>>(grid, block, 2 * kImage, s, a)
-                   : launch<requantize_absmax_kernel<false, 2>>(grid, block, 2 * kImage, s, a);
-    return rht ? launch<requantize_absmax_kernel<true, 1>>(grid, block, kImage, s, a)
-               : launch<requantize_absmax_kernel<false, 1>>(grid, block, kImage, s, a);
+    return (int)tiles_of(R[i], C[i], chunks_per_block(R, C, count));
 }
 
-hipError_t launch_quantize_requant(const QuantizeArgs &q, hipStream_t s)
+hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int64_t *C, int rht, const uint64_t *seed_rht,
+                                 float *const *amax, int count, hipStream_t s)
 {
-    const int ch = chunks_per_block(q.R, q.C);
-    RequantArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr, ch);
-    a.amax = q.amax; a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale;
-    a.tbuf = q.tbuf; a.amax_out = q.amax_accum;
-    const dim3 grid((unsigned)a.tiles), block(256 * ch);
-#define QII_REQ(MODE, RHT)                                                                                \
-    return ch == 2 ? launch<requantize_cols_kernel<MODE, RHT, 2>>(grid, block, 2 * kImage, s, a)          \
-                   : launch<requantize_cols_kernel<MODE, RHT, 1>>(grid, block, kImage, s, a)
+    const int ch = chunks_per_block(R, C, count);
+    RequantArgs a[2];
+    int64_t all = 0;
+    for (int i = 0; i < count; ++i) {
+        a[i] = make_args(src[i], R[i], C[i], seed_rht[i], 0, ch);
+        a[i].amax_out = reinterpret_cast<uint32_t *>(amax[i]);
+        all += a[i].tiles;
+    }
+    // at most 512 blocks, shared out by size
+    int n[2] = {0, 0};
+    for (int i = 0; i < count; ++i) {
+        n[i] = all <= 512 ? a[i].tiles : (int)(512 * (int64_t)a[i].tiles / all);
+        if (n[i] < 1) n[i] = 1;
+    }
+    const dim3 grid((unsigned)(n[0] + n[1])), block(256 * ch);
+    if (ch == 2)
+        return rht ? launch<requantize_absmax_kernel<true, 2>>(grid, block, 2 * kImage, s, a, count, n[0])
+                   : launch<requantize_absmax_kernel<false, 2>>(grid, block, 2 * kImage, s, a, count, n[0]);
+    return rht ? launch<requantize_absmax_kernel<true, 1>>(grid, block, kImage, s, a, count, n[0])
+               : launch<requantize_absmax_kernel<false, 1>>(grid, block, kImage, s, a, count, n[0]);
+}
+
+hipError_t launch_quantize_requant(const QuantizeArgs *q, int count, hipStream_t s)
+{
+    int64_t R[2], C[2];
+    for (int i = 0; i < count; ++i) { R[i] = q[i].R; C[i] = q[i].C; }
+    const int ch = chunks_per_block(R, C, count);
+    RequantArgs a[2];
+    int blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        a[i] = make_args(q[i].src, q[i].R, q[i].C, q[i].seed_rht, q[i].seed_sr, ch);
+        a[i].amax = q[i].amax; a[i].codes = q[i].codes; a[i].scales = q[i].scales; a[i].tensor_scale = q[i].tensor_scale;
+        a[i].tbuf = q[i].tbuf; a[i].amax_out = q[i].amax_accum; a[i].words = q[i].amax_words;
+        blocks += a[i].tiles;
+    }
+    const dim3 grid((unsigned)blocks), block(256 * ch);
+#define QII_REQ(MODE, RHT)                                                                                                      \
+    return ch == 2 ? launch<requantize_cols_kernel<MODE, RHT, 2>>(grid, block, 2 * kImage, s, a, count, a[0].tiles)             \
+                   : launch<requantize_cols_kernel<MODE, RHT, 1>>(grid, block, kImage, s, a, count, a[0].tiles)
 #define QII_REQ_MODE(RHT)                                        \
-    switch (q.mode) {                                            \
+    switch (q[0].mode) {                                         \
         case QII_RTN: QII_REQ(QII_RTN, RHT);                     \
         case QII_SR: QII_REQ(QII_SR, RHT);                       \
         case QII_RTN_46: QII_REQ(QII_RTN_46, RHT);               \
         case QII_MS_EDEN_PH: QII_REQ(QII_MS_EDEN_PH, RHT);       \
         default: QII_REQ(QII_MS_EDEN, RHT);                      \
     }
-    if (q.rht) QII_REQ_MODE(true)
+    if (q[0].rht) QII_REQ_MODE(true)
     else QII_REQ_MODE(false)
 #undef QII_REQ_MODE
 #undef QII_REQ

@@ -31,7 +31,8 @@ struct RowsArgs {
     uint8_t *scales;
     float *tensor_scale;
     uint32_t *amax_out;  // abs-max kernel (one word, or one per block), and the heavy pass of the post hoc scheme
-                         // (kAmaxSpread words, nullable there)
+                         // (nullable there: the spread words, or, words != 0, one per block)
+    int words;
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
     uint8_t *tiled;      // nullable: a second copy of the scale bytes, [row / 256][C / 256][row % 256][16]
     int wpr;             // waves of a block that sit side by side on a row: 1, 2 or 4
@@ -247,8 +248,7 @@ __device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
         if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
         __syncthreads();
         if (threadIdx.x == 0)
-            max_to_global(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])),
-                          amax_spread_word(a.amax_out, (uint32_t)block));
+            leave_block_max(fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3])), a.amax_out, a.words, block);
     }
 }
 
@@ -361,6 +361,7 @@ RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
     a.seed_sr = seed_sr;
     a.amax = nullptr; a.n_amax = 1; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr;
     a.tbuf = nullptr;
+    a.words = 0;
     a.tiled = nullptr;
     a.wpr = rows_wpr(C);
     const int64_t nch = (C / 16 + 7) / 8;
@@ -394,7 +395,7 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
 {
     RowsArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr);
     a.amax = q.amax; a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale;
-    a.tbuf = q.tbuf; a.amax_out = q.amax_accum;
+    a.tbuf = q.tbuf; a.amax_out = q.amax_accum; a.words = q.amax_words;
     if (q.scales_tiled) {
         if (q.rht || q.C % 256 != 0 || q.mode == QII_MS_EDEN_PH) return hipErrorInvalidValue;
         a.tiled = q.scales_tiled;
@@ -416,6 +417,8 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
 #undef QII_ROWS
     return hipGetLastError();
 }
+
+int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, 0).x; }
 
 // Forward pass: Q(X) and Q(W), no rotation, RTN or RTN with 4/6.  Where a maximum is not supplied it is measured
 // first: at most kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each.
