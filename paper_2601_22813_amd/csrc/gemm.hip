@@ -19,6 +19,8 @@
 // one scale group per lane: lanes 0..31 supply k 0..31 of a 64-element K slice and
 // lanes 32..63 supply k 32..63, four MFMAs walk the four dwords of a lane's 16 bytes
 // (the order of k inside the contraction is free as long as A and B agree).
+#include <utility>
+
 #include "gemm_common.h"
 #include "gemm_sharing_map.h"
 #include "qii_device.h"
@@ -240,30 +242,63 @@ __global__ void retile_scales_kernel(const uint8_t *__restrict__ a_scales, uint8
     *reinterpret_cast<uint4 *>(tiled + (((row >> 8) * ksn + ks) * 256 + (row & 255)) * 16) = v;
 }
 
-__device__ __forceinline__ void issue_tile_loads4(uint8_t *stage, const uint8_t *a_codes, const uint8_t *a_tiled,
-                                                  const uint8_t *b_codes, const uint8_t *b_tiled, int64_t M,
-                                                  int64_t N, int64_t K, int64_t m0, int64_t n0, int64_t kt,
-                                                  int wave)
+// One operand's side of the LDS-direct loads of a block: buffer descriptors over the tile's rows (rows beyond the
+// matrix read as zeros) and over its re-tiled scales, and this thread's offset of its 16-byte piece in row t / 8.
+struct TileSource {
+    uint8_t *codes_base, *scales_base;
+    int codes_bytes, scales_bytes;
+    uint32_t voff, row32;   // row32: bytes of 32 rows
+};
+
+__device__ __forceinline__ TileSource tile_source(const uint8_t *codes, const uint8_t *tiled, int64_t row0, int64_t rows_total, int64_t K)
 {
+    const int64_t left = rows_total - row0, rows = left < BM ? left : BM, pitch = K / 2;
     const int t = threadIdx.x;
-    const int64_t kbyte = kt * (BK4 / 2);
-#pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        const int row = p * 32 + (t >> 3);
-        const int seg = (t & 7) ^ (row & 7);
-        int64_t ra = m0 + row, rb = n0 + row;
-        ra = ra < M ? ra : M - 1;   // rows beyond the matrix read a valid row; their results are dropped
-        rb = rb < N ? rb : N - 1;
-        __builtin_amdgcn_global_load_lds(a_codes + ra * (K / 2) + kbyte + 16 * seg,
-                                         (__attribute__((address_space(3))) void *)(stage + kOff4A + (p * 256 + wave * 64) * 16), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds(b_codes + rb * (K / 2) + kbyte + 16 * seg,
-                                         (__attribute__((address_space(3))) void *)(stage + kOff4B + (p * 256 + wave * 64) * 16), 16, 0, 0);
+    TileSource o;
+    o.codes_base = const_cast<uint8_t *>(codes) + row0 * pitch;
+    o.scales_base = const_cast<uint8_t *>(tiled) + (row0 >> 8) * (K * 16);
+    o.codes_bytes = (int)(rows * pitch);
+    o.scales_bytes = (int)(K * 16);
+    // the piece is chosen so that the LDS image is swizzled (rows of a thread differ by multiples of 32)
+    o.voff = (uint32_t)((t >> 3) * pitch) + 16u * (uint32_t)((t & 7) ^ ((t >> 3) & 7));
+    o.row32 = (uint32_t)(32 * pitch);
+    return o;
+}
+
+// the descriptors; a K tile beyond the last takes empty ones: its loads read nothing
+struct TileDescriptors {
+    __amdgpu_buffer_rsrc_t ac, as, bc, bs;
+};
+__device__ __forceinline__ TileDescriptors descriptors(const TileSource &a, const TileSource &b, bool on)
+{
+    return TileDescriptors{__builtin_amdgcn_make_buffer_rsrc(a.codes_base, 0, on ? a.codes_bytes : 0, 0x00020000),
+                           __builtin_amdgcn_make_buffer_rsrc(a.scales_base, 0, on ? a.scales_bytes : 0, 0x00020000),
+                           __builtin_amdgcn_make_buffer_rsrc(b.codes_base, 0, on ? b.codes_bytes : 0, 0x00020000),
+                           __builtin_amdgcn_make_buffer_rsrc(b.scales_base, 0, on ? b.scales_bytes : 0, 0x00020000)};
+}
+
+// load I of the 18 that a thread issues per K tile: 8 code pieces of A, 8 of B, the scales of A and of B.  (The row
+// part sits in the vector offset, which the descriptor's bounds check covers; the scalar offset stays inside a row.)
+template <int I>
+__device__ __forceinline__ void issue_tile_load(uint8_t *stage, const TileSource &a, const TileSource &b, const TileDescriptors &d, int kt, int wave)
+{
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    if constexpr (I < 16) {
+        constexpr int p = I & 7;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(I < 8 ? d.ac : d.bc, (lds_ptr)(stage + (I < 8 ? kOff4A : kOff4B) + (p * 256 + wave * 64) * 16), 16,
+                                                 I < 8 ? a.voff + p * a.row32 : b.voff + p * b.row32, kt * (BK4 / 2), 0, 0);
+    } else {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(I == 16 ? d.as : d.bs, (lds_ptr)(stage + (I == 16 ? kOff4As : kOff4Bs) + (wave * 64) * 16), 16,
+                                                 threadIdx.x * 16u, kt * 4096, 0, 0);
     }
-    const int64_t ksn = K / BK4;
-    __builtin_amdgcn_global_load_lds(a_tiled + (((m0 >> 8) * ksn + kt) * 256 + t) * 16,
-                                     (__attribute__((address_space(3))) void *)(stage + kOff4As + (wave * 64) * 16), 16, 0, 0);
-    __builtin_amdgcn_global_load_lds(b_tiled + (((n0 >> 8) * ksn + kt) * 256 + t) * 16,
-                                     (__attribute__((address_space(3))) void *)(stage + kOff4Bs + (wave * 64) * 16), 16, 0, 0);
+}
+
+template <int... I>
+__device__ __forceinline__ void issue_tile_loads(std::integer_sequence<int, I...>, uint8_t *stage, const TileSource &a, const TileSource &b,
+                                                 int kt, int wave)
+{
+    const TileDescriptors d = descriptors(a, b, true);
+    (issue_tile_load<I>(stage, a, b, d, kt, wave), ...);
 }
 
 // ---- fragment pipeline of the main kernel -------------------------------------------------
@@ -282,19 +317,32 @@ struct FragAddr {
     uint32_t xo[4];         // swizzled 16-byte slot of K slice j, times 16
 };
 
+// LDS addresses of one slice's reads
+struct ReadAddr {
+    uint32_t a, b, sa, sb;
+};
+
 template <int J>
-__device__ __forceinline__ void frag_read_issue(RawFrag4 &f, const FragAddr &fa, uint32_t stage_off)
+__device__ __forceinline__ ReadAddr read_addr(const FragAddr &fa, uint32_t stage_off)
 {
-    const uint32_t va = fa.a + fa.xo[J] + stage_off, vb = fa.b + fa.xo[J] + stage_off;
-    const uint32_t vsa = fa.sa + stage_off, vsb = fa.sb + stage_off;
-    // rows 32 t: codes 32 * 128 bytes apart, re-tiled scales 32 * 16 bytes apart
-#define QII_RD(T)                                                                                       \
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[T]) : "v"(va), "n"(T * 4096));              \
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(vb), "n"(T * 4096));              \
-    asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sa[T]) : "v"(vsa), "n"(T * 512 + 4 * J));      \
-    asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sb[T]) : "v"(vsb), "n"(T * 512 + 4 * J))
-    QII_RD(0); QII_RD(1); QII_RD(2); QII_RD(3);
-#undef QII_RD
+    return ReadAddr{fa.a + fa.xo[J] + stage_off, fa.b + fa.xo[J] + stage_off, fa.sa + stage_off, fa.sb + stage_off};
+}
+
+// read I (0..15) of K slice J: rows 32 T (codes 32 * 128 bytes apart, re-tiled scales 32 * 16 bytes apart), T = I / 4
+template <int J, int I>
+__device__ __forceinline__ void frag_read_one(RawFrag4 &f, const ReadAddr &r)
+{
+    constexpr int T = I >> 2;
+    if constexpr ((I & 3) == 0) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[T]) : "v"(r.a), "n"(T * 4096));
+    else if constexpr ((I & 3) == 1) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(r.b), "n"(T * 4096));
+    else if constexpr ((I & 3) == 2) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sa[T]) : "v"(r.sa), "n"(T * 512 + 4 * J));
+    else asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sb[T]) : "v"(r.sb), "n"(T * 512 + 4 * J));
+}
+
+template <int J, int... I>
+__device__ __forceinline__ void frag_read_issue(std::integer_sequence<int, I...>, RawFrag4 &f, const ReadAddr &r)
+{
+    (frag_read_one<J, I>(f, r), ...);
 }
 
 // all outstanding LDS reads have landed; ties the registers of f to the wait
@@ -327,20 +375,52 @@ __device__ __forceinline__ void dequant_chunk(Frags &nx, RawFrag4 &f)
 }
 
 // One step = 16 matrix instructions on the fragments in cu, with the fragments of the next
-// step (dword D of f) dequantized into nx in between, one chunk per matrix instruction; the
-// scheduling barriers keep that order, so the conversions run in the shadow of the matrix pipe.
-template <int D>
-__device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, RawFrag4 &f)
+// step (dword D of f) dequantized into nx in between, one chunk per matrix instruction, and the memory
+// operations side(I) spread over the step; the scheduling barriers keep that order, so the conversions and
+// the issue of the memory operations run in the shadow of the matrix pipe.  (A K tile's 18 loads, with their
+// address arithmetic, and 64 LDS reads used to be issued in blocks between the steps, with the matrix pipe idle:
+// 16384 x 2048 x 8192 441 -> 412 us, 32768 x 16384 x 2048 1820 -> 1743, 8192^3 827 -> 797 on one box.)
+struct NoSide {
+    template <int I>
+    __device__ __forceinline__ void at() const {}
+};
+
+template <int D, class Side>
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, RawFrag4 &f, const Side &side)
 {
 #define QII_MMA(I)                                                                                          \
     acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.a[(I) >> 2], cu.b[(I) & 3],          \
                                                                     acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
+    side.template at<I>();                                                                                  \
     dequant_chunk<I, D>(nx, f);                                                                             \
     __builtin_amdgcn_sched_barrier(0)
     QII_MMA(0); QII_MMA(1); QII_MMA(2); QII_MMA(3); QII_MMA(4); QII_MMA(5); QII_MMA(6); QII_MMA(7);
     QII_MMA(8); QII_MMA(9); QII_MMA(10); QII_MMA(11); QII_MMA(12); QII_MMA(13); QII_MMA(14); QII_MMA(15);
 #undef QII_MMA
 }
+
+// the 16 reads of K slice J into g, one per matrix instruction
+template <int J>
+struct ReadSide {
+    RawFrag4 &g;
+    const ReadAddr r;
+    template <int I>
+    __device__ __forceinline__ void at() const { frag_read_one<J, I>(g, r); }
+};
+
+// loads kFirst + I of K tile kt (those below 18), one per matrix instruction
+template <int kFirst>
+struct LoadSide {
+    uint8_t *stage;
+    const TileSource &a, &b;
+    const TileDescriptors &d;
+    int kt, wave;
+    template <int I>
+    __device__ __forceinline__ void at() const
+    {
+        if constexpr (kFirst + I < 18) issue_tile_load<kFirst + I>(stage, a, b, d, kt, wave);
+    }
+};
 
 // Launch position -> origin of the output tile (about 32 tiles an XCD works on at once share 4 A panels and
 // 8 B panels, 3.5 MiB at K = 2048, instead of 1 + 32).
@@ -414,11 +494,13 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
         for (int j = 0; j < 4; ++j) fa.xo[j] = (uint32_t)(((2 * j + kb) ^ (li & 7)) * 16);
     }
 
-    issue_tile_loads4(smem, a_codes, a_tiled, b_codes, b_tiled, M, N, K, m0, n0, kt0, wave);
+    const TileSource src_a = tile_source(a_codes, a_tiled, m0, M, K), src_b = tile_source(b_codes, b_tiled, n0, N, K);
+    const std::make_integer_sequence<int, 18> all_loads;
+    const std::make_integer_sequence<int, 16> all_reads;
+    issue_tile_loads(all_loads, smem, src_a, src_b, kt0, wave);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (ktiles > 1)
-        issue_tile_loads4(smem + kStage4Bytes, a_codes, a_tiled, b_codes, b_tiled, M, N, K, m0, n0, kt0 + 1, wave);
+    if (ktiles > 1) issue_tile_loads(all_loads, smem + kStage4Bytes, src_a, src_b, kt0 + 1, wave);
 
     // Pipeline over K, in steps of 16 columns of K per lane half (4 steps = one 64-wide slice,
     // 4 slices = one tile).  While step n multiplies, the fragments of step n+1 are dequantized;
@@ -430,8 +512,8 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     // stage and the current stage can take tile kt+2.
     RawFrag4 fe, fo;
     Frags x, y;
-    frag_read_issue<0>(fe, fa, 0);
-    frag_read_issue<1>(fo, fa, 0);
+    frag_read_issue<0>(all_reads, fe, read_addr<0>(fa, 0));
+    frag_read_issue<1>(all_reads, fo, read_addr<1>(fa, 0));
     frag_read_wait(fe);   // (waits for both)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -444,40 +526,37 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     }
     for (int kt = 0; kt < ktiles; ++kt) {
         const uint32_t cur_off = (kt & 1) * kStage4Bytes, nxt_off = ((kt + 1) & 1) * kStage4Bytes;
+        const NoSide none;
         // slice 0 (raw: fe)
-        mma_step<1>(acc, x, y, fe);
-        mma_step<2>(acc, y, x, fe);
-        mma_step<3>(acc, x, y, fe);
+        mma_step<1>(acc, x, y, fe, none);
+        mma_step<2>(acc, y, x, fe, none);
+        mma_step<3>(acc, x, y, fe, none);
         frag_read_wait(fo);
-        frag_read_issue<2>(fe, fa, cur_off);
-        mma_step<0>(acc, y, x, fo);
+        mma_step<0>(acc, y, x, fo, ReadSide<2>{fe, read_addr<2>(fa, cur_off)});
         // slice 1 (raw: fo)
-        mma_step<1>(acc, x, y, fo);
-        mma_step<2>(acc, y, x, fo);
-        mma_step<3>(acc, x, y, fo);
+        mma_step<1>(acc, x, y, fo, none);
+        mma_step<2>(acc, y, x, fo, none);
+        mma_step<3>(acc, x, y, fo, none);
         frag_read_wait(fe);
-        frag_read_issue<3>(fo, fa, cur_off);
-        mma_step<0>(acc, y, x, fe);
+        mma_step<0>(acc, y, x, fe, ReadSide<3>{fo, read_addr<3>(fa, cur_off)});
         // slice 2 (raw: fe)
-        mma_step<1>(acc, x, y, fe);
-        mma_step<2>(acc, y, x, fe);
-        mma_step<3>(acc, x, y, fe);
+        mma_step<1>(acc, x, y, fe, none);
+        mma_step<2>(acc, y, x, fe, none);
+        mma_step<3>(acc, x, y, fe, none);
         frag_read_wait(fo);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (kt + 2 < ktiles)
-            issue_tile_loads4(smem + cur_off, a_codes, a_tiled, b_codes, b_tiled, M, N, K, m0, n0, kt0 + kt + 2, wave);
-        // (after the last tile the two reads below fetch a stale stage; the values are never used)
-        frag_read_issue<0>(fe, fa, nxt_off);
-        mma_step<0>(acc, y, x, fo);
+        // (after the last tile the reads of slices 0 and 1 fetch a stale stage; the values are never used)
+        mma_step<0>(acc, y, x, fo, ReadSide<0>{fe, read_addr<0>(fa, nxt_off)});
+        const TileDescriptors d = descriptors(src_a, src_b, kt + 2 < ktiles);
         // slice 3 (raw: fo)
-        mma_step<1>(acc, x, y, fo);
-        mma_step<2>(acc, y, x, fo);
-        mma_step<3>(acc, x, y, fo);
+        mma_step<1>(acc, x, y, fo, LoadSide<0>{smem + cur_off, src_a, src_b, d, kt0 + kt + 2, wave});
+        mma_step<2>(acc, y, x, fo, LoadSide<16>{smem + cur_off, src_a, src_b, d, kt0 + kt + 2, wave});
+        mma_step<3>(acc, x, y, fo, none);
         frag_read_wait(fe);
-        frag_read_issue<1>(fo, fa, nxt_off);
-        mma_step<0>(acc, y, x, fe);
+        mma_step<0>(acc, y, x, fe, ReadSide<1>{fo, read_addr<1>(fa, nxt_off)});
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (loads beyond the last tile write zeros: they land before LDS is reused)
     // the last read block is still in flight: its registers and the stages are reused below
     frag_read_wait(fo);
     __syncthreads();
@@ -682,6 +761,8 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 // 3 us of launch and first loads, 4.5 of re-tiling where the scale bytes are not tiled yet.
 enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide };
 
+constexpr int64_t kMaxMainK = (int64_t)1 << 23;
+
 static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool retile)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
@@ -710,7 +791,7 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool re
 
 bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
 {
-    return K % BK4 == 0 && M > 0 && N > 0 && choose_route(M, N, K, true, false) == kRouteMain;
+    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && choose_route(M, N, K, true, false) == kRouteMain;
 }
 
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
@@ -729,7 +810,8 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
     const bool a_ok = (pretiled & 5) || (reinterpret_cast<uintptr_t>(A.scales) & 15) == 0;
     const bool b_ok = (pretiled & 10) || (reinterpret_cast<uintptr_t>(B.scales) & 15) == 0;
-    const bool main_ok = K % BK4 == 0 && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
+    // (K: offsets within a tile's rows stay below 2^31)
+    const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
     const bool retile = !(pretiled & 5) || !(pretiled & 10);
     Route route = choose_route(M, N, K, main_ok, retile);
     uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
