@@ -19,6 +19,16 @@ constexpr uint32_t kStreamDerive = 0x44525600u;
 // ---------------------------------------------------------------- Philox4x32-10
 struct U4 { uint32_t x, y, z, w; };
 
+// a ^ b ^ c: one three-input instruction on the device
+__host__ __device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+#else
+    return a ^ b ^ c;
+#endif
+}
+
 __host__ __device__ inline U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                             uint32_t k0, uint32_t k1)
 {
@@ -26,8 +36,8 @@ __host__ __device__ inline U4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c
     for (int r = 0; r < 10; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
-        const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
-        const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
+        const uint32_t n0 = xor3((uint32_t)(p1 >> 32), c1, k0);
+        const uint32_t n2 = xor3((uint32_t)(p0 >> 32), c3, k1);
         c1 = (uint32_t)p1;
         c3 = (uint32_t)p0;
         c0 = n0;
@@ -109,12 +119,14 @@ __device__ __forceinline__ uint32_t e2m1_mag_code(float c)
 
 // stochastic rounding of |q| with 16 random bits R: up iff R + d >= 2^16, d the
 // position between the neighbours scaled to 2^16; returns the 3-bit code.
+// (both ranges are computed and one is selected: a branch per element costs more than the few instructions it
+// skips; at a >= 6 the large range gives 7 or more)
 __device__ __forceinline__ uint32_t e2m1_sr_code(float a, uint32_t r16)
 {
-    if (a < 1.0f) return ((uint32_t)(a * 0x1p17f) + r16) >> 16;
-    if (a >= 6.0f) return 7u;
+    const uint32_t small = ((uint32_t)(a * 0x1p17f) + r16) >> 16;
     const uint32_t m = ((f2u(a) + (r16 << 6)) >> 22) - 252u;
-    return m > 7u ? 7u : m;
+    const uint32_t large = m > 7u ? 7u : m;
+    return a < 1.0f ? small : large;
 }
 
 __device__ __forceinline__ float e2m1_decode_mag(uint32_t m)

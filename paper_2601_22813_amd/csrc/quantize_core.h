@@ -304,9 +304,9 @@ __device__ __forceinline__ uint32_t quantize_group16(const float y[16], const Te
     const float r = div_by_tensor_const<kFast>(group_absmax(y), tc);
     const uint32_t b_rtn = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(r, 0.0f, 448.0f), 0.0f, 0, false);
     if (kMode == QII_SR) {
+        // (a group whose scale byte is 0 has zero codes; it runs the arithmetic like any other)
         packed[0] = 0u;
         packed[1] = 0u;
-        if (b_rtn == 0u) return 0u;
         const float inv = group_inv<kFast, kTab>(b_rtn, tc, inv_tab);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -320,6 +320,8 @@ __device__ __forceinline__ uint32_t quantize_group16(const float y[16], const Te
                 packed[h] |= code << (4 * j);
             }
         }
+        packed[0] = b_rtn != 0u ? packed[0] : 0u;
+        packed[1] = b_rtn != 0u ? packed[1] : 0u;
         return b_rtn;
     }
     // A group whose scale byte is 0 has zero codes.  It runs the arithmetic below like any other
