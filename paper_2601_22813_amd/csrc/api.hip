@@ -298,10 +298,8 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
                : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_c), 0u, 1, 1, s);
         if (e != hipSuccess) return hip_fail(e, "fill");
     }
-    if (!ph) {   // Algorithm 1 needs both rotated maxima before any scale: two abs-max passes, then one read for both outputs
-        e = qii::launch_absmax(src, rows, cols, 1, seed_rht_r, slot_r, s);
-        if (e != hipSuccess) return hip_fail(e, "absmax");
-        e = qii::launch_absmax(srct, cols, rows, 1, seed_rht_c, slot_c, s);
+    if (!ph) {   // Algorithm 1 needs both rotated maxima before any scale: one read for both, then one for both outputs
+        e = qii::launch_absmax_tiles(src, rows, cols, seed_rht_r, slot_r, seed_rht_c, slot_c, s);
         if (e != hipSuccess) return hip_fail(e, "absmax");
     }
     qii::PairQuantizeArgs p;

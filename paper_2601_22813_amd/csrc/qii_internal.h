@@ -82,6 +82,10 @@ struct PairQuantizeArgs {
 bool pair_kernel_applies(const Source &src, int64_t rows, int64_t cols);
 hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s);
 
+bool absmax_tiles_pay(int64_t rows, int64_t cols);
+hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, uint64_t seed_rht_r, float *amax_r, uint64_t seed_rht_c,
+                               float *amax_c, hipStream_t s);
+
 // p[i * stride_words] = v for i < count (count <= 256); a kernel, not a memset node, so that the
 // calls can be captured in a HIP graph
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int count, int stride_words, hipStream_t s);

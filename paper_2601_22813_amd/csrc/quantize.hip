@@ -445,6 +445,10 @@ hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint6
 {
     if (R == 0 || C == 0) return hipSuccess;
     if (rows_kernels_apply(src, R, C)) return launch_absmax_rows(src, R, C, rht, seed_rht, amax, s);
+    Source plain = src;   // a rotated transposed matrix that the tile kernels take: R columns, C rows
+    plain.transpose = 0;
+    if (rht && src.transpose && pair_kernel_applies(plain, C, R) && absmax_tiles_pay(C, R))
+        return launch_absmax_tiles(plain, C, R, 0, nullptr, seed_rht, amax, s);
     if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(&src, &R, &C, rht, &seed_rht, &amax, 1, s);
     if (cols_kernels_apply(src, R, C)) return launch_absmax_cols(src, R, C, rht, seed_rht, amax, s);
     const dim3 grid((unsigned)grid_for(R, C, 256)), block(256);

@@ -1,0 +1,31 @@
+"""Rotated abs-max by 128 x 128 tiles (along the columns, and along both orientations for Algorithm 1's pair): bit for
+bit the oracle's maximum where the tile kernel can go wrong: one tile, fewer tiles than a block has wave groups, tile
+counts that leave some groups without a tile in the last round, more rounds than one, a leading dimension beyond the row
+whose extra columns are huge, and a maximum that sits in the last tile."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2601_22813_amd import binding as qii
+from paper_2601_22813_amd import synth
+
+from gpu_util import assert_nv_equal, to_dev, ws
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rows,cols", [(128, 128), (128, 384), (640, 384), (256, 1152), (1280, 6656), (4224, 4352)])
+def test_rotated_abs_max_by_tiles(oracle, rows, cols):
+    x = synth.student_t_bf16((rows, cols), 3, 0.1, seed=rows + cols)
+    x[rows - 128:, cols - 128:] = synth.normal_bf16((128, 128), 5.0, 3)   # the largest values in the last tile
+    full = to_dev(np.concatenate([x, np.full((rows, 128), 0x7000, np.uint16)], axis=1))[:, :cols]   # 1.6e29 beyond the row
+    amax = torch.full((1,), float("nan"), device="cuda")
+    qii.qii_absmax(full, True, 128, 91, amax)
+    _, want = oracle.rht(x, transpose=True, rht_group=128, seed_rht=91)
+    assert amax.item() == want
+    if rows * cols > 1 << 20:
+        return
+    out_r, out_c = qii.NVFP4Tensor.empty(rows, cols), qii.NVFP4Tensor.empty(cols, rows)
+    qii.qii_quantize_pair_nvfp4(full, qii.MS_EDEN, 91, 92, 93, 94, out_r, out_c, ws(qii.qii_quantize_pair_workspace_bytes(rows, cols, qii.MS_EDEN)))
+    assert_nv_equal(out_r, oracle.quantize(x, qii.MS_EDEN, seed_rht=91, seed_sr=92), "rows")
+    assert_nv_equal(out_c, oracle.quantize(x, qii.MS_EDEN, transpose=True, seed_rht=93, seed_sr=94), "columns")
