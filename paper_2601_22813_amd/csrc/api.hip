@@ -760,16 +760,18 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
         }
     }
     // dX = Q(E) Q(W^T)^T : inner dimension d_out;  dW = Q(E^T) Q(X^T)^T : inner dimension T
-    if (!together) {
-        st = requantize_saved(Wq, 1, mode, 128, sd[0], sd[3], &WTq, slot_q[0], tbuf, s, true, tile_dx);
-        if (st != QII_OK) return st;
+    if (together) {   // (the GEMMs' arguments were checked above, before the first launch)
+        const qii::GemmCall c[2] = {{&Eq, &WTq, dX, d_in, tile_dx ? 3 : 0}, {&ETq, &XTq, dW, d_in, tile_dw ? 3 : 0}};
+        e = qii::launch_gemm2(c, g_dt == QII_BF16, gws, gws_bytes, s);
+        if (e != hipSuccess) return hip_fail(e, "gemm");
+        return QII_OK;
     }
+    st = requantize_saved(Wq, 1, mode, 128, sd[0], sd[3], &WTq, slot_q[0], tbuf, s, true, tile_dx);
+    if (st != QII_OK) return st;
     st = gemm_internal(&Eq, &WTq, dX, g_dt, d_in, gws, gws_bytes, stream, tile_dx ? 3 : 0);
     if (st != QII_OK) return st;
-    if (!together) {
-        st = requantize_saved(Xq, 1, mode, 128, sd[1], sd[5], &XTq, slot_q[1], tbuf, s, true, tile_dw);
-        if (st != QII_OK) return st;
-    }
+    st = requantize_saved(Xq, 1, mode, 128, sd[1], sd[5], &XTq, slot_q[1], tbuf, s, true, tile_dw);
+    if (st != QII_OK) return st;
     return gemm_internal(&ETq, &XTq, dW, g_dt, d_in, gws, gws_bytes, stream, tile_dw ? 3 : 0);
 }
 

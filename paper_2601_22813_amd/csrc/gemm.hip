@@ -794,6 +794,21 @@ bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
     return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && choose_route(M, N, K, true, false) == kRouteMain;
 }
 
+// whether the main kernel can run, and the route, for operands and a workspace as launch_gemm has them
+static Route route_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, size_t ws_bytes, int pretiled)
+{
+    const int64_t M = A.rows, N = B.rows, K = A.cols;
+    // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
+    const bool a_ok = (pretiled & 5) || (reinterpret_cast<uintptr_t>(A.scales) & 15) == 0;
+    const bool b_ok = (pretiled & 10) || (reinterpret_cast<uintptr_t>(B.scales) & 15) == 0;
+    // (K: offsets within a tile's rows stay below 2^31)
+    const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= scales_workspace_bytes(M, N, K) &&
+                         (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
+    return choose_route(M, N, K, main_ok, !(pretiled & 5) || !(pretiled & 10));
+}
+
+static SmallTile small_tile(Route route) { return route == kRoute64 ? kTile64 : route == kRoute128Wide ? kTile128Wide : kTile128; }
+
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
                        float *amax_c, void *ws, size_t ws_bytes, hipStream_t s, int pretiled)
 {
@@ -807,13 +822,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     if (M == 0 || N == 0) return hipSuccess;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     const size_t need = K % BK4 == 0 ? scales_workspace_bytes(M, N, K) : 0;
-    // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
-    const bool a_ok = (pretiled & 5) || (reinterpret_cast<uintptr_t>(A.scales) & 15) == 0;
-    const bool b_ok = (pretiled & 10) || (reinterpret_cast<uintptr_t>(B.scales) & 15) == 0;
-    // (K: offsets within a tile's rows stay below 2^31)
-    const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= need && (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
-    const bool retile = !(pretiled & 5) || !(pretiled & 10);
-    Route route = choose_route(M, N, K, main_ok, retile);
+    const Route route = route_of(A, B, ws, ws_bytes, pretiled);
     uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
     uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
     if (route == kRouteMain) {
@@ -847,8 +856,28 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
         return hipGetLastError();
     }
     // an operand that is tiled only (bits 0, 1) is read tiled, any other row-major
-    const SmallTile tile = route == kRoute64 ? kTile64 : route == kRoute128Wide ? kTile128Wide : kTile128;
-    return launch_gemm_small(A, (pretiled & 1) != 0, B, (pretiled & 2) != 0, C, c_is_bf16, ldc, amax_out, tile, s);
+    const SmallGemm one = {&A, &B, (pretiled & 1) != 0, (pretiled & 2) != 0, C, c_is_bf16, ldc, amax_out};
+    return launch_gemm_small(&one, 1, small_tile(route), s);
+}
+
+hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_bytes, hipStream_t s)
+{
+    Route r[2];
+    SmallGemm two[2];
+    bool small = true;
+    for (int i = 0; i < 2; ++i) {
+        if (c[i].A->rows == 0 || c[i].B->rows == 0 || (c[i].pretiled && c[i].A->cols % BK4 != 0)) { small = false; break; }
+        r[i] = route_of(*c[i].A, *c[i].B, ws, ws_bytes, c[i].pretiled);
+        small = small && r[i] != kRouteMain && !(r[i] == kRouteNoWorkspace && !c[i].pretiled);
+        two[i] = SmallGemm{c[i].A, c[i].B, (c[i].pretiled & 1) != 0, (c[i].pretiled & 2) != 0, c[i].C, c_is_bf16, c[i].ldc, nullptr};
+    }
+    if (small && small_tile(r[0]) == small_tile(r[1]) && (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0))
+        return launch_gemm_small(two, 2, small_tile(r[0]), s);
+    for (int i = 0; i < 2; ++i) {
+        const hipError_t e = launch_gemm(*c[i].A, *c[i].B, c[i].C, c_is_bf16, c[i].ldc, nullptr, ws, ws_bytes, s, c[i].pretiled);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace qii

@@ -300,14 +300,18 @@ __device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&
 }
 
 template <bool kBf16Out, class G, bool kAnyK>
-__global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_kernel(SmallArgs g)
+__global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_kernel(SmallArgs g0, SmallArgs g1, int n0_blocks)
 {
+    // one product, or two in one launch: the first n0_blocks blocks take g0, the others g1
+    const bool first = (int)blockIdx.x < n0_blocks;   // uniform
+    SmallArgs g = g0;
+    if (!first) g = g1;
     extern __shared__ __align__(16) uint8_t smem[];
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6), wm = wave % G::WM, kg = wave / G::WM;
     const int li = lane & 31, kb = lane >> 5;
     int tm, tn;
-    tile_coords((int)blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+    tile_coords((int)blockIdx.x - (first ? 0 : n0_blocks), g.tiles_m, g.tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * G::BM, n0 = (int64_t)tn * G::BN;
 
     Sources<G> src;
@@ -464,15 +468,20 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
 }
 
 template <bool kBf16Out, class G>
-hipError_t launch(SmallArgs g, hipStream_t s)
+hipError_t launch(SmallArgs *g, int count, hipStream_t s)
 {
-    g.tiles_m = (int)((g.M + G::BM - 1) / G::BM);
-    g.tiles_n = (int)((g.N + G::BN - 1) / G::BN);
-    const auto kern = g.K % BK != 0 ? gemm_small_kernel<kBf16Out, G, true> : gemm_small_kernel<kBf16Out, G, false>;
-    const hipError_t e = g.K % BK != 0 ? allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, true>>(G::kLds)
-                                       : allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, false>>(G::kLds);
+    int blocks = 0;
+    for (int i = 0; i < count; ++i) {
+        g[i].tiles_m = (int)((g[i].M + G::BM - 1) / G::BM);
+        g[i].tiles_n = (int)((g[i].N + G::BN - 1) / G::BN);
+        blocks += g[i].tiles_m * g[i].tiles_n;
+    }
+    const bool any = g[0].K % BK != 0;
+    const auto kern = any ? gemm_small_kernel<kBf16Out, G, true> : gemm_small_kernel<kBf16Out, G, false>;
+    const hipError_t e = any ? allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, true>>(G::kLds)
+                             : allow_dynamic_lds<gemm_small_kernel<kBf16Out, G, false>>(G::kLds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3((unsigned)(g.tiles_m * g.tiles_n)), dim3(G::kThreads), G::kLds, s, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(G::kThreads), G::kLds, s, g[0], g[count - 1], g[0].tiles_m * g[0].tiles_n);
     return hipGetLastError();
 }
 
@@ -483,19 +492,22 @@ ScaleView view(const qii_nvfp4 &t, bool tiled)
 
 }  // namespace
 
-hipError_t launch_gemm_small(const qii_nvfp4 &A, bool a_tiled, const qii_nvfp4 &B, bool b_tiled, void *C, int c_is_bf16, int64_t ldc,
-                             uint32_t *amax_out, SmallTile tile, hipStream_t s)
+hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipStream_t s)
 {
-    SmallArgs g;
-    g.a_codes = A.codes; g.b_codes = B.codes;
-    g.as = view(A, a_tiled); g.bs = view(B, b_tiled);
-    g.a_ts = A.tensor_scale; g.b_ts = B.tensor_scale;
-    g.M = A.rows; g.N = B.rows; g.K = A.cols;
-    g.C = C; g.ldc = ldc; g.amax_out = amax_out;
-    g.tiles_m = g.tiles_n = 0;   // (launch fills them in)
-    if (tile == kTile64) return c_is_bf16 ? launch<true, Geo<2, 2, 1, 4>>(g, s) : launch<false, Geo<2, 2, 1, 4>>(g, s);
-    if (tile == kTile128Wide) return c_is_bf16 ? launch<true, Geo<4, 4, 1, 4>>(g, s) : launch<false, Geo<4, 4, 1, 4>>(g, s);
-    return c_is_bf16 ? launch<true, Geo<2, 4, 2, 2>>(g, s) : launch<false, Geo<2, 4, 2, 2>>(g, s);
+    SmallArgs g[2];
+    for (int i = 0; i < count; ++i) {
+        const qii_nvfp4 &A = *c[i].A, &B = *c[i].B;
+        if ((A.cols % BK != 0) != (c[0].A->cols % BK != 0) || c[i].c_is_bf16 != c[0].c_is_bf16) return hipErrorInvalidValue;
+        g[i].a_codes = A.codes; g[i].b_codes = B.codes;
+        g[i].as = view(A, c[i].a_tiled); g[i].bs = view(B, c[i].b_tiled);
+        g[i].a_ts = A.tensor_scale; g[i].b_ts = B.tensor_scale;
+        g[i].M = A.rows; g[i].N = B.rows; g[i].K = A.cols;
+        g[i].C = c[i].C; g[i].ldc = c[i].ldc; g[i].amax_out = c[i].amax_out;
+    }
+    const int bf = c[0].c_is_bf16;
+    if (tile == kTile64) return bf ? launch<true, Geo<2, 2, 1, 4>>(g, count, s) : launch<false, Geo<2, 2, 1, 4>>(g, count, s);
+    if (tile == kTile128Wide) return bf ? launch<true, Geo<4, 4, 1, 4>>(g, count, s) : launch<false, Geo<4, 4, 1, 4>>(g, count, s);
+    return bf ? launch<true, Geo<2, 4, 2, 2>>(g, count, s) : launch<false, Geo<2, 4, 2, 2>>(g, count, s);
 }
 
 }  // namespace qii

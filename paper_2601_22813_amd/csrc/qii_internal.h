@@ -151,11 +151,27 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
 // whether launch_gemm, given a workspace and tiled scale bytes, would run the main kernel: only then is
 // it worth a quantizer's while to write the tiled copy
 bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K);
-// the same product by the small-tile kernels (gemm_small.hip): any K; each operand's scale bytes row-major
-// or, K a multiple of 256, tiled
+// products by the small-tile kernels (gemm_small.hip), one or two in one launch (with one result type, and K a
+// multiple of 256 in both or in neither): any K; each operand's scale bytes row-major or, K a multiple of 256, tiled
 enum SmallTile { kTile64, kTile128, kTile128Wide };
-hipError_t launch_gemm_small(const qii_nvfp4 &A, bool a_tiled, const qii_nvfp4 &B, bool b_tiled, void *C, int c_is_bf16, int64_t ldc,
-                             uint32_t *amax_out, SmallTile tile, hipStream_t s);
+struct SmallGemm {
+    const qii_nvfp4 *A, *B;
+    bool a_tiled, b_tiled;
+    void *C;
+    int c_is_bf16;
+    int64_t ldc;
+    uint32_t *amax_out;
+};
+hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipStream_t s);
+// two products whose operands are both ready: in one launch when they take the same small-tile kernel, else one
+// launch_gemm after the other (arguments as there, no maxima)
+struct GemmCall {
+    const qii_nvfp4 *A, *B;
+    void *C;
+    int64_t ldc;
+    int pretiled;
+};
+hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_bytes, hipStream_t s);
 
 // host-only test aids for the shared last round of the main GEMM kernel (gemm_sharing_map.h):
 // plan = {positions run one block per tile, shared tiles, sharing blocks}; the segments of a
