@@ -643,7 +643,9 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // partial tile (they are stored with plain stores, not streaming ones, and mostly still in cache).  Sharing is used where the model promises at least 7 %.  Measured on one
 // box, plain -> shared: 2048 x 2048 x 32768 600 -> 226, 3072 x 3072 x 16384 307 -> 267, 11264 x 2048 x
 // 16384 654 -> 573; 6144 x 2048 x 32768 would go 655 -> 618 for 112 MiB of partial tiles and 2048 x
-// 5632 x 16384 298 -> 320: both stay plain.
+// 5632 x 16384 298 -> 320: both stay plain.  (Those figures and the fit are from before the memory operations
+// were spread between the matrix instructions, which made a K tile 4 to 7 % faster, plain and shared alike; 2048 x 2048
+// products with K up to some 65000 now go to the small-tile kernels.)
 struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
@@ -746,14 +748,19 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 
 // Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to
 // event timings of every kernel over M x N = 64 x 64 .. 16384 x 2048 and K = 256 .. 16384 (bf16 results;
-// kt = K / 256, b = blocks / 256 compute units), for instance:
+// kt = K / 256, b = blocks / 256 compute units).  Measured on one box, each kernel forced in turn; the model takes
+// the fastest at each of these:
 //                         64 x 64   128 x 128 KG 2   128 x 128 (4, 4)   256 x 256 (with re-tiling)
-//    512 x  512 x   512       5.4              8.9              11.6     21.5
-//   1024 x 1024 x  4096      17.6             36.3              28.7     53.0 (shared last round)
-//   2048 x 2048 x  2048      24.5             22.8              21.6     47.6
-//   2048 x 2048 x 16384     150.4            135.0             110.8    135.8 (shared)
-//   4096 x 2048 x  2048      42.7             35.0              39.4     47.7
-//   4096 x 4096 x  4096     150.8            123.5             127.8    102.7
+//    512 x  512 x   512       8.9              9.4              12.1     20.4
+//   1024 x 1024 x  4096      17.5             36.8              29.2     44.8 (shared last round)
+//   2048 x 2048 x  2048      26.9             24.5              23.4     45.6
+//   2048 x 2048 x 16384     160.3            153.9             114.1    134.5 (shared)
+//   4096 x 2048 x  2048      46.9             38.2              43.6     47.5
+//   4096 x 2048 x  8192     157.4            131.2             120.9    133.1 (shared)
+//   2048 x 5632 x  2048      60.7             53.9              61.4     48.7
+//   4096 x 4096 x  1024      54.1             40.3              57.5     35.3
+//   4096 x 4096 x  4096     161.8            132.7             137.5    104.9
+//   2816 x 2048 x 16384     221.6            218.5             191.0    185.8 (shared)
 // 64 x 64 tiles: up to three blocks run on a unit and their time adds up from one block per unit on.
 // 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units

@@ -9,8 +9,8 @@
 // allow even where the block's tile is small.  The waves of a block therefore share K, not M and N: the
 // four 64-wide slices of a 256-wide K tile go to KG groups of waves, and the groups' accumulators are added
 // through LDS at the end, in a fixed order.
-//   128 x 128 block tile: 2 waves of 64 x 128 (MT, NT = 2, 4) per group, 2 groups (4 waves, two blocks
-//                         per compute unit) or 4 groups (8 waves, when there is one block per unit);
+//   128 x 128 block tile: 2 waves of 64 x 128 (MT, NT = 2, 4) per group, 2 groups (two blocks per compute unit);
+//                         or one wave of 128 x 128 (4, 4) per group, 4 groups (one block per unit);
 //   64 x 64 block tile:   one wave of 64 x 64 (2, 2) per group, 4 groups.
 //
 // Operands are staged through registers (global -> VGPR -> LDS): a tile is small enough for that (at
