@@ -761,11 +761,16 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 //   4096 x 4096 x  1024      54.1             40.3              57.5     35.3
 //   4096 x 4096 x  4096     161.8            132.7             137.5    104.9
 //   2816 x 2048 x 16384     221.6            218.5             191.0    185.8 (shared)
-// 64 x 64 tiles: up to three blocks run on a unit and their time adds up from one block per unit on.
+// 64 x 64 tiles: up to three blocks run on a unit and their time adds up, so the unit with the most blocks counts
+// (2176 x 1024 x 20992, 544 blocks: 140 us, 128 x 128 (4, 4) 116).
 // 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
 // work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan;
-// 3 us of launch and first loads, 4.5 of re-tiling where the scale bytes are not tiled yet.
+// 3 us of launch and first loads (a shared last round takes some 7 less than the plan's own, careful, figure: 512 x 128
+// x 26624 73 us, 64 x 64 tiles 79), 4.5 of re-tiling where the scale bytes are not tiled yet.
+// The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
+// 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 12.6 : 9.8 : 12.5 and 14.8 : 12.1 : 18.0, 4096 x 4096 41.0 : 22.3 : 13.7
+// and 49.7 : 28.7 : 20.9, 8192 x 8192 155 : 71 : 47 and 185 : 101 : 75.
 enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide };
 
 constexpr int64_t kMaxMainK = (int64_t)1 << 23;
@@ -776,14 +781,16 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool re
     const bool any = K % BK4 != 0;
     const double kt = (double)((K + BK4 - 1) / BK4), n64 = count(64), n128 = count(128), n256 = count(256);
     const double b64 = n64 > 256.0 ? n64 / 256.0 : 1.0, b = n128 > 256.0 ? n128 / 256.0 : 1.0;
-    const double us64 = 3.3 + 0.85 * b64 + (0.15 + 0.54 * b64) * kt * (any ? 1.3 : 1.0);
+    const double most64 = (double)(int64_t)((n64 + 255.0) / 256.0);
+    const double us64 = 3.3 + 0.85 * b64 + (0.15 + 0.54 * most64) * kt * (any ? 1.3 : 1.0);
     const double pairs = (double)(int64_t)(b / 2.0), last = b - 2.0 * pairs;
     const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.4 + 0.55 * last : 2.6 + 0.53 * last);
-    const double us128 = 4.0 + 1.7 * b + slope * kt * (any ? 1.25 : 1.0);
+    const double us128 = (any ? 5.0 : 4.0) + 1.7 * b + slope * kt * (any ? 1.25 : 1.0);
     const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
     const double us_wide = rounds * (8.3 + (1.15 + 0.45 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.17 : 1.0));
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full;
-    const double us_v2 = 8.0 + (full + (rem > 0.0 ? 1.0 : 0.0)) * 5.0 + (7.0 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.7 : 0.0)) * kt;
+    const double us_v2 = 3.0 + (full + (rem > 0.0 ? 1.0 : 0.0)) * 6.7 +
+                         (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0);
     Route best = kRoute64;
     double us = us64;
     auto offer = [&](Route r, double t) {
@@ -791,7 +798,10 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool re
     };
     offer(kRoute128, us128);
     offer(kRoute128Wide, us_wide);
-    if (main_ok) offer(kRouteMain, stream_plan(M, N, K).us + 3.0 + (retile ? 4.5 : 0.0));
+    if (main_ok) {
+        const StreamPlan plan = stream_plan(M, N, K);
+        offer(kRouteMain, plan.us + (plan.rem ? -4.0 : 3.0) + (retile ? 4.5 : 0.0));
+    }
     else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
     return best;
 }
