@@ -7,8 +7,8 @@
 // separate quantizer calls.
 //
 // A block takes one 128 x 128 tile: 16-byte loads along the rows (256 contiguous bytes per row)
-// into an LDS image, then the row part in the octet layout (a lane = one 16-element group of a
-// row, 4 rows per lane) and the column part in the quad layout (a lane quad = one 128-chunk of
+// into an LDS image, then four waves run the row part in the octet layout (a lane = one 16-element group
+// of a row, 4 rows per lane) and four the column part in the quad layout (a lane quad = one 128-chunk of
 // two columns), both reading the image.  LDS image: row r keeps its 4-byte word w (two bf16
 // columns) at word w ^ (8 (r / 32)): the column part's 64 lanes (rows 32 q + i for q = 0..3,
 // 16 consecutive words) then hit 32 different banks per half wave, and the row part's 32-byte
@@ -51,24 +51,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region(const void *base, int64
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
 
+// Eight waves: 0..3 take the rows, 4..7 the columns.  (Four waves that did the rows and then the columns left small
+// tensors bound by that chain and large ones with too few waves in flight: whole post hoc calls 512 x 512 13.2 -> 11.2 us,
+// 2048 x 2048 16.0 -> 13.9, 4096 x 4096 29.9 -> 26.8, 8192 x 4096 50.8 -> 48.9; Algorithm 1 17.2 -> 15.5, 20.5 -> 19.0,
+// 46.1 -> 43.2, 69.4 -> 65.3.)
 template <int kMode>
-__global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
+__global__ __launch_bounds__(512) void quantize_pair_kernel(PairArgs a)
 {
+
     __shared__ __align__(16) uint8_t tile[128 * 256];
     __shared__ float inv_r[128], inv_c[128];
     __shared__ float wave_m[2][4];
     const int t = threadIdx.x, lane = t & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wave_id = __builtin_amdgcn_readfirstlane(t >> 6), wave = wave_id & 3;
+    const bool take_rows = wave_id < 4;   // (wave-uniform)
     const int ty = (int)blockIdx.x / a.tiles_x, tx = (int)blockIdx.x - ty * a.tiles_x;
     const int64_t row0 = (int64_t)ty * 128, col0 = (int64_t)tx * 128;
 
-    // ---- the tile's loads first: 8 pieces of 16 bytes per thread, 16 threads per row
-    u32x4 w[8];
+    // ---- the tile's loads first: 4 pieces of 16 bytes per thread, 16 threads per row
+    u32x4 w[4];
     {
         const __amdgpu_buffer_rsrc_t src = region(a.x + row0 * a.ld + col0, (127 * a.ld + 128) * 2);
         const uint32_t voff = (uint32_t)(((t >> 4) * a.ld + (t & 15) * 8) * 2);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (int)(i * 16 * a.ld * 2), 0);
+        for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (int)(i * 32 * a.ld * 2), 0);
     }
 
     // ---- tensor constants and reciprocal tables of the two sides while the loads are in flight
@@ -82,13 +88,13 @@ __global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
         }
         const uint32_t b = t & 127;
         const float x32 = t < 128 ? tcr.x32 : tcc.x32;
-        (t < 128 ? inv_r : inv_c)[b] = b == 0u ? 0.0f : 1.0f / (e4m3_decode(b) * x32);
+        if (t < 256) (t < 128 ? inv_r : inv_c)[b] = b == 0u ? 0.0f : 1.0f / (e4m3_decode(b) * x32);
     }
 
     // ---- LDS image (swizzled, see the file header)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int r = (t >> 4) + 16 * i, p = (t & 15) ^ (2 * (r >> 5));
+    for (int i = 0; i < 4; ++i) {
+        const int r = (t >> 4) + 32 * i, p = (t & 15) ^ (2 * (r >> 5));
         *reinterpret_cast<u32x4 *>(tile + r * 256 + p * 16) = w[i];
     }
     __syncthreads();
@@ -97,7 +103,7 @@ __global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
 
     // ---- row part: Q(x).  quad = 4 consecutive rows of the tile (one draw call serves them);
     // the 8 lanes of an octet own the 8 groups of those rows inside the tile
-    {
+    if (take_rows) {
         const OctetLane L = octet_lane(lane, a.r.sign);
         uint32_t mask[8];
         make_masks<true>(L.sign16, mask);
@@ -141,7 +147,7 @@ __global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
 
     // ---- column part: Q(x^T).  The tile is chunk `ty` of the columns' 128-chunks; wave w takes the
     // tile's columns 32 w .. 32 w + 31, a lane quad two of them, lane q of the quad rows 32 q .. 32 q + 31
-    {
+    if (!take_rows) {
         const int q = lane & 3, jp = lane >> 2;
         const uint8_t *src = tile + (32 * q) * 256 + 4 * ((16 * wave + jp) ^ (8 * q));
         uint32_t raw[32];
@@ -195,7 +201,7 @@ __global__ __launch_bounds__(256) void quantize_pair_kernel(PairArgs a)
     if (kMode == QII_MS_EDEN_PH && (a.r.amax_out || a.c.amax_out)) {   // uniform
         m_r = wave_max(m_r);
         m_c = wave_max(m_c);
-        if (lane == 0) { wave_m[0][wave] = m_r; wave_m[1][wave] = m_c; }
+        if (lane == 0) wave_m[take_rows ? 0 : 1][wave] = take_rows ? m_r : m_c;
         __syncthreads();
         if (t < 2) {
             uint32_t *out = t == 0 ? a.r.amax_out : a.c.amax_out;
@@ -329,7 +335,7 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
         out[i]->codes = in[i]->codes; out[i]->scales = in[i]->scales; out[i]->tensor_scale = in[i]->tensor_scale;
         out[i]->tbuf = in[i]->tbuf; out[i]->amax_out = in[i]->amax_accum;
     }
-    const dim3 grid((unsigned)((p.rows / 128) * (p.cols / 128))), block(256);
+    const dim3 grid((unsigned)((p.rows / 128) * (p.cols / 128))), block(512);
     if (p.mode == QII_MS_EDEN_PH) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN_PH>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN>), grid, block, 0, s, a);
     return hipGetLastError();
