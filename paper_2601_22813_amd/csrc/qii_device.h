@@ -67,6 +67,14 @@ __device__ __forceinline__ void store_codes16(uint8_t *dst, uint32_t c0, uint32_
 __device__ __forceinline__ uint32_t f2u(float f) { return __float_as_uint(f); }
 __device__ __forceinline__ float u2f(uint32_t u) { return __uint_as_float(u); }
 
+// ---------------------------------------------------------------- running maximum
+// (non-negative floats order like their bit patterns)
+__device__ __forceinline__ void max_to_global(float m, uint32_t *amax_bits)
+{
+    // the running maximum only grows, so a stale read can only cause a redundant atomic
+    if (f2u(m) > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, f2u(m));
+}
+
 // ---------------------------------------------------------------- E4M3 (scales, >= 0)
 // decode: the byte placed in bits 27..20 of a binary32 is the same number with
 // exponent bias 127 instead of 7 (subnormals included), so one exact scaling by 2^120

@@ -259,12 +259,6 @@ __device__ __forceinline__ uint32_t *amax_spread_word(uint32_t *region, uint32_t
     return region + (block_index & (kAmaxSpread - 1)) * kAmaxStrideWords;
 }
 
-__device__ __forceinline__ void max_to_global(float m, uint32_t *amax_bits)
-{
-    // the running maximum only grows, so a stale read can only cause a redundant atomic
-    if (f2u(m) > __atomic_load_n(amax_bits, __ATOMIC_RELAXED)) atomicMax(amax_bits, f2u(m));
-}
-
 // A block's maximum at the end of a heavy pass: into a word of its own (words != 0; at most kMaxBlockWords
 // blocks, nothing has to be cleared first), else into the spread running maximum.  The scales pass reads every
 // word in every block: up to 1024 words that costs less than the clearing launch, at 4096 as much.
