@@ -335,6 +335,11 @@ void qii_gemm_sharing_plan(int64_t M, int64_t N, int64_t K, int32_t plan[3]);
 int qii_gemm_sharing_segments(int rem, int ktotal, int grid, int block_id, int32_t *out);
 void qii_gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t out[2]);
 
+/* Test aids for rules that pick a kernel (host computations, no device work).
+ * qii_absmax_takes_tiles: whether max |rotated x| along the columns of a contiguous bf16 matrix x of
+ *   rows x cols, both multiples of 128, is measured by 128 x 128 tiles.                     */
+int qii_absmax_takes_tiles(int64_t rows, int64_t cols);
+
 /* Host helpers.                                                                        */
 uint64_t qii_derive_seed(uint64_t seed, uint32_t i); /* backward sub-seed i (0..5)      */
 const char *qii_status_string(qii_status s);

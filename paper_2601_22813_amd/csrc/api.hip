@@ -795,6 +795,11 @@ void qii_gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t 
     qii::gemm_sharing_tile_slots(rem, ktotal, grid, lt, out);
 }
 
+int qii_absmax_takes_tiles(int64_t rows, int64_t cols)
+{
+    return rows > 0 && cols > 0 && rows % 128 == 0 && cols % 128 == 0 && qii::absmax_tiles_pay(rows, cols);
+}
+
 qii_status qii_selftest_conversions(uint64_t *counts, void *stream)
 {
     if (!counts || !aligned(counts, 8)) return fail(QII_INVALID_ARG, "counts must be 8 device uint64, 8-byte aligned");

@@ -341,17 +341,31 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
     return hipGetLastError();
 }
 
-// max |rotated| along the columns and, amax_r not null, along the rows of a matrix that pair_kernel_applies to; the
-// words must hold 0
-// Along the columns alone, 513 to 1024 tiles leave units idle (640 tiles, 4096 x 2560: 21.8 us against 19.6 of the
-// columns kernel's pass; 1024 tiles 25.6 : 24.2, but 256 16.0 : 16.4, 1280 35.3 : 36.6, 4096 67 : 75, each with the
-// quantizer).
+// Along the columns alone: the tile kernel or absmax_cols_kernel (quantize_cols.hip).  The tile kernel works in rounds of 1024
+// tiles (four a block, a block per unit), so a round with few tiles costs as much as a full one; below one round it has fewer
+// waves in flight than the other.  The other reads 64-byte pieces of a source row, and fetches a line twice unless
+// neighbouring column blocks run on one die (`local`: the number of its row blocks is a multiple of 8, or its stripe order
+// applies).  Whole MS-EDEN calls, us, columns kernel : tile kernel, on one box:
+//   128 tiles  1024 x 2048 13.0 : 12.5            4096 x  512 (local) 13.0 : 12.5   128 x 16384 (local) 15.5 : 11.8
+//   256 tiles  2048 x 2048 14.6 : 15.7            4096 x 1024 (local) 14.5 : 14.2   512 x  8192 (local) 14.6 : 15.0
+//   512 tiles  4096 x 2048 (local) 17.0 : 18.8    1024 x 8192 (local) 17.3 : 17.5
+//  1088 tiles  8704 x 2048 34.7 : 36.0            2176 x 8192 (local) 25.9 : 30.2
+//  1280 tiles 10240 x 2048 38.0 : 36.0            4096 x 5120 (local) 27.5 : 32.6
+//  1792 tiles  7168 x 4096 47.2 : 41.7           28672 x 1024 (local) 34.2 : 35.3
+//  2048 tiles                                     4096 x 8192 (local) 41.1 : 37.5
+//  2112 and 2176 tiles  8448 x 4096 52.8 : 49.1  2176 x 16384 (local) 42.8 : 44.6
+//  2560 tiles 10240 x 4096 61.0 : 52.9            5120 x 8192 (local) 47.5 : 45.2
 bool absmax_tiles_pay(int64_t rows, int64_t cols)
 {
     const int64_t tiles = (rows / 128) * (cols / 128);
-    return tiles <= 512 || tiles > 1024;
+    if (tiles <= 128) return true;
+    const bool local = ((rows + 511) / 512) % 8 == 0 || (cols + 31) / 32 % 256 == 0;
+    if (!local) return tiles >= 1280;
+    return (tiles > 1792 && tiles <= 2048) || tiles >= 2560;
 }
 
+// max |rotated| along the columns and, amax_r not null, along the rows of a matrix that pair_kernel_applies to; the
+// words must hold 0
 hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, uint64_t seed_rht_r, float *amax_r, uint64_t seed_rht_c,
                                float *amax_c, hipStream_t s)
 {

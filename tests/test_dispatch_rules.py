@@ -1,0 +1,32 @@
+"""Rules that pick between two kernels for one call, against the faster of the two as measured (host computations of the library,
+no device work)."""
+import os
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def libqii():
+    from paper_2601_22813_amd import binding, build
+    if not os.path.exists(binding.LIB_PATH):
+        build.build(force=True)
+    return binding
+
+
+# whole MS-EDEN calls along the columns of a bf16 matrix, us: abs-max by column blocks, by 128 x 128 tiles; shapes where the
+# two differ by more than their repeated runs do
+ABSMAX_US = {
+    (128, 8192): (12.7, 10.8), (1024, 2048): (13.0, 12.5), (4096, 512): (13.0, 12.5), (128, 16384): (15.5, 11.8),
+    (3328, 1024): (12.8, 14.3), (2048, 2048): (14.6, 15.7), (896, 8192): (15.8, 17.9), (4096, 2048): (17.0, 18.8),
+    (8320, 2048): (32.9, 35.6), (8704, 2048): (34.7, 36.0), (2176, 8192): (25.9, 30.2), (1152, 16384): (27.8, 32.4),
+    (3712, 5120): (26.9, 32.5), (4096, 5120): (27.5, 32.6), (20480, 1024): (27.3, 31.5), (3712, 6144): (31.3, 35.0),
+    (28672, 1024): (34.2, 35.3), (2176, 16384): (42.8, 44.6), (5376, 4096): (39.8, 36.8), (10240, 2048): (38.0, 36.0),
+    (22528, 1024): (43.0, 37.6), (6144, 5120): (51.8, 43.4), (4096, 8192): (41.1, 37.5), (8448, 4096): (52.8, 49.1),
+    (5120, 8192): (47.5, 45.2), (10240, 4096): (61.0, 52.9), (8192, 8192): (66.0, 62.6),
+}
+
+
+@pytest.mark.parametrize("rows,cols", ABSMAX_US)
+def test_the_faster_abs_max_pass_along_columns(libqii, rows, cols):
+    columns, tiles = ABSMAX_US[rows, cols]
+    assert bool(libqii.lib().qii_absmax_takes_tiles(rows, cols)) == (tiles < columns)

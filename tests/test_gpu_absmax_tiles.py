@@ -1,7 +1,8 @@
 """Rotated abs-max by 128 x 128 tiles (along the columns, and along both orientations for Algorithm 1's pair): bit for
-bit the oracle's maximum where the tile kernel can go wrong: one tile, fewer tiles than a block has wave groups, tile
-counts that leave some groups without a tile in the last round, more rounds than one, a leading dimension beyond the row
-whose extra columns are huge, and a maximum that sits in the last tile."""
+bit the oracle's maximum where the tile kernel can go wrong: one tile, fewer tiles than a block has wave groups, a
+tile count that leaves some groups without a tile in the last of two rounds (4480 x 5248; at 1280 x 6656 and 4224 x 4352
+qii_absmax takes the columns kernel), a leading dimension beyond the row whose extra columns are huge, and a maximum that
+sits in the last tile."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ from gpu_util import assert_nv_equal, to_dev, ws
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rows,cols", [(128, 128), (128, 384), (640, 384), (256, 1152), (1280, 6656), (4224, 4352)])
+@pytest.mark.parametrize("rows,cols", [(128, 128), (128, 384), (640, 384), (256, 1152), (1280, 6656), (4224, 4352), (4480, 5248)])
 def test_rotated_abs_max_by_tiles(oracle, rows, cols):
     x = synth.student_t_bf16((rows, cols), 3, 0.1, seed=rows + cols)
     x[rows - 128:, cols - 128:] = synth.normal_bf16((128, 128), 5.0, 3)   # the largest values in the last tile
