@@ -55,7 +55,8 @@ struct QuantizeArgs {
     // bytes apart, a region of 16 KiB) at amax_accum (nullable: the caller supplies the maximum itself); launch_posthoc_scales finishes
     float *tbuf;
     uint32_t *amax_accum;
-    int amax_words = 0;      // != 0: one word per block at amax_accum instead (posthoc_words, requant_blocks)
+    int amax_words = 0;      // != 0: one word per block at amax_accum instead (posthoc_words, requant_blocks); in the other
+                             // modes: words at amax whose maximum is the tensor's (requant_amax_words)
     // a second copy of the scale bytes in the main GEMM kernel's tiled layout (nullable; only where
     // rows_kernels_apply, no rotation, C a multiple of 256; room for R rounded up to 256 rows)
     uint8_t *scales_tiled = nullptr;
@@ -135,8 +136,11 @@ hipError_t launch_quantize_cols(const QuantizeArgs &a, hipStream_t s);
 bool requant_kernels_apply(const Source &src, int64_t R, int64_t C);
 // (one or two tensors in one launch, quantized in the same mode; requant_blocks: blocks of tensor i of such a launch)
 int requant_blocks(const int64_t *R, const int64_t *C, int count, int i);
+// words: one word per block at amax (one tensor, requant_amax_words of them), else one word that must hold 0
 hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int64_t *C, int rht, const uint64_t *seed_rht,
-                                 float *const *amax, int count, hipStream_t s);
+                                 float *const *amax, int count, hipStream_t s, int words = 0);
+// words that the blocks of the abs-max pass over one such tensor leave: at most 64 (a 256-byte slot), else 0
+int requant_amax_words(const Source &src, int64_t R, int64_t C);
 hipError_t launch_quantize_requant(const QuantizeArgs *a, int count, hipStream_t s);
 // ws (nullable): gemm_workspace_bytes(M, N, K) bytes, 16-byte aligned, for the re-tiled scale
 // bytes of the fast kernel; without it a slower kernel reads the row-major scales directly

@@ -30,12 +30,12 @@ struct RequantArgs {
     int64_t R, C;        // logical shape: R = stored columns (output rows), C = stored rows
     uint32_t sign[4];
     uint64_t seed_sr;
-    const float *amax;
+    const float *amax;   // the tensor maximum (words == 0), or that of the `words` words the abs-max kernel's blocks left
     uint8_t *codes;
     uint8_t *scales;
     float *tensor_scale;
-    uint32_t *amax_out;  // abs-max kernel (one word), heavy pass of the post hoc scheme (nullable there): the spread words,
-    int words;           // or, words != 0, one word per block
+    uint32_t *amax_out;  // abs-max kernel (one running word), heavy pass of the post hoc scheme (nullable there): the spread
+    int words;           // words; or, words != 0, one word per block
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
     int tiles_x;         // tiles along a stored row
     int tiles;
@@ -174,8 +174,10 @@ __global__ __launch_bounds__(256 * kChunks) void requantize_cols_kernel(RequantA
     RawTile raw;
     load_tile<kChunks>(raw, a, chunk0, col0);
     // (the heavy pass of the post hoc scheme knows no tensor maximum: tc stays unused there)
-    const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{} : tensor_consts(kMode, *a.amax);
+    TensorConsts tc = TensorConsts{};
     if (kMode != QII_MS_EDEN_PH) {
+        const float amax = a.words ? wave_max(lane < a.words ? a.amax[lane] : 0.0f) : *a.amax;   // uniform
+        tc = tensor_consts(kMode, amax);
         if (block == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
         fill_inv_table(inv_tab, tc);
     }
@@ -277,7 +279,8 @@ __global__ __launch_bounds__(256 * kChunks) void requantize_absmax_kernel(Requan
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 1; i < 4 * kChunks; ++i) m = fmaxf(m, wave_m[i]);
-        max_to_global(m, a.amax_out);
+        if (a.words) a.amax_out[block] = f2u(m);
+        else max_to_global(m, a.amax_out);
     }
 }
 
@@ -322,13 +325,20 @@ bool requant_kernels_apply(const Source &src, int64_t R, int64_t C)
            ((R + 127) / 128) * (C / 128) < ((int64_t)1 << 31);
 }
 
+int requant_amax_words(const Source &src, int64_t R, int64_t C)
+{
+    if (!requant_kernels_apply(src, R, C)) return 0;
+    const int n = requant_blocks(&R, &C, 1, 0);
+    return n <= 64 ? n : 0;
+}
+
 int requant_blocks(const int64_t *R, const int64_t *C, int count, int i)
 {
     return (int)tiles_of(R[i], C[i], chunks_per_block(R, C, count));
 }
 
 hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int64_t *C, int rht, const uint64_t *seed_rht,
-                                 float *const *amax, int count, hipStream_t s)
+                                 float *const *amax, int count, hipStream_t s, int words)
 {
     const int ch = chunks_per_block(R, C, count);
     RequantArgs a[2];
@@ -336,6 +346,7 @@ hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int6
     for (int i = 0; i < count; ++i) {
         a[i] = make_args(src[i], R[i], C[i], seed_rht[i], 0, ch);
         a[i].amax_out = reinterpret_cast<uint32_t *>(amax[i]);
+        a[i].words = words;
         all += a[i].tiles;
     }
     // at most 512 blocks, shared out by size
