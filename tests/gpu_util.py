@@ -1,4 +1,6 @@
 """Helpers of the GPU parity tests: numpy <-> device tensors, NVFP4 containers."""
+import statistics
+
 import numpy as np
 import torch
 
@@ -37,3 +39,19 @@ def ws(nbytes: int) -> torch.Tensor:
 
 def bf16_to_f64(t: torch.Tensor) -> np.ndarray:
     return t.float().cpu().numpy().astype(np.float64)
+
+
+def median_us(call, passes=20):
+    """A pass of `call` among others, by events: the median of 7 runs."""
+    call()
+    torch.cuda.synchronize()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    out = []
+    for _ in range(7):
+        a.record()
+        for _ in range(passes):
+            call()
+        b.record()
+        torch.cuda.synchronize()
+        out.append(a.elapsed_time(b) / passes * 1e3)
+    return statistics.median(out)

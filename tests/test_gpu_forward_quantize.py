@@ -9,7 +9,7 @@ import torch
 from paper_2601_22813_amd import binding as qii
 from paper_2601_22813_amd import synth
 
-from gpu_util import assert_nv_equal, to_dev, ws
+from gpu_util import assert_nv_equal, median_us, to_dev, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,22 @@ def test_forward_operands_from_two_launches(oracle, T, d_in, d_out, f32):
                 qii.qii_linear_fwd_mode(X, W, mode, Y, Xq, Wq, w, amax_x=px, amax_w=pw)
                 assert_nv_equal(Xq, oXq, "X")
                 assert_nv_equal(Wq, oWq, "W")
+
+
+@pytest.mark.parametrize("T,d_in,mode,f32", [(16384, 3072, qii.RTN_46, True), (16384, 4096, qii.RTN_46, False)])
+def test_quantizing_in_the_forward_pass_costs_no_more_than_alone(T, d_in, mode, f32):
+    """A layer of one group of outputs is its quantizer: the pass beside the quantizer's own call and the product.  A block that
+    waits for its rows before it reduces the maximum's words makes the quantize launch a quarter to a third longer: the pass
+    then took 1.13 and 1.17 times as long as the two calls, 0.99 times without that wait."""
+    g = torch.Generator(device="cuda").manual_seed(6)
+    X = torch.randn((T, d_in), device="cuda", generator=g)
+    W = torch.randn((16, d_in), device="cuda", generator=g)
+    if not f32:
+        X, W = X.bfloat16(), W.bfloat16()
+    Xq, Wq, Y = qii.NVFP4Tensor.empty(T, d_in), qii.NVFP4Tensor.empty(16, d_in), torch.empty((T, 16), device="cuda")
+    w = ws(max(qii.qii_linear_fwd_workspace_bytes(T, d_in, 16), qii.qii_gemm_workspace_bytes(T, 16, d_in)))
+    whole = median_us(lambda: qii.qii_linear_fwd_mode(X, W, mode, Y, Xq, Wq, w))
+    alone = median_us(lambda: qii.qii_quantize_nvfp4(X, False, mode, 0, 0, 0, None, Xq, w))
+    product = median_us(lambda: qii.qii_gemm_nvfp4(Xq, Wq, Y, w))
+    print(f"{T}x{d_in} mode {mode} f32 {f32}: forward {whole:.1f} us, quantizer {alone:.1f}, product {product:.1f}", flush=True)
+    assert whole <= 1.08 * (alone + product)

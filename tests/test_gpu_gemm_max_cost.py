@@ -1,31 +1,14 @@
 """max |C| as a by-product of the GEMM costs little beside the product, also where the product is cut into thousands of small
 tiles: atomics on the one result word are resolved one after the other, so one per wave of a 128 x 128 or 64 x 64 tile
 would take longer than the product.  The value is the largest stored |C| (also checked with ragged tiles)."""
-import statistics
-
 import pytest
 import torch
 
 from paper_2601_22813_amd import binding as qii
 
-from gpu_util import ws
+from gpu_util import median_us, ws
 
 pytestmark = pytest.mark.gpu
-
-
-def median_us(call, passes=20):
-    call()
-    torch.cuda.synchronize()
-    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    out = []
-    for _ in range(7):
-        a.record()
-        for _ in range(passes):
-            call()
-        b.record()
-        torch.cuda.synchronize()
-        out.append(a.elapsed_time(b) / passes * 1e3)
-    return statistics.median(out)
 
 
 @pytest.mark.parametrize("M,N,K", [(20000, 3000, 112), (25683, 304, 864), (11790, 2272, 304)])
