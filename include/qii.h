@@ -187,9 +187,10 @@ qii_status qii_dequantize_nvfp4(const qii_nvfp4 *in, float *y, void *stream);
  * take the fast kernel, which first copies the scale bytes into a tile-contiguous layout and, when the
  * number of 256 x 256 output tiles leaves the last round of the grid mostly idle, shares those
  * tiles between blocks (f32 partial tiles in ws, added in a fixed order: results do not depend on
- * timing).  Small products and every other K take kernels with smaller tiles that need no ws.  Without ws
- * large products take a slower kernel; with a ws too small for the partial tiles, one block per tile.
- * Either way every product is formed exactly and accumulated in f32.
+ * timing).  Small products and every other K take kernels with smaller tiles that use no ws
+ * (the query does not look at that: its size is what the fast kernel would need).  Without ws
+ * large products take a slower kernel; a ws too small for the partial tiles is used for one block per tile where that
+ * is faster than the kernels that need none.  Either way every product is formed exactly and accumulated in f32.
  * errors: QII_INVALID_ARG / QII_BAD_SHAPE before anything is launched; C is then untouched. */
 qii_status qii_gemm_nvfp4(const qii_nvfp4 *A, const qii_nvfp4 *B, void *C, qii_dtype c_dt,
                           int64_t ldc, void *ws, size_t ws_bytes, void *stream);
@@ -339,6 +340,11 @@ void qii_gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t 
  * qii_absmax_takes_tiles: whether max |rotated x| along the columns of a contiguous bf16 matrix x of
  *   rows x cols, both multiples of 128, is measured by 128 x 128 tiles.                     */
 int qii_absmax_takes_tiles(int64_t rows, int64_t cols);
+/* qii_gemm_route: the kernel that a GEMM of M x N x K takes when its workspace has ws_bytes (0: none given): 0 the
+ *   256 x 256 kernel that uses the workspace, 1 the 256 x 256 kernel without one, 2 tiles of 64 x 64, 3 of 128 x 128 in
+ *   two K groups, 4 of 128 x 128 in four; -1 for sizes the GEMM refuses.  tiled != 0 (K a multiple of 256): both operands'
+ *   scale bytes are already in the tiled layout, as in the layer passes.                                            */
+int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
 
 /* Host helpers.                                                                        */
 uint64_t qii_derive_seed(uint64_t seed, uint32_t i); /* backward sub-seed i (0..5)      */

@@ -28,7 +28,7 @@ EXPORTS = [
     "qii_quantize_nvfp4_noalloc", "qii_gemm_nvfp4_amax", "qii_linear_fwd_amax",
     "qii_quantize_pair_nvfp4", "qii_quantize_pair_workspace_bytes",
     "qii_gemm_sharing_plan", "qii_gemm_sharing_segments", "qii_gemm_sharing_tile_slots",
-    "qii_absmax_takes_tiles",
+    "qii_absmax_takes_tiles", "qii_gemm_route",
 ]
 
 
@@ -94,6 +94,8 @@ def lib() -> ctypes.CDLL:
                      "qii_linear_bwd_workspace_bytes"):
             getattr(L, name).argtypes = [i64, i64, i64]
             getattr(L, name).restype = sz
+        L.qii_gemm_route.argtypes = [i64, i64, i64, sz, c.c_int]
+        L.qii_gemm_route.restype = c.c_int
         L.qii_absmax_takes_tiles.argtypes = [i64, i64]
         L.qii_absmax_takes_tiles.restype = c.c_int
         L.qii_selftest_conversions.argtypes = [vp, vp]

@@ -802,6 +802,11 @@ void qii_gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t 
     qii::gemm_sharing_tile_slots(rem, ktotal, grid, lt, out);
 }
 
+int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
+{
+    return M <= 0 || N <= 0 || K <= 0 || K % 16 != 0 || (tiled && K % 256 != 0) ? -1 : qii::gemm_route(M, N, K, ws_bytes, tiled);
+}
+
 int qii_absmax_takes_tiles(int64_t rows, int64_t cols)
 {
     return rows > 0 && cols > 0 && rows % 128 == 0 && cols % 128 == 0 && qii::absmax_tiles_pay(rows, cols);

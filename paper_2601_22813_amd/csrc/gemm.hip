@@ -653,7 +653,8 @@ struct StreamPlan {
     double us;  // modelled time of the main kernel (and the second one), without the re-tiling launch
 };
 
-static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
+// (share = false: one block per tile, as where the workspace has no room for the partial tiles)
+static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K, bool share = true)
 {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), ktiles = K / BK4;
     const int64_t rounds = tiles / 256, rem = tiles % 256;
@@ -661,7 +662,7 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K)
     const double kt_us = 4.6 + (rem > 176 ? 1.2 * (double)(rem - 176) / 80.0 : 0.0);
     const double plain_us = full_us + (rem ? kt_us * (double)ktiles + 5.0 : 0.0);
     StreamPlan plan{(int)tiles, 0, 0, plain_us};
-    if (K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8 || rem == 0) return plan;
+    if (!share || K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8 || rem == 0) return plan;
     const int64_t units = rem * ktiles;
     int64_t grid = units / 4 < 256 ? units / 4 : 256;
     if (grid >= 8) grid &= ~(int64_t)7;
@@ -683,12 +684,24 @@ static size_t scales_workspace_bytes(int64_t M, int64_t N, int64_t K)
     return (size_t)((mp + np) * (K / 16));
 }
 
+// where the partial tiles begin: behind the re-tiled scales, 256-byte aligned
+static size_t partial_offset(int64_t M, int64_t N, int64_t K) { return (scales_workspace_bytes(M, N, K) + 255) / 256 * 256; }
+
+static size_t plan_bytes(int64_t M, int64_t N, int64_t K, const StreamPlan &plan)
+{
+    return plan.rem ? partial_offset(M, N, K) + (size_t)(plan.grid + plan.rem) * BM * BN * 4 : scales_workspace_bytes(M, N, K);
+}
+
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
-    if (K % BK4 != 0) return 0;
+    return K % BK4 != 0 ? 0 : plan_bytes(M, N, K, stream_plan(M, N, K));
+}
+
+// the plan that a workspace of ws_bytes (at least the scales) has room for
+static StreamPlan plan_that_fits(int64_t M, int64_t N, int64_t K, size_t ws_bytes)
+{
     const StreamPlan plan = stream_plan(M, N, K);
-    const size_t sc = scales_workspace_bytes(M, N, K);
-    return plan.rem ? (sc + 255) / 256 * 256 + (size_t)(plan.grid + plan.rem) * BM * BN * 4 : sc;
+    return ws_bytes >= plan_bytes(M, N, K, plan) ? plan : stream_plan(M, N, K, false);
 }
 
 // test aids (host only): the sharing plan of a shape and the mapping the kernels use
@@ -775,7 +788,8 @@ enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide }
 
 constexpr int64_t kMaxMainK = (int64_t)1 << 23;
 
-static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool retile)
+// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run
+static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
     const bool any = K % BK4 != 0;
@@ -798,8 +812,8 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool re
     };
     offer(kRoute128, us128);
     offer(kRoute128Wide, us_wide);
-    if (main_ok) {
-        const StreamPlan plan = stream_plan(M, N, K);
+    if (main_ws) {
+        const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
         offer(kRouteMain, plan.us + (plan.rem ? -4.0 : 3.0) + (retile ? 4.5 : 0.0));
     }
     else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
@@ -808,7 +822,7 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, bool main_ok, bool re
 
 bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
 {
-    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && choose_route(M, N, K, true, false) == kRouteMain;
+    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && choose_route(M, N, K, gemm_workspace_bytes(M, N, K), false) == kRouteMain;
 }
 
 // whether the main kernel can run, and the route, for operands and a workspace as launch_gemm has them
@@ -821,7 +835,14 @@ static Route route_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, si
     // (K: offsets within a tile's rows stay below 2^31)
     const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= scales_workspace_bytes(M, N, K) &&
                          (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
-    return choose_route(M, N, K, main_ok, !(pretiled & 5) || !(pretiled & 10));
+    return choose_route(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10));
+}
+
+int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
+{
+    const qii_nvfp4 a = {nullptr, nullptr, nullptr, M, K}, b = {nullptr, nullptr, nullptr, N, K};
+    // (a stand-in address: the route looks at its alignment)
+    return (int)route_of(a, b, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
 }
 
 static SmallTile small_tile(Route route) { return route == kRoute64 ? kTile64 : route == kRoute128Wide ? kTile128Wide : kTile128; }
@@ -838,7 +859,6 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     }
     if (M == 0 || N == 0) return hipSuccess;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    const size_t need = K % BK4 == 0 ? scales_workspace_bytes(M, N, K) : 0;
     const Route route = route_of(A, B, ws, ws_bytes, pretiled);
     uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
     uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
@@ -847,10 +867,8 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
         const uint8_t *b_tiled = (pretiled & 2) ? B.scales : b_ws;
         // the tiles of an incomplete last round are shared between blocks when the caller's workspace
         // has room for their partial tiles (behind the scales, 256-byte aligned)
-        StreamPlan plan = stream_plan(M, N, K);
-        const size_t poff = (need + 255) / 256 * 256;
-        if (plan.rem && ws_bytes < poff + (size_t)(plan.grid + plan.rem) * BM * BN * 4) plan = StreamPlan{(int)(tiles_m * tiles_n), 0, 0, 0.0};
-        float *partial = plan.rem ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(ws) + poff) : nullptr;
+        const StreamPlan plan = plan_that_fits(M, N, K, ws_bytes);
+        float *partial = plan.rem ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(ws) + partial_offset(M, N, K)) : nullptr;
         // (an operand whose scales arrive tiled takes no part: zero rows)
         const int64_t ma = (pretiled & 5) ? 0 : M, nb_rows = (pretiled & 10) ? 0 : N;
         const int64_t na = ma * (K / 256), nb = nb_rows * (K / 256);

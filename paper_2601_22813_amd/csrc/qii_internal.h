@@ -184,6 +184,8 @@ hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_
 void gemm_sharing_plan(int64_t M, int64_t N, int64_t K, int32_t plan[3]);
 int gemm_sharing_segments(int rem, int ktotal, int grid, int block_id, int32_t *out);
 void gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t out[2]);
+// the kernel that launch_gemm would run: see qii_gemm_route
+int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
 
 // sweeps of the hardware conversions and short division sequences against their value-space
 // rules; counts[0..7] (device) receive the numbers of mismatches (selftest.hip)

@@ -30,3 +30,31 @@ ABSMAX_US = {
 def test_the_faster_abs_max_pass_along_columns(libqii, rows, cols):
     columns, tiles = ABSMAX_US[rows, cols]
     assert bool(libqii.lib().qii_absmax_takes_tiles(rows, cols)) == (tiles < columns)
+
+
+MAIN, NO_WORKSPACE, T64, T128, T128_WIDE = range(5)
+
+
+def scales_bytes(M, N, K):
+    return ((M + 255) // 256 * 256 + (N + 255) // 256 * 256) * (K // 16)
+
+
+@pytest.mark.parametrize("M,N,K", [(512, 128, 26624), (300, 520, 30720), (256, 256, 32768), (2816, 2048, 16384), (8448, 2048, 8192)])
+def test_a_route_is_priced_for_the_workspace_it_has(libqii, M, N, K):
+    """These products share the tiles of their last round between blocks, partial tiles in the workspace.  Where that holds the
+    scales only, the main kernel would run one block per tile (512 x 128 x 26624: 433 us; 64 x 64 tiles 78, shared 70)."""
+    L = libqii.lib()
+    full = libqii.qii_gemm_workspace_bytes(M, N, K)
+    assert full > scales_bytes(M, N, K)
+    assert L.qii_gemm_route(M, N, K, full, 0) == MAIN
+    for too_small in (scales_bytes(M, N, K), full - 256):
+        assert L.qii_gemm_route(M, N, K, too_small, 0) == L.qii_gemm_route(M, N, K, 0, 0) != MAIN
+
+
+def test_routes_of_refused_and_smallest_sizes(libqii):
+    L = libqii.lib()
+    for bad in ((0, 8, 16, 0, 0), (8, 0, 16, 0, 0), (8, 8, 0, 0, 0), (8, 8, 24, 0, 0), (8, 8, 128, 0, 1)):
+        assert L.qii_gemm_route(*bad) == -1
+    assert L.qii_gemm_route(1, 1, 16, 0, 0) == T64
+    # beyond 2^23 columns the main kernel's 32-bit offsets do not reach
+    assert L.qii_gemm_route(512, 512, (1 << 23) + 256, 1 << 40, 0) != MAIN

@@ -8,7 +8,7 @@ import torch
 
 from paper_2601_22813_amd import binding as qii
 
-from gpu_util import nv_to_dev, ws
+from gpu_util import median_us, nv_to_dev, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +68,18 @@ def test_small_tile_kernels_match_the_oracle(oracle, M, N, K):
 ])
 def test_large_products_match_the_oracle(oracle, M, N, K, use_ws):
     check_product(oracle, M, N, K, use_ws)
+
+
+@pytest.mark.parametrize("M,N,K", [(512, 128, 26624), (256, 256, 32768)])
+def test_a_workspace_for_the_scales_alone_is_no_slower_than_none(M, N, K):
+    """Few tiles and a long K, with a workspace that has no room for the partial tiles of a shared round: one block per 256 x 256
+    tile takes more than five times as long as the 64 x 64 tiles that run without a workspace."""
+    g = torch.Generator(device="cuda").manual_seed(9)
+    A, B = qii.NVFP4Tensor.empty(M, K), qii.NVFP4Tensor.empty(N, K)
+    for t in (A, B):
+        qii.qii_quantize_nvfp4(torch.randn((t.rows, K), device="cuda", generator=g), False, qii.RTN, 0, 0, 0, None, t, ws(256))
+    C = torch.empty((M, N), device="cuda")
+    scales = ws(((M + 255) // 256 * 256 + (N + 255) // 256 * 256) * (K // 16))
+    with_it, without = (median_us(lambda: qii.qii_gemm_nvfp4(A, B, C, w)) for w in (scales, None))
+    print(f"gemm {M}x{N}x{K}: scales' workspace {with_it:.1f} us, none {without:.1f}", flush=True)
+    assert with_it <= 1.15 * without
