@@ -18,7 +18,12 @@ def operand(oracle, rng, rows, K):
                         np.array([0.0625], np.float32))
 
 
-def check_product(oracle, M, N, K, use_ws):
+# the library's names for its kernels (qii_gemm_route)
+MAIN, NO_WORKSPACE, T64, T128, T128_WIDE = range(5)
+
+
+def check_product(oracle, M, N, K, use_ws, route):
+    assert qii.lib().qii_gemm_route(M, N, K, qii.qii_gemm_workspace_bytes(M, N, K) if use_ws else 0, 0) == route
     rng = np.random.default_rng(M + 3 * N + 7 * K)
     qa, qb = operand(oracle, rng, M, K), operand(oracle, rng, N, K)
     # every corner and edge of the matrix and of its 64- and 128-wide tiles, and random entries
@@ -47,27 +52,31 @@ def check_product(oracle, M, N, K, use_ws):
         assert np.all(err <= tol), f"worst at ({ms[worst]}, {ns[worst]}): error {err[worst]}, tolerance {tol[worst]}"
 
 
-@pytest.mark.parametrize("M,N,K", [
+@pytest.mark.parametrize("M,N,K,route", [
     # 64 x 64 tiles: one element; one row of tiles; one past a tile; K shorter than, equal to and one group beyond a
     # K tile; an odd multiple of 16 (rows 8-byte aligned, the last 16-byte piece half valid); three whole K tiles
-    (1, 1, 16), (63, 65, 256), (64, 64, 272), (65, 130, 240), (129, 127, 528), (200, 72, 768), (7, 300, 1040),
-    # 128 x 128 tiles, two K groups: ragged edges with one, two and three K tiles, K ragged and whole
-    (2040, 1990, 256), (2047, 1921, 512), (2040, 1990, 528),
+    (1, 1, 16, T64), (63, 65, 256, T64), (64, 64, 272, T64), (65, 130, 240, T64), (129, 127, 528, T64), (200, 72, 768, T64),
+    (7, 300, 1040, T64),
+    # 128 x 128 tiles, two K groups: ragged edges with one and two K tiles, whole; one to three K tiles, the last one partial
+    (2040, 1990, 256, T128), (2047, 1921, 512, T128), (2040, 1990, 272, T128), (2900, 2899, 400, T128), (2300, 2301, 528, T128),
     # 128 x 128 tiles, four waves of 4 x 4: odd and even numbers of K tiles, K ragged and whole
-    (2000, 1930, 2064), (2000, 1921, 2304), (1930, 2040, 2560), (2041, 1928, 2320),
+    (2040, 1990, 528, T128_WIDE), (2000, 1930, 2064, T128_WIDE), (2000, 1921, 2304, T128_WIDE), (1930, 2040, 2560, T128_WIDE),
+    (2041, 1928, 2320, T128_WIDE),
 ])
-def test_small_tile_kernels_match_the_oracle(oracle, M, N, K):
-    check_product(oracle, M, N, K, use_ws=True)
+def test_small_tile_kernels_match_the_oracle(oracle, M, N, K, route):
+    check_product(oracle, M, N, K, True, route)
 
 
-@pytest.mark.parametrize("M,N,K,use_ws", [
-    (8190, 4090, 1152, True),    # K a multiple of 128: the kernel without a workspace
-    (8190, 4090, 2048, False),   # no workspace given: the same kernel
-    (4090, 4080, 2048, True),    # the main kernel, ragged edges
-    (4200, 4200, 8192, True),    # 289 tiles: a full round, then 33 tiles shared between blocks
+@pytest.mark.parametrize("M,N,K,use_ws,route", [
+    # the kernel without a workspace: K an odd multiple of 128 (nine, three, one K tiles), and, without a workspace, an even one
+    (8190, 4090, 1152, True, NO_WORKSPACE), (4090, 4080, 384, True, NO_WORKSPACE), (4090, 4080, 128, True, NO_WORKSPACE),
+    (4090, 4080, 256, False, NO_WORKSPACE), (4090, 4080, 512, False, NO_WORKSPACE),
+    (8190, 4090, 2048, False, T128),   # a large product without a workspace
+    (4090, 4080, 2048, True, MAIN),    # the main kernel, ragged edges
+    (4200, 4200, 8192, True, MAIN),    # 289 tiles: a full round, then 33 tiles shared between blocks
 ])
-def test_large_products_match_the_oracle(oracle, M, N, K, use_ws):
-    check_product(oracle, M, N, K, use_ws)
+def test_large_products_match_the_oracle(oracle, M, N, K, use_ws, route):
+    check_product(oracle, M, N, K, use_ws, route)
 
 
 @pytest.mark.parametrize("M,N,K", [(512, 128, 26624), (256, 256, 32768)])
