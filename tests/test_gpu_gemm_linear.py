@@ -20,7 +20,7 @@ E2M1 = np.array([0.0, 0.5, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0, -0.0, -0.5, -1.0, -1.5,
 
 
 def gemm_gpu(qa, qb, dtype, ldc=None, use_ws=True):
-    """With a workspace the fast kernel runs (when K is a multiple of 256); without, the fallbacks."""
+    """With the workspace that the library asks for, or with none."""
     M, N = qa.rows, qb.rows
     ldc = ldc or N
     C = torch.full((M, ldc), float("nan"), dtype=dtype, device="cuda")
@@ -66,14 +66,17 @@ def test_gemm_ragged_shapes(oracle, M, N, K):
     check(gemm_gpu(qa, qb, torch.bfloat16, ldc=N + 3, use_ws=False), ref, absum, True)
 
 
-@pytest.mark.parametrize("M,N,K", [(512, 512, 8192), (300, 520, 4096), (1280, 256, 6144), (256, 256, 4096), (6100, 2800, 4096)])
-def test_gemm_shares_the_tiles_of_an_incomplete_round(oracle, M, N, K):
+@pytest.mark.parametrize("M,N,K,shared", [(512, 512, 8192, False), (300, 520, 4096, False), (1280, 256, 6144, False), (256, 256, 4096, False),
+                                          (6100, 2800, 4096, True), (512, 128, 26624, True), (300, 520, 30720, True), (256, 256, 32768, True)])
+def test_gemm_shares_the_tiles_of_an_incomplete_round(oracle, M, N, K, shared):
     """Tiles beyond the last full round of 256 (all of them when there are fewer) are shared between
     blocks: contiguous ranges of K tiles, partial tiles in the workspace, added up in a fixed order.
     Same tolerance, same result on a repeated call, and the emitted max |C| is that of the stored
-    values; without room for the partial tiles the plain path runs.  The shapes cover 4 / 6 / 5 / 1
-    tiles (block counts 32, 24, 24, 4; an odd tile count with ranges that span two tiles; ragged
-    edges) and 264 tiles (one full round, then 8 shared tiles)."""
+    values; without room for the partial tiles the product runs all the same.  The shapes with `shared` cover 264
+    tiles (one full round, then 8 tiles shared by 32 blocks) and few tiles with no full round: 2 tiles and 48 blocks,
+    6 and 176 (ranges that span two tiles, ragged edges), 1 and 32.  The others have a sharing plan too, and a workspace
+    for it, but are faster in 64 x 64 tiles."""
+    assert qii.lib().qii_gemm_route(M, N, K, qii.qii_gemm_workspace_bytes(M, N, K), 0) == (0 if shared else 2)
     rng = np.random.default_rng(M + N + K)
     a = (rng.standard_t(3, size=(M, K)) * 0.1).astype(np.float32)
     b = rng.standard_normal((N, K)).astype(np.float32)
@@ -95,7 +98,7 @@ def test_gemm_shares_the_tiles_of_an_incomplete_round(oracle, M, N, K):
         qii.qii_gemm_nvfp4_amax(A, B, C, amax, ws(need))
         torch.cuda.synchronize()
         assert float(amax[0]) == float(C.float().abs().max())
-    # a workspace that only holds the re-tiled scales: one block per tile
+    # a workspace that only holds the re-tiled scales
     small = ws((M + 255) // 256 * 256 * (K // 16) + (N + 255) // 256 * 256 * (K // 16))
     C = torch.empty((M, N), dtype=torch.float32, device="cuda")
     qii.qii_gemm_nvfp4(A, B, C, small)
@@ -162,7 +165,8 @@ def test_linear_forward_and_backward(oracle):
 def test_linear_backward_with_post_hoc_range_alignment(oracle, T, d_in, d_out):
     """Backward pass of Sec. 5 with the four quantizers in the two-kernel form of Sec. 7.  (Where a
     GEMM's inner dimension, d_out or T, is a multiple of 256 the scales pass writes the scale bytes
-    in the GEMM kernel's tiled layout; the shapes cover both, one and none of the two GEMMs.)"""
+    in the GEMM kernel's tiled layout; the shapes cover both, one and none of the two GEMMs, all in 64 x 64
+    tiles: the larger tiles are in test_gpu_backward_launches.py.)"""
     Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=8)
     E = to_dev(Eb)
     oXq, oWq = oracle.linear_fwd(Xb, Wb)
@@ -212,10 +216,10 @@ def test_linear_forward_with_four_over_six(oracle):
 
 @pytest.mark.parametrize("T,d_in,d_out,zero_x", [(320, 768, 272, False), (320, 384, 272, False), (320, 768, 272, True)])
 def test_linear_forward_scale_layouts(oracle, T, d_in, d_out, zero_x):
-    """With d_in a multiple of 256 the forward quantizers also write their scale bytes in the GEMM
-    kernel's tiled layout (ragged row counts here: 320 and 272 rows in tiles of 256); otherwise the
-    GEMM reads the row-major bytes.  Saved operands and Y must match either way, also for an all-zero
-    X, whose quantizer takes a separate path."""
+    """Where the main GEMM kernel will run, the forward quantizers also write their scale bytes in that kernel's tiled
+    layout (the test below); otherwise, as at these sizes, the GEMM reads the row-major bytes, with d_in a multiple of
+    256 or not.  Saved operands and Y, also for an all-zero X, whose quantizer takes a separate path."""
+    assert qii.lib().qii_gemm_route(T, d_out, d_in, qii.qii_gemm_workspace_bytes(T, d_out, d_in), 0) != 0
     Xb, Wb, _ = synth.linear_layer_bf16(T, d_in, d_out, seed=11)
     if zero_x:
         Xb = np.zeros_like(Xb)
@@ -230,6 +234,34 @@ def test_linear_forward_scale_layouts(oracle, T, d_in, d_out, zero_x):
         ref, absum = oracle.gemm(oXq, oWq, with_abs=True)
         torch.cuda.synchronize()
         check(Y.cpu().numpy().astype(np.float64), ref, absum, False)
+        if zero_x:
+            assert float(Y.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("T,d_in,d_out,zero_x", [(4090, 256, 2090, False), (2500, 512, 3300, False), (4090, 256, 2090, True)])
+def test_linear_forward_writes_tiled_scales_for_the_main_kernel(oracle, T, d_in, d_out, zero_x):
+    """Sizes at which the main GEMM kernel reads the tiled copy that the forward quantizers write, with row counts that end
+    inside a tile of 256 for X and for W; an all-zero X takes a separate path in its quantizer.  A workspace of stale bytes."""
+    assert qii.lib().qii_gemm_route(T, d_out, d_in, qii.qii_gemm_workspace_bytes(T, d_out, d_in), 1) == 0
+    Xb, Wb, _ = synth.linear_layer_bf16(T, d_in, d_out, seed=12)
+    if zero_x:
+        Xb = np.zeros_like(Xb)
+    X, W = to_dev(Xb), to_dev(Wb)
+    rng = np.random.default_rng(T)
+    ms = np.concatenate([rng.integers(0, T, 4000), rng.integers(T // 256 * 256, T, 2000), [0, 0, T - 1, T - 1]])
+    ns = np.concatenate([rng.integers(0, d_out, 2000), rng.integers(d_out // 256 * 256, d_out, 4000), [0, d_out - 1, 0, d_out - 1]])
+    for mode, omode in ((qii.RTN, oracle.RTN), (qii.RTN_46, oracle.RTN_46)):
+        Xq, Wq = qii.NVFP4Tensor.empty(T, d_in), qii.NVFP4Tensor.empty(d_out, d_in)
+        Y = torch.full((T, d_out), 7.0, dtype=torch.float32, device="cuda")
+        w = ws(qii.qii_linear_fwd_workspace_bytes(T, d_in, d_out))
+        w.fill_(0x7F)
+        qii.qii_linear_fwd_mode(X, W, mode, Y, Xq, Wq, w)
+        oXq, oWq = oracle.linear_fwd(Xb, Wb, mode=omode)
+        assert_nv_equal(Xq, oXq, "saved X")
+        assert_nv_equal(Wq, oWq, "saved W")
+        assert torch.isfinite(Y).all()
+        ref, absum = oracle.gemm_sampled(oXq, oWq, ms, ns)
+        check(Y.cpu().numpy().astype(np.float64)[ms, ns], ref, absum, False)
         if zero_x:
             assert float(Y.abs().max()) == 0.0
 
@@ -289,9 +321,10 @@ def test_layer_passes_replay_from_a_hip_graph(oracle):
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_gemm_emits_the_abs_max_of_what_it_stores(oracle, M, N, K, use_ws, dtype):
     """max |C| out of the GEMM's epilogue (the abs-max the consumer's quantizer needs, App. D): it
-    must equal the maximum over the stored matrix bit for bit, in all three kernels, and entries of
-    the padded tile beyond M x N must not leak into it.  K = 48 also covers an inner dimension that
-    is a multiple of 16 but not of 32."""
+    must equal the maximum over the stored matrix bit for bit, and entries of the padded tile beyond M x N must
+    not leak into it.  K = 48 also covers an inner dimension that is a multiple of 16 but not of 32.  (All these sizes
+    take 64 x 64 tiles; the other kernels' maxima are checked in test_gpu_gemm_small.py and, shared, above.)"""
+    assert qii.lib().qii_gemm_route(M, N, K, qii.qii_gemm_workspace_bytes(M, N, K) if use_ws else 0, 0) == 2
     rng = np.random.default_rng(M * 7 + N + K)
     a = (rng.standard_t(3, size=(M, K)) * 0.1).astype(np.float32)
     b = rng.standard_normal((N, K)).astype(np.float32)
