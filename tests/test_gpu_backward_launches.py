@@ -36,3 +36,42 @@ def test_backward_at_both_sides_of_the_launch_rules(oracle, T, d_in, d_out, mode
             ref, absum = oracle.gemm(a, b, with_abs=True)
             tol = 1e-5 * absum + (2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else 0.0) + 1e-30
             assert np.all(np.abs(bf16_to_f64(got) - ref) <= tol)
+
+
+# the library's names for its kernels (qii_gemm_route)
+MAIN, T64, T128, T128_WIDE = 0, 2, 3, 4
+
+
+@pytest.mark.parametrize("T,d_in,d_out,routes", [
+    (2048, 2048, 2048, (T128_WIDE, T128_WIDE)),    # both products in one launch, 128 x 128 tiles in four K groups
+    (1792, 2064, 1792, (T128_WIDE, T128_WIDE)),    # ragged d_in: tiled scales (post hoc form) of a last, partial row tile
+    (1280, 4112, 1280, (T128, T128)),              # 128 x 128 tiles in two K groups, five K tiles
+    (384, 16400, 384, (T128, T128)),               # K no multiple of 256; W and X re-quantized by blocks of two chunks, three chunks each
+    (2048, 2048, 5632, (T128_WIDE, MAIN)),         # dX and dW by different kernels, so in two launches
+])
+@pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
+def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, mode):
+    ph = mode == qii.MS_EDEN_PH
+    for (M, K), route in zip(((T, d_out), (d_out, T)), routes):
+        assert qii.lib().qii_gemm_route(M, d_in, K, qii.qii_gemm_workspace_bytes(M, d_in, K), int(ph and K % 256 == 0)) == route
+    Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=7)
+    oXq, oWq = oracle.linear_fwd(Xb, Wb)
+    Eq, WTq, ETq, XTq = oracle.linear_bwd_operands(Eb, oXq, oWq, 10, mode)
+    E, Xq, Wq = to_dev(Eb), nv_to_dev(oXq), nv_to_dev(oWq)
+    rng = np.random.default_rng(T + d_in)
+    for dtype in (torch.float32, torch.bfloat16):
+        print(f"backward T={T} {d_in}->{d_out} mode {mode} {dtype}", flush=True)
+        dX = torch.full((T, d_in), float("nan"), dtype=dtype, device="cuda")
+        dW = torch.full((d_out, d_in), float("nan"), dtype=dtype, device="cuda")
+        w = ws(qii.qii_linear_bwd_mode_workspace_bytes(T, d_in, d_out, mode))
+        w.fill_(0x7F)
+        qii.qii_linear_bwd_mode(E, Xq, Wq, 10, mode, dX, dW, w)
+        torch.cuda.synchronize()
+        for got, (a, b) in ((dX, (Eq, WTq)), (dW, (ETq, XTq))):
+            assert torch.isfinite(got).all()
+            # random entries, and as many in the last columns (a partial tile where d_in is ragged), and the corners
+            ms = np.concatenate([rng.integers(0, a.rows, 6000), [0, 0, a.rows - 1, a.rows - 1]])
+            ns = np.concatenate([rng.integers(0, b.rows, 3000), rng.integers(b.rows - 100, b.rows, 3000), [0, b.rows - 1, 0, b.rows - 1]])
+            ref, absum = oracle.gemm_sampled(a, b, ms, ns)
+            tol = 1e-5 * absum + (2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else 0.0) + 1e-30
+            assert np.all(np.abs(bf16_to_f64(got)[ms, ns] - ref) <= tol)
