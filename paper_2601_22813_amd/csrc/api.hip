@@ -189,20 +189,7 @@ qii_status carve_quantize_ws(qii_mode mode, const float *amax_in, int64_t R, int
     return QII_OK;
 }
 
-// the two quantizer front ends on caller-carved workspace pieces (layer passes: their abs-max
-// slots are cleared by one launch for the whole pass)
-qii_status quantize_dense(const void *x, qii_dtype dt, int64_t rows, int64_t cols, int64_t ld, int transpose,
-                          qii_mode mode, int rht_group, uint64_t seed_rht, uint64_t seed_sr,
-                          const float *amax_in, const qii_nvfp4 *out, float *slot, float *tbuf, hipStream_t s,
-                          bool slot_zeroed)
-{
-    qii::Source src;
-    int64_t R, C;
-    qii_status st = dense_source(x, dt, rows, cols, ld, transpose, rht_group, &src, &R, &C);
-    if (st != QII_OK) return st;
-    return quantize_source(src, R, C, mode, rht_group, seed_rht, seed_sr, amax_in, out, slot, tbuf, s, slot_zeroed);
-}
-
+// the re-quantizer on caller-carved workspace pieces (layer passes)
 qii_status requantize_saved(const qii_nvfp4 *in, int transpose, qii_mode mode, int rht_group, uint64_t seed_rht,
                             uint64_t seed_sr, const qii_nvfp4 *out, float *slot, float *tbuf, hipStream_t s,
                             bool slot_zeroed, bool tiled_scales = false)
@@ -687,9 +674,9 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     if (!ws || ws_bytes < need || !aligned(ws, kSlot))
         return fail(QII_WORKSPACE_TOO_SMALL, "linear_bwd needs %zu bytes of 256-byte aligned workspace", need);
     uint8_t *p = reinterpret_cast<uint8_t *>(ws);
-    // quantizer workspace: four abs-max slots, cleared by one launch, and, for the post hoc
-    // scheme, one per-group f32 buffer sized for the largest tensor and used by the four
-    // quantizers one after the other on the stream
+    // quantizer workspace: four abs-max areas and, for the post hoc scheme, per-group f32 buffers: two for Q(E) and
+    // Q(E^T), whose heavy pass is one launch; once their scales pass has run, the same bytes hold those of W and of X
+    // where both fit (else W's and X's in turn)
     hipStream_t s = (hipStream_t)stream;
     float *slots = reinterpret_cast<float *>(p);
     const bool ph = mode == QII_MS_EDEN_PH;

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256) void quantize_rows2_kernel(RowsArgs a0, RowsAr
 }
 
 // Abs-max pass.  Its result is one word that every block has to fold its maximum into, and such
-// device-wide atomics on one address are resolved one after the other (about 4 ns each), so this
+// device-wide atomics on one address are resolved one after the other (about 10 ns each), so this
 // kernel runs as few, long-lived blocks (two per compute unit) that stride over the row quads with
 // the next quad's loads in flight, and issue one atomic each at the very end.
 template <bool kBf16, bool kRht>
@@ -437,7 +437,8 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
 int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, 0).x; }
 
 // Forward pass: Q(X) and Q(W), no rotation, RTN or RTN with 4/6.  Where a maximum is not supplied it is measured
-// first: at most kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each.
+// first: about kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each (rows longer than 4096
+// elements take whole rows of blocks, so that both tensors together can have more; each has at most kForwardMaxWords).
 hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStream_t s)
 {
     RowsArgs a[2];
