@@ -640,12 +640,13 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // a higher clock, so filling idle units gains less than their number suggests); a tile costs 5 more
 // for its first loads and its stores; a sharing block 26 more (all blocks store their 256 KiB
 // partial tiles at the same moment), 38 when its range spans two tiles; the second kernel 0.05 per
-// partial tile (they are stored with plain stores, not streaming ones, and mostly still in cache).  Sharing is used where the model promises at least 7 %.  Measured on one
-// box, plain -> shared: 2048 x 2048 x 32768 600 -> 226, 3072 x 3072 x 16384 307 -> 267, 11264 x 2048 x
-// 16384 654 -> 573; 6144 x 2048 x 32768 would go 655 -> 618 for 112 MiB of partial tiles and 2048 x
-// 5632 x 16384 298 -> 320: both stay plain.  (Those figures and the fit are from before the memory operations
-// were spread between the matrix instructions, which made a K tile 4 to 7 % faster, plain and shared alike; 2048 x 2048
-// products with K up to some 65000 now go to the small-tile kernels.)
+// partial tile (they are stored with plain stores, not streaming ones, and mostly still in cache).  Sharing is used
+// where the model promises at least 7 %.  The constants were fitted before the memory operations were spread between the
+// matrix instructions, which makes a K tile 4 to 7 % faster, plain and shared alike.  Measured with the present kernel on
+// one box, bf16 results, one block per tile -> shared: 256 x 256 x 32768 519 -> 69, 512 x 128 x 26624 433 -> 69,
+// 300 x 520 x 30720 496 -> 89, 2816 x 2048 x 16384 273 -> 176, 3072 x 3072 x 16384 278 -> 256, 6100 x 2800 x 4096 175 -> 153,
+// 8448 x 2048 x 8192 321 -> 239, 4200 x 4200 x 8192 325 -> 272, 11264 x 2048 x 16384 622 -> 555; 5120 x 5120 x 8192 (400 tiles, 144
+// of them shared) is one where it loses, 329 -> 353.
 struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
