@@ -643,10 +643,9 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // partial tile (they are stored with plain stores, not streaming ones, and mostly still in cache).  Sharing is used
 // where the model promises at least 7 %.  The constants were fitted before the memory operations were spread between the
 // matrix instructions, which makes a K tile 4 to 7 % faster, plain and shared alike.  Measured with the present kernel on
-// one box, bf16 results, one block per tile -> shared: 256 x 256 x 32768 519 -> 69, 512 x 128 x 26624 433 -> 69,
-// 300 x 520 x 30720 496 -> 89, 2816 x 2048 x 16384 273 -> 176, 3072 x 3072 x 16384 278 -> 256, 6100 x 2800 x 4096 175 -> 153,
-// 8448 x 2048 x 8192 321 -> 239, 4200 x 4200 x 8192 325 -> 272, 11264 x 2048 x 16384 622 -> 555; 5120 x 5120 x 8192 (400 tiles, 144
-// of them shared) is one where it loses, 329 -> 353.
+// one box in turn, bf16 results, one block per tile -> shared: 256 x 256 x 32768 522 -> 72, 512 x 128 x 26624 434 -> 70,
+// 300 x 520 x 30720 497 -> 92, 2816 x 2048 x 16384 287 -> 186, 3072 x 3072 x 16384 314 -> 274, 6100 x 2800 x 4096 181 -> 156,
+// 8448 x 2048 x 8192 327 -> 246, 4200 x 4200 x 8192 334 -> 283, 11264 x 2048 x 16384 647 -> 581.
 struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
