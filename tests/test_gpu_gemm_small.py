@@ -33,7 +33,8 @@ def check_product(oracle, M, N, K, use_ws, route):
     ns = np.concatenate([rng.choice(cols, 3000), rng.integers(0, N, 3000), [0, N - 1, 0, N - 1]])
     ref, absum = oracle.gemm_sampled(qa, qb, ms, ns)
     A, B = nv_to_dev(qa), nv_to_dev(qb)
-    for dtype, ldc in ((torch.float32, N + 4), (torch.bfloat16, N), (torch.bfloat16, N + 3)):
+    # leading dimensions of any alignment, and two whose rows are 16-byte aligned, with a last piece that N may cut
+    for dtype, ldc in ((torch.float32, N + 4), (torch.bfloat16, N), (torch.bfloat16, N + 3), (torch.float32, (N + 3) // 4 * 4), (torch.bfloat16, (N + 15) // 8 * 8)):
         print(f"gemm {M}x{N}x{K} {dtype} ldc {ldc}", flush=True)
         C = torch.full((M, ldc), float("nan"), dtype=dtype, device="cuda")
         amax = torch.full((1,), float("nan"), device="cuda")
@@ -92,3 +93,20 @@ def test_a_workspace_for_the_scales_alone_is_no_slower_than_none(M, N, K):
     with_it, without = (median_us(lambda: qii.qii_gemm_nvfp4(A, B, C, w)) for w in (scales, None))
     print(f"gemm {M}x{N}x{K}: scales' workspace {with_it:.1f} us, none {without:.1f}", flush=True)
     assert with_it <= 1.15 * without
+
+
+@pytest.mark.parametrize("M,N,K,most", [(9420, 2177, 176, 1.7), (922, 12753, 176, 1.4)])
+def test_rows_of_any_alignment_cost_little_more(M, N, K, most):
+    """A C whose rows begin anywhere against one of a column less: with the entries of a 16-byte piece stored by one lane, one after the
+    other, the first took 2.04 and 1.56 times as long as the second; with consecutive lanes on consecutive entries 1.43 and 1.19."""
+    assert qii.lib().qii_gemm_route(M, N, K, 0, 0) == T128
+    g = torch.Generator(device="cuda").manual_seed(11)
+    A, B = qii.NVFP4Tensor.empty(M, K), qii.NVFP4Tensor.empty(N, K)
+    for t in (A, B):
+        qii.qii_quantize_nvfp4(torch.randn((t.rows, K), device="cuda", generator=g), False, qii.RTN, 0, 0, 0, None, t, ws(256))
+    odd, even = torch.empty((M, N), device="cuda", dtype=torch.bfloat16), torch.empty((M, N - 1), device="cuda", dtype=torch.bfloat16)
+    B1 = qii.NVFP4Tensor(B.codes[:N - 1], B.scales[:N - 1], B.tensor_scale, N - 1, K)
+    any_rows, aligned = (median_us(lambda: qii.qii_gemm_nvfp4(A, b, c, None)) for b, c in ((B, odd), (B1, even)))
+    print(f"gemm {M}x{N}x{K}: {any_rows:.1f} us, a column less {aligned:.1f}", flush=True)
+    assert torch.equal(odd[:, :N - 1], even)
+    assert any_rows <= most * aligned
