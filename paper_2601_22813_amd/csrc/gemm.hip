@@ -651,6 +651,7 @@ struct StreamPlan {
     int rem;    // positions after them whose tiles are shared (0: none)
     int grid;   // blocks that share them
     double us;  // modelled time of the main kernel (and the second one), without the re-tiling launch
+    bool spans; // priced for ranges that span two tiles
 };
 
 // (share = false: one block per tile, as where the workspace has no room for the partial tiles)
@@ -661,7 +662,7 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K, bool share = true
     const double full_us = (double)rounds * (5.8 * (double)ktiles + 5.0);
     const double kt_us = 4.6 + (rem > 176 ? 1.2 * (double)(rem - 176) / 80.0 : 0.0);
     const double plain_us = full_us + (rem ? kt_us * (double)ktiles + 5.0 : 0.0);
-    StreamPlan plan{(int)tiles, 0, 0, plain_us};
+    StreamPlan plan{(int)tiles, 0, 0, plain_us, false};
     if (!share || K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8 || rem == 0) return plan;
     const int64_t units = rem * ktiles;
     int64_t grid = units / 4 < 256 ? units / 4 : 256;
@@ -675,6 +676,7 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K, bool share = true
     plan.rem = (int)rem;
     plan.grid = (int)grid;
     plan.us = shared_us;
+    plan.spans = !one_segment;
     return plan;
 }
 
@@ -780,7 +782,10 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
 // work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan;
 // 3 us of launch and first loads (a shared last round takes some 7 less than the plan's own, careful, figure: 512 x 128
-// x 26624 73 us, 64 x 64 tiles 79), 4.5 of re-tiling where the scale bytes are not tiled yet.
+// x 26624 73 us, 64 x 64 tiles 79), 4.5 of re-tiling where the scale bytes are not tiled yet.  The plan counts 12
+// for ranges that span two tiles wherever ranges differ in length; of one tile, or of two and an even number of blocks,
+// none does and the 12 go (main kernel : 64 x 64 tiles, us, re-tiling included: 128 x 128 x 24320 bf16 59.5 : 71.2,
+// 256 x 256 x 19456 bf16 56.9 : 58.4, 256 x 512 x 22784 f32 62.9 : 70.1).
 // The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
 // 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 12.6 : 9.8 : 12.5 and 14.8 : 12.1 : 18.0, 4096 x 4096 41.0 : 22.3 : 13.7
 // and 49.7 : 28.7 : 20.9, 8192 x 8192 155 : 71 : 47 and 185 : 101 : 75.
@@ -814,7 +819,9 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     offer(kRoute128Wide, us_wide);
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        offer(kRouteMain, plan.us + (plan.rem ? -4.0 : 3.0) + (retile ? 4.5 : 0.0));
+        double main_us = plan.us + (plan.rem ? -4.0 : 3.0) + (retile ? 4.5 : 0.0);
+        if (plan.spans && plan.full == 0 && plan.rem <= 2 && plan.grid % plan.rem == 0) main_us -= 12.0;
+        offer(kRouteMain, main_us);
     }
     else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
     return best;

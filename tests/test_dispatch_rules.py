@@ -51,6 +51,28 @@ def test_a_route_is_priced_for_the_workspace_it_has(libqii, M, N, K):
         assert L.qii_gemm_route(M, N, K, too_small, 0) == L.qii_gemm_route(M, N, K, 0, 0) != MAIN
 
 
+# products of one or two 256 x 256 tiles, us: 64 x 64 tiles, the shared main kernel (its re-tiling launch included)
+SHARED_US = {
+    (128, 128, 19968): (60.6, 55.6), (128, 128, 24320): (71.2, 59.5), (256, 128, 22528): (66.3, 60.2), (256, 256, 19456): (58.4, 56.9),
+    (256, 256, 24320): (72.1, 61.2), (256, 512, 19712): (61.2, 58.9), (256, 512, 22784): (70.1, 62.9), (384, 256, 22272): (66.6, 62.3),
+}
+
+
+@pytest.mark.parametrize("M,N,K", SHARED_US)
+def test_one_or_two_shared_tiles_are_priced_without_spans(libqii, M, N, K):
+    """No block's range of such a plan spans two tiles, whatever its length, so that no block stores two partial tiles."""
+    import ctypes
+    L = libqii.lib()
+    small, main = SHARED_US[M, N, K]
+    route = L.qii_gemm_route(M, N, K, libqii.qii_gemm_workspace_bytes(M, N, K), 0)
+    assert main < small and route == MAIN
+    plan = (ctypes.c_int32 * 3)()
+    L.qii_gemm_sharing_plan(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), plan)
+    segments = (ctypes.c_int32 * 64)()
+    assert plan[0] == 0 and plan[1] in (1, 2)
+    assert all(L.qii_gemm_sharing_segments(plan[1], K // 256, plan[2], b, segments) == 1 for b in range(plan[2]))
+
+
 def test_routes_of_refused_and_smallest_sizes(libqii):
     L = libqii.lib()
     for bad in ((0, 8, 16, 0, 0), (8, 0, 16, 0, 0), (8, 8, 0, 0, 0), (8, 8, 24, 0, 0), (8, 8, 128, 0, 1)):
