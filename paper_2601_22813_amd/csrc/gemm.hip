@@ -53,6 +53,17 @@ __device__ __forceinline__ uint32_t scale_pair(uint32_t two_bytes, int which)
     return (b << 7) | (b << 23);
 }
 
+// The epilogue of a wave's 128 x 128 tile: two bands at a time (bf16) or one (f32), room for two groups, so that a
+// group's stores leave while the next one is converted.  (The caller guarantees that nobody reads the stages any more.)
+template <bool kBf16Out, bool kStreaming>
+__device__ __forceinline__ void store_wave_tile(const floatx16 (&acc)[4][4], uint8_t *smem, float ts, void *Cout, int64_t ldc, int64_t M,
+                                                int64_t N, int64_t row0, int64_t col0, int wave, int lane, uint32_t *amax_out)
+{
+    constexpr int kGroup = kBf16Out ? 2 : 1, kArea = 2 * kGroup * 32 * staging_pitch<kBf16Out, 4>();
+    static_assert(4 * kArea <= 144 * 1024, "staging areas fit");
+    store_tile<kBf16Out, kStreaming, 4, 4, kGroup, 2 * kGroup>(acc, smem + wave * kArea, ts, Cout, ldc, M, N, row0, col0, lane, amax_out);
+}
+
 // ------------------------------------------------------------------------------------------
 // Kernel without a workspace (K a multiple of 128).
 //  * global -> LDS with global_load_lds (no staging registers, no VALU, no ds_write): each
@@ -67,7 +78,8 @@ __device__ __forceinline__ uint32_t scale_pair(uint32_t two_bytes, int which)
 //    LDS tile, then stored as 16-byte pieces of full rows.
 constexpr int kStages = 3;
 constexpr int kOffA = 0, kOffB = 16384, kOffAs = 32768, kOffBs = 34816, kStage2Bytes = 36864;
-constexpr int kSmem2 = kStages * kStage2Bytes;   // 108 KiB, also reused by the epilogue
+constexpr int kSmem2 = 144 * 1024;   // three stages are 108 KiB; the epilogue's staging areas take up to 136
+static_assert(kStages * kStage2Bytes <= kSmem2, "stages fit");
 
 struct RawFrag {
     uint4 a[4], b[4];
@@ -137,7 +149,7 @@ __device__ __forceinline__ void mma_slice(floatx16 (&acc)[4][4], const RawFrag &
         for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
             for (int tj = 0; tj < 4; ++tj)
-                acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[ti], fb[tj], acc[ti][tj], 0, 0, 0);
+                acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[tj], fa[ti], acc[ti][tj], 0, 0, 0);   // (B first: store_tile)
     }
 }
 
@@ -162,6 +174,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restri
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, kb = lane >> 5;
+    const float ts_a = *a_ts, ts_b = *b_ts;
 
     floatx16 acc[4][4];
 #pragma unroll
@@ -201,7 +214,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restri
         st_cur = st_next;
     }
 
-    store_tile_through_lds<kBf16Out>(acc, smem, (*a_ts) * (*b_ts), Cout, ldc, M, N, m0, n0, wave, wm, wn, lane, li, kb, amax_out);
+    store_wave_tile<kBf16Out, true>(acc, smem, ts_a * ts_b, Cout, ldc, M, N, m0 + wm * 128, n0 + wn * 128, wave, lane, amax_out);
 }
 
 
@@ -389,7 +402,7 @@ template <int D, class Side>
 __device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, RawFrag4 &f, const Side &side)
 {
 #define QII_MMA(I)                                                                                          \
-    acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.a[(I) >> 2], cu.b[(I) & 3],          \
+    acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[(I) & 3], cu.a[(I) >> 2],          \
                                                                     acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
     side.template at<I>();                                                                                  \
     dequant_chunk<I, D>(nx, f);                                                                             \
@@ -455,6 +468,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, kb = lane >> 5;
+    float ts_a = 1.0f, ts_b = 1.0f;
 
     const int ktotal = (int)(K / BK4);
     // this block's range of units [u, u_end) and its number among the blocks (kStream)
@@ -498,9 +512,20 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     const std::make_integer_sequence<int, 18> all_loads;
     const std::make_integer_sequence<int, 16> all_reads;
     issue_tile_loads(all_loads, smem, src_a, src_b, kt0, wave);
+    // in the shadow of these loads: the tensor scales (not when the epilogue needs them) and the accumulators' zeros (the
+    // compiler would put their 256 writes behind the barrier, 0.5 us of a tile)
+    __builtin_amdgcn_sched_barrier(0);
+    if (!kStream) {
+        ts_a = *a_ts;
+        ts_b = *b_ts;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[i][j]));
+    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (ktiles > 1) issue_tile_loads(all_loads, smem + kStage4Bytes, src_a, src_b, kt0 + 1, wave);
 
     // Pipeline over K, in steps of 16 columns of K per lane half (4 steps = one 64-wide slice,
     // 4 slices = one tile).  While step n multiplies, the fragments of step n+1 are dequantized;
@@ -514,6 +539,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     Frags x, y;
     frag_read_issue<0>(all_reads, fe, read_addr<0>(fa, 0));
     frag_read_issue<1>(all_reads, fo, read_addr<1>(fa, 0));
+    if (ktiles > 1) issue_tile_loads(all_loads, smem + kStage4Bytes, src_a, src_b, kt0 + 1, wave);
     frag_read_wait(fe);   // (waits for both)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -561,11 +587,11 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     frag_read_wait(fo);
     __syncthreads();
     if (!kStream) {
-        store_tile_through_lds<kBf16Out>(acc, smem, (*a_ts) * (*b_ts), Cout, ldc, M, N, m0, n0, wave, wm, wn, lane, li, kb, amax_out);
+        store_wave_tile<kBf16Out, true>(acc, smem, ts_a * ts_b, Cout, ldc, M, N, m0 + wm * 128, n0 + wn * 128, wave, lane, amax_out);
         break;
     }
-    store_tile_through_lds<false, false>(acc, smem, 1.0f, partial + (int64_t)sharing_slot(blk, lt) * (BM * BN), BN, BM, BN, 0, 0, wave, wm, wn, lane,
-                                  li, kb, nullptr);
+    store_wave_tile<false, false>(acc, smem, 1.0f, partial + (int64_t)sharing_slot(blk, lt) * (BM * BN), BN, BM, BN, wm * 128, wn * 128, wave,
+                                  lane, nullptr);
     u += ktiles;
     if (u >= u_end) break;
     __syncthreads();   // every wave is done with its staging tile before the next segment's loads land in LDS

@@ -80,74 +80,143 @@ __device__ __forceinline__ void dequant_half(half8_t &dst, uint32_t codes, uint3
     dst[4 * H] = h0[0]; dst[4 * H + 1] = h0[1]; dst[4 * H + 2] = h1[0]; dst[4 * H + 3] = h1[1];
 }
 
-// epilogue: C = acc * (x32_A * x32_B).  acc[r] of a 32x32 tile is row
-// 8*(r/4) + 4*(lane/32) + r%4, column lane%32.  One 32-row band of the wave's 32 MT x 32 NT tile
-// at a time goes through a per-wave LDS tile (row pitch padded by 16 bytes) and leaves as
-// 16-byte pieces of full rows.  The caller guarantees that nobody reads the stages any more.
-template <bool kBf16Out, bool kStreaming = true, int MT = 4, int NT = 4>
-__device__ __forceinline__ void store_tile_through_lds(floatx16 (&acc)[MT][NT], uint8_t *smem, float ts,
-                                                       void *Cout, int64_t ldc, int64_t M, int64_t N,
-                                                       int64_t m0, int64_t n0, int wave, int wm, int wn,
-                                                       int lane, int li, int kb, uint32_t *amax_out)
+// The lanes of a wave exchange data through LDS: its LDS operations run in order, so nothing has to be waited
+// for; the compiler only must not move accesses across this point.
+__device__ __forceinline__ void wave_lds_fence()
 {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Epilogue: C = acc * ts for a wave's tile of 32 MT x 32 NT entries at (row0, col0).  The matrix instructions take B's
+// fragment as their first operand and A's as their second, so entry r of accumulator (i, j) is row 32 i + lane % 32,
+// column 32 j + 8 (r / 4) + 4 (lane / 32) + r % 4: a lane holds four neighbouring entries of a row, which go into
+// the wave's staging area as 8 (bf16) or 16 bytes at once (row pitch padded by 16 bytes: no bank conflicts for the
+// 16-byte accesses).  kGroup bands of 32 rows are staged, then stored as 16-byte pieces of full rows while the next group
+// is converted; the area holds kRoom bands.  (One band at a time, two bytes per LDS write, with the wave waiting for
+// each: 6.1 us for the main kernel's 256 x 256 bf16 tile and 9.3 for f32; now 3.6 and 7.3; the
+// 128 x 128 form of the small-tile kernels, reduction included, 5.4 -> 2.7.)
+// A tile that lies inside C with 16-byte aligned rows takes the loop without checks; where the rows are aligned only the
+// pieces that N cuts go entry by entry; other rows: consecutive lanes store consecutive entries, eight rows in flight.
+// kStreaming: C is written once and not read again here, so the stores are non-temporal (false: a partial tile that
+// the next kernel reads back).  All threads of the block must call it if amax_out is given.
+template <bool kBf16Out, int NT>
+constexpr int staging_pitch() { return 32 * NT * (kBf16Out ? 2 : 4) + 16; }
+
+template <bool kBf16Out, bool kStreaming, int MT, int NT, int kGroup, int kRoom>
+__device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_t *area, float ts, void *Cout, int64_t ldc, int64_t M,
+                                           int64_t N, int64_t row0, int64_t col0, int lane, uint32_t *amax_out)
+{
+    constexpr int esz = kBf16Out ? 2 : 4, cols = 32 * NT, pitch = staging_pitch<kBf16Out, NT>(), entries = 16 / esz;
+    constexpr int per_row = cols / entries, rows_per_pass = 64 / per_row, kPasses = 32 * kGroup / rows_per_pass;
+    static_assert(MT % kGroup == 0 && kRoom % kGroup == 0, "whole groups");
+    const int64_t rb = ldc * esz;   // bytes from row to row of C
+    uint8_t *out = reinterpret_cast<uint8_t *>(Cout) + row0 * rb + col0 * esz;
+    const int live_rows = (int)(M - row0 < 32 * MT ? M - row0 : 32 * MT), live_cols = (int)(N - col0 < cols ? N - col0 : cols);   // (may be negative)
+    const bool aligned = ((reinterpret_cast<uintptr_t>(Cout) | (uintptr_t)rb) & 15) == 0;   // (col0: a multiple of 32)
+    const bool whole = aligned && live_rows == 32 * MT && live_cols == cols && rb < (1 << 26);
+    const int piece = lane % per_row, row_l = lane / per_row;
+    uint8_t *lane_write = area + (lane & 31) * pitch + (lane >> 5) * 4 * esz;
+    const uint8_t *lane_read = area + row_l * pitch + piece * 16;
     float cmax = 0.0f;
-    constexpr int esz = kBf16Out ? 2 : 4;
-    constexpr int pitch = 32 * NT * esz + 16;
-    uint8_t *wtile = smem + wave * (32 * pitch);
-    constexpr int per_row = 32 * NT * esz / 16;          // 16-byte pieces per row
-    constexpr int rows_per_pass = 64 / per_row;      // rows covered by one wave-wide store
+    auto fold = [&](const u32x4 &v) {
 #pragma unroll
-    for (int ti = 0; ti < MT; ++ti) {
+        for (int e = 0; e < entries; ++e)
+            cmax = fmaxf(cmax, fabsf(kBf16Out ? u2f((e & 1) ? (v[e >> 1] & 0xFFFF0000u) : (v[e >> 1] << 16)) : u2f(v[e & 3])));
+    };
+    auto put = [&](uint8_t *dst, const u32x4 &v) {
+        if (kStreaming) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(dst));
+        else *reinterpret_cast<u32x4 *>(dst) = v;
+    };
+    auto put_entry = [&](int row, int col, const uint8_t *src) {
+        uint8_t *dst = out + row * rb + col * esz;
+        uint32_t v;
+        if (kBf16Out) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)(v = *reinterpret_cast<const uint16_t *>(src));
+        else *reinterpret_cast<uint32_t *>(dst) = v = *reinterpret_cast<const uint32_t *>(src);
+        cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v << 16 : v)));
+    };
 #pragma unroll
-        for (int tj = 0; tj < NT; ++tj)
+    for (int g = 0; g < MT; g += kGroup) {
+        constexpr int kBand = 32 * pitch;
+        const int band0 = g % kRoom;   // (a compile-time constant)
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                // two consecutive rows of one column: one packed conversion (round to nearest even)
-                const int row = 8 * (r >> 2) + 4 * kb + (r & 3), col = tj * 32 + li;
-                const float v0 = acc[ti][tj][r] * ts, v1 = acc[ti][tj][r + 1] * ts;
-                if (kBf16Out) {
-                    const bf16x2_t pk = __builtin_convertvector(float2_t{v0, v1}, bf16x2_t);
-                    const uint32_t bits = __builtin_bit_cast(uint32_t, pk);
-                    *reinterpret_cast<uint16_t *>(wtile + row * pitch + col * 2) = (uint16_t)bits;
-                    *reinterpret_cast<uint16_t *>(wtile + (row + 1) * pitch + col * 2) = (uint16_t)(bits >> 16);
-                } else {
-                    *reinterpret_cast<float *>(wtile + row * pitch + col * 4) = v0;
-                    *reinterpret_cast<float *>(wtile + (row + 1) * pitch + col * 4) = v1;
+        for (int b = 0; b < kGroup; ++b)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const floatx16 &a = acc[g + b][j];
+                    const float v0 = a[4 * q] * ts, v1 = a[4 * q + 1] * ts, v2 = a[4 * q + 2] * ts, v3 = a[4 * q + 3] * ts;
+                    uint8_t *dst = lane_write + (band0 + b) * kBand + (32 * j + 8 * q) * esz;
+                    if (kBf16Out) {   // (two packed conversions, round to nearest even)
+                        const uint32_t lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{v0, v1}, bf16x2_t));
+                        const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{v2, v3}, bf16x2_t));
+                        *reinterpret_cast<uint2 *>(dst) = make_uint2(lo, hi);
+                    } else {
+                        *reinterpret_cast<float4 *>(dst) = make_float4(v0, v1, v2, v3);
+                    }
+                }
+        wave_lds_fence();
+        const uint8_t *src = lane_read + band0 * kBand;
+        uint8_t *row_out = out + 32 * g * rb;   // (uniform)
+        if (whole) {   // uniform
+            const uint32_t voff = (uint32_t)row_l * (uint32_t)rb + (uint32_t)piece * 16u;
+            constexpr int kAtOnce = kPasses < 8 ? kPasses : 8;
+#pragma unroll
+            for (int p0 = 0; p0 < kPasses; p0 += kAtOnce) {
+                u32x4 v[kAtOnce];
+#pragma unroll
+                for (int p = 0; p < kAtOnce; ++p) v[p] = *reinterpret_cast<const u32x4 *>(src + (p0 + p) * rows_per_pass * pitch);
+#pragma unroll
+                for (int p = 0; p < kAtOnce; ++p) put(row_out + (p0 + p) * rows_per_pass * rb + voff, v[p]);
+                if (amax_out)   // uniform
+#pragma unroll
+                    for (int p = 0; p < kAtOnce; ++p) fold(v[p]);
+            }
+        } else if (aligned) {
+#pragma unroll 1
+            for (int p = 0; p < kPasses; ++p) {
+                const int row = 32 * g + p * rows_per_pass + row_l;
+                if (row < live_rows && (piece + 1) * entries <= live_cols) {
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(src + p * rows_per_pass * pitch);
+                    put(out + row * rb + piece * 16, v);
+                    if (amax_out) fold(v);
                 }
             }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // wave-local: same wave reads below
+            if (live_cols > 0 && live_cols % entries != 0 && lane < 32)   // the rows' last, partial piece
+#pragma unroll 1
+                for (int b = 0; b < kGroup; ++b)
+                    if (32 * (g + b) + lane < live_rows)
+#pragma unroll 1
+                        for (int col = live_cols / entries * entries; col < live_cols; ++col)
+                            put_entry(32 * (g + b) + lane, col, area + ((band0 + b) * 32 + lane) * pitch + col * esz);
+        } else {
+            constexpr int lanes = cols < 64 ? cols : 64, rows_at_once = 64 / lanes, kAtOnce = 8;
+#pragma unroll 1
+            for (int c0 = 0; c0 < cols; c0 += lanes) {
+                const int col = c0 + lane % lanes;
+#pragma unroll 1
+                for (int r0 = lane / lanes; r0 < 32 * kGroup; r0 += kAtOnce * rows_at_once) {
+                    uint32_t v[kAtOnce];   // the reads of several rows do not wait for the stores of those before
 #pragma unroll
-        for (int pass = 0; pass < 32 / rows_per_pass; ++pass) {
-            const int row = pass * rows_per_pass + lane / per_row, piece = lane % per_row;
-            const uint4 v = *reinterpret_cast<const uint4 *>(wtile + row * pitch + piece * 16);
-            const int64_t grow = m0 + wm * (32 * MT) + ti * 32 + row;
-            const int64_t gcol = n0 + wn * (32 * NT) + piece * (16 / esz);
-            if (grow < M) {
-                if (amax_out) {   // uniform: max |C| over the entries of this piece that lie inside the matrix
-                    const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+                    for (int i = 0; i < kAtOnce; ++i) {
+                        const uint8_t *e = area + (band0 * 32 + r0 + i * rows_at_once) * pitch + col * esz;
+                        v[i] = kBf16Out ? (uint32_t)*reinterpret_cast<const uint16_t *>(e) : *reinterpret_cast<const uint32_t *>(e);
+                    }
 #pragma unroll
-                    for (int e = 0; e < 16 / esz; ++e)
-                        if (gcol + e < N)
-                            cmax = fmaxf(cmax, fabsf(kBf16Out ? u2f((e & 1) ? (w4[e >> 1] & 0xFFFF0000u) : (w4[e >> 1] << 16)) : u2f(w4[e])));
-                }
-                uint8_t *dst = reinterpret_cast<uint8_t *>(Cout) + (grow * ldc + gcol) * esz;
-                if (gcol + 16 / esz <= N && ((reinterpret_cast<uintptr_t>(dst) & 15) == 0)) {
-                    // C is written once and not read again here: a streaming (non-temporal) store
-                    // (kStreaming = false: a partial tile that the next kernel reads back)
-                    if (kStreaming) __builtin_nontemporal_store(u32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4 *>(dst));
-                    else *reinterpret_cast<u32x4 *>(dst) = u32x4{v.x, v.y, v.z, v.w};
-                } else {
-                    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int e = 0; e < 16 / esz; ++e)
-                        if (gcol + e < N) {
-                            if (kBf16Out) reinterpret_cast<uint16_t *>(dst)[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-                            else reinterpret_cast<uint32_t *>(dst)[e] = w[e];
+                    for (int i = 0; i < kAtOnce; ++i) {
+                        const int row = 32 * g + r0 + i * rows_at_once;
+                        if (row < live_rows && col < live_cols) {
+                            uint8_t *dst = out + row * rb + col * esz;
+                            if (kBf16Out) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v[i];
+                            else *reinterpret_cast<uint32_t *>(dst) = v[i];
+                            cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v[i] << 16 : v[i])));
                         }
+                    }
                 }
             }
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // reads done before the next band overwrites
+        wave_lds_fence();   // the reads come before the writes of a group that takes the same room
     }
     emit_tile_max(cmax, amax_out);
 }

@@ -60,11 +60,13 @@ struct Geo {
     static constexpr int kSlices = 4 / KG;                    // of a K tile per group
     static constexpr int kStage = (BM + BN) * (128 + 16);     // LDS bytes of one K tile
     static constexpr int kUnits = MT * NT;                    // 32 x 32 accumulator tiles of a wave
-    // LDS: two stages; the reduction's first round (half of every wave's accumulators)
-    static constexpr int kReduce = WM * KG * (kUnits / 2) * 4096;
-    static constexpr int kLds = 2 * kStage > kReduce ? 2 * kStage : kReduce;
-    // (the two-group epilogue's staging: 32 MT rows of 16 NT f32, padded, per wave)
-    static_assert(KG != 2 || WM * KG * 32 * MT * (64 * NT + 16) <= kLds, "staged tiles fit");
+    // what a wave finishes once the groups' accumulators are added up
+    static constexpr int FM = KG == 2 ? MT / 2 : 1, FN = KG == 2 || MT == 4 ? NT : NT / 2;
+    static_assert(FM * FN * KG == kUnits, "the groups share the tile");
+    // LDS: two stages; then, per wave, half of its accumulators (the reduction's first round) or the rows it stores
+    static constexpr int kStaged = FM * 32 * staging_pitch<false, FN>();
+    static constexpr int kArea = (kUnits / 2) * 4096 > kStaged ? (kUnits / 2) * 4096 : kStaged;
+    static constexpr int kLds = 2 * kStage > WM * KG * kArea ? 2 * kStage : WM * KG * kArea;
 };
 
 // One thread's share of a K tile on its way to LDS: 16-byte pieces of code rows and, for threads below
@@ -74,21 +76,36 @@ struct Staged {
     uint4 a[G::kPassA], b[G::kPassB], s;
 };
 
-// Rows are 8-byte (codes) and byte (scales) aligned when K is an odd multiple of 16; then a K tile may
-// also end at K, half way through a 16-byte piece: what lies beyond is staged as zeros.
+// Where a thread finds its pieces of one K tile: byte offsets from its source addresses.  Rows are 8-byte (codes) and
+// byte (scales) aligned when K is an odd multiple of 16 (kAnyK), so a piece of codes is two halves; the last tile may
+// also end at K, half way through a piece: what lies beyond is read from the tile's first 8 bytes, which every row has,
+// the scale bytes as the 16 that end with the row, and finish_tail makes zeros of the surplus when the tile goes to LDS.
+// So the last tile's loads are those of any other, in the same places between the matrix instructions.  (As a burst of
+// their own, each scale byte behind its own branch, they cost 1 us: the forward pass of
+// 1900 x 1360 -> 2136 28.3 -> 27.6 us.)
+struct TileOffsets {
+    int64_t lo, hi, s;
+};
+
 template <bool kAnyK>
-__device__ __forceinline__ uint4 load_codes16(const uint8_t *p)
+__device__ __forceinline__ TileOffsets tile_offsets(int kt, int64_t kt_stride, int64_t K)
 {
-    if (!kAnyK) return *reinterpret_cast<const uint4 *>(p);
-    const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 8);
-    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+    const int64_t k0 = (int64_t)kt * BK;
+    TileOffsets o = {k0 / 2, k0 / 2 + 8, kt * kt_stride};
+    if (kAnyK && k0 + BK > K) {   // uniform
+        const int off = 16 * (int)(threadIdx.x & 7), left = (int)(K - k0) - 2 * off;
+        if (left <= 0) o.lo -= off;
+        if (left <= 16) o.hi = k0 / 2 - off;
+        if (kt > 0) o.s += (K - k0) / 16 - 16;
+    }
+    return o;
 }
 
-__device__ __forceinline__ uint4 load_codes16_tail(const uint8_t *p, int64_t left)   // left: elements up to K
+template <bool kAnyK>
+__device__ __forceinline__ uint4 load_codes16(const uint8_t *p, const TileOffsets &o)
 {
-    uint2 lo = make_uint2(0u, 0u), hi = make_uint2(0u, 0u);
-    if (left > 0) lo = *reinterpret_cast<const uint2 *>(p);
-    if (left > 16) hi = *reinterpret_cast<const uint2 *>(p + 8);
+    if (!kAnyK) return *reinterpret_cast<const uint4 *>(p + o.lo);
+    const uint2 lo = *reinterpret_cast<const uint2 *>(p + o.lo), hi = *reinterpret_cast<const uint2 *>(p + o.hi);
     return make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
@@ -104,12 +121,12 @@ __device__ __forceinline__ uint4 load_scales16(const uint8_t *p)
     return make_uint4(lo.x, lo.y, hi.x, hi.y);
 }
 
-__device__ __forceinline__ uint4 load_scales16_tail(const uint8_t *p, int64_t left)
+// rows of fewer than 16 scale bytes (K < 256)
+__device__ __forceinline__ uint4 load_scales_short(const uint8_t *p, int groups)
 {
     uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int i = 0; i < 16; ++i)
-        if (16 * i < left) w[i >> 2] |= (uint32_t)p[i] << (8 * (i & 3));
+    for (int i = 0; i < 16; ++i) w[i >> 2] |= (i < groups ? (uint32_t)p[i < groups ? i : 0] : 0u) << (8 * (i & 3));
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
@@ -121,25 +138,37 @@ struct Sources {
     int64_t kt_stride;
 };
 
-template <class G, bool kAnyK>
+template <class G, bool kAnyK, bool kFirst>
 __device__ __forceinline__ void load_tile(Staged<G> &st, const Sources<G> &src, int kt, int64_t K)
 {
-    const int64_t k0 = (int64_t)kt * BK;
-    const bool scales = (int)threadIdx.x < G::BM + G::BN;
-    if (kAnyK && k0 + BK > K) {   // uniform: the last, partial tile
-        const int64_t left = K - k0 - 32 * (threadIdx.x & 7);
+    const TileOffsets o = tile_offsets<kAnyK>(kt, src.kt_stride, K);
 #pragma unroll
-        for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16_tail(src.a[p] + k0 / 2, left);
+    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<kAnyK>(src.a[p], o);
 #pragma unroll
-        for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16_tail(src.b[p] + k0 / 2, left);
-        if (scales) st.s = load_scales16_tail(src.s + kt * src.kt_stride, K - k0);
-        return;
+    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<kAnyK>(src.b[p], o);
+    if ((int)threadIdx.x < G::BM + G::BN) {
+        if (kAnyK && kFirst && K < BK) st.s = load_scales_short(src.s, (int)K / 16);   // uniform
+        else st.s = load_scales16<kAnyK>(src.s + o.s);
     }
+}
+
+// The last, partial tile as it came: zeros beyond K, the scale bytes to the front.
+template <class G>
+__device__ __forceinline__ void finish_tail(Staged<G> &st, int kt, int64_t K)
+{
+    const int tail = (int)(K - (int64_t)kt * BK), left = tail - 32 * (int)(threadIdx.x & 7);
+    const uint32_t lo = left > 0 ? 0xFFFFFFFFu : 0u, hi = left > 16 ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<kAnyK>(src.a[p] + k0 / 2);
+    for (int p = 0; p < G::kPassA; ++p) st.a[p] = make_uint4(st.a[p].x & lo, st.a[p].y & lo, st.a[p].z & hi, st.a[p].w & hi);
 #pragma unroll
-    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<kAnyK>(src.b[p] + k0 / 2);
-    if (scales) st.s = load_scales16<kAnyK>(src.s + kt * src.kt_stride);
+    for (int p = 0; p < G::kPassB; ++p) st.b[p] = make_uint4(st.b[p].x & lo, st.b[p].y & lo, st.b[p].z & hi, st.b[p].w & hi);
+    if (kt > 0) {   // (rows of 16 bytes or more)
+        const int drop = 8 * (16 - tail / 16);   // bits, 8 .. 120
+        uint64_t l = (uint64_t)st.s.y << 32 | st.s.x, h = (uint64_t)st.s.w << 32 | st.s.z;
+        l = drop < 64 ? (l >> drop) | (h << (64 - drop)) : h >> (drop - 64);
+        h = drop < 64 ? h >> drop : 0;
+        st.s = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+    }
 }
 
 // LDS stage: A codes, B codes (128 bytes per row; row r keeps its 16-byte piece s in slot s ^ (r & 7), so
@@ -211,7 +240,7 @@ __device__ __forceinline__ void mma_dword(floatx16 (&acc)[G::kUnits], const RawF
     for (int j = 0; j < G::NT; ++j)
 #pragma unroll
         for (int i = 0; i < G::MT; ++i)
-            acc[j * G::MT + i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i], fb[j], acc[j * G::MT + i], 0, 0, 0);
+            acc[i * G::NT + j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[j], fa[i], acc[i * G::NT + j], 0, 0, 0);   // (B first: store_tile)
 }
 
 // first and second half of the 64-wide K slice held in f
@@ -264,26 +293,28 @@ __device__ __forceinline__ void mma_step(floatx16 (&acc)[G::kUnits], const Frags
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int row = i >> 2, col = i & 3;
-        acc[col * G::MT + row] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.a[row], cu.b[col], acc[col * G::MT + row], 0, 0, 0);
+        acc[row * G::NT + col] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[col], cu.a[row], acc[row * G::NT + col], 0, 0, 0);
         side(i);
         dequant_chunk<G, D>(nx, f, i);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-// One round of the reduction over the K groups: groups kg and kg ^ D exchange halves of their N accumulator
-// tiles through LDS; the group with bit D clear keeps and completes the first half, the other the second.
-template <class G, int N, int D>
-__device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&out)[N / 2], uint8_t *smem, int wave, int kg, int lane)
+// One round of the reduction over the K groups: groups kg and kg ^ D exchange halves of their N accumulator tiles
+// through LDS; the group with bit D clear keeps and completes the first half, the other the second.  A wave writes the
+// area `own` and reads its partner's, `other`, which nobody else reads: after a round that area is the wave's own, for
+// the next round or the epilogue, with no barrier between.  The two halves are two pieces of code (the branch is
+// wave-uniform): chosen by value they cost a select per accumulator and round, 1.2 us of the 128 x 128 form's 5.5 from
+// the last product to the last store.
+template <int N, bool kHi>
+__device__ __forceinline__ void reduce_half(const floatx16 (&u)[N], floatx16 (&out)[N / 2], float4 *own, const float4 *other)
 {
-    const bool hi = (kg & D) != 0;   // wave-uniform
-    float4 *own = reinterpret_cast<float4 *>(smem) + wave * (N / 2) * 256 + lane;
-    const float4 *other = reinterpret_cast<const float4 *>(smem) + (wave ^ (D * G::WM)) * (N / 2) * 256 + lane;
+    constexpr int kGive = kHi ? 0 : N / 2, kKeep = kHi ? N / 2 : 0;
 #pragma unroll
     for (int k = 0; k < N / 2; ++k)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const floatx16 &give = hi ? u[k] : u[N / 2 + k];
+            const floatx16 &give = u[kGive + k];
             own[(k * 4 + r) * 64] = make_float4(give[4 * r], give[4 * r + 1], give[4 * r + 2], give[4 * r + 3]);
         }
     __syncthreads();
@@ -292,109 +323,34 @@ __device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float4 v = other[(k * 4 + r) * 64];
-            const floatx16 &keep = hi ? u[N / 2 + k] : u[k];
+            const floatx16 &keep = u[kKeep + k];
             out[k][4 * r] = keep[4 * r] + v.x;
             out[k][4 * r + 1] = keep[4 * r + 1] + v.y;
             out[k][4 * r + 2] = keep[4 * r + 2] + v.z;
             out[k][4 * r + 3] = keep[4 * r + 3] + v.w;
         }
-    __syncthreads();   // the area is written again by the next round or the epilogue
 }
 
-// Rows [32 ti, 32 ti + 32) of a wave's tile, scaled and converted, into its staging tile (row pitch `pitch`) from row `row0` on
-template <bool kBf16Out, int NT>
-__device__ __forceinline__ void stage_band(const floatx16 (&acc)[NT], uint8_t *wtile, int pitch, int row0, float ts, int li, int kb)
+template <int N>
+__device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&out)[N / 2], bool hi, uint8_t *own, const uint8_t *other, int lane)
 {
-    constexpr int esz = kBf16Out ? 2 : 4;
-#pragma unroll
-    for (int tj = 0; tj < NT; ++tj)
-#pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-            uint8_t *dst = wtile + (row0 + 8 * (r >> 2) + 4 * kb + (r & 3)) * pitch + (tj * 32 + li) * esz;
-            const float v0 = acc[tj][r] * ts, v1 = acc[tj][r + 1] * ts;
-            if (kBf16Out) {
-                const uint32_t bits = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{v0, v1}, bf16x2_t));
-                *reinterpret_cast<uint16_t *>(dst) = (uint16_t)bits;
-                *reinterpret_cast<uint16_t *>(dst + pitch) = (uint16_t)(bits >> 16);
-            } else {
-                *reinterpret_cast<float *>(dst) = v0;
-                *reinterpret_cast<float *>(dst + pitch) = v1;
-            }
-        }
+    if (hi) reduce_half<N, true>(u, out, reinterpret_cast<float4 *>(own) + lane, reinterpret_cast<const float4 *>(other) + lane);
+    else reduce_half<N, false>(u, out, reinterpret_cast<float4 *>(own) + lane, reinterpret_cast<const float4 *>(other) + lane);
 }
 
-// The epilogue of the two-group form (same arithmetic as store_tile_through_lds).  With K of a few hundred it is a large part of a
-// block, down to fetching its code, so rows of C that are 16-byte aligned have a kernel of their own (kAligned): 16-byte pieces, band
-// by band, and no code for other rows beside each piece.  Other rows: consecutive lanes store consecutive entries, from a staging tile of
-// all the wave's rows, eight rows in flight (the entries of a piece from one lane, one after the other, touch eight lines per store).
-// us, store_tile_through_lds -> this: bf16 9420 x 2177 x 176 53.6 -> 35.7, 922 x 12753 x 176 35.6 -> 25.4, 922 x 6000 x 176 13.2 -> 11.9;
-// f32 9420 x 2177 x 176 46.1 -> 36.9, 9420 x 2176 x 176 30.1 -> 28.8.
-template <bool kBf16Out, bool kAligned, int MT, int NT>
-__device__ __forceinline__ void store_tile_split(const floatx16 (&acc)[MT][NT], uint8_t *smem, float ts, void *Cout, int64_t ldc, int64_t M,
-                                                 int64_t N, int64_t row0, int64_t col0, int wave, int lane, int li, int kb, uint32_t *amax_out)
+// stores what the wave has finished: FM x FN tiles
+template <bool kBf16Out, class G>
+__device__ __forceinline__ void finish(const floatx16 (&u)[G::FM * G::FN], uint8_t *area, float ts, const SmallArgs &g, int64_t row0, int64_t col0, int lane)
 {
-    constexpr int esz = kBf16Out ? 2 : 4, rows = 32 * MT, cols = 32 * NT, pitch = cols * esz + 16;
-    constexpr int entries = 16 / esz, per_row = cols / entries, rows_per_pass = 64 / per_row;
-    static_assert(cols == 64, "a store of single entries covers one row");
-    uint8_t *wtile = smem + wave * (rows * pitch);
-    uint8_t *out = reinterpret_cast<uint8_t *>(Cout) + (row0 * ldc + col0) * esz;
-    const int live_rows = (int)(M - row0 < rows ? M - row0 : rows), live_cols = (int)(N - col0 < cols ? N - col0 : cols);   // (may be negative)
-    float cmax = 0.0f;
-    auto entry = [&](int row, int col) {
-        const uint8_t *src = wtile + row * pitch + col * esz;
-        return kBf16Out ? (uint32_t)*reinterpret_cast<const uint16_t *>(src) : *reinterpret_cast<const uint32_t *>(src);
-    };
-    auto put = [&](int row, int col, uint32_t v) {
-        uint8_t *dst = out + ((int64_t)row * ldc + col) * esz;
-        if (kBf16Out) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v;
-        else *reinterpret_cast<uint32_t *>(dst) = v;
-        cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v << 16 : v)));
-    };
-    if constexpr (kAligned) {   // (col0: a multiple of 32)
-        const int piece = lane % per_row, row_l = lane / per_row;
+    floatx16 c[G::FM][G::FN];
 #pragma unroll
-        for (int ti = 0; ti < MT; ++ti) {
-            stage_band<kBf16Out, NT>(acc[ti], wtile, pitch, ti * 32, ts, li, kb);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // wave-local: same wave reads below
+    for (int i = 0; i < G::FM; ++i)
 #pragma unroll
-            for (int pass = 0; pass < 32 / rows_per_pass; ++pass) {
-                const int row = ti * 32 + pass * rows_per_pass + row_l;
-                const u32x4 v = *reinterpret_cast<const u32x4 *>(wtile + row * pitch + piece * 16);
-                if (row < live_rows && (piece + 1) * entries <= live_cols) {
-                    if (amax_out)   // uniform
-#pragma unroll
-                        for (int e = 0; e < entries; ++e)
-                            cmax = fmaxf(cmax, fabsf(kBf16Out ? u2f((e & 1) ? (v[e >> 1] & 0xFFFF0000u) : (v[e >> 1] << 16)) : u2f(v[e & 3])));
-                    // C is written once and not read again here: a streaming (non-temporal) store
-                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(out + ((int64_t)row * ldc + piece * entries) * esz));
-                }
-            }
-        }
-        if (live_cols > 0 && live_cols % entries != 0 && lane < live_rows)   // the rows' last, partial piece (rows == 64)
-#pragma unroll 1
-            for (int col = live_cols / entries * entries; col < live_cols; ++col) put(lane, col, entry(lane, col));
-    } else {
-#pragma unroll
-        for (int ti = 0; ti < MT; ++ti) stage_band<kBf16Out, NT>(acc[ti], wtile, pitch, ti * 32, ts, li, kb);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (lane < live_cols) {
-            constexpr int kAtOnce = 8;   // the reads of several rows do not wait for the stores of those before
-#pragma unroll 1
-            for (int row = 0; row < live_rows; row += kAtOnce) {
-                uint32_t v[kAtOnce];
-#pragma unroll
-                for (int i = 0; i < kAtOnce; ++i) v[i] = entry(row + i, lane);
-#pragma unroll
-                for (int i = 0; i < kAtOnce; ++i)
-                    if (row + i < live_rows) put(row + i, lane, v[i]);
-            }
-        }
-    }
-    emit_tile_max(cmax, amax_out);
+        for (int j = 0; j < G::FN; ++j) c[i][j] = u[i * G::FN + j];
+    store_tile<kBf16Out, true, G::FM, G::FN, 1, 1>(c, area, ts, g.C, g.ldc, g.M, g.N, row0, col0, lane, g.amax_out);
 }
 
-// kAligned: the rows of every C are 16-byte aligned (used by the two-group form)
-template <bool kBf16Out, class G, bool kAnyK, bool kAligned>
+template <bool kBf16Out, class G, bool kAnyK>
 __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_kernel(SmallArgs g0, SmallArgs g1, int n0_blocks)
 {
     // one product, or two in one launch: the first n0_blocks blocks take g0, the others g1
@@ -428,7 +384,7 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
         src.kt_stride = of_a ? g.as.kt_stride : g.bs.kt_stride;
     }
 
-    floatx16 acc[G::kUnits];   // tile (i, j) of the wave at j MT + i
+    floatx16 acc[G::kUnits];   // tile (i, j) of the wave at i NT + j
 #pragma unroll
     for (int u = 0; u < G::kUnits; ++u)
 #pragma unroll
@@ -439,19 +395,30 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
     // fragments are in registers by then: all reads of this tile's stage are done, and the first slice of
     // the next tile is read while the rest is multiplied.
     const int ktiles = (int)((g.K + BK - 1) / BK);
+    const int partial = kAnyK ? ktiles - 1 : -1;   // the tile that K cuts
+    float ts_a, ts_b;
+    auto tensor_scales = [&]() {   // requested behind the first loads, not before them and not when the epilogue needs them
+        __builtin_amdgcn_sched_barrier(0);
+        ts_a = *g.a_ts;
+        ts_b = *g.b_ts;
+        __builtin_amdgcn_sched_barrier(0);
+    };
     Staged<G> st;
     if constexpr (G::MT == 4) {   // the first two tiles are requested together: one memory latency before the loop, not two
         // (2048 x 2048 x 5632 46.7 -> 44.7 us, 2048 x 2048 x 16384 117 -> 110; the other forms, with two waves per
         // SIMD, lose 1-2 %)
         Staged<G> st0;
-        load_tile<G, kAnyK>(st0, src, 0, g.K);
-        if (ktiles > 1) load_tile<G, kAnyK>(st, src, 1, g.K);
-        __builtin_amdgcn_sched_barrier(0);
+        load_tile<G, kAnyK, true>(st0, src, 0, g.K);
+        if (ktiles > 1) load_tile<G, kAnyK, false>(st, src, 1, g.K);
+        tensor_scales();
+        if (partial == 0) finish_tail<G>(st0, 0, g.K);
         store_tile<G>(st0, smem);
     } else {
-        load_tile<G, kAnyK>(st, src, 0, g.K);
+        load_tile<G, kAnyK, true>(st, src, 0, g.K);
+        tensor_scales();
+        if (partial == 0) finish_tail<G>(st, 0, g.K);
         store_tile<G>(st, smem);
-        if (ktiles > 1) load_tile<G, kAnyK>(st, src, 1, g.K);
+        if (ktiles > 1) load_tile<G, kAnyK, false>(st, src, 1, g.K);
     }
     __syncthreads();
     const int j0 = kg * G::kSlices;
@@ -464,22 +431,22 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
         // one tile: fc holds its raw slice, x its first fragments; fn takes the next tile's slice
         auto one_tile = [&](int kt, RawFrags<G> &fc, RawFrags<G> &fn) {
             uint8_t *nxt = smem + ((kt + 1) & 1) * G::kStage;
-            const bool whole = !kAnyK || (int64_t)(kt + 3) * BK <= g.K;   // tile kt + 2 is not the partial one (uniform)
-            const int64_t k2 = (int64_t)(kt + 2) * BK;
             const bool more = kt + 2 < ktiles;
+            if (kt + 1 == partial) finish_tail<G>(st, kt + 1, g.K);
+            const TileOffsets o = tile_offsets<kAnyK>(more ? kt + 2 : 0, src.kt_stride, g.K);
             uint8_t *dst = nxt + (t >> 3) * 128 + ((t & 7) ^ ((t >> 3) & 7)) * 16;
             auto no_side = [](int) {};
             auto move = [&](int i) {   // piece i of tile kt + 1 to LDS, its register takes tile kt + 2's piece
                 if (i < G::kPassA) {
                     *reinterpret_cast<uint4 *>(dst + i * G::kRowsPerPass * 128) = st.a[i];
-                    if (more && whole) st.a[i] = load_codes16<kAnyK>(src.a[i] + k2 / 2);
+                    if (more) st.a[i] = load_codes16<kAnyK>(src.a[i], o);
                 } else if (i < G::kPassA + G::kPassB) {
                     const int p = i - G::kPassA;
                     *reinterpret_cast<uint4 *>(dst + (G::BM + p * G::kRowsPerPass) * 128) = st.b[p];
-                    if (more && whole) st.b[p] = load_codes16<kAnyK>(src.b[p] + k2 / 2);
+                    if (more) st.b[p] = load_codes16<kAnyK>(src.b[p], o);
                 } else if (i == G::kPassA + G::kPassB) {   // (256 threads, 256 rows)
                     *reinterpret_cast<uint4 *>(nxt + (G::BM + G::BN) * 128 + t * 16) = st.s;
-                    if (more && whole) st.s = load_scales16<kAnyK>(src.s + (kt + 2) * src.kt_stride);
+                    if (more) st.s = load_scales16<kAnyK>(src.s + o.s);
                 }
             };
             const int slot = ((2 * j0 + kb) ^ (li & 7)) * 16, sc = 4 * j0 + 2 * kb;
@@ -494,7 +461,6 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
                 }
             };
             mma_step<G, 1>(acc, x, y, fc, move);
-            if (kAnyK && more && !whole) load_tile<G, kAnyK>(st, src, kt + 2, g.K);
             __syncthreads();
             mma_step<G, 2>(acc, y, x, fc, fetch);
             mma_step<G, 3>(acc, x, y, fc, no_side);
@@ -515,8 +481,9 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
     for (int kt = 0; kt < ktiles; ++kt) {
         uint8_t *cur = smem + (kt & 1) * G::kStage, *nxt = smem + ((kt + 1) & 1) * G::kStage;
         if (kt + 1 < ktiles) {
+            if (kt + 1 == partial) finish_tail<G>(st, kt + 1, g.K);
             store_tile<G>(st, nxt);
-            if (kt + 2 < ktiles) load_tile<G, kAnyK>(st, src, kt + 2, g.K);
+            if (kt + 2 < ktiles) load_tile<G, kAnyK, false>(st, src, kt + 2, g.K);
         }
         if (G::kSlices == 2) {
             // (one set of raw fragments: the other block on the compute unit covers their latency)
@@ -537,28 +504,20 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
     }
     __syncthreads();   // the reduction overlays the stages
 
-    const float ts = (*g.a_ts) * (*g.b_ts);
-    if constexpr (G::KG == 2) {   // groups finish columns 32 NT / 2 kg and on
+    // (wave w of the block has area w; partners have the same wm)
+    const float ts = ts_a * ts_b;
+    auto area = [&](int group) { return smem + (group * G::WM + wm) * G::kArea; };
+    const int64_t row0 = m0 + wm * 32 * G::MT;
+    if constexpr (G::KG == 2) {   // groups finish the first and the last MT / 2 bands
         floatx16 h[G::kUnits / 2];
-        reduce_round<G, G::kUnits, 1>(acc, h, smem, wave, kg, lane);
-        floatx16 c[G::MT][G::NT / 2];
-#pragma unroll
-        for (int i = 0; i < G::MT; ++i)
-#pragma unroll
-            for (int j = 0; j < G::NT / 2; ++j) c[i][j] = h[j * G::MT + i];
-        store_tile_split<kBf16Out, kAligned, G::MT, G::NT / 2>(c, smem, ts, g.C, g.ldc, g.M, g.N, m0 + wm * 32 * G::MT, n0 + kg * 16 * G::NT, wave, lane,
-                                                      li, kb, g.amax_out);
-    } else {
+        reduce_round(acc, h, kg != 0, area(kg), area(kg ^ 1), lane);
+        finish<kBf16Out, G>(h, area(kg ^ 1), ts, g, row0 + kg * 32 * G::FM, n0, lane);
+    } else {   // groups finish a band each, or (2 x 2) a tile each
         floatx16 h[G::kUnits / 2], q[G::kUnits / 4];
-        reduce_round<G, G::kUnits, 2>(acc, h, smem, wave, kg, lane);
-        reduce_round<G, G::kUnits / 2, 1>(h, q, smem, wave, kg, lane);
-        constexpr int kRows = G::kUnits / 4 >= G::MT ? G::MT : 1;   // a whole column of tiles, or one tile
-        floatx16 c[kRows][1];
-#pragma unroll
-        for (int i = 0; i < kRows; ++i) c[i][0] = q[i];
-        const int row = kRows == G::MT ? 0 : (kg & 1) * 32, col = kRows == G::MT ? kg * 32 : (kg >> 1) * 32;
-        store_tile_through_lds<kBf16Out, true, kRows, 1>(c, smem, ts, g.C, g.ldc, g.M, g.N, m0 + wm * 32 * G::MT + row, n0 + col, wave, 0, 0,
-                                                         lane, li, kb, g.amax_out);
+        reduce_round(acc, h, (kg & 2) != 0, area(kg), area(kg ^ 2), lane);
+        reduce_round(h, q, (kg & 1) != 0, area(kg ^ 2), area(kg ^ 3), lane);
+        const bool band = G::FN == G::NT;
+        finish<kBf16Out, G>(q, area(kg ^ 3), ts, g, row0 + (band ? kg : kg >> 1) * 32, n0 + (band ? 0 : kg & 1) * 32, lane);
     }
 }
 
@@ -575,20 +534,13 @@ template <bool kBf16Out, class G>
 hipError_t launch(SmallArgs *g, int count, hipStream_t s)
 {
     int blocks = 0;
-    bool aligned = G::KG == 2;   // (the other forms have one kernel for all rows)
     for (int i = 0; i < count; ++i) {
         g[i].tiles_m = (int)((g[i].M + G::BM - 1) / G::BM);
         g[i].tiles_n = (int)((g[i].N + G::BN - 1) / G::BN);
         blocks += g[i].tiles_m * g[i].tiles_n;
-        aligned = aligned && ((reinterpret_cast<uintptr_t>(g[i].C) | (uintptr_t)(g[i].ldc * (kBf16Out ? 2 : 4))) & 15) == 0;
     }
-    const bool any = g[0].K % BK != 0;
-    if constexpr (G::KG == 2)
-        if (aligned)
-            return any ? launch_kernel<gemm_small_kernel<kBf16Out, G, true, true>>(blocks, G::kThreads, G::kLds, g, count, s)
-                       : launch_kernel<gemm_small_kernel<kBf16Out, G, false, true>>(blocks, G::kThreads, G::kLds, g, count, s);
-    return any ? launch_kernel<gemm_small_kernel<kBf16Out, G, true, false>>(blocks, G::kThreads, G::kLds, g, count, s)
-               : launch_kernel<gemm_small_kernel<kBf16Out, G, false, false>>(blocks, G::kThreads, G::kLds, g, count, s);
+    return g[0].K % BK != 0 ? launch_kernel<gemm_small_kernel<kBf16Out, G, true>>(blocks, G::kThreads, G::kLds, g, count, s)
+                            : launch_kernel<gemm_small_kernel<kBf16Out, G, false>>(blocks, G::kThreads, G::kLds, g, count, s);
 }
 
 ScaleView view(const qii_nvfp4 &t, bool tiled)

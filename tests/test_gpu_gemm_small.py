@@ -68,6 +68,17 @@ def test_small_tile_kernels_match_the_oracle(oracle, M, N, K, route):
     check_product(oracle, M, N, K, True, route)
 
 
+@pytest.mark.parametrize("M,N,K,route", [
+    # the last K tile in each kernel: 2, 7, 8, 9 and 15 scale groups of it (its scale bytes are read as the 16 that end with the row), the
+    # second tile of two and the third of three, and rows shorter than 16 scale bytes
+    (65, 33, 288, T64), (65, 33, 368, T64), (65, 33, 384, T64), (65, 33, 400, T64), (65, 33, 496, T64), (130, 70, 880, T64), (33, 65, 112, T64),
+    (2040, 1990, 2080, T128_WIDE), (2040, 1990, 2160, T128_WIDE), (2040, 1990, 2192, T128_WIDE), (2040, 1990, 2288, T128_WIDE),
+    (2040, 1990, 752, T128_WIDE), (2040, 1990, 496, T128), (2300, 2301, 624, T128), (2040, 1990, 144, T128),
+])
+def test_the_last_k_tile_matches_the_oracle(oracle, M, N, K, route):
+    check_product(oracle, M, N, K, False, route)
+
+
 @pytest.mark.parametrize("M,N,K,use_ws,route", [
     # the kernel without a workspace: K an odd multiple of 128 (nine, three, one K tiles), and, without a workspace, an even one
     (8190, 4090, 1152, True, NO_WORKSPACE), (4090, 4080, 384, True, NO_WORKSPACE), (4090, 4080, 128, True, NO_WORKSPACE),
