@@ -533,13 +533,15 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     // slice g+2 at the start of step (g, 3), once the last conversion of slice g is done, a
     // full slice ahead of their first use.  The hand-over between the two LDS stages sits at
     // step (2, 3) of a tile: this wave's last read of the current stage (slice 3) has landed,
-    // so after the barrier tile kt+1, issued a whole tile earlier, is complete in the other
-    // stage and the current stage can take tile kt+2.
+    // so after the barrier tile kt+1, whose loads went out in slice 0 of this tile, is complete in the other
+    // stage and the current stage can take tile kt+2.  (Loads in slice 0, not a slice earlier behind the barrier: two
+    // and a half slices cover them as well, and a block begins with one tile's loads instead of two, 0.5 us: bf16
+    // 4096 x 4096 x 512 20.35 -> 20.09 us, 4096 x 4096 x 1024 31.05 -> 30.78, 8192 x 8192 x 512 72.2 -> 71.3, 2816 x 2048 x
+    // 16384 162.9 -> 162.1, one box in turn.)
     RawFrag4 fe, fo;
     Frags x, y;
     frag_read_issue<0>(all_reads, fe, read_addr<0>(fa, 0));
     frag_read_issue<1>(all_reads, fo, read_addr<1>(fa, 0));
-    if (ktiles > 1) issue_tile_loads(all_loads, smem + kStage4Bytes, src_a, src_b, kt0 + 1, wave);
     frag_read_wait(fe);   // (waits for both)
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -553,9 +555,10 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     for (int kt = 0; kt < ktiles; ++kt) {
         const uint32_t cur_off = (kt & 1) * kStage4Bytes, nxt_off = ((kt + 1) & 1) * kStage4Bytes;
         const NoSide none;
+        const TileDescriptors d = descriptors(src_a, src_b, kt + 1 < ktiles);
         // slice 0 (raw: fe)
-        mma_step<1>(acc, x, y, fe, none);
-        mma_step<2>(acc, y, x, fe, none);
+        mma_step<1>(acc, x, y, fe, LoadSide<0>{smem + nxt_off, src_a, src_b, d, kt0 + kt + 1, wave});
+        mma_step<2>(acc, y, x, fe, LoadSide<16>{smem + nxt_off, src_a, src_b, d, kt0 + kt + 1, wave});
         mma_step<3>(acc, x, y, fe, none);
         frag_read_wait(fo);
         mma_step<0>(acc, y, x, fo, ReadSide<2>{fe, read_addr<2>(fa, cur_off)});
@@ -574,15 +577,13 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
         __syncthreads();
         // (after the last tile the reads of slices 0 and 1 fetch a stale stage; the values are never used)
         mma_step<0>(acc, y, x, fo, ReadSide<0>{fe, read_addr<0>(fa, nxt_off)});
-        const TileDescriptors d = descriptors(src_a, src_b, kt + 2 < ktiles);
         // slice 3 (raw: fo)
-        mma_step<1>(acc, x, y, fo, LoadSide<0>{smem + cur_off, src_a, src_b, d, kt0 + kt + 2, wave});
-        mma_step<2>(acc, y, x, fo, LoadSide<16>{smem + cur_off, src_a, src_b, d, kt0 + kt + 2, wave});
+        mma_step<1>(acc, x, y, fo, none);
+        mma_step<2>(acc, y, x, fo, none);
         mma_step<3>(acc, x, y, fo, none);
         frag_read_wait(fe);
         mma_step<0>(acc, y, x, fe, ReadSide<1>{fo, read_addr<1>(fa, nxt_off)});
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (loads beyond the last tile write zeros: they land before LDS is reused)
     // the last read block is still in flight: its registers and the stages are reused below
     frag_read_wait(fo);
     __syncthreads();
