@@ -32,6 +32,11 @@ constexpr size_t kRegion = qii::kAmaxRegionBytes;   // the spread running maximu
 constexpr size_t kForwardWords = 2 * (size_t)qii::kForwardMaxWords * 4;   // forward pass: block maxima of X and of W
 size_t align_up(size_t v) { return (v + kSlot - 1) / kSlot * kSlot; }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
+bool overlap(const void *a, size_t na, const void *b, size_t nb)
+{
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return na && nb && pa < pb + nb && pb < pa + na;
+}
 
 qii_status check_nvfp4(const qii_nvfp4 *t, const char *name)
 {
@@ -263,6 +268,21 @@ qii_status scratch_address(void **out)
     return QII_OK;
 }
 
+// the single-read launch's arguments (words: post hoc scheme, one word per block)
+qii::PairQuantizeArgs pair_arguments(const qii::Source &src, int64_t rows, int64_t cols, qii_mode mode, uint64_t seed_rht_r, uint64_t seed_sr_r,
+                                     uint64_t seed_rht_c, uint64_t seed_sr_c, const qii_nvfp4 *out_r, const qii_nvfp4 *out_c, float *slot_r,
+                                     float *slot_c, float *tbuf_r, float *tbuf_c, int words)
+{
+    const bool ph = mode == QII_MS_EDEN_PH;
+    qii::PairQuantizeArgs p;
+    p.src = src; p.rows = rows; p.cols = cols; p.mode = (int)mode; p.amax_words = words;
+    p.r = {seed_rht_r, seed_sr_r, ph ? nullptr : slot_r, out_r->codes, out_r->scales, out_r->tensor_scale, tbuf_r,
+           ph ? reinterpret_cast<uint32_t *>(slot_r) : nullptr};
+    p.c = {seed_rht_c, seed_sr_c, ph ? nullptr : slot_c, out_c->codes, out_c->scales, out_c->tensor_scale, tbuf_c,
+           ph ? reinterpret_cast<uint32_t *>(slot_c) : nullptr};
+    return p;
+}
+
 // Q(x) and Q(x^T) of one dense matrix (MS-EDEN or its post hoc form, rotation over 128).  slots:
 // two abs-max areas (256 bytes each, or two 16 KiB regions for the post hoc scheme), tbufs: two
 // per-group buffers (post hoc scheme).  Uses the single-read kernel where it applies, else the two
@@ -296,12 +316,8 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
         e = qii::launch_absmax_tiles(src, rows, cols, seed_rht_r, slot_r, seed_rht_c, slot_c, s);
         if (e != hipSuccess) return hip_fail(e, "absmax");
     }
-    qii::PairQuantizeArgs p;
-    p.src = src; p.rows = rows; p.cols = cols; p.mode = (int)mode; p.amax_words = words;
-    p.r = {seed_rht_r, seed_sr_r, ph ? nullptr : slot_r, out_r->codes, out_r->scales, out_r->tensor_scale, tbuf_r,
-           ph ? reinterpret_cast<uint32_t *>(slot_r) : nullptr};
-    p.c = {seed_rht_c, seed_sr_c, ph ? nullptr : slot_c, out_c->codes, out_c->scales, out_c->tensor_scale, tbuf_c,
-           ph ? reinterpret_cast<uint32_t *>(slot_c) : nullptr};
+    const qii::PairQuantizeArgs p = pair_arguments(src, rows, cols, mode, seed_rht_r, seed_sr_r, seed_rht_c, seed_sr_c, out_r, out_c, slot_r,
+                                                   slot_c, tbuf_r, tbuf_c, words);
     e = qii::launch_quantize_pair(p, s);
     if (e != hipSuccess) return hip_fail(e, "quantize (both orientations)");
     if (ph) {
@@ -675,8 +691,8 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
         return fail(QII_WORKSPACE_TOO_SMALL, "linear_bwd needs %zu bytes of 256-byte aligned workspace", need);
     uint8_t *p = reinterpret_cast<uint8_t *>(ws);
     // quantizer workspace: four abs-max areas and, for the post hoc scheme, per-group f32 buffers: two for Q(E) and
-    // Q(E^T), whose heavy pass is one launch; once their scales pass has run, the same bytes hold those of W and of X
-    // where both fit (else W's and X's in turn)
+    // Q(E^T), whose heavy pass is one launch; those of W and X lie in the results (`at_once` below), or in the same bytes
+    // once E's scales pass has run, where both fit (else W's and X's in turn)
     hipStream_t s = (hipStream_t)stream;
     float *slots = reinterpret_cast<float *>(p);
     const bool ph = mode == QII_MS_EDEN_PH;
@@ -696,8 +712,8 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     // bytes come from the scales pass, which writes them straight into the layout the main GEMM
     // kernel reads when the GEMM's inner dimension allows that kernel: no re-tiling launch.
     const bool tile_dx = ph && d_out % 256 == 0, tile_dw = ph && T % 256 == 0;
-    // W and X are re-quantized by shared launches: heavy passes (post hoc scheme; both need a per-group buffer,
-    // which the two of E are by then free for, if the sizes allow) or abs-max and quantize passes.
+    // W and X are re-quantized by shared launches: heavy passes (post hoc scheme; both need a per-group buffer) or
+    // abs-max and quantize passes.
     qii::Source sq[2] = {};
     int64_t Rq[2] = {}, Cq[2] = {};
     st = nvfp4_source(Wq, 1, 128, &sq[0], &Rq[0], &Cq[0]);
@@ -705,14 +721,29 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     st = nvfp4_source(Xq, 1, 128, &sq[1], &Rq[1], &Cq[1]);
     if (st != QII_OK) return st;
     const size_t tw = align_up((size_t)(Rq[0] * (Cq[0] / 16)) * 4), tx = align_up((size_t)(Rq[1] * (Cq[1] / 16)) * 4);
-    const bool together = d_in > 0 && qii::requant_kernels_apply(sq[0], Rq[0], Cq[0]) && qii::requant_kernels_apply(sq[1], Rq[1], Cq[1]) &&
-                          (!ph || 4 * kRegion + tw + tx <= posthoc_region_bytes(T, d_in, d_out, mode));
+    const bool shared = d_in > 0 && qii::requant_kernels_apply(sq[0], Rq[0], Cq[0]) && qii::requant_kernels_apply(sq[1], Rq[1], Cq[1]);
+    const bool pair_e = qii::pair_kernel_applies(se, T, d_out);
+    // All four quantizations in one launch where E takes the single-read kernel.  The post hoc scheme then needs the
+    // per-group buffers of W and X beside those of E, for which the workspace has no room: the results, not yet
+    // written, take them (4 bytes per group of 16 entries), unless one is misaligned for it or shares bytes with
+    // something that the launch reads or writes.
+    const size_t g_esz = g_dt == QII_BF16 ? 2 : 4, dx_bytes = (size_t)(T * d_in) * g_esz, dw_bytes = (size_t)(d_out * d_in) * g_esz;
+    const void *used[] = {dY, Xq->codes, Xq->scales, Xq->tensor_scale, Wq->codes, Wq->scales, Wq->tensor_scale, ws, dX};
+    const size_t used_bytes[] = {(size_t)(T * d_out) * (dt == QII_BF16 ? 2 : 4), (size_t)(T * d_in / 2), (size_t)(T * (d_in / 16)), 4,
+                                 (size_t)(d_out * d_in / 2), (size_t)(d_out * (d_in / 16)), 4, need, dx_bytes};
+    bool at_once = shared && pair_e;
+    if (ph && at_once) {
+        at_once = aligned(dX, 16) && aligned(dW, 16);
+        for (int i = 0; i < 9; ++i)
+            if (overlap(dW, dw_bytes, used[i], used_bytes[i]) || (i < 8 && overlap(dX, dx_bytes, used[i], used_bytes[i]))) at_once = false;
+    }
+    const bool together = shared && (at_once || !ph || 4 * kRegion + tw + tx <= posthoc_region_bytes(T, d_in, d_out, mode));
     int words_q[2] = {0, 0};
     if (ph && together)
         for (int i = 0; i < 2; ++i) words_q[i] = qii::requant_blocks(Rq, Cq, 2, i);
     const bool words_ok = words_q[0] > 0 && words_q[0] <= qii::kMaxBlockWords && words_q[1] > 0 && words_q[1] <= qii::kMaxBlockWords;
     if (!words_ok) words_q[0] = words_q[1] = 0;
-    const bool words_e = ph && qii::pair_kernel_applies(se, T, d_out) && (T / 128) * (d_out / 128) <= qii::kMaxBlockWords;
+    const bool words_e = ph && pair_e && (T / 128) * (d_out / 128) <= qii::kMaxBlockWords;
     // (the post hoc scheme spreads each running maximum over 64 words, 256 bytes apart, where its blocks are too
     // many for a word each: the four regions are contiguous, so one launch clears all 256 words)
     hipError_t e = hipSuccess;
@@ -722,15 +753,25 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     if (e != hipSuccess) return hip_fail(e, "fill");
     // Q(E) and Q(E^T) from one read of dY: rotation sd[0] along d_out for the dX GEMM, sd[1] along
     // the tokens for the dW GEMM (their abs-max areas are the first and third of the four)
-    st = quantize_pair(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words, tbuf,
-                       tbuf2, s, true, tile_dx, tile_dw);
-    if (st != QII_OK) return st;
+    if (!at_once) {
+        st = quantize_pair(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words, tbuf,
+                           tbuf2, s, true, tile_dx, tile_dw);
+        if (st != QII_OK) return st;
+    }
     float *slot_q[2] = {slots + slot_words, slots + 3 * slot_words};
     if (together) {
         const qii_nvfp4 *out[2] = {&WTq, &XTq};
         const uint64_t rht[2] = {sd[0], sd[1]}, sr[2] = {sd[3], sd[5]};
         float *tb[2] = {tbuf, ph ? tbuf + tw / 4 : nullptr};
+        if (ph && at_once) {
+            tb[0] = reinterpret_cast<float *>(dW);
+            tb[1] = reinterpret_cast<float *>(dX);
+        }
         if (!ph) {
+            if (at_once) {
+                e = qii::launch_absmax_tiles(se, T, d_out, sd[0], slots, sd[1], slots + 2 * slot_words, s);
+                if (e != hipSuccess) return hip_fail(e, "absmax");
+            }
             e = qii::launch_absmax_requant(sq, Rq, Cq, 1, rht, slot_q, 2, s);
             if (e != hipSuccess) return hip_fail(e, "absmax");
         }
@@ -743,13 +784,19 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
             q[i].tbuf = tb[i]; q[i].amax_accum = ph ? reinterpret_cast<uint32_t *>(slot_q[i]) : nullptr;
             q[i].amax_words = words_q[i];
         }
-        e = qii::launch_quantize_requant(q, 2, s);
+        const int e_words = words_e ? (int)((T / 128) * (d_out / 128)) : 0;
+        if (at_once)
+            e = qii::launch_quantize_backward(pair_arguments(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words,
+                                                             tbuf, tbuf2, e_words), q, s);
+        else e = qii::launch_quantize_requant(q, 2, s);
         if (e != hipSuccess) return hip_fail(e, "quantize");
         if (ph) {
-            const qii::PosthocScales sc[2] = {
+            const qii::PosthocScales sc[4] = {
                 {tb[0], slot_q[0], false, words_q[0], Rq[0], Cq[0], sr[0], WTq.scales, WTq.tensor_scale, tile_dx},
-                {tb[1], slot_q[1], false, words_q[1], Rq[1], Cq[1], sr[1], XTq.scales, XTq.tensor_scale, tile_dw}};
-            e = qii::launch_posthoc_scales(sc, 2, s);
+                {tb[1], slot_q[1], false, words_q[1], Rq[1], Cq[1], sr[1], XTq.scales, XTq.tensor_scale, tile_dw},
+                {tbuf, slots, false, e_words, T, d_out, sd[2], Eq.scales, Eq.tensor_scale, tile_dx},
+                {tbuf2, slots + 2 * slot_words, false, e_words, d_out, T, sd[4], ETq.scales, ETq.tensor_scale, tile_dw}};
+            e = qii::launch_posthoc_scales(sc, at_once ? 4 : 2, s);
             if (e != hipSuccess) return hip_fail(e, "quantize (scales pass)");
         }
     }

@@ -95,7 +95,7 @@ hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint6
 hipError_t launch_rht(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, float *y,
                       float *amax /* nullable, must hold 0 */, hipStream_t s);
 hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s);
-// The scales pass of one or two tensors in one launch.  The maximum is supplied by the caller (one word), or
+// The scales pass of one to four tensors in one launch.  The maximum is supplied by the caller (one word), or
 // that of `words` words left by the heavy pass's blocks, or (words == 0) of its spread running maximum.  tiled (C
 // a multiple of 256): the scale bytes go out in the layout the main GEMM kernel reads ([row / 256][C / 256][row %
 // 256][16 bytes]; room for the row count rounded up to 256) instead of row-major
@@ -142,6 +142,9 @@ hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int6
 // words that the blocks of the abs-max pass over one such tensor leave: at most 64 (a 256-byte slot), else 0
 int requant_amax_words(const Source &src, int64_t R, int64_t C);
 hipError_t launch_quantize_requant(const QuantizeArgs *a, int count, hipStream_t s);
+// Q(E), Q(E^T) and the re-quantizations q of W and X in one launch (pair_kernel_applies to E, requant_kernels_apply to
+// both, all in one mode, the arguments as for the two launches; quantize_backward.hip)
+hipError_t launch_quantize_backward(const PairQuantizeArgs &e, const QuantizeArgs q[2], hipStream_t s);
 // ws (nullable): gemm_workspace_bytes(M, N, K) bytes, 16-byte aligned, for the re-tiled scale
 // bytes of the fast kernel; without it a slower kernel reads the row-major scales directly
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);

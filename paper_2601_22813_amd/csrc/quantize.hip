@@ -296,8 +296,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(Loader load, int64_t R, i
 // Algorithm 1 uses.  One thread takes 4 rows x 4 groups: four Philox calls (a call serves the
 // four rows of one group) and, when whole, one 16-byte load and one 4-byte store per row.  The vector unit
 // bounds it (the Philox calls above all).  The divisions take the short exact sequence, and the roundings the
-// form without subnormals, wherever a whole wave's operands allow.  Up to two tensors in one launch: the first n0
-// blocks take a0, the others a1.
+// form without subnormals, wherever a whole wave's operands allow.  Up to four tensors in one launch (the backward
+// pass's, quantize_backward.hip); a launch for one has its arguments at a fixed place, with no scalar load that waits for another.
 struct ScalesArgs {
     const float *tbuf, *amax;   // the tensor maximum is that of n_amax words, `stride` words apart
     int n_amax, stride;
@@ -337,13 +337,26 @@ __device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_
     return b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
 }
 
-__global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesArgs a0, ScalesArgs a1, int n0)
+template <int kTensors>
+struct ScalesLaunch {
+    ScalesArgs a[kTensors];
+    int end[kTensors];   // tensor i's blocks end here
+};
+
+template <int kTensors>
+__global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTensors> l)
 {
     __shared__ float wave_m[4];
-    const bool first = (int)blockIdx.x < n0;   // uniform
-    ScalesArgs a = a0;
-    if (!first) a = a1;
-    const int64_t block = (int64_t)blockIdx.x - (first ? 0 : n0);
+    const int id = (int)blockIdx.x;
+    ScalesArgs a = l.a[0];
+    int begin = 0;
+#pragma unroll
+    for (int i = 0; i + 1 < kTensors; ++i)
+        if (id >= l.end[i]) {   // uniform
+            a = l.a[i + 1];
+            begin = l.end[i];
+        }
+    const int64_t block = id - begin;
     float amax = 0.0f;
     for (int i = threadIdx.x; i < a.n_amax; i += 256) amax = fmaxf(amax, a.amax[(int64_t)i * a.stride]);
     amax = wave_max(amax);
@@ -505,21 +518,30 @@ int posthoc_words(const Source &src, int64_t R, int64_t C)
     return n <= kMaxBlockWords ? (int)n : 0;
 }
 
+template <int kTensors>
+static hipError_t launch_scales(const PosthocScales *p, int count, hipStream_t s)
+{
+    ScalesLaunch<kTensors> l = {};
+    int64_t blocks = 0;
+    for (int i = 0; i < kTensors; ++i) {
+        if (i < count) {
+            const int64_t G = p[i].C / 16;
+            if (p[i].tiled && p[i].C % 256 != 0) return hipErrorInvalidValue;
+            l.a[i] = ScalesArgs{p[i].tbuf, p[i].amax, p[i].words ? p[i].words : p[i].supplied ? 1 : (int)kAmaxSpread,
+                                p[i].words ? 1 : (int)kAmaxStrideWords, p[i].R, G, p[i].seed_sr, p[i].scales, p[i].tensor_scale,
+                                p[i].tiled ? p[i].C / 256 : (int64_t)0};
+            blocks += (((p[i].R + 3) / 4) * ((G + 3) / 4) + 255) / 256;
+        }
+        l.end[i] = (int)blocks;
+    }
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(posthoc_scales_kernel<kTensors>, dim3((unsigned)blocks), dim3(256), 0, s, l);
+    return hipGetLastError();
+}
+
 hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t s)
 {
-    ScalesArgs a[2];
-    int64_t blocks[2] = {0, 0};
-    for (int i = 0; i < count; ++i) {
-        const int64_t G = p[i].C / 16;
-        if (p[i].tiled && p[i].C % 256 != 0) return hipErrorInvalidValue;
-        a[i] = ScalesArgs{p[i].tbuf, p[i].amax, p[i].words ? p[i].words : p[i].supplied ? 1 : (int)kAmaxSpread,
-                          p[i].words ? 1 : (int)kAmaxStrideWords, p[i].R, G, p[i].seed_sr, p[i].scales, p[i].tensor_scale,
-                          p[i].tiled ? p[i].C / 256 : (int64_t)0};
-        blocks[i] = (((p[i].R + 3) / 4) * ((G + 3) / 4) + 255) / 256;
-    }
-    if (blocks[0] + blocks[1] == 0) return hipSuccess;
-    hipLaunchKernelGGL(posthoc_scales_kernel, dim3((unsigned)(blocks[0] + blocks[1])), dim3(256), 0, s, a[0], a[count - 1], (int)blocks[0]);
-    return hipGetLastError();
+    return count == 1 ? launch_scales<1>(p, count, s) : count == 2 ? launch_scales<2>(p, count, s) : launch_scales<4>(p, count, s);
 }
 
 hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const float *ts,

@@ -75,3 +75,45 @@ def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, m
             ref, absum = oracle.gemm_sampled(a, b, ms, ns)
             tol = 1e-5 * absum + (2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else 0.0) + 1e-30
             assert np.all(np.abs(bf16_to_f64(got)[ms, ns] - ref) <= tol)
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [(128, 128, 128), (512, 512, 512), (384, 208, 256), (1024, 2048, 2048), (4096, 2048, 4096)])
+@pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
+@pytest.mark.parametrize("place", ["apart", "misaligned", "dX in dY", "dW in dY", "dX beside dW"])
+def test_where_the_results_lie_makes_no_difference(T, d_in, d_out, mode, place):
+    """The four quantizations of a pass run in one launch, whose buffers of W and X the results' memory takes; results that are
+    misaligned for it, or share bytes with the gradient that the launch reads, get the launches one after the other.  The same bits."""
+    n_e, n_x, n_w = T * d_out, T * d_in, d_out * d_in
+    if (place == "dX in dY" and n_x > n_e) or (place == "dW in dY" and n_w > n_e):
+        pytest.skip("the result is larger than the gradient")
+    Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=8)
+    Xq, Wq = qii.NVFP4Tensor.empty(T, d_in), qii.NVFP4Tensor.empty(d_out, d_in)
+    for x, q in ((Xb, Xq), (Wb, Wq)):
+        qii.qii_quantize_nvfp4(to_dev(x), False, qii.RTN, 0, 0, 0, None, q, ws(256))
+
+    def run(E, dX, dW):
+        E.copy_(to_dev(Eb))
+        w = ws(qii.qii_linear_bwd_mode_workspace_bytes(T, d_in, d_out, mode))
+        w.fill_(0x7F)
+        qii.qii_linear_bwd_mode(E, Xq, Wq, 11, mode, dX, dW, w)
+        torch.cuda.synchronize()
+        return dX.clone(), dW.clone()
+
+    def buf(n, shape, off=0):
+        return torch.full((n + 16,), float("nan"), dtype=torch.bfloat16, device="cuda")[off:off + n].view(shape)
+
+    print(f"backward T={T} {d_in}->{d_out} mode {mode} {place}", flush=True)
+    eX, eW = run(buf(n_e, (T, d_out)), buf(n_x, (T, d_in), 1), buf(n_w, (d_out, d_in), 1))
+    E, dX, dW = buf(n_e, (T, d_out)), buf(n_x, (T, d_in)), buf(n_w, (d_out, d_in))
+    if place == "misaligned":
+        dW = buf(n_w, (d_out, d_in), 3)
+    elif place == "dX in dY":
+        dX = E.view(-1)[:n_x].view(T, d_in)
+    elif place == "dW in dY":
+        dW = E.view(-1)[n_e - n_w:].view(d_out, d_in)
+    elif place == "dX beside dW":
+        both = buf(n_x + n_w, (n_x + n_w,))
+        dX, dW = both[:n_x].view(T, d_in), both[n_x:].view(d_out, d_in)
+    gX, gW = run(E, dX, dW)
+    assert torch.isfinite(gX).all() and torch.isfinite(gW).all()
+    assert torch.equal(gX, eX) and torch.equal(gW, eW)
