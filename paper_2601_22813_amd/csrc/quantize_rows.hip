@@ -345,20 +345,41 @@ __global__ __launch_bounds__(256) void absmax_rows2_kernel(RowsArgs a0, RowsArgs
 }
 
 
-// waves of a block side by side on a row: as many as the row needs, at most 4
-int rows_wpr(int64_t C)
+// Waves of a block side by side on a row (a wave takes 8 chunks of 128).  Those beyond the row's end run the arithmetic
+// all the same, so a block's waves are as many as divide the row's: 4, 2 or 1.  Measured, whole calls, us, waves of a block
+// 1 : 2 : 4 (abs-max pass as below):
+//   5 waves   8192 x 4112 f32 SR 65.1 : 68.1 : 76.7, bf16 RTN 32.7 : 31.6 : 35.0; 2048 x 5120 f32 SR 26.3 : 25.8 : 28.7
+//   6 waves   8192 x 5632 f32 SR 79.5 : 78.0 : 89.2, bf16 MS-EDEN 46.3 : 46.1 : 52.1; 2048 x 5632 f32 SR 26.5 : 26.8 : 29.2
+//   7 waves   8192 x 7168 f32 SR 93.2 : 96.6 : 97.1, bf16 MS-EDEN 54.2 : 55.9 : 56.1
+//   4, 8      8192 x 8192 bf16 MS-EDEN 61.7 : 60.1 : 59.4, 1024 x 4096 bf16 forward pass 29.3 : 28.5 : 28.1
+//   3 waves   8192 x 2560 f32 SR 42.3 : 47.8 : 46.6, bf16 MS-EDEN 29.8 : 32.6 : 31.6; but in fours where the last chunk is a partial
+//             one (8192 x 2064 bf16 RTN 20.2 : 21.8 : 19.3) or rows are few (2048 x 3072 bf16 forward pass 32.7 : 32.2 : 32.0)
+int rows_waves(int64_t C) { return (int)(((C / 16 + 7) / 8 + 7) / 8); }
+
+int rows_wpr(int64_t R, int64_t C)
 {
-    const int64_t nch = (C / 16 + 7) / 8;   // 128-chunks per row; a wave takes 8
-    return nch <= 8 ? 1 : nch <= 16 ? 2 : 4;
+    const int waves = rows_waves(C);
+    if (waves == 3 && (C % 128 != 0 || R < 4096)) return 4;
+    return waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
 }
+
+// The abs-max passes: as many as the row needs, at most 4, but 2 where fours would leave some beyond the end of 5 waves or
+// more (2 : 4, quantizer as above: 8192 x 4112 bf16 RTN 32.7 : 35.2, 8192 x 5632 bf16 MS-EDEN 46.1 : 47.1, f32 SR 78.0 : 80.0; one
+// wave a block would leave every other one of a 1040-wide tensor's idle, and with it half of the dies).
+int absmax_wpr(int64_t C)
+{
+    const int waves = rows_waves(C);
+    return waves >= 5 && waves % 4 != 0 ? 2 : waves >= 3 ? 4 : waves;
+}
+
+// blocks side by side on a row
+int64_t rows_gy(int64_t C, int wpr) { return ((C / 16 + 7) / 8 + 8 * wpr - 1) / (8 * wpr); }
 
 // one wave per row quad x 1024 columns; max_block_rows > 0 caps the number of blocks below one
 // another (the abs-max pass then strides over the rest)
-dim3 rows_grid(int64_t R, int64_t C, int64_t max_block_rows)
+dim3 rows_grid(int64_t R, int64_t C, int wpr, int64_t max_block_rows)
 {
-    const int64_t G = C / 16, nch = (G + 7) / 8;
-    const int wpr = rows_wpr(C);
-    const int64_t gy = (nch + 8 * wpr - 1) / (8 * wpr);
+    const int64_t gy = rows_gy(C, wpr);
     const int64_t quads = (R + 3) / 4, qpb = 4 / wpr;
     int64_t gx = (quads + qpb - 1) / qpb;
     if (max_block_rows > 0 && gx > max_block_rows) {
@@ -368,7 +389,7 @@ dim3 rows_grid(int64_t R, int64_t C, int64_t max_block_rows)
     return dim3((unsigned)((gx < 1 ? 1 : gx) * gy), 1u);
 }
 
-RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, uint64_t seed_sr)
+RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, uint64_t seed_sr, int wpr)
 {
     RowsArgs a;
     a.x = src.x; a.ld = src.ld; a.R = R; a.C = C;
@@ -379,9 +400,8 @@ RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
     a.tbuf = nullptr;
     a.words = 0;
     a.tiled = nullptr;
-    a.wpr = rows_wpr(C);
-    const int64_t nch = (C / 16 + 7) / 8;
-    a.gy = (int)((nch + 8 * a.wpr - 1) / (8 * a.wpr));
+    a.wpr = wpr;
+    a.gy = (int)rows_gy(C, wpr);
     return a;
 }
 
@@ -397,10 +417,10 @@ bool rows_kernels_apply(const Source &src, int64_t R, int64_t C)
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s)
 {
-    RowsArgs a = make_args(src, R, C, seed_rht, 0);
+    RowsArgs a = make_args(src, R, C, seed_rht, 0, absmax_wpr(C));
     a.amax_out = reinterpret_cast<uint32_t *>(amax);
     const int64_t gy_ = a.gy;
-    const dim3 grid = rows_grid(R, C, 512 / gy_ > 0 ? 512 / gy_ : 1), block(256);   // two blocks per compute unit
+    const dim3 grid = rows_grid(R, C, a.wpr, 512 / gy_ > 0 ? 512 / gy_ : 1), block(256);   // two blocks per compute unit
     const bool bf = src.kind == kSrcBF16;
     if (bf) { if (rht) hipLaunchKernelGGL((absmax_rows_kernel<true, true>), grid, block, 0, s, a); else hipLaunchKernelGGL((absmax_rows_kernel<true, false>), grid, block, 0, s, a); }
     else { if (rht) hipLaunchKernelGGL((absmax_rows_kernel<false, true>), grid, block, 0, s, a); else hipLaunchKernelGGL((absmax_rows_kernel<false, false>), grid, block, 0, s, a); }
@@ -409,14 +429,14 @@ hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, 
 
 hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
 {
-    RowsArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr);
+    RowsArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr, rows_wpr(q.R, q.C));
     a.amax = q.amax; a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale;
     a.tbuf = q.tbuf; a.amax_out = q.amax_accum; a.words = q.amax_words;
     if (q.scales_tiled) {
         if (q.rht || q.C % 256 != 0 || q.mode == QII_MS_EDEN_PH) return hipErrorInvalidValue;
         a.tiled = q.scales_tiled;
     }
-    const dim3 grid = rows_grid(q.R, q.C, 0), block(256);
+    const dim3 grid = rows_grid(q.R, q.C, a.wpr, 0), block(256);
     const bool bf = q.src.kind == kSrcBF16;
 #define QII_ROWS(BF, MODE, RHT) hipLaunchKernelGGL((quantize_rows_kernel<BF, MODE, RHT>), grid, block, 0, s, a)
 #define QII_ROWS_MODE(BF, RHT)                                   \
@@ -434,17 +454,18 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
     return hipGetLastError();
 }
 
-int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, 0).x; }
+int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, rows_wpr(R, C), 0).x; }
 
 // Forward pass: Q(X) and Q(W), no rotation, RTN or RTN with 4/6.  Where a maximum is not supplied it is measured
 // first: about kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each (rows longer than 4096
 // elements take whole rows of blocks, so that both tensors together can have more; each has at most kForwardMaxWords).
 hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStream_t s)
 {
-    RowsArgs a[2];
+    RowsArgs a[2], m[2];   // of the quantize and of the abs-max launch
     int64_t size[2];
     for (int i = 0; i < 2; ++i) {
-        a[i] = make_args(q[i].src, q[i].R, q[i].C, 0, 0);
+        a[i] = make_args(q[i].src, q[i].R, q[i].C, 0, 0, rows_wpr(q[i].R, q[i].C));
+        m[i] = make_args(q[i].src, q[i].R, q[i].C, 0, 0, absmax_wpr(q[i].C));
         a[i].amax = q[i].amax;
         a[i].codes = q[i].codes; a[i].scales = q[i].scales; a[i].tensor_scale = q[i].tensor_scale;
         a[i].tiled = q[i].scales_tiled;
@@ -457,21 +478,21 @@ hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStr
         int n[2] = {0, 0};
         for (int i = 0; i < 2; ++i) {
             if (size[i] == 0) continue;
-            int64_t share = (int64_t)((double)kForwardMaxWords * (double)size[i] / (double)(size[0] + size[1])) / a[i].gy;
-            if (share * a[i].gy > kForwardMaxWords - 64) share = (kForwardMaxWords - 64) / a[i].gy;   // (the other tensor has room)
+            int64_t share = (int64_t)((double)kForwardMaxWords * (double)size[i] / (double)(size[0] + size[1])) / m[i].gy;
+            if (share * m[i].gy > kForwardMaxWords - 64) share = (kForwardMaxWords - 64) / m[i].gy;   // (the other tensor has room)
             if (share < 1) share = 1;
-            n[i] = (int)rows_grid(q[i].R, q[i].C, share).x;
+            n[i] = (int)rows_grid(q[i].R, q[i].C, m[i].wpr, share).x;
             if (n[i] > kForwardMaxWords) return hipErrorInvalidValue;   // (see forward_quantize_applies)
-            a[i].amax_out = reinterpret_cast<uint32_t *>(words + i * kForwardMaxWords);
+            m[i].amax_out = reinterpret_cast<uint32_t *>(words + i * kForwardMaxWords);
             a[i].amax = words + i * kForwardMaxWords;
             a[i].n_amax = n[i];
         }
         const dim3 grid((unsigned)(n[0] + n[1]));
-        if (bf) hipLaunchKernelGGL((absmax_rows2_kernel<true>), grid, block, 0, s, a[0], a[1], n[0]);
-        else hipLaunchKernelGGL((absmax_rows2_kernel<false>), grid, block, 0, s, a[0], a[1], n[0]);
+        if (bf) hipLaunchKernelGGL((absmax_rows2_kernel<true>), grid, block, 0, s, m[0], m[1], n[0]);
+        else hipLaunchKernelGGL((absmax_rows2_kernel<false>), grid, block, 0, s, m[0], m[1], n[0]);
     }
-    const int n0 = (int)rows_grid(q[0].R, q[0].C, 0).x;
-    const dim3 grid((unsigned)n0 + rows_grid(q[1].R, q[1].C, 0).x);
+    const int n0 = (int)rows_grid(q[0].R, q[0].C, a[0].wpr, 0).x;
+    const dim3 grid((unsigned)n0 + rows_grid(q[1].R, q[1].C, a[1].wpr, 0).x);
 #define QII_FWD(BF, MODE) hipLaunchKernelGGL((quantize_rows2_kernel<BF, MODE>), grid, block, 0, s, a[0], a[1], n0)
     if (q[0].mode == QII_RTN) { if (bf) QII_FWD(true, QII_RTN); else QII_FWD(false, QII_RTN); }
     else { if (bf) QII_FWD(true, QII_RTN_46); else QII_FWD(false, QII_RTN_46); }
