@@ -144,29 +144,33 @@ qii_status quantize_source(const qii::Source &src, int64_t R, int64_t C, qii_mod
         return QII_OK;
     }
     if (tiled_scales) return fail(QII_INVALID_ARG, "tiled scales are written by the post hoc scheme only");
-    const float *amax = amax_in;
+    qii::QuantizeArgs a;
+    a.src = src; a.R = R; a.C = C; a.mode = (int)mode; a.rht = rht_group == 128;
+    a.seed_rht = seed_rht; a.seed_sr = seed_sr; a.amax = amax_in;
+    a.codes = out->codes; a.scales = out->scales; a.tensor_scale = out->tensor_scale;
+    a.tbuf = nullptr; a.amax_accum = nullptr;
+    a.scales_tiled = tiled_copy;
+    if (!amax_in && !amax_slot) return fail(QII_WORKSPACE_TOO_SMALL, "workspace needed to measure the abs-max");
+    if (!amax_in && qii::measures_itself(a)) {
+        hipError_t e = qii::launch_quantize_small(a, s);
+        if (e != hipSuccess) return hip_fail(e, "quantize");
+        return QII_OK;
+    }
     // a re-quantization of few blocks leaves a word per block and needs no clearing launch
     const int words = amax_in ? 0 : qii::requant_amax_words(src, R, C);
-    if (words && amax_slot) {
+    if (words) {
         hipError_t e = qii::launch_absmax_requant(&src, &R, &C, rht_group == 128, &seed_rht, &amax_slot, 1, s, words);
         if (e != hipSuccess) return hip_fail(e, "absmax");
-        amax = amax_slot;
-    } else if (!amax) {
-        if (!amax_slot) return fail(QII_WORKSPACE_TOO_SMALL, "workspace needed to measure the abs-max");
+        a.amax = amax_slot;
+    } else if (!amax_in) {
         hipError_t e = hipSuccess;
         if (!slot_zeroed) e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_slot), 0u, 1, 1, s);
         if (e != hipSuccess) return hip_fail(e, "fill");
         e = qii::launch_absmax(src, R, C, rht_group == 128, seed_rht, amax_slot, s);
         if (e != hipSuccess) return hip_fail(e, "absmax");
-        amax = amax_slot;
+        a.amax = amax_slot;
     }
-    qii::QuantizeArgs a;
-    a.src = src; a.R = R; a.C = C; a.mode = (int)mode; a.rht = rht_group == 128;
-    a.seed_rht = seed_rht; a.seed_sr = seed_sr; a.amax = amax;
-    a.codes = out->codes; a.scales = out->scales; a.tensor_scale = out->tensor_scale;
-    a.tbuf = nullptr; a.amax_accum = nullptr;
     a.amax_words = words;
-    a.scales_tiled = tiled_copy;
     hipError_t e = qii::launch_quantize(a, s);
     if (e != hipSuccess) return hip_fail(e, "quantize");
     return QII_OK;

@@ -122,6 +122,9 @@ bool rows_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s);
 hipError_t launch_quantize_rows(const QuantizeArgs &a, hipStream_t s);
+// a small tensor (no rotation; amax not needed) whose blocks measure it themselves
+bool measures_itself(const QuantizeArgs &q);
+hipError_t launch_quantize_small(const QuantizeArgs &q, hipStream_t s);
 // Q(X) and Q(W) of a forward pass (no rotation, QII_RTN or QII_RTN_46) in one launch, after one that measures the
 // maxima that are not supplied (amax null); words: room for 2 * kForwardMaxWords floats
 constexpr int kForwardMaxWords = 1024;

@@ -3,9 +3,8 @@
 //
 // Layout of the work: a lane owns one 16-element scale group, 8 lanes one 128-chunk, a wave
 // 8 consecutive chunks of a row (1024 elements, 2 KiB of bf16) of one quad of 4 rows (one
-// scale-rounding draw call serves the 4 rows of a group), a block 4 waves: side by side on
-// wide tensors, or, when a row needs fewer than 4 waves, 2 or 4 row quads.  blockIdx.y selects
-// the column range, blockIdx.x the row quads.  The four rows of a quad are requested together
+// scale-rounding draw call serves the 4 rows of a group), or of one row of a small tensor; a block 4
+// waves, side by side on a row or below one another (rows_wpr).  A wave's rows are requested together
 // (32 B per lane and row) before anything else happens in the kernel.
 // The octet register layout and its rotation are in quantize_lanes.h.
 #include "qii_device.h"
@@ -40,13 +39,11 @@ struct RowsArgs {
 };
 
 struct LaneSetup : OctetLane {
-    int quad;             // this wave's row quad (rows 4 quad .. 4 quad + 3); wave-uniform
+    int unit;             // this wave's rows: kRows unit .. kRows unit + kRows - 1; wave-uniform
     int64_t g;            // scale group within the row
     bool col_ok;
 };
 
-// kQuadsPerWave: row quads a wave takes (the quantizers: 1; the abs-max pass: 2)
-template <int kQuadsPerWave>
 __device__ __forceinline__ LaneSetup lane_setup(const RowsArgs &a, int64_t G, int block)
 {
     LaneSetup L;
@@ -54,11 +51,11 @@ __device__ __forceinline__ LaneSetup lane_setup(const RowsArgs &a, int64_t G, in
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, kept in a scalar register
     static_cast<OctetLane &>(L) = octet_lane(lane, a.sign);
     // wpr waves side by side, 4 / wpr waves below one another
-    const int wcol = wave & (a.wpr - 1), wq = wave / a.wpr, qpb = 4 / a.wpr;
+    const int wcol = wave & (a.wpr - 1), wq = wave / a.wpr, upb = 4 / a.wpr;
     // consecutive blocks walk along a row first, then down the rows: blocks that run at the same
     // time read one contiguous region of the tensor
     const int bx = block / a.gy, by = block - bx * a.gy;
-    L.quad = (bx * qpb + wq) * kQuadsPerWave;
+    L.unit = bx * upb + wq;
     const int64_t chunk = ((int64_t)by * a.wpr + wcol) * 8 + (lane >> 3);
     L.g = chunk * 8 + L.blk;
     L.col_ok = L.g < G;
@@ -100,11 +97,11 @@ __device__ __forceinline__ void load_raw(Raw<kBf16> &r, const RowsArgs &a, int r
     for (int i = 0; i < n; ++i) r.q[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff + 16u * i, 0, 0);
 }
 
-template <bool kBf16>
-__device__ __forceinline__ void load_quad(Raw<kBf16> raw[4], const RowsArgs &a, int quad, uint32_t voff)
+template <bool kBf16, int kRows>
+__device__ __forceinline__ void load_rows(Raw<kBf16> raw[kRows], const RowsArgs &a, int unit, uint32_t voff)
 {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) load_raw<kBf16>(raw[it], a, quad * 4 + it, voff);
+    for (int it = 0; it < kRows; ++it) load_raw<kBf16>(raw[it], a, unit * kRows + it, voff);
 }
 
 // widen to f32 and apply the rotation signs (sign masks are lane constants)
@@ -136,21 +133,22 @@ struct StoreOffsets {
     uint32_t tiled8;   // the chunk's 8 scale bytes within the tiled copy, relative to (row tile, row)
 };
 
-// One quad of rows for one lane: the four rows' raw words are in registers (requested at the very
+// A wave's rows (a quad or one) for one lane: their raw words are in registers (requested at the very
 // start of the kernel).
-template <bool kBf16, int kMode, bool kRht, int kFast>
-__device__ __forceinline__ void quantize_quad(const RowsArgs &a, const LaneSetup &L, const TensorConsts &tc,
-                                              const uint32_t *mask, Raw<kBf16> raw[4], int64_t G,
+template <bool kBf16, int kMode, bool kRht, int kFast, int kRows>
+__device__ __forceinline__ void quantize_rows(const RowsArgs &a, const LaneSetup &L, const TensorConsts &tc,
+                                              const uint32_t *mask, Raw<kBf16> raw[kRows], int64_t G,
                                               const StoreOffsets &so, float &m, const float *inv_tab)
 {
     uint32_t draw[4] = {0u, 0u, 0u, 0u};
     if (kMode == QII_MS_EDEN) {
-        const U4 w = philox_seeded(a.seed_sr, (uint32_t)L.g, (uint32_t)L.quad, 0, kStreamScale);
+        const U4 w = philox_seeded(a.seed_sr, (uint32_t)L.g, (uint32_t)(L.unit * kRows / 4), 0, kStreamScale);
         draw[0] = w.x >> 12; draw[1] = w.y >> 12; draw[2] = w.z >> 12; draw[3] = w.w >> 12;
+        if (kRows == 1) draw[0] = draw[L.unit & 3];   // (wave-uniform)
     }
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int row = L.quad * 4 + it;   // wave-uniform
+    for (int it = 0; it < kRows; ++it) {
+        const int row = L.unit * kRows + it;   // wave-uniform
         float v[16];
         unpack_signed<kBf16, kRht>(raw[it], v, mask);
         if (kRht) rht128_lane(v, L);
@@ -211,28 +209,68 @@ __device__ __forceinline__ float reduce_words(const RowsArgs &a, const float w[4
     return fmaxf(fmaxf(wave_m[0], wave_m[1]), fmaxf(wave_m[2], wave_m[3]));
 }
 
+constexpr int kMeasuringWaves = 16;   // of a block that measures its tensor
+
+// A small dense tensor's maximum, measured by every block of kMeasuringWaves waves for itself: contiguous 16-byte pieces, eight
+// in flight per thread (beyond the tensor they read as zeros).
+template <bool kBf16>
+__device__ __forceinline__ float measure_tensor(const RowsArgs &a, float *wave_m)
+{
+    constexpr int kAtOnce = 8, kStep = kMeasuringWaves * 64 * 16;
+    const int bytes = (int)(a.R * a.C * (kBf16 ? 2 : 4));
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(a.x), 0, bytes, 0x00020000);
+    float m = 0.0f;
+    for (int base = 0; base < bytes; base += kAtOnce * kStep) {
+        u32x4 w[kAtOnce];
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, base + i * kStep + (int)threadIdx.x * 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < kAtOnce; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (kBf16) m = fmaxf(fmaxf(m, fabsf(bf16_lo(w[i][j]))), fabsf(bf16_hi(w[i][j])));
+                else m = fmaxf(m, fabsf(u2f(w[i][j])));
+            }
+    }
+    m = wave_max(m);
+    if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = wave_m[0];
+#pragma unroll
+    for (int i = 1; i < kMeasuringWaves; ++i) m = fmaxf(m, wave_m[i]);
+    return m;
+}
+
 // One wave = one quad of rows x 1024 columns, one block = 4 such pieces; the grid covers the tensor.
 // Blocks are short-lived on purpose: many independent blocks that start and finish at different
 // times keep the memory traffic of the chip smooth, where long-lived waves marching in step (a
 // grid-stride loop with prefetch was measured) load and compute in bursts and ran 10 % slower.
-// kWords: the maximum may be that of several words.
-template <bool kBf16, int kMode, bool kRht, bool kWords>
+// kMax: the tensor's maximum is one word, or may be that of several, or every block measures it (a small tensor).
+enum MaxFrom { kOneWord, kWords, kMeasured };
+
+template <bool kBf16, int kMode, bool kRht, MaxFrom kMax, int kRows>
 __device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
 {
     __shared__ float inv_tab[128];
-    __shared__ float wave_m[4];
+    __shared__ float wave_m[kMax == kMeasured ? kMeasuringWaves : 4];
     constexpr int esz = kBf16 ? 2 : 4;
     const int64_t G = a.C / 16;
-    const LaneSetup L = lane_setup<1>(a, G, block);
+    // (the waves beyond the fourth of a measuring block have no rows: they load nothing and end once the maximum is known)
+    const bool has_rows = kMax != kMeasured || threadIdx.x < 256;   // wave-uniform
+    LaneSetup L = lane_setup(a, G, block);
+    if (!has_rows) L.unit = (int)(a.R + 1);
     // the rows are requested before anything else: the loads do not depend on the tensor
     // constants, whose set-up (a dependent load, divisions, the table) then overlaps them
     const uint32_t voff = (uint32_t)L.g * (16u * esz);   // (beyond the row for lanes beyond the last column)
     float words[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (kWords) request_words(a, words);
-    Raw<kBf16> raw[4];
-    load_quad<kBf16>(raw, a, L.quad, voff);
+    if (kMax == kWords) request_words(a, words);
+    Raw<kBf16> raw[kRows];
+    load_rows<kBf16, kRows>(raw, a, L.unit, voff);
     // (the heavy pass of the post hoc scheme knows no tensor maximum: tc stays unused there)
-    const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{} : tensor_consts(kMode, kWords ? reduce_words(a, words, wave_m) : *a.amax);
+    const TensorConsts tc = kMode == QII_MS_EDEN_PH ? TensorConsts{}
+                                                    : tensor_consts(kMode, kMax == kMeasured ? measure_tensor<kBf16>(a, wave_m)
+                                                                           : kMax == kWords  ? reduce_words(a, words, wave_m) : *a.amax);
+    if (!has_rows) return;   // (a wave that has ended takes no part in barriers)
     if (kMode != QII_MS_EDEN_PH && block == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
     StoreOffsets so;
     so.codes = L.col_ok ? (uint32_t)L.g * 8u : kNoStore;
@@ -241,8 +279,8 @@ __device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
     so.t4 = L.col_ok ? (uint32_t)L.g * 4u : kNoStore;
     so.tiled8 = (L.col_ok && L.blk == 0) ? (uint32_t)(L.g >> 4) * 4096u + (uint32_t)((L.g >> 3) & 1) * 8u : kNoStore;
     if (tc.zero) {  // uniform: an all-zero tensor is emitted as zero bytes
-        for (int it = 0; it < 4; ++it) {
-            const int64_t row = (int64_t)L.quad * 4 + it;
+        for (int it = 0; it < kRows; ++it) {
+            const int64_t row = (int64_t)L.unit * kRows + it;
             if (L.col_ok && row < a.R) {
                 *reinterpret_cast<uint2 *>(a.codes + (row * a.C + L.g * 16) / 2) = make_uint2(0u, 0u);
                 a.scales[row * G + L.g] = 0;
@@ -256,9 +294,9 @@ __device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
     make_masks<kBf16>(L.sign16, mask);
     float m = 0.0f;
     if (kMode == QII_MS_EDEN_PH || tc.fast)   // uniform: one branch for the whole kernel
-        quantize_quad<kBf16, kMode, kRht, 1>(a, L, tc, mask, raw, G, so, m, inv_tab);
+        quantize_rows<kBf16, kMode, kRht, 1, kRows>(a, L, tc, mask, raw, G, so, m, inv_tab);
     else
-        quantize_quad<kBf16, kMode, kRht, 0>(a, L, tc, mask, raw, G, so, m, inv_tab);
+        quantize_rows<kBf16, kMode, kRht, 0, kRows>(a, L, tc, mask, raw, G, so, m, inv_tab);
     if (kMode == QII_MS_EDEN_PH && a.amax_out) {   // uniform: one update per block, spread over the slot's words
         m = wave_max(m);
         if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = m;
@@ -268,20 +306,30 @@ __device__ __forceinline__ void quantize_rows_body(const RowsArgs &a, int block)
     }
 }
 
-template <bool kBf16, int kMode, bool kRht>
+template <bool kBf16, int kMode, bool kRht, int kRows>
 __global__ __launch_bounds__(256) void quantize_rows_kernel(RowsArgs a)
 {
-    quantize_rows_body<kBf16, kMode, kRht, false>(a, (int)blockIdx.x);
+    quantize_rows_body<kBf16, kMode, kRht, kOneWord, kRows>(a, (int)blockIdx.x);
 }
 
 // X and W of a forward pass in one launch: the first n0 blocks take a0
-template <bool kBf16, int kMode>
+template <bool kBf16, int kMode, int kRows>
 __global__ __launch_bounds__(256) void quantize_rows2_kernel(RowsArgs a0, RowsArgs a1, int n0)
 {
     const bool first = (int)blockIdx.x < n0;   // uniform
     RowsArgs a = a0;
     if (!first) a = a1;
-    quantize_rows_body<kBf16, kMode, false, true>(a, (int)blockIdx.x - (first ? 0 : n0));
+    quantize_rows_body<kBf16, kMode, false, kWords, kRows>(a, (int)blockIdx.x - (first ? 0 : n0));
+}
+
+// The same for small tensors whose maxima are not supplied, one or two of them: every block measures its tensor.
+template <bool kBf16, int kMode>
+__global__ __launch_bounds__(64 * kMeasuringWaves) void quantize_small_rows_kernel(RowsArgs a0, RowsArgs a1, int n0)
+{
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    RowsArgs a = a0;
+    if (!first) a = a1;
+    quantize_rows_body<kBf16, kMode, false, kMeasured, 1>(a, (int)blockIdx.x - (first ? 0 : n0));
 }
 
 // Abs-max pass.  Its result is one word that every block has to fold its maximum into, and such
@@ -294,7 +342,7 @@ __device__ __forceinline__ float absmax_rows_body(const RowsArgs &a, int block, 
     constexpr int esz = kBf16 ? 2 : 4;
     __shared__ float wave_m[4];
     const int64_t G = a.C / 16;
-    const LaneSetup L = lane_setup<1>(a, G, block);
+    const LaneSetup L = lane_setup(a, G, block);
     const int quads = (int)((a.R + 3) / 4);
     const int step = (blocks / a.gy) * (4 / a.wpr);
     const uint32_t voff = (uint32_t)L.g * (16u * esz);
@@ -302,10 +350,10 @@ __device__ __forceinline__ float absmax_rows_body(const RowsArgs &a, int block, 
     make_masks<kBf16>(L.sign16, mask);
     float m = 0.0f;
     Raw<kBf16> raw[4];
-    load_quad<kBf16>(raw, a, L.quad, voff);   // (rows and columns beyond the tensor read as 0 and cannot change the maximum)
-    for (int quad = L.quad; quad < quads; quad += step) {
+    load_rows<kBf16, 4>(raw, a, L.unit, voff);   // (rows and columns beyond the tensor read as 0 and cannot change the maximum)
+    for (int quad = L.unit; quad < quads; quad += step) {
         Raw<kBf16> nxt[4];
-        load_quad<kBf16>(nxt, a, quad + step, voff);
+        load_rows<kBf16, 4>(nxt, a, quad + step, voff);
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             float v[16];
@@ -363,6 +411,21 @@ int rows_wpr(int64_t R, int64_t C)
     return waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
 }
 
+// Rows of a quantizer's wave: a quad, whose rows share a scale-rounding draw call, or one where quads leave the GPU's 1024
+// vector units short of waves, each of which then works its four rows off one after the other.  Whole calls, us, quads : rows
+// (`waves`: those that quads make):
+//   64 waves     256 x  256 f32 RTN 8.6 : 7.6, 4/6 9.7 : 7.9, SR 10.6 : 8.2, MS-EDEN 11.0 : 9.0, post hoc 9.9 : 7.8
+//   256 waves   1024 x 1024 bf16 RTN 8.5 : 7.6, 4/6 9.7 : 8.1, SR 10.7 : 8.3, MS-EDEN 10.9 : 9.1, post hoc 10.4 : 8.4
+//   512 waves   2048 x 1024 bf16 RTN 9.3 : 8.5, MS-EDEN 11.7 : 10.3, post hoc 10.5 : 9.2; f32 RTN 10.1 : 10.2
+//   1024 waves  2048 x 2048 bf16 RTN 10.8 : 11.3, MS-EDEN 13.0 : 14.0, post hoc 11.0 : 11.3; f32 12.1 : 12.8, 15.2 : 15.0
+//   2048 waves  4096 x 2048 f32 RTN 18.1 : 20.0, bf16 post hoc 13.7 : 14.5
+// 4/6 has twice the arithmetic per row and gains a little longer (forward passes, both tensors' waves: 1280 26.8 : 25.2, 2048 31.8 : 31.4,
+// 4096 46.2 : 46.1).
+int rows_per_wave(int64_t R, int64_t C, int mode)
+{
+    return (R + 3) / 4 * rows_waves(C) < (mode == QII_RTN_46 ? 2048 : 1024) ? 1 : 4;
+}
+
 // The abs-max passes: as many as the row needs, at most 4, but 2 where fours would leave some beyond the end of 5 waves or
 // more (2 : 4, quantizer as above: 8192 x 4112 bf16 RTN 32.7 : 35.2, 8192 x 5632 bf16 MS-EDEN 46.1 : 47.1, f32 SR 78.0 : 80.0; one
 // wave a block would leave every other one of a 1040-wide tensor's idle, and with it half of the dies).
@@ -375,13 +438,13 @@ int absmax_wpr(int64_t C)
 // blocks side by side on a row
 int64_t rows_gy(int64_t C, int wpr) { return ((C / 16 + 7) / 8 + 8 * wpr - 1) / (8 * wpr); }
 
-// one wave per row quad x 1024 columns; max_block_rows > 0 caps the number of blocks below one
+// one wave per `rows` rows (4, or 1: rows_per_wave) x 1024 columns; max_block_rows > 0 caps the number of blocks below one
 // another (the abs-max pass then strides over the rest)
-dim3 rows_grid(int64_t R, int64_t C, int wpr, int64_t max_block_rows)
+dim3 rows_grid(int64_t R, int64_t C, int wpr, int64_t max_block_rows, int rows = 4)
 {
     const int64_t gy = rows_gy(C, wpr);
-    const int64_t quads = (R + 3) / 4, qpb = 4 / wpr;
-    int64_t gx = (quads + qpb - 1) / qpb;
+    const int64_t units = (R + rows - 1) / rows, upb = 4 / wpr;
+    int64_t gx = (units + upb - 1) / upb;
     if (max_block_rows > 0 && gx > max_block_rows) {
         const int64_t iters = (gx + max_block_rows - 1) / max_block_rows;
         gx = (gx + iters - 1) / iters;   // even split
@@ -414,6 +477,39 @@ bool rows_kernels_apply(const Source &src, int64_t R, int64_t C)
            R < ((int64_t)1 << 31) - 8;   // row indices are 32-bit in the kernels
 }
 
+// A tensor so small that the blocks of its quantizer had better measure it themselves (from L2, all of it, each) than
+// wait for an abs-max launch, and in a call of its own for a clearing launch too.  Whole calls, us, abs-max launch : measured by
+// every block (one row per wave in both): 128 x 128 f32 RTN 7.5 : 4.4, SR 8.0 : 5.0; 256 x 256 f32 RTN 7.6 : 5.4, forward pass
+// 10.6 : 9.8, bf16 10.3 : 8.8; 256 x 512 bf16 RTN 7.2 : 5.5, forward pass 11.0 : 10.6, f32 7.7 : 7.2, forward pass 11.4 : 12.4;
+// 512 x 512 bf16 RTN 7.4 : 7.6.  Rows add blocks, each of which reads everything: 2048 x 128 bf16 RTN 8.4 : 14.6.
+constexpr int64_t kMeasuredBytes = 256 * 1024, kMeasuredRows = 512;
+
+bool measures_itself(const QuantizeArgs &q)
+{
+    return q.rht == 0 && (q.mode == QII_RTN || q.mode == QII_RTN_46 || q.mode == QII_SR) && q.src.ld == q.C && rows_kernels_apply(q.src, q.R, q.C) &&
+           q.R <= kMeasuredRows &&
+           q.R * q.C * (q.src.kind == kSrcBF16 ? 2 : 4) <= kMeasuredBytes;
+}
+
+// a: make_args and the outputs of q, one or two tensors of one mode and type
+static hipError_t launch_small_rows(const RowsArgs *a, const QuantizeArgs *q, int count, hipStream_t s)
+{
+    int n[2] = {0, 0};
+    for (int i = 0; i < count; ++i) n[i] = (int)rows_grid(q[i].R, q[i].C, a[i].wpr, 0, 1).x;
+    const dim3 grid((unsigned)(n[0] + n[1])), block(64 * kMeasuringWaves);
+    const bool bf = q[0].src.kind == kSrcBF16;
+#define QII_SMALL(MODE)                                                                                                              \
+    do {                                                                                                                             \
+        if (bf) hipLaunchKernelGGL((quantize_small_rows_kernel<true, MODE>), grid, block, 0, s, a[0], a[count - 1], n[0]);            \
+        else hipLaunchKernelGGL((quantize_small_rows_kernel<false, MODE>), grid, block, 0, s, a[0], a[count - 1], n[0]);              \
+    } while (0)
+    if (q[0].mode == QII_RTN) QII_SMALL(QII_RTN);
+    else if (q[0].mode == QII_SR) QII_SMALL(QII_SR);
+    else QII_SMALL(QII_RTN_46);
+#undef QII_SMALL
+    return hipGetLastError();
+}
+
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s)
 {
@@ -436,9 +532,14 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
         if (q.rht || q.C % 256 != 0 || q.mode == QII_MS_EDEN_PH) return hipErrorInvalidValue;
         a.tiled = q.scales_tiled;
     }
-    const dim3 grid = rows_grid(q.R, q.C, a.wpr, 0), block(256);
+    const int rows = rows_per_wave(q.R, q.C, q.mode);
+    const dim3 grid = rows_grid(q.R, q.C, a.wpr, 0, rows), block(256);
     const bool bf = q.src.kind == kSrcBF16;
-#define QII_ROWS(BF, MODE, RHT) hipLaunchKernelGGL((quantize_rows_kernel<BF, MODE, RHT>), grid, block, 0, s, a)
+#define QII_ROWS(BF, MODE, RHT)                                                                          \
+    do {                                                                                                 \
+        if (rows == 1) hipLaunchKernelGGL((quantize_rows_kernel<BF, MODE, RHT, 1>), grid, block, 0, s, a); \
+        else hipLaunchKernelGGL((quantize_rows_kernel<BF, MODE, RHT, 4>), grid, block, 0, s, a);          \
+    } while (0)
 #define QII_ROWS_MODE(BF, RHT)                                   \
     do {                                                         \
         if (q.mode == QII_RTN) QII_ROWS(BF, QII_RTN, RHT);       \
@@ -454,7 +555,15 @@ hipError_t launch_quantize_rows(const QuantizeArgs &q, hipStream_t s)
     return hipGetLastError();
 }
 
-int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, rows_wpr(R, C), 0).x; }
+hipError_t launch_quantize_small(const QuantizeArgs &q, hipStream_t s)
+{
+    RowsArgs a = make_args(q.src, q.R, q.C, 0, q.seed_sr, rows_wpr(q.R, q.C));
+    a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale; a.tiled = q.scales_tiled;
+    if (a.tiled && q.C % 256 != 0) return hipErrorInvalidValue;
+    return launch_small_rows(&a, &q, 1, s);
+}
+
+int rows_blocks(int64_t R, int64_t C) { return (int)rows_grid(R, C, rows_wpr(R, C), 0, rows_per_wave(R, C, QII_MS_EDEN_PH)).x; }
 
 // Forward pass: Q(X) and Q(W), no rotation, RTN or RTN with 4/6.  Where a maximum is not supplied it is measured
 // first: about kForwardMaxWords blocks in all, shared out by the tensors' sizes, leave one word each (rows longer than 4096
@@ -474,6 +583,7 @@ hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStr
     }
     const bool bf = q[0].src.kind == kSrcBF16;
     const dim3 block(256);
+    if (!q[0].amax && !q[1].amax && measures_itself(q[0]) && measures_itself(q[1])) return launch_small_rows(a, q, 2, s);
     if (size[0] + size[1] > 0) {
         int n[2] = {0, 0};
         for (int i = 0; i < 2; ++i) {
@@ -491,9 +601,14 @@ hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStr
         if (bf) hipLaunchKernelGGL((absmax_rows2_kernel<true>), grid, block, 0, s, m[0], m[1], n[0]);
         else hipLaunchKernelGGL((absmax_rows2_kernel<false>), grid, block, 0, s, m[0], m[1], n[0]);
     }
-    const int n0 = (int)rows_grid(q[0].R, q[0].C, a[0].wpr, 0).x;
-    const dim3 grid((unsigned)n0 + rows_grid(q[1].R, q[1].C, a[1].wpr, 0).x);
-#define QII_FWD(BF, MODE) hipLaunchKernelGGL((quantize_rows2_kernel<BF, MODE>), grid, block, 0, s, a[0], a[1], n0)
+    const int rows = rows_per_wave(q[0].R + q[1].R, q[0].C, q[0].mode);
+    const int n0 = (int)rows_grid(q[0].R, q[0].C, a[0].wpr, 0, rows).x;
+    const dim3 grid((unsigned)n0 + rows_grid(q[1].R, q[1].C, a[1].wpr, 0, rows).x);
+#define QII_FWD(BF, MODE)                                                                                          \
+    do {                                                                                                           \
+        if (rows == 1) hipLaunchKernelGGL((quantize_rows2_kernel<BF, MODE, 1>), grid, block, 0, s, a[0], a[1], n0); \
+        else hipLaunchKernelGGL((quantize_rows2_kernel<BF, MODE, 4>), grid, block, 0, s, a[0], a[1], n0);           \
+    } while (0)
     if (q[0].mode == QII_RTN) { if (bf) QII_FWD(true, QII_RTN); else QII_FWD(false, QII_RTN); }
     else { if (bf) QII_FWD(true, QII_RTN_46); else QII_FWD(false, QII_RTN_46); }
 #undef QII_FWD

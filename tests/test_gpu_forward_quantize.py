@@ -14,7 +14,9 @@ from gpu_util import assert_nv_equal, median_us, to_dev, ws
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,d_in,d_out", [(1, 16, 1), (5, 4112, 3), (3, 8448, 700), (9000, 48, 2), (2, 256, 9000), (1027, 1040, 333)])
+@pytest.mark.parametrize("T,d_in,d_out", [(1, 16, 1), (5, 4112, 3), (3, 8448, 700), (9000, 48, 2), (2, 256, 9000), (1027, 1040, 333)] +
+                         # tensors that every block measures for itself, and a row or a column group beyond that
+                         [(256, 256, 256), (257, 256, 255), (512, 64, 512), (513, 64, 300), (31, 2064, 7), (64, 1040, 5)])
 @pytest.mark.parametrize("f32", [False, True])
 def test_forward_operands_from_two_launches(oracle, T, d_in, d_out, f32):
     Xb, Wb, _ = synth.linear_layer_bf16(T, d_in, d_out, seed=4)
