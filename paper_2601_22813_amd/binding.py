@@ -120,8 +120,15 @@ def _check(status: int):
         raise QiiError(f"{L.qii_status_string(status).decode()}: {L.qii_last_error().decode()}")
 
 
+# The current stream's handle, without a torch.cuda.Stream object around it: 2.9 -> 0.3 us of every call, a fifth of a
+# small layer's pass.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dt(t: torch.Tensor) -> int:
