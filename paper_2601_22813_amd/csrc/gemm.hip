@@ -842,7 +842,7 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     auto offer = [&](Route r, double t) {
         if (t < us) { us = t; best = r; }
     };
-    offer(kRoute128, us128);
+    if (K <= kMaxNarrowK) offer(kRoute128, us128);
     offer(kRoute128Wide, us_wide);
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
@@ -879,7 +879,10 @@ int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
     return (int)route_of(a, b, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
 }
 
-static SmallTile small_tile(Route route) { return route == kRoute64 ? kTile64 : route == kRoute128Wide ? kTile128Wide : kTile128; }
+static SmallTile small_tile(Route route, int64_t K)
+{
+    return route == kRoute64 ? kTile64 : route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : kTile128;
+}
 
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
                        float *amax_c, void *ws, size_t ws_bytes, hipStream_t s, int pretiled)
@@ -926,7 +929,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     }
     // an operand that is tiled only (bits 0, 1) is read tiled, any other row-major
     const SmallGemm one = {&A, &B, (pretiled & 1) != 0, (pretiled & 2) != 0, C, c_is_bf16, ldc, amax_out};
-    return launch_gemm_small(&one, 1, small_tile(route), s);
+    return launch_gemm_small(&one, 1, small_tile(route, K), s);
 }
 
 hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_bytes, hipStream_t s)
@@ -940,8 +943,8 @@ hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_
         small = small && r[i] != kRouteMain && !(r[i] == kRouteNoWorkspace && !c[i].pretiled);
         two[i] = SmallGemm{c[i].A, c[i].B, (c[i].pretiled & 1) != 0, (c[i].pretiled & 2) != 0, c[i].C, c_is_bf16, c[i].ldc, nullptr};
     }
-    if (small && small_tile(r[0]) == small_tile(r[1]) && (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0))
-        return launch_gemm_small(two, 2, small_tile(r[0]), s);
+    if (small && small_tile(r[0], c[0].A->cols) == small_tile(r[1], c[1].A->cols) && (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0))
+        return launch_gemm_small(two, 2, small_tile(r[0], c[0].A->cols), s);
     for (int i = 0; i < 2; ++i) {
         const hipError_t e = launch_gemm(*c[i].A, *c[i].B, c[i].C, c_is_bf16, c[i].ldc, nullptr, ws, ws_bytes, s, c[i].pretiled);
         if (e != hipSuccess) return e;

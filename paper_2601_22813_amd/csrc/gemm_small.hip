@@ -57,6 +57,7 @@ struct Geo {
     static constexpr int BM = 32 * MT * WM, BN = 32 * NT, kThreads = 64 * WM * KG;
     static constexpr int kRowsPerPass = kThreads / 8;         // 8 pieces of 16 bytes per code row
     static constexpr int kPassA = BM / kRowsPerPass, kPassB = BN / kRowsPerPass;
+    static constexpr bool kNarrow = KG == 2;                  // see Sources
     static constexpr int kSlices = 4 / KG;                    // of a K tile per group
     static constexpr int kStage = (BM + BN) * (128 + 16);     // LDS bytes of one K tile
     static constexpr int kUnits = MT * NT;                    // 32 x 32 accumulator tiles of a wave
@@ -84,29 +85,56 @@ struct Staged {
 // their own, each scale byte behind its own branch, they cost 1 us: the forward pass of
 // 1900 x 1360 -> 2136 28.3 -> 27.6 us.)
 struct TileOffsets {
-    int64_t lo, hi, s;
+    int64_t k;     // uniform: of the tile in a row of codes
+    int lo, hi;    // of the two halves of this thread's pieces, beyond that
+    int64_t s;     // of the tile in a row of scale bytes
 };
 
 template <bool kAnyK>
 __device__ __forceinline__ TileOffsets tile_offsets(int kt, int64_t kt_stride, int64_t K)
 {
     const int64_t k0 = (int64_t)kt * BK;
-    TileOffsets o = {k0 / 2, k0 / 2 + 8, kt * kt_stride};
+    TileOffsets o = {k0 / 2, 0, 8, kt * kt_stride};
     if (kAnyK && k0 + BK > K) {   // uniform
         const int off = 16 * (int)(threadIdx.x & 7), left = (int)(K - k0) - 2 * off;
-        if (left <= 0) o.lo -= off;
-        if (left <= 16) o.hi = k0 / 2 - off;
+        if (left <= 0) o.lo = -off;
+        if (left <= 16) o.hi = -off;
         if (kt > 0) o.s += (K - k0) / 16 - 16;
     }
     return o;
 }
 
-template <bool kAnyK>
-__device__ __forceinline__ uint4 load_codes16(const uint8_t *p, const TileOffsets &o)
+// This thread's source addresses (K tile 0), rows beyond the matrix replaced by its last row (their results land in
+// accumulator rows or columns that are never stored).  kNarrow (the two-group form, whose 256 registers are all in use): 32-bit
+// offsets from the tile's first row, which is in scalar registers; a block tile's rows are then below 4 GiB (kMaxNarrowK).  With
+// 64-bit addresses the compiler keeps the scale bytes on their way to LDS in scratch memory, and every K tile
+// waits for its successor's loads: 2048 x 2048 x 1024 14.4 us instead of 12.8, 2816 x 2048 x 4096 62.4 instead of 56.5.
+template <class G>
+struct Sources {
+    const uint8_t *a0, *b0, *s0;   // uniform (kNarrow)
+    const uint8_t *a[G::kNarrow ? 1 : G::kPassA], *b[G::kNarrow ? 1 : G::kPassB], *s;
+    uint32_t a_off[G::kPassA], b_off[G::kPassB], s_off;
+    int64_t kt_stride;
+};
+
+// piece p of A's (or B's) rows in the tile that o stands for
+template <class G, bool kAnyK, bool kA>
+__device__ __forceinline__ uint4 load_codes16(const Sources<G> &src, int p, const TileOffsets &o)
 {
-    if (!kAnyK) return *reinterpret_cast<const uint4 *>(p + o.lo);
-    const uint2 lo = *reinterpret_cast<const uint2 *>(p + o.lo), hi = *reinterpret_cast<const uint2 *>(p + o.hi);
-    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+    const uint8_t *lo, *hi;
+    if constexpr (G::kNarrow) {
+        const uint8_t *base = (kA ? src.a0 : src.b0) + o.k;   // uniform
+        const uint32_t off = kA ? src.a_off[p] : src.b_off[p];
+        lo = base + (uint32_t)(off + o.lo);
+        hi = base + (uint32_t)(off + o.hi);
+    } else {
+        const uint8_t *row = kA ? src.a[p] : src.b[p];
+        lo = row + (o.k + o.lo);
+        hi = row + (o.k + o.hi);
+    }
+    if (!kAnyK) return *reinterpret_cast<const uint4 *>(lo);
+    const uint2 l = *reinterpret_cast<const uint2 *>(lo), h = *reinterpret_cast<const uint2 *>(hi);
+    return make_uint4(l.x, l.y, h.x, h.y);
 }
 
 template <bool kAnyK>
@@ -130,25 +158,24 @@ __device__ __forceinline__ uint4 load_scales_short(const uint8_t *p, int groups)
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// this thread's source addresses (K tile 0), rows beyond the matrix replaced by its last row (their
-// results land in accumulator rows or columns that are never stored)
 template <class G>
-struct Sources {
-    const uint8_t *a[G::kPassA], *b[G::kPassB], *s;
-    int64_t kt_stride;
-};
+__device__ __forceinline__ const uint8_t *scales_at(const Sources<G> &src, int64_t offset)
+{
+    if constexpr (G::kNarrow) return src.s0 + offset + src.s_off;
+    else return src.s + offset;
+}
 
 template <class G, bool kAnyK, bool kFirst>
 __device__ __forceinline__ void load_tile(Staged<G> &st, const Sources<G> &src, int kt, int64_t K)
 {
     const TileOffsets o = tile_offsets<kAnyK>(kt, src.kt_stride, K);
 #pragma unroll
-    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<kAnyK>(src.a[p], o);
+    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<G, kAnyK, true>(src, p, o);
 #pragma unroll
-    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<kAnyK>(src.b[p], o);
+    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<G, kAnyK, false>(src, p, o);
     if ((int)threadIdx.x < G::BM + G::BN) {
-        if (kAnyK && kFirst && K < BK) st.s = load_scales_short(src.s, (int)K / 16);   // uniform
-        else st.s = load_scales16<kAnyK>(src.s + o.s);
+        if (kAnyK && kFirst && K < BK) st.s = load_scales_short(scales_at(src, 0), (int)K / 16);   // uniform
+        else st.s = load_scales16<kAnyK>(scales_at(src, o.s));
     }
 }
 
@@ -367,21 +394,35 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
 
     Sources<G> src;
     {
-        const int64_t pitch = g.K / 2, off = 16 * (t & 7);
+        const int64_t pitch = g.K / 2;
+        const int off = 16 * (t & 7);
+        auto row_of = [](int64_t r, int64_t rows) { return r < rows ? r : rows - 1; };
+        if constexpr (G::kNarrow) {
+            src.a0 = g.a_codes + m0 * pitch;
+            src.b0 = g.b_codes + n0 * pitch;
 #pragma unroll
-        for (int p = 0; p < G::kPassA; ++p) {
-            const int64_t r = m0 + p * G::kRowsPerPass + (t >> 3);
-            src.a[p] = g.a_codes + (r < g.M ? r : g.M - 1) * pitch + off;
-        }
+            for (int p = 0; p < G::kPassA; ++p)
+                src.a_off[p] = (uint32_t)(row_of(m0 + p * G::kRowsPerPass + (t >> 3), g.M) - m0) * (uint32_t)pitch + (uint32_t)off;
 #pragma unroll
-        for (int p = 0; p < G::kPassB; ++p) {
-            const int64_t r = n0 + p * G::kRowsPerPass + (t >> 3);
-            src.b[p] = g.b_codes + (r < g.N ? r : g.N - 1) * pitch + off;
+            for (int p = 0; p < G::kPassB; ++p)
+                src.b_off[p] = (uint32_t)(row_of(n0 + p * G::kRowsPerPass + (t >> 3), g.N) - n0) * (uint32_t)pitch + (uint32_t)off;
+            // (whole waves take A's rows or B's: BM and BN are multiples of 64, and there are as many threads as rows)
+            static_assert(G::BM % 64 == 0 && G::BM + G::BN == G::kThreads, "a wave's scale rows are one operand's");
+            const bool of_a = wave * 64 < G::BM;   // uniform
+            const ScaleView v = of_a ? g.as : g.bs;
+            const int64_t first = of_a ? m0 : n0, row = row_of(first + t - (of_a ? 0 : G::BM), of_a ? g.M : g.N);
+            src.s0 = scale_row(v, first);
+            src.s_off = (uint32_t)(scale_row(v, row) - src.s0);
+            src.kt_stride = v.kt_stride;
+        } else {
+#pragma unroll
+            for (int p = 0; p < G::kPassA; ++p) src.a[p] = g.a_codes + row_of(m0 + p * G::kRowsPerPass + (t >> 3), g.M) * pitch + off;
+#pragma unroll
+            for (int p = 0; p < G::kPassB; ++p) src.b[p] = g.b_codes + row_of(n0 + p * G::kRowsPerPass + (t >> 3), g.N) * pitch + off;
+            const bool of_a = t < G::BM;   // (threads beyond BM + BN load no scales)
+            src.s = of_a ? scale_row(g.as, row_of(m0 + t, g.M)) : scale_row(g.bs, row_of(n0 + t - G::BM, g.N));
+            src.kt_stride = of_a ? g.as.kt_stride : g.bs.kt_stride;
         }
-        const bool of_a = t < G::BM;   // (threads beyond BM + BN load no scales)
-        const int64_t ra = m0 + t, rb = n0 + t - G::BM;
-        src.s = of_a ? scale_row(g.as, ra < g.M ? ra : g.M - 1) : scale_row(g.bs, rb < g.N ? rb : g.N - 1);
-        src.kt_stride = of_a ? g.as.kt_stride : g.bs.kt_stride;
     }
 
     floatx16 acc[G::kUnits];   // tile (i, j) of the wave at i NT + j
@@ -439,14 +480,14 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
             auto move = [&](int i) {   // piece i of tile kt + 1 to LDS, its register takes tile kt + 2's piece
                 if (i < G::kPassA) {
                     *reinterpret_cast<uint4 *>(dst + i * G::kRowsPerPass * 128) = st.a[i];
-                    if (more) st.a[i] = load_codes16<kAnyK>(src.a[i], o);
+                    if (more) st.a[i] = load_codes16<G, kAnyK, true>(src, i, o);
                 } else if (i < G::kPassA + G::kPassB) {
                     const int p = i - G::kPassA;
                     *reinterpret_cast<uint4 *>(dst + (G::BM + p * G::kRowsPerPass) * 128) = st.b[p];
-                    if (more) st.b[p] = load_codes16<kAnyK>(src.b[p], o);
+                    if (more) st.b[p] = load_codes16<G, kAnyK, false>(src, p, o);
                 } else if (i == G::kPassA + G::kPassB) {   // (256 threads, 256 rows)
                     *reinterpret_cast<uint4 *>(nxt + (G::BM + G::BN) * 128 + t * 16) = st.s;
-                    if (more) st.s = load_scales16<kAnyK>(src.s + o.s);
+                    if (more) st.s = load_scales16<kAnyK>(scales_at(src, o.s));
                 }
             };
             const int slot = ((2 * j0 + kb) ^ (li & 7)) * 16, sc = 4 * j0 + 2 * kb;
@@ -555,7 +596,9 @@ hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipS
     SmallArgs g[2];
     for (int i = 0; i < count; ++i) {
         const qii_nvfp4 &A = *c[i].A, &B = *c[i].B;
-        if ((A.cols % BK != 0) != (c[0].A->cols % BK != 0) || c[i].c_is_bf16 != c[0].c_is_bf16) return hipErrorInvalidValue;
+        if ((A.cols % BK != 0) != (c[0].A->cols % BK != 0) || c[i].c_is_bf16 != c[0].c_is_bf16 ||
+            (tile == kTile128 && A.cols > kMaxNarrowK))
+            return hipErrorInvalidValue;
         g[i].a_codes = A.codes; g[i].b_codes = B.codes;
         g[i].as = view(A, c[i].a_tiled); g[i].bs = view(B, c[i].b_tiled);
         g[i].a_ts = A.tensor_scale; g[i].b_ts = B.tensor_scale;
