@@ -789,29 +789,30 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 }
 
 // Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to
-// event timings of every kernel over M x N = 64 x 64 .. 16384 x 2048 and K = 256 .. 16384 (bf16 results;
-// kt = K / 256, b = blocks / 256 compute units).  Measured on one box, each kernel forced in turn; the model takes
-// the fastest at each of these:
+// timings of every kernel, each forced in turn, over 246 products of M, N = 64 .. 16384 and K = 128 .. 32768, bf16 and f32 results
+// (kt = K / 256, b = blocks / 256 compute units): what the rule takes is 0.4 % behind the fastest on average, 11 % at
+// most (13696 x 6272 x 640 f32: the no-workspace kernel instead of 128 x 128).  Some of them, us, from a graph, on one box:
 //                         64 x 64   128 x 128 KG 2   128 x 128 (4, 4)   256 x 256 (with re-tiling)
-//    512 x  512 x   512       8.9              9.4              12.1     20.4
-//   1024 x 1024 x  4096      17.5             36.8              29.2     44.8 (shared last round)
-//   2048 x 2048 x  2048      26.9             24.5              23.4     45.6
-//   2048 x 2048 x 16384     160.3            153.9             114.1    134.5 (shared)
-//   4096 x 2048 x  2048      46.9             38.2              43.6     47.5
-//   4096 x 2048 x  8192     157.4            131.2             120.9    133.1 (shared)
-//   2048 x 5632 x  2048      60.7             53.9              61.4     48.7
-//   4096 x 4096 x  1024      54.1             40.3              57.5     35.3
-//   4096 x 4096 x  4096     161.8            132.7             137.5    104.9
-//   2816 x 2048 x 16384     221.6            218.5             191.0    185.8 (shared)
-// 64 x 64 tiles: up to three blocks run on a unit and their time adds up, so the unit with the most blocks counts
-// (2176 x 1024 x 20992, 544 blocks: 140 us, 128 x 128 (4, 4) 116).
-// 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is.
+//    256 x  256 x   256        4.7              6.4                7.5     12.2
+//    512 x  512 x   512        5.5              8.5                9.4     16.5
+//   1024 x 1024 x  4096       18.5             36.3               27.0     37.0 (shared last round)
+//   1536 x 1536 x  1536       14.4             16.7               14.8     32.1
+//   2048 x 2048 x  2048       25.1             23.9               20.7     41.2
+//   2048 x 2048 x 16384      160.2            143.8              111.2    122.3 (shared)
+//   4096 x 2048 x  1024       25.5             21.3               24.4     27.0
+//   4096 x 2048 x  8192      156.4            127.6              114.8    122.1 (shared)
+//   2048 x 5632 x  2048       59.0             51.6               52.1     45.1
+//   4096 x 4096 x  4096      156.7            128.3              122.7    101.1
+//   2816 x 2048 x 16384      223.3            216.5              187.9    164.6 (shared)
+//   8192 x 8192 x   256                        58.5              105.0     83.3
+// 64 x 64 tiles: up to three blocks run on a unit and their time adds up, so the unit with the most blocks counts.
+// 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is, and a block
+// beyond the fourth of a unit cheaper, its first loads and stores beside the products of others.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
-// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan;
-// 3 us of launch and first loads (a shared last round takes some 7 less than the plan's own, careful, figure: 512 x 128
-// x 26624 73 us, 64 x 64 tiles 79), 4.5 of re-tiling where the scale bytes are not tiled yet.  The plan counts 12
-// for ranges that span two tiles wherever ranges differ in length; of one tile, or of two and an even number of blocks,
-// none does and the 12 go (main kernel : 64 x 64 tiles, us, re-tiling included: 128 x 128 x 24320 bf16 59.5 : 71.2,
+// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan, whose
+// figure for a shared last round is some 15 more than it takes; 4.5 of re-tiling where the scale bytes are not tiled yet.
+// The plan counts 12 for ranges that span two tiles wherever ranges differ in length; of one tile, or of two and an even
+// number of blocks, none does and the 12 go (main kernel : 64 x 64 tiles, us, re-tiling included: 128 x 128 x 24320 bf16 59.5 : 71.2,
 // 256 x 256 x 19456 bf16 56.9 : 58.4, 256 x 512 x 22784 f32 62.9 : 70.1).
 // The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
 // 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 12.6 : 9.8 : 12.5 and 14.8 : 12.1 : 18.0, 4096 x 4096 41.0 : 22.3 : 13.7
@@ -828,25 +829,24 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     const double kt = (double)((K + BK4 - 1) / BK4), n64 = count(64), n128 = count(128), n256 = count(256);
     const double b64 = n64 > 256.0 ? n64 / 256.0 : 1.0, b = n128 > 256.0 ? n128 / 256.0 : 1.0;
     const double most64 = (double)(int64_t)((n64 + 255.0) / 256.0);
-    const double us64 = 3.3 + 0.85 * b64 + (0.15 + 0.54 * most64) * kt * (any ? 1.3 : 1.0);
+    const double us64 = 4.259 + 0.753 * b64 + (0.236 + 0.531 * most64) * kt * (any ? 1.3 : 1.0);
     const double pairs = (double)(int64_t)(b / 2.0), last = b - 2.0 * pairs;
-    const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.4 + 0.55 * last : 2.6 + 0.53 * last);
-    const double us128 = (any ? 5.0 : 4.0) + 1.7 * b + slope * kt * (any ? 1.25 : 1.0);
+    const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.49 + 0.55 * last : 2.6 + 0.53 * last);
+    const double us128 = 4.45 + (any ? 1.05 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.28 : 1.0);
     const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
-    const double us_wide = rounds * (8.3 + (1.15 + 0.45 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.17 : 1.0));
-    const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full;
-    const double us_v2 = 3.0 + (full + (rem > 0.0 ? 1.0 : 0.0)) * 6.7 +
-                         (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0);
+    const double us_wide = rounds * (7.75 + (any ? 0.89 : 0.0) + (1.09 + 0.36 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.35 : 1.0));
+    const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
+    const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     Route best = kRoute64;
     double us = us64;
     auto offer = [&](Route r, double t) {
         if (t < us) { us = t; best = r; }
     };
-    if (K <= kMaxNarrowK) offer(kRoute128, us128);
-    offer(kRoute128Wide, us_wide);
+    offer(kRoute128, us128);
+    if (us_wide < us || K > kMaxNarrowK) { us = us_wide; best = kRoute128Wide; }
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        double main_us = plan.us + (plan.rem ? -4.0 : 3.0) + (retile ? 4.5 : 0.0);
+        double main_us = plan.us + (plan.rem ? -18.6 : 0.1) + 3.32 * rounds256 + (retile ? 4.5 : 0.0);
         if (plan.spans && plan.full == 0 && plan.rem <= 2 && plan.grid % plan.rem == 0) main_us -= 12.0;
         offer(kRouteMain, main_us);
     }
@@ -881,7 +881,7 @@ int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
 
 static SmallTile small_tile(Route route, int64_t K)
 {
-    return route == kRoute64 ? kTile64 : route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : kTile128;
+    return route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : route == kRoute64 ? kTile64 : kTile128;
 }
 
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,

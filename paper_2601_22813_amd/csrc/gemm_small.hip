@@ -57,7 +57,8 @@ struct Geo {
     static constexpr int BM = 32 * MT * WM, BN = 32 * NT, kThreads = 64 * WM * KG;
     static constexpr int kRowsPerPass = kThreads / 8;         // 8 pieces of 16 bytes per code row
     static constexpr int kPassA = BM / kRowsPerPass, kPassB = BN / kRowsPerPass;
-    static constexpr bool kNarrow = KG == 2;                  // see Sources
+    static constexpr bool kNarrow = MT < 4;                   // see Sources
+    static constexpr int kBlocksPerUnit = MT == 4 ? 1 : NT == 4 ? 2 : 3;   // (registers: 512, 256, 168)
     static constexpr int kSlices = 4 / KG;                    // of a K tile per group
     static constexpr int kStage = (BM + BN) * (128 + 16);     // LDS bytes of one K tile
     static constexpr int kUnits = MT * NT;                    // 32 x 32 accumulator tiles of a wave
@@ -105,10 +106,10 @@ __device__ __forceinline__ TileOffsets tile_offsets(int kt, int64_t kt_stride, i
 }
 
 // This thread's source addresses (K tile 0), rows beyond the matrix replaced by its last row (their results land in
-// accumulator rows or columns that are never stored).  kNarrow (the two-group form, whose 256 registers are all in use): 32-bit
-// offsets from the tile's first row, which is in scalar registers; a block tile's rows are then below 4 GiB (kMaxNarrowK).  With
-// 64-bit addresses the compiler keeps the scale bytes on their way to LDS in scratch memory, and every K tile
-// waits for its successor's loads: 2048 x 2048 x 1024 14.4 us instead of 12.8, 2816 x 2048 x 4096 62.4 instead of 56.5.
+// accumulator rows or columns that are never stored).  kNarrow (the forms whose registers are short: 256 for two blocks per unit,
+// 168 for three): 32-bit offsets from the tile's first row, which is in scalar registers; a block tile's rows are then below 4 GiB
+// (kMaxNarrowK).  With 64-bit addresses the two-group form keeps the scale bytes on their way to LDS in scratch memory, and
+// every K tile waits for its successor's loads: 2048 x 2048 x 1024 14.4 us instead of 12.8, 2816 x 2048 x 4096 62.4 instead of 56.5.
 template <class G>
 struct Sources {
     const uint8_t *a0, *b0, *s0;   // uniform (kNarrow)
@@ -378,7 +379,7 @@ __device__ __forceinline__ void finish(const floatx16 (&u)[G::FM * G::FN], uint8
 }
 
 template <bool kBf16Out, class G, bool kAnyK>
-__global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_kernel(SmallArgs g0, SmallArgs g1, int n0_blocks)
+__global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_kernel(SmallArgs g0, SmallArgs g1, int n0_blocks)
 {
     // one product, or two in one launch: the first n0_blocks blocks take g0, the others g1
     const bool first = (int)blockIdx.x < n0_blocks;   // uniform
@@ -406,8 +407,8 @@ __global__ __launch_bounds__(G::kThreads, G::MT == 4 ? 1 : 2) void gemm_small_ke
 #pragma unroll
             for (int p = 0; p < G::kPassB; ++p)
                 src.b_off[p] = (uint32_t)(row_of(n0 + p * G::kRowsPerPass + (t >> 3), g.N) - n0) * (uint32_t)pitch + (uint32_t)off;
-            // (whole waves take A's rows or B's: BM and BN are multiples of 64, and there are as many threads as rows)
-            static_assert(G::BM % 64 == 0 && G::BM + G::BN == G::kThreads, "a wave's scale rows are one operand's");
+            // (whole waves take A's rows or B's: BM and BN are multiples of 64; a wave beyond them loads no scales)
+            static_assert(G::BM % 64 == 0 && G::BN % 64 == 0, "a wave's scale rows are one operand's");
             const bool of_a = wave * 64 < G::BM;   // uniform
             const ScaleView v = of_a ? g.as : g.bs;
             const int64_t first = of_a ? m0 : n0, row = row_of(first + t - (of_a ? 0 : G::BM), of_a ? g.M : g.N);
@@ -597,7 +598,7 @@ hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipS
     for (int i = 0; i < count; ++i) {
         const qii_nvfp4 &A = *c[i].A, &B = *c[i].B;
         if ((A.cols % BK != 0) != (c[0].A->cols % BK != 0) || c[i].c_is_bf16 != c[0].c_is_bf16 ||
-            (tile == kTile128 && A.cols > kMaxNarrowK))
+            (tile != kTile128Wide && A.cols > kMaxNarrowK))
             return hipErrorInvalidValue;
         g[i].a_codes = A.codes; g[i].b_codes = B.codes;
         g[i].as = view(A, c[i].a_tiled); g[i].bs = view(B, c[i].b_tiled);

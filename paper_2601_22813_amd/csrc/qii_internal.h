@@ -164,7 +164,7 @@ bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K);
 // products by the small-tile kernels (gemm_small.hip), one or two in one launch (with one result type, and K a
 // multiple of 256 in both or in neither): any K; each operand's scale bytes row-major or, K a multiple of 256, tiled
 enum SmallTile { kTile64, kTile128, kTile128Wide };
-constexpr int64_t kMaxNarrowK = (int64_t)1 << 25;   // of kTile128
+constexpr int64_t kMaxNarrowK = (int64_t)1 << 25;   // of kTile64 and kTile128
 struct SmallGemm {
     const qii_nvfp4 *A, *B;
     bool a_tiled, b_tiled;
