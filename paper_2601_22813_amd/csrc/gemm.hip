@@ -146,9 +146,9 @@ __device__ __forceinline__ void mma_slice(floatx16 (&acc)[4][4], const RawFrag &
             fb[t] = dequant8(wb, scale_pair(f.sb[t], d >> 1));
         }
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti)
+        for (int tj = 0; tj < 4; ++tj)   // (columns outside: with rows outside a K tile takes 2.5 % longer)
 #pragma unroll
-            for (int tj = 0; tj < 4; ++tj)
+            for (int ti = 0; ti < 4; ++ti)
                 acc[ti][tj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[tj], fa[ti], acc[ti][tj], 0, 0, 0);   // (B first: store_tile)
     }
 }
@@ -174,7 +174,6 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restri
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, kb = lane >> 5;
-    const float ts_a = *a_ts, ts_b = *b_ts;
 
     floatx16 acc[4][4];
 #pragma unroll
@@ -188,6 +187,9 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restri
     issue_tile_loads(smem, a_codes, a_scales, b_codes, b_scales, M, N, K, m0, n0, 0, wave);
     if (ktiles > 1)
         issue_tile_loads(smem + kStage2Bytes, a_codes, a_scales, b_codes, b_scales, M, N, K, m0, n0, BK, wave);
+    __builtin_amdgcn_sched_barrier(0);   // (the tensor scales are requested behind the first loads)
+    const float ts_a = *a_ts, ts_b = *b_ts;
+    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 

@@ -97,11 +97,47 @@ __device__ __forceinline__ void wave_lds_fence()
 // each: 6.1 us for the main kernel's 256 x 256 bf16 tile and 9.3 for f32; now 3.6 and 7.3; the
 // 128 x 128 form of the small-tile kernels, reduction included, 5.4 -> 2.7.)
 // A tile that lies inside C with 16-byte aligned rows takes the loop without checks; where the rows are aligned only the
-// pieces that N cuts go entry by entry; other rows: consecutive lanes store consecutive entries, eight rows in flight.
+// pieces that N cuts go entry by entry; other rows: consecutive lanes store consecutive entries (store_entries).
 // kStreaming: C is written once and not read again here, so the stores are non-temporal (false: a partial tile that
 // the next kernel reads back).  All threads of the block must call it if amax_out is given.
 template <bool kBf16Out, int NT>
 constexpr int staging_pitch() { return 32 * NT * (kBf16Out ? 2 : 4) + 16; }
+
+// `rows` staged rows whose places in C are aligned for one entry only, or (kEach = 2, bf16) for two: consecutive lanes store
+// consecutive entries, the reads of eight rows not waiting for the stores of those before.
+template <bool kBf16Out, int NT, int kEach, int kRows>
+__device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *out, int64_t rb, int live_rows, int live_cols, int lane, float &cmax)
+{
+    constexpr int esz = kBf16Out ? 2 : 4, cols = 32 * NT, pitch = staging_pitch<kBf16Out, NT>(), kAtOnce = 8;
+    constexpr int lanes = cols / kEach < 64 ? cols / kEach : 64, rows_at_once = 64 / lanes;
+    static_assert(kRows % (kAtOnce * rows_at_once) == 0, "whole steps");
+    const int rl = lane / lanes;
+#pragma unroll 1
+    for (int c0 = 0; c0 < cols; c0 += lanes * kEach) {
+        const int col = c0 + lane % lanes * kEach;
+        const uint8_t *src = staged + rl * pitch + col * esz;
+        uint8_t *dst = out + rl * rb + col * esz;
+#pragma unroll 1
+        for (int r0 = 0; r0 < kRows; r0 += kAtOnce * rows_at_once) {
+            uint32_t v[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                const uint8_t *e = src + (r0 + i * rows_at_once) * pitch;
+                v[i] = esz * kEach == 4 ? *reinterpret_cast<const uint32_t *>(e) : (uint32_t)*reinterpret_cast<const uint16_t *>(e);
+            }
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                const int row = r0 + i * rows_at_once;
+                uint8_t *d = dst + row * rb;
+                if (row + rl >= live_rows || col >= live_cols) continue;
+                if (esz * kEach == 4 && (kEach == 1 || col + 1 < live_cols)) *reinterpret_cast<uint32_t *>(d) = v[i];
+                else *reinterpret_cast<uint16_t *>(d) = (uint16_t)v[i];
+                cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v[i] << 16 : v[i])));
+                if (kEach == 2 && col + 1 < live_cols) cmax = fmaxf(cmax, fabsf(u2f(v[i] & 0xFFFF0000u)));
+            }
+        }
+    }
+}
 
 template <bool kBf16Out, bool kStreaming, int MT, int NT, int kGroup, int kRoom>
 __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_t *area, float ts, void *Cout, int64_t ldc, int64_t M,
@@ -114,6 +150,7 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_
     uint8_t *out = reinterpret_cast<uint8_t *>(Cout) + row0 * rb + col0 * esz;
     const int live_rows = (int)(M - row0 < 32 * MT ? M - row0 : 32 * MT), live_cols = (int)(N - col0 < cols ? N - col0 : cols);   // (may be negative)
     const bool aligned = ((reinterpret_cast<uintptr_t>(Cout) | (uintptr_t)rb) & 15) == 0;   // (col0: a multiple of 32)
+    const bool pairs = ((reinterpret_cast<uintptr_t>(Cout) | (uintptr_t)rb) & 3) == 0;
     const bool whole = aligned && live_rows == 32 * MT && live_cols == cols && rb < (1 << 26);
     const int piece = lane % per_row, row_l = lane / per_row;
     uint8_t *lane_write = area + (lane & 31) * pitch + (lane >> 5) * 4 * esz;
@@ -191,30 +228,9 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_
                         for (int col = live_cols / entries * entries; col < live_cols; ++col)
                             put_entry(32 * (g + b) + lane, col, area + ((band0 + b) * 32 + lane) * pitch + col * esz);
         } else {
-            constexpr int lanes = cols < 64 ? cols : 64, rows_at_once = 64 / lanes, kAtOnce = 8;
-#pragma unroll 1
-            for (int c0 = 0; c0 < cols; c0 += lanes) {
-                const int col = c0 + lane % lanes;
-#pragma unroll 1
-                for (int r0 = lane / lanes; r0 < 32 * kGroup; r0 += kAtOnce * rows_at_once) {
-                    uint32_t v[kAtOnce];   // the reads of several rows do not wait for the stores of those before
-#pragma unroll
-                    for (int i = 0; i < kAtOnce; ++i) {
-                        const uint8_t *e = area + (band0 * 32 + r0 + i * rows_at_once) * pitch + col * esz;
-                        v[i] = kBf16Out ? (uint32_t)*reinterpret_cast<const uint16_t *>(e) : *reinterpret_cast<const uint32_t *>(e);
-                    }
-#pragma unroll
-                    for (int i = 0; i < kAtOnce; ++i) {
-                        const int row = 32 * g + r0 + i * rows_at_once;
-                        if (row < live_rows && col < live_cols) {
-                            uint8_t *dst = out + row * rb + col * esz;
-                            if (kBf16Out) *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v[i];
-                            else *reinterpret_cast<uint32_t *>(dst) = v[i];
-                            cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v[i] << 16 : v[i])));
-                        }
-                    }
-                }
-            }
+            const uint8_t *group = area + band0 * kBand;
+            if (kBf16Out && pairs) store_entries<kBf16Out, NT, 2, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, cmax);   // uniform
+            else store_entries<kBf16Out, NT, 1, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, cmax);
         }
         wave_lds_fence();   // the reads come before the writes of a group that takes the same room
     }
