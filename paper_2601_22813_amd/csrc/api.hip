@@ -275,15 +275,15 @@ qii_status scratch_address(void **out)
 // the single-read launch's arguments (words: post hoc scheme, one word per block)
 qii::PairQuantizeArgs pair_arguments(const qii::Source &src, int64_t rows, int64_t cols, qii_mode mode, uint64_t seed_rht_r, uint64_t seed_sr_r,
                                      uint64_t seed_rht_c, uint64_t seed_sr_c, const qii_nvfp4 *out_r, const qii_nvfp4 *out_c, float *slot_r,
-                                     float *slot_c, float *tbuf_r, float *tbuf_c, int words)
+                                     float *slot_c, float *tbuf_r, float *tbuf_c, int words, bool tiled_r = false, bool tiled_c = false)
 {
     const bool ph = mode == QII_MS_EDEN_PH;
     qii::PairQuantizeArgs p;
     p.src = src; p.rows = rows; p.cols = cols; p.mode = (int)mode; p.amax_words = words;
     p.r = {seed_rht_r, seed_sr_r, ph ? nullptr : slot_r, out_r->codes, out_r->scales, out_r->tensor_scale, tbuf_r,
-           ph ? reinterpret_cast<uint32_t *>(slot_r) : nullptr};
+           ph ? reinterpret_cast<uint32_t *>(slot_r) : nullptr, tiled_r};
     p.c = {seed_rht_c, seed_sr_c, ph ? nullptr : slot_c, out_c->codes, out_c->scales, out_c->tensor_scale, tbuf_c,
-           ph ? reinterpret_cast<uint32_t *>(slot_c) : nullptr};
+           ph ? reinterpret_cast<uint32_t *>(slot_c) : nullptr, tiled_c};
     return p;
 }
 
@@ -712,10 +712,6 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     const size_t gws_bytes = reinterpret_cast<uint8_t *>(ws) + ws_bytes - p;
     uint64_t sd[6];
     for (uint32_t i = 0; i < 6; ++i) sd[i] = qii_derive_seed(seed, i);
-    // The four quantized operands live only in this workspace.  In the post hoc scheme their scale
-    // bytes come from the scales pass, which writes them straight into the layout the main GEMM
-    // kernel reads when the GEMM's inner dimension allows that kernel: no re-tiling launch.
-    const bool tile_dx = ph && d_out % 256 == 0, tile_dw = ph && T % 256 == 0;
     // W and X are re-quantized by shared launches: heavy passes (post hoc scheme; both need a per-group buffer) or
     // abs-max and quantize passes.
     qii::Source sq[2] = {};
@@ -741,6 +737,10 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
         for (int i = 0; i < 9; ++i)
             if (overlap(dW, dw_bytes, used[i], used_bytes[i]) || (i < 8 && overlap(dX, dx_bytes, used[i], used_bytes[i]))) at_once = false;
     }
+    // The four quantized operands live only in this workspace.  Their scale bytes come from the scales pass of the post hoc
+    // scheme, or from the launch that quantizes all four, and go straight into the layout the main GEMM kernel reads when the
+    // GEMM's inner dimension allows that kernel: no re-tiling launch (the small-tile kernels read either layout).
+    const bool tile_dx = (ph || at_once) && d_out % 256 == 0, tile_dw = (ph || at_once) && T % 256 == 0;
     const bool together = shared && (at_once || !ph || 4 * kRegion + tw + tx <= posthoc_region_bytes(T, d_in, d_out, mode));
     int words_q[2] = {0, 0};
     if (ph && together)
@@ -787,11 +787,12 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
             q[i].codes = out[i]->codes; q[i].scales = out[i]->scales; q[i].tensor_scale = out[i]->tensor_scale;
             q[i].tbuf = tb[i]; q[i].amax_accum = ph ? reinterpret_cast<uint32_t *>(slot_q[i]) : nullptr;
             q[i].amax_words = words_q[i];
+            q[i].tiled = !ph && (i == 0 ? tile_dx : tile_dw);   // (not set unless at_once)
         }
         const int e_words = words_e ? (int)((T / 128) * (d_out / 128)) : 0;
         if (at_once)
             e = qii::launch_quantize_backward(pair_arguments(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words,
-                                                             tbuf, tbuf2, e_words), q, s);
+                                                             tbuf, tbuf2, e_words, !ph && tile_dx, !ph && tile_dw), q, s);
         else e = qii::launch_quantize_requant(q, 2, s);
         if (e != hipSuccess) return hip_fail(e, "quantize");
         if (ph) {

@@ -60,6 +60,8 @@ struct QuantizeArgs {
     // a second copy of the scale bytes in the main GEMM kernel's tiled layout (nullable; only where
     // rows_kernels_apply, no rotation, C a multiple of 256; room for R rounded up to 256 rows)
     uint8_t *scales_tiled = nullptr;
+    // the scale bytes themselves in that layout (launch_quantize_backward only; C a multiple of 256, room as above)
+    bool tiled = false;
 };
 
 // One read of a dense matrix producing Q(x) (side r: rows x cols) and Q(x^T) (side c: cols x rows),
@@ -78,6 +80,7 @@ struct PairQuantizeArgs {
         float *tensor_scale;
         float *tbuf;
         uint32_t *amax_accum;
+        bool tiled;          // QII_MS_EDEN: scale bytes in the main GEMM kernel's layout (that side's columns a multiple of 256, room for its rows rounded up)
     } r, c;
 };
 bool pair_kernel_applies(const Source &src, int64_t rows, int64_t cols);

@@ -224,4 +224,10 @@ __device__ __forceinline__ uint2 gather_quad_scales(uint32_t two_bytes, int q)
     return make_uint2(t, other);
 }
 
+// the 8 scale bytes of a row's chunk of 128 in the layout the main GEMM kernel reads: [row / 256][K / 256 = ksn][row % 256][16 bytes]
+__device__ __forceinline__ uint8_t *tiled_scales(uint8_t *scales, int64_t ksn, int64_t row, int64_t chunk)
+{
+    return scales + ((row >> 8) * ksn + (chunk >> 1)) * 4096 + (row & 255) * 16 + (chunk & 1) * 8;
+}
+
 }  // namespace qii

@@ -34,6 +34,7 @@ struct PairSide {
     float *tensor_scale;
     float *tbuf;           // QII_MS_EDEN_PH: corrected pseudo-scales, one f32 per group
     uint32_t *amax_out;    // QII_MS_EDEN_PH: spread running maximum, or one word per block (nullable)
+    int ksn;               // QII_MS_EDEN: 0, or the K tiles of the main GEMM kernel's layout, which the scale bytes then go out in
 };
 
 struct PairArgs {
@@ -58,8 +59,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region(const void *base, int64
 // 46.1 -> 43.2, 69.4 -> 65.3.)
 constexpr int kPairImage = 128 * 256;   // LDS bytes of the tile
 
-// tile: kPairImage bytes of LDS
-template <int kMode>
+// tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it)
+template <int kMode, bool kMayTile = false>
 __device__ __forceinline__ void pair_block(const PairArgs &a, int block, uint8_t *tile)
 {
     __shared__ float inv_r[128], inv_c[128];
@@ -118,7 +119,8 @@ __device__ __forceinline__ void pair_block(const PairArgs &a, int block, uint8_t
         }
         // this tile's part of the outputs: 64 code bytes, 8 scale bytes (or 8 f32) per row
         const __amdgpu_buffer_rsrc_t rc = region(a.r.codes + row0 * cpitch + col0 / 2, 127 * cpitch + 64);
-        const __amdgpu_buffer_rsrc_t rs = region(a.r.scales + row0 * G + col0 / 16, 127 * G + 8);
+        const int64_t ksn = kMayTile ? a.r.ksn : 0, spitch = ksn ? 16 : G;   // (uniform; a tile's rows lie in one tile of 256 rows of the tiled layout)
+        const __amdgpu_buffer_rsrc_t rs = region(ksn ? tiled_scales(a.r.scales, ksn, row0, tx) : a.r.scales + row0 * G + col0 / 16, 127 * spitch + 8);
         const bool zero = kMode == QII_MS_EDEN && tcr.zero;   // uniform: an all-zero tensor is emitted as zero bytes
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
@@ -143,7 +145,7 @@ __device__ __forceinline__ void pair_block(const PairArgs &a, int block, uint8_t
             if (zero) { packed[0] = 0u; packed[1] = 0u; b = 0u; }
             __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, 0);
             const uint2 sc = gather_scale_bytes(b, L.blk);
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{sc.x, sc.y}, rs, L.blk == 0 ? (uint32_t)(r * G) : kNoStore, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{sc.x, sc.y}, rs, L.blk == 0 ? (uint32_t)(r * spitch) : kNoStore, 0, 0);
         }
     }
 
@@ -195,7 +197,7 @@ __device__ __forceinline__ void pair_block(const PairArgs &a, int block, uint8_t
             if (zero) { codes[0] = codes[1] = codes[2] = codes[3] = 0u; sc = 0u; }
             const uint2 s8 = gather_quad_scales(sc, q);
             *reinterpret_cast<uint4 *>(a.c.codes + (j0 + e) * cpitch + chunk * 64 + 16 * q) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
-            if (q == 0) *reinterpret_cast<uint2 *>(a.c.scales + (j0 + e) * G + chunk * 8) = s8;
+            if (q == 0) *reinterpret_cast<uint2 *>(kMayTile && a.c.ksn ? tiled_scales(a.c.scales, a.c.ksn, j0 + e, chunk) : a.c.scales + (j0 + e) * G + chunk * 8) = s8;
         }
     }
 
@@ -228,6 +230,7 @@ inline PairArgs pair_args(const PairQuantizeArgs &p)
         out[i]->amax = in[i]->amax;
         out[i]->codes = in[i]->codes; out[i]->scales = in[i]->scales; out[i]->tensor_scale = in[i]->tensor_scale;
         out[i]->tbuf = in[i]->tbuf; out[i]->amax_out = in[i]->amax_accum;
+        out[i]->ksn = in[i]->tiled ? (int)((i == 0 ? p.cols : p.rows) / 256) : 0;
     }
     return a;
 }

@@ -38,6 +38,7 @@ struct RequantArgs {
     uint32_t *amax_out;  // abs-max kernel (one running word), heavy pass of the post hoc scheme (nullable there): the spread
     int words;           // words; or, words != 0, one word per block
     float *tbuf;         // post hoc scheme: corrected pseudo-scales [R][C/16]
+    int64_t ksn;         // 0, or the K tiles of the main GEMM kernel's layout, which the scale bytes then go out in (modes with scale bytes)
     int tiles_x;         // tiles along a stored row
     int tiles;
 };
@@ -137,7 +138,7 @@ __device__ __forceinline__ void read_columns(float v[2][32], const RequantArgs &
 }
 
 // the four scale groups of a lane (two per column), their stores
-template <int kMode, int kFast>
+template <int kMode, int kFast, bool kMayTile>
 __device__ __forceinline__ void finish_groups(const RequantArgs &a, float v[2][32], const TensorConsts &tc, const uint32_t draw[2][2],
                                               int64_t chunk, int64_t j0, int q, const float *inv_tab)
 {
@@ -152,13 +153,14 @@ __device__ __forceinline__ void finish_groups(const RequantArgs &a, float v[2][3
         const uint2 s8 = gather_quad_scales(sc, q);
         if (j0 + e < a.R) {
             store_codes16(a.codes + (j0 + e) * (a.C / 2) + chunk * 64 + 16 * q, codes[0], codes[1], codes[2], codes[3]);
-            if (q == 0) *reinterpret_cast<uint2 *>(a.scales + (j0 + e) * (a.C / 16) + chunk * 8) = s8;
+            if (q == 0)
+                *reinterpret_cast<uint2 *>(kMayTile && a.ksn ? tiled_scales(a.scales, a.ksn, j0 + e, chunk) : a.scales + (j0 + e) * (a.C / 16) + chunk * 8) = s8;
         }
     }
 }
 
-// 256 kChunks threads; image: kChunks * kImage bytes of LDS
-template <int kMode, bool kRht, int kChunks>
+// 256 kChunks threads; image: kChunks * kImage bytes of LDS; kMayTile: heeds ksn
+template <int kMode, bool kRht, int kChunks, bool kMayTile = false>
 __device__ __forceinline__ void requant_block(const RequantArgs &a, int block, uint8_t *image)
 {
     __shared__ float inv_tab[128], wave_m[4 * kChunks];
@@ -223,8 +225,8 @@ __device__ __forceinline__ void requant_block(const RequantArgs &a, int block, u
     if (!live) return;
     uint32_t draw[2][2] = {{0u, 0u}, {0u, 0u}};
     if (kMode == QII_MS_EDEN) octet_draws(draw, a.seed_sr, chunk, j0, q);
-    if (tc.fast) finish_groups<kMode, 1>(a, v, tc, draw, chunk, j0, q, inv_tab);   // uniform
-    else finish_groups<kMode, 0>(a, v, tc, draw, chunk, j0, q, inv_tab);
+    if (tc.fast) finish_groups<kMode, 1, kMayTile>(a, v, tc, draw, chunk, j0, q, inv_tab);   // uniform
+    else finish_groups<kMode, 0, kMayTile>(a, v, tc, draw, chunk, j0, q, inv_tab);
 }
 
 inline RequantArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, uint64_t seed_sr, int chunks)
@@ -234,7 +236,7 @@ inline RequantArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t s
     const U4 w = philox_seeded(seed_rht, 0, 0, 0, kStreamRht);
     a.sign[0] = w.x; a.sign[1] = w.y; a.sign[2] = w.z; a.sign[3] = w.w;
     a.seed_sr = seed_sr;
-    a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr; a.tbuf = nullptr; a.words = 0;
+    a.amax = nullptr; a.codes = nullptr; a.scales = nullptr; a.tensor_scale = nullptr; a.amax_out = nullptr; a.tbuf = nullptr; a.words = 0; a.ksn = 0;
     a.tiles_x = (int)((R + 127) / 128);
     a.tiles = (int)((C / 128 + chunks - 1) / chunks) * a.tiles_x;
     return a;
@@ -245,6 +247,7 @@ inline RequantArgs requant_args(const QuantizeArgs &q, int chunks)
     RequantArgs a = make_args(q.src, q.R, q.C, q.seed_rht, q.seed_sr, chunks);
     a.amax = q.amax; a.codes = q.codes; a.scales = q.scales; a.tensor_scale = q.tensor_scale;
     a.tbuf = q.tbuf; a.amax_out = q.amax_accum; a.words = q.amax_words;
+    a.ksn = q.tiled ? q.C / 256 : 0;
     return a;
 }
 
