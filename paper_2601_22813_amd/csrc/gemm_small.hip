@@ -18,6 +18,7 @@
 // needs no padding of the operands: codes and scales beyond K are staged as zeros.  The scale bytes are
 // read row-major or in the tiled layout, whichever the operand has: no re-tiling launch, no workspace.
 #include "gemm_common.h"
+#include "gemm_reduce.h"
 #include "qii_device.h"
 #include "qii_internal.h"
 
@@ -65,6 +66,9 @@ struct Geo {
     // what a wave finishes once the groups' accumulators are added up
     static constexpr int FM = KG == 2 ? MT / 2 : 1, FN = KG == 2 || MT == 4 ? NT : NT / 2;
     static_assert(FM * FN * KG == kUnits, "the groups share the tile");
+    // a wave's fragments of A and B are in the order that reduce_groups asks of its group: unit i NT + j is tile (i ^ row_flip, j ^ col_flip)
+    __device__ static constexpr int row_flip(int kg) { return reduce_flip<KG, kUnits>(kg) / NT; }
+    __device__ static constexpr int col_flip(int kg) { return reduce_flip<KG, kUnits>(kg) % NT; }
     // LDS: two stages; then, per wave, half of its accumulators (the reduction's first round) or the rows it stores
     static constexpr int kStaged = FM * 32 * staging_pitch<false, FN>();
     static constexpr int kArea = (kUnits / 2) * 4096 > kStaged ? (kUnits / 2) * 4096 : kStaged;
@@ -221,19 +225,19 @@ struct RawFrags {
 };
 
 template <class G>
-__device__ __forceinline__ void read_slice(RawFrags<G> &f, const uint8_t *stage, int j, int wm, int li, int kb)
+__device__ __forceinline__ void read_slice(RawFrags<G> &f, const uint8_t *stage, int j, int wm, int kg, int li, int kb)
 {
     const int slot = ((2 * j + kb) ^ (li & 7)) * 16, sc = 4 * j + 2 * kb;
     const uint8_t *codes = stage, *scales = stage + (G::BM + G::BN) * 128;
 #pragma unroll
     for (int t = 0; t < G::MT; ++t) {
-        const int row = (wm * G::MT + t) * 32 + li;
+        const int row = (wm * G::MT + (t ^ G::row_flip(kg))) * 32 + li;
         f.a[t] = *reinterpret_cast<const u32x4 *>(codes + row * 128 + slot);
         f.sa[t] = *reinterpret_cast<const uint16_t *>(scales + row * 16 + sc);
     }
 #pragma unroll
     for (int t = 0; t < G::NT; ++t) {
-        const int row = G::BM + t * 32 + li;
+        const int row = G::BM + (t ^ G::col_flip(kg)) * 32 + li;
         f.b[t] = *reinterpret_cast<const u32x4 *>(codes + row * 128 + slot);
         f.sb[t] = *reinterpret_cast<const uint16_t *>(scales + row * 16 + sc);
     }
@@ -330,44 +334,6 @@ __device__ __forceinline__ void mma_step(floatx16 (&acc)[G::kUnits], const Frags
     }
 }
 
-// One round of the reduction over the K groups: groups kg and kg ^ D exchange halves of their N accumulator tiles
-// through LDS; the group with bit D clear keeps and completes the first half, the other the second.  A wave writes the
-// area `own` and reads its partner's, `other`, which nobody else reads: after a round that area is the wave's own, for
-// the next round or the epilogue, with no barrier between.  The two halves are two pieces of code (the branch is
-// wave-uniform): chosen by value they cost a select per accumulator and round, 1.2 us of the 128 x 128 form's 5.5 from
-// the last product to the last store.
-template <int N, bool kHi>
-__device__ __forceinline__ void reduce_half(const floatx16 (&u)[N], floatx16 (&out)[N / 2], float4 *own, const float4 *other)
-{
-    constexpr int kGive = kHi ? 0 : N / 2, kKeep = kHi ? N / 2 : 0;
-#pragma unroll
-    for (int k = 0; k < N / 2; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const floatx16 &give = u[kGive + k];
-            own[(k * 4 + r) * 64] = make_float4(give[4 * r], give[4 * r + 1], give[4 * r + 2], give[4 * r + 3]);
-        }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N / 2; ++k)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float4 v = other[(k * 4 + r) * 64];
-            const floatx16 &keep = u[kKeep + k];
-            out[k][4 * r] = keep[4 * r] + v.x;
-            out[k][4 * r + 1] = keep[4 * r + 1] + v.y;
-            out[k][4 * r + 2] = keep[4 * r + 2] + v.z;
-            out[k][4 * r + 3] = keep[4 * r + 3] + v.w;
-        }
-}
-
-template <int N>
-__device__ __forceinline__ void reduce_round(const floatx16 (&u)[N], floatx16 (&out)[N / 2], bool hi, uint8_t *own, const uint8_t *other, int lane)
-{
-    if (hi) reduce_half<N, true>(u, out, reinterpret_cast<float4 *>(own) + lane, reinterpret_cast<const float4 *>(other) + lane);
-    else reduce_half<N, false>(u, out, reinterpret_cast<float4 *>(own) + lane, reinterpret_cast<const float4 *>(other) + lane);
-}
-
 // stores what the wave has finished: FM x FN tiles
 template <bool kBf16Out, class G>
 __device__ __forceinline__ void finish(const floatx16 (&u)[G::FM * G::FN], uint8_t *area, float ts, const SmallArgs &g, int64_t row0, int64_t col0, int lane)
@@ -428,7 +394,7 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
         }
     }
 
-    floatx16 acc[G::kUnits];   // tile (i, j) of the wave at i NT + j
+    floatx16 acc[G::kUnits];   // tile (i ^ row_flip, j ^ col_flip) of the wave at i NT + j
 #pragma unroll
     for (int u = 0; u < G::kUnits; ++u)
 #pragma unroll
@@ -467,7 +433,7 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
     __syncthreads();
     const int j0 = kg * G::kSlices;
     RawFrags<G> f0, f1;
-    read_slice<G>(f0, smem, j0, wm, li, kb);
+    read_slice<G>(f0, smem, j0, wm, kg, li, kb);
     if constexpr (G::MT == 4) {
         Frags<G> x, y;
 #pragma unroll
@@ -495,10 +461,13 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
             };
             const int slot = ((2 * j0 + kb) ^ (li & 7)) * 16, sc = 4 * j0 + 2 * kb;
             const uint8_t *codes = nxt + li * 128 + slot, *scales = nxt + (G::BM + G::BN) * 128 + li * 16 + sc;
+            constexpr int kBand = 32 * 128;   // bytes of 32 rows of codes, 8 times those of their scale bytes
+            const int flip = G::row_flip(kg) * kBand;   // (uniform)
             auto fetch = [&](int i) {   // (after the last tile: a stale stage, never multiplied)
                 if (i < 4) {
-                    fn.a[i] = *reinterpret_cast<const u32x4 *>(codes + i * 32 * 128);
-                    fn.sa[i] = *reinterpret_cast<const uint16_t *>(scales + i * 32 * 16);
+                    const int band = (i * kBand) ^ flip;
+                    fn.a[i] = *reinterpret_cast<const u32x4 *>(codes + band);
+                    fn.sa[i] = *reinterpret_cast<const uint16_t *>(scales + (band >> 3));
                 } else if (i < 8) {
                     fn.b[i - 4] = *reinterpret_cast<const u32x4 *>(codes + (G::BM + (i - 4) * 32) * 128);
                     fn.sb[i - 4] = *reinterpret_cast<const uint16_t *>(scales + (G::BM + (i - 4) * 32) * 16);
@@ -533,35 +502,30 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
             // (one set of raw fragments: the other block on the compute unit covers their latency)
             mma_first<G>(acc, f0);
             mma_second<G>(acc, f0);
-            read_slice<G>(f0, cur, j0 + 1, wm, li, kb);
+            read_slice<G>(f0, cur, j0 + 1, wm, kg, li, kb);
             mma_first<G>(acc, f0);
             __syncthreads();
             mma_second<G>(acc, f0);
-            if (kt + 1 < ktiles) read_slice<G>(f0, nxt, j0, wm, li, kb);
+            if (kt + 1 < ktiles) read_slice<G>(f0, nxt, j0, wm, kg, li, kb);
         } else {
             mma_first<G>(acc, f0);
             __syncthreads();
-            if (kt + 1 < ktiles) read_slice<G>(f1, nxt, j0, wm, li, kb);
+            if (kt + 1 < ktiles) read_slice<G>(f1, nxt, j0, wm, kg, li, kb);
             mma_second<G>(acc, f0);
             f0 = f1;
         }
     }
     __syncthreads();   // the reduction overlays the stages
 
-    // (wave w of the block has area w; partners have the same wm)
     const float ts = ts_a * ts_b;
-    auto area = [&](int group) { return smem + (group * G::WM + wm) * G::kArea; };
     const int64_t row0 = m0 + wm * 32 * G::MT;
+    floatx16 sum[G::kUnits / G::KG];
+    uint8_t *const area = reduce_groups<G::WM, G::KG, G::kArea>(acc, sum, smem, kg, wm, lane);
     if constexpr (G::KG == 2) {   // groups finish the first and the last MT / 2 bands
-        floatx16 h[G::kUnits / 2];
-        reduce_round(acc, h, kg != 0, area(kg), area(kg ^ 1), lane);
-        finish<kBf16Out, G>(h, area(kg ^ 1), ts, g, row0 + kg * 32 * G::FM, n0, lane);
+        finish<kBf16Out, G>(sum, area, ts, g, row0 + kg * 32 * G::FM, n0, lane);
     } else {   // groups finish a band each, or (2 x 2) a tile each
-        floatx16 h[G::kUnits / 2], q[G::kUnits / 4];
-        reduce_round(acc, h, (kg & 2) != 0, area(kg), area(kg ^ 2), lane);
-        reduce_round(h, q, (kg & 1) != 0, area(kg ^ 2), area(kg ^ 3), lane);
         const bool band = G::FN == G::NT;
-        finish<kBf16Out, G>(q, area(kg ^ 3), ts, g, row0 + (band ? kg : kg >> 1) * 32, n0 + (band ? 0 : kg & 1) * 32, lane);
+        finish<kBf16Out, G>(sum, area, ts, g, row0 + (band ? kg : kg >> 1) * 32, n0 + (band ? 0 : kg & 1) * 32, lane);
     }
 }
 

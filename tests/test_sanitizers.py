@@ -50,3 +50,15 @@ def test_library_host_code_under_asan_and_ubsan(tmp_path):
     r = run([exe], env=env, timeout=300)
     assert r.returncode == 0 and "abi sanitize: ok" in r.stdout, r.stdout
     assert "runtime error" not in r.stdout and "AddressSanitizer" not in r.stdout, r.stdout
+
+
+def test_reduction_of_the_k_groups_lane_by_lane(tmp_path):
+    """The small-tile GEMM kernels' reduction, run with a thread per lane: one barrier for the whole block, and every two accesses to
+    one place of LDS are ordered by a barrier or a fence, up to the epilogue's use of the area."""
+    exe = str(tmp_path / "reduce_check")
+    # (-O0: every barrier of the source is a call of its own)
+    b = run(["g++", "-std=c++17", "-O0", "-Wno-unknown-pragmas", "-Wno-psabi", "-pthread",
+             os.path.join(ROOT, "tests", "sanitize", "reduce_check.cc"), "-o", exe])
+    assert b.returncode == 0, b.stdout
+    r = run([exe], timeout=120)
+    assert r.returncode == 0 and "reduce check: ok" in r.stdout, r.stdout
