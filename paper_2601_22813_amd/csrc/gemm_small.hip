@@ -19,6 +19,7 @@
 // read row-major or in the tiled layout, whichever the operand has: no re-tiling launch, no workspace.
 #include "gemm_common.h"
 #include "gemm_reduce.h"
+#include "gemm_tail.h"
 #include "qii_device.h"
 #include "qii_internal.h"
 
@@ -82,33 +83,6 @@ struct Staged {
     uint4 a[G::kPassA], b[G::kPassB], s;
 };
 
-// Where a thread finds its pieces of one K tile: byte offsets from its source addresses.  Rows are 8-byte (codes) and
-// byte (scales) aligned when K is an odd multiple of 16 (kAnyK), so a piece of codes is two halves; the last tile may
-// also end at K, half way through a piece: what lies beyond is read from the tile's first 8 bytes, which every row has,
-// the scale bytes as the 16 that end with the row, and finish_tail makes zeros of the surplus when the tile goes to LDS.
-// So the last tile's loads are those of any other, in the same places between the matrix instructions.  (As a burst of
-// their own, each scale byte behind its own branch, they cost 1 us: the forward pass of
-// 1900 x 1360 -> 2136 28.3 -> 27.6 us.)
-struct TileOffsets {
-    int64_t k;     // uniform: of the tile in a row of codes
-    int lo, hi;    // of the two halves of this thread's pieces, beyond that
-    int64_t s;     // of the tile in a row of scale bytes
-};
-
-template <bool kAnyK>
-__device__ __forceinline__ TileOffsets tile_offsets(int kt, int64_t kt_stride, int64_t K)
-{
-    const int64_t k0 = (int64_t)kt * BK;
-    TileOffsets o = {k0 / 2, 0, 8, kt * kt_stride};
-    if (kAnyK && k0 + BK > K) {   // uniform
-        const int off = 16 * (int)(threadIdx.x & 7), left = (int)(K - k0) - 2 * off;
-        if (left <= 0) o.lo = -off;
-        if (left <= 16) o.hi = -off;
-        if (kt > 0) o.s += (K - k0) / 16 - 16;
-    }
-    return o;
-}
-
 // This thread's source addresses (K tile 0), rows beyond the matrix replaced by its last row (their results land in
 // accumulator rows or columns that are never stored).  kNarrow (the forms whose registers are short: 256 for two blocks per unit,
 // 168 for three): 32-bit offsets from the tile's first row, which is in scalar registers; a block tile's rows are then below 4 GiB
@@ -123,22 +97,19 @@ struct Sources {
 };
 
 // piece p of A's (or B's) rows in the tile that o stands for
+template <class G, bool kA>
+__device__ __forceinline__ const uint8_t *codes_at(const Sources<G> &src, int p, const TileOffsets &o)
+{
+    if constexpr (G::kNarrow) return piece_at(kA ? src.a0 : src.b0, kA ? src.a_off[p] : src.b_off[p], o);
+    else return piece_at(kA ? src.a[p] : src.b[p], o);
+}
+
 template <class G, bool kAnyK, bool kA>
 __device__ __forceinline__ uint4 load_codes16(const Sources<G> &src, int p, const TileOffsets &o)
 {
-    const uint8_t *lo, *hi;
-    if constexpr (G::kNarrow) {
-        const uint8_t *base = (kA ? src.a0 : src.b0) + o.k;   // uniform
-        const uint32_t off = kA ? src.a_off[p] : src.b_off[p];
-        lo = base + (uint32_t)(off + o.lo);
-        hi = base + (uint32_t)(off + o.hi);
-    } else {
-        const uint8_t *row = kA ? src.a[p] : src.b[p];
-        lo = row + (o.k + o.lo);
-        hi = row + (o.k + o.hi);
-    }
-    if (!kAnyK) return *reinterpret_cast<const uint4 *>(lo);
-    const uint2 l = *reinterpret_cast<const uint2 *>(lo), h = *reinterpret_cast<const uint2 *>(hi);
+    const uint8_t *c = codes_at<G, kA>(src, p, o);
+    if (!kAnyK) return *reinterpret_cast<const uint4 *>(c);
+    const uint2 l = *reinterpret_cast<const uint2 *>(c), h = *reinterpret_cast<const uint2 *>(c + 8);
     return make_uint4(l.x, l.y, h.x, h.y);
 }
 
@@ -173,34 +144,35 @@ __device__ __forceinline__ const uint8_t *scales_at(const Sources<G> &src, int64
 template <class G, bool kAnyK, bool kFirst>
 __device__ __forceinline__ void load_tile(Staged<G> &st, const Sources<G> &src, int kt, int64_t K)
 {
-    const TileOffsets o = tile_offsets<kAnyK>(kt, src.kt_stride, K);
+    const TileOffsets o = tile_offsets<kAnyK>(kt, src.kt_stride, K, threadIdx.x & 7);
+    if (kAnyK && kFirst && K < 32) {   // uniform: 8 bytes a row
 #pragma unroll
-    for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<G, kAnyK, true>(src, p, o);
+        for (int p = 0; p < G::kPassA + G::kPassB; ++p) {
+            const uint2 c = *reinterpret_cast<const uint2 *>(p < G::kPassA ? codes_at<G, true>(src, p, o) : codes_at<G, false>(src, p - G::kPassA, o));
+            (p < G::kPassA ? st.a[p] : st.b[p - G::kPassA]) = make_uint4(0u, 0u, c.x, c.y);
+        }
+    } else {
 #pragma unroll
-    for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<G, kAnyK, false>(src, p, o);
+        for (int p = 0; p < G::kPassA; ++p) st.a[p] = load_codes16<G, kAnyK, true>(src, p, o);
+#pragma unroll
+        for (int p = 0; p < G::kPassB; ++p) st.b[p] = load_codes16<G, kAnyK, false>(src, p, o);
+    }
     if ((int)threadIdx.x < G::BM + G::BN) {
         if (kAnyK && kFirst && K < BK) st.s = load_scales_short(scales_at(src, 0), (int)K / 16);   // uniform
         else st.s = load_scales16<kAnyK>(scales_at(src, o.s));
     }
 }
 
-// The last, partial tile as it came: zeros beyond K, the scale bytes to the front.
+// The last, partial tile: what came from the end of the row to its place, zeros beyond K.
 template <class G>
 __device__ __forceinline__ void finish_tail(Staged<G> &st, int kt, int64_t K)
 {
     const int tail = (int)(K - (int64_t)kt * BK), left = tail - 32 * (int)(threadIdx.x & 7);
-    const uint32_t lo = left > 0 ? 0xFFFFFFFFu : 0u, hi = left > 16 ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-    for (int p = 0; p < G::kPassA; ++p) st.a[p] = make_uint4(st.a[p].x & lo, st.a[p].y & lo, st.a[p].z & hi, st.a[p].w & hi);
+    for (int p = 0; p < G::kPassA; ++p) finish_piece(st.a[p], left);
 #pragma unroll
-    for (int p = 0; p < G::kPassB; ++p) st.b[p] = make_uint4(st.b[p].x & lo, st.b[p].y & lo, st.b[p].z & hi, st.b[p].w & hi);
-    if (kt > 0) {   // (rows of 16 bytes or more)
-        const int drop = 8 * (16 - tail / 16);   // bits, 8 .. 120
-        uint64_t l = (uint64_t)st.s.y << 32 | st.s.x, h = (uint64_t)st.s.w << 32 | st.s.z;
-        l = drop < 64 ? (l >> drop) | (h << (64 - drop)) : h >> (drop - 64);
-        h = drop < 64 ? h >> drop : 0;
-        st.s = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
-    }
+    for (int p = 0; p < G::kPassB; ++p) finish_piece(st.b[p], left);
+    if (kt > 0) finish_scales(st.s, tail);   // (rows of 16 bytes or more)
 }
 
 // LDS stage: A codes, B codes (128 bytes per row; row r keeps its 16-byte piece s in slot s ^ (r & 7), so
@@ -443,7 +415,7 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
             uint8_t *nxt = smem + ((kt + 1) & 1) * G::kStage;
             const bool more = kt + 2 < ktiles;
             if (kt + 1 == partial) finish_tail<G>(st, kt + 1, g.K);
-            const TileOffsets o = tile_offsets<kAnyK>(more ? kt + 2 : 0, src.kt_stride, g.K);
+            const TileOffsets o = tile_offsets<kAnyK>(more ? kt + 2 : 0, src.kt_stride, g.K, t & 7);
             uint8_t *dst = nxt + (t >> 3) * 128 + ((t & 7) ^ ((t >> 3) & 7)) * 16;
             auto no_side = [](int) {};
             auto move = [&](int i) {   // piece i of tile kt + 1 to LDS, its register takes tile kt + 2's piece

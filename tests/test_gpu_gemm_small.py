@@ -69,8 +69,9 @@ def test_small_tile_kernels_match_the_oracle(oracle, M, N, K, route):
 
 
 @pytest.mark.parametrize("M,N,K,route", [
-    # the last K tile in each kernel: 2, 7, 8, 9 and 15 scale groups of it (its scale bytes are read as the 16 that end with the row), the
-    # second tile of two and the third of three, and rows shorter than 16 scale bytes
+    # the last K tile in each kernel: 2, 7, 8, 9 and 15 scale groups of it (its codes and scale bytes are read as the 16 that end with the
+    # row), the second tile of two and the third of three, rows shorter than 16 scale bytes, and of 8 and 16 bytes of codes
+    (65, 33, 16, T64), (65, 33, 32, T64),
     (65, 33, 288, T64), (65, 33, 368, T64), (65, 33, 384, T64), (65, 33, 400, T64), (65, 33, 496, T64), (130, 70, 880, T64), (33, 65, 112, T64),
     (2040, 1990, 2080, T128_WIDE), (2040, 1990, 2160, T128_WIDE), (2040, 1990, 2192, T128_WIDE), (2040, 1990, 2288, T128_WIDE),
     (2040, 1990, 752, T128_WIDE), (2040, 1990, 496, T128), (2300, 2301, 624, T128), (2040, 1990, 144, T128),
@@ -121,3 +122,20 @@ def test_rows_of_any_alignment_cost_little_more(M, N, K, most):
     print(f"gemm {M}x{N}x{K}: {any_rows:.1f} us, a column less {aligned:.1f}", flush=True)
     assert torch.equal(odd[:, :N - 1], even)
     assert any_rows <= most * aligned
+
+
+@pytest.mark.parametrize("M,N,K,most", [(2857, 123, 20976, 1.15), (896, 1280, 14272, 1.39)])
+def test_a_ragged_k_costs_little_more(M, N, K, most):
+    """K cut in the last of many K tiles against the next whole number of tiles: with an address for each half of a 16-byte piece the
+    first took 1.21 and 1.45 times as long as the second; with one for both 1.08 and 1.34 (half-width loads, unaligned scale bytes)."""
+    g = torch.Generator(device="cuda").manual_seed(12)
+    C = torch.empty((M, N), device="cuda", dtype=torch.bfloat16)
+    us = []
+    for k in (K, (K + 255) // 256 * 256):
+        A, B = qii.NVFP4Tensor.empty(M, k), qii.NVFP4Tensor.empty(N, k)
+        for t in (A, B):
+            qii.qii_quantize_nvfp4(torch.randn((t.rows, k), device="cuda", generator=g), False, qii.RTN, 0, 0, 0, None, t, ws(256))
+        assert qii.lib().qii_gemm_route(M, N, k, 0, 0) in (T64, T128_WIDE)
+        us.append(median_us(lambda: qii.qii_gemm_nvfp4(A, B, C, None)))
+    print(f"gemm {M}x{N}x{K}: {us[0]:.1f} us, with whole K tiles {us[1]:.1f}", flush=True)
+    assert us[0] <= most * us[1]

@@ -62,3 +62,13 @@ def test_reduction_of_the_k_groups_lane_by_lane(tmp_path):
     assert b.returncode == 0, b.stdout
     r = run([exe], timeout=120)
     assert r.returncode == 0 and "reduce check: ok" in r.stdout, r.stdout
+
+
+def test_operand_addresses_of_every_k_tile(tmp_path):
+    """The small-tile GEMM kernels' addresses and last K tile for every K up to five tiles, under the sanitizers."""
+    exe = str(tmp_path / "tail_check")
+    b = run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+             os.path.join(ROOT, "tests", "sanitize", "tail_check.cc"), "-o", exe])
+    assert b.returncode == 0, b.stdout
+    r = run([exe], env=ENV, timeout=120)
+    assert r.returncode == 0 and "tail check: ok" in r.stdout, r.stdout
