@@ -346,6 +346,9 @@ int qii_absmax_takes_tiles(int64_t rows, int64_t cols);
  *   two K groups, 4 of 128 x 128 in four; -1 for sizes the GEMM refuses.  tiled != 0 (K a multiple of 256): both operands'
  *   scale bytes are already in the tiled layout, as in the layer passes.                                            */
 int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
+/* qii_rows_per_wave: rows that a wave of the quantizer along rows takes for a contiguous rows x cols matrix (4, or 1 where
+ *   the matrix is small); -1 for sizes that it refuses.                                      */
+int qii_rows_per_wave(int64_t rows, int64_t cols, qii_mode mode);
 
 /* Host helpers.                                                                        */
 uint64_t qii_derive_seed(uint64_t seed, uint32_t i); /* backward sub-seed i (0..5)      */

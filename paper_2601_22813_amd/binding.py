@@ -28,7 +28,7 @@ EXPORTS = [
     "qii_quantize_nvfp4_noalloc", "qii_gemm_nvfp4_amax", "qii_linear_fwd_amax",
     "qii_quantize_pair_nvfp4", "qii_quantize_pair_workspace_bytes",
     "qii_gemm_sharing_plan", "qii_gemm_sharing_segments", "qii_gemm_sharing_tile_slots",
-    "qii_absmax_takes_tiles", "qii_gemm_route",
+    "qii_absmax_takes_tiles", "qii_gemm_route", "qii_rows_per_wave",
 ]
 
 
@@ -98,6 +98,8 @@ def lib() -> ctypes.CDLL:
         L.qii_gemm_route.restype = c.c_int
         L.qii_absmax_takes_tiles.argtypes = [i64, i64]
         L.qii_absmax_takes_tiles.restype = c.c_int
+        L.qii_rows_per_wave.argtypes = [i64, i64, c.c_int]
+        L.qii_rows_per_wave.restype = c.c_int
         L.qii_selftest_conversions.argtypes = [vp, vp]
         L.qii_selftest_conversions.restype = c.c_int
         L.qii_microbench.argtypes = [c.c_int, vp, vp, c.c_uint64, c.c_int, c.c_int, vp]

@@ -851,6 +851,11 @@ int qii_absmax_takes_tiles(int64_t rows, int64_t cols)
     return rows > 0 && cols > 0 && rows % 128 == 0 && cols % 128 == 0 && qii::absmax_tiles_pay(rows, cols);
 }
 
+int qii_rows_per_wave(int64_t rows, int64_t cols, qii_mode mode)
+{
+    return rows <= 0 || cols <= 0 || cols % 16 != 0 ? -1 : qii::rows_per_wave(rows, cols, (int)mode);
+}
+
 qii_status qii_selftest_conversions(uint64_t *counts, void *stream)
 {
     if (!counts || !aligned(counts, 8)) return fail(QII_INVALID_ARG, "counts must be 8 device uint64, 8-byte aligned");

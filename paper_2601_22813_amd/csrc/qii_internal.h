@@ -117,6 +117,7 @@ hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t 
 // word per block (at most 1024 of them, 4 KiB); else 0
 int posthoc_words(const Source &src, int64_t R, int64_t C);
 int rows_blocks(int64_t R, int64_t C);
+int rows_per_wave(int64_t R, int64_t C, int mode);   // 4, or 1 where the tensor is small
 int cols_blocks(int64_t R, int64_t C);
 hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const float *ts,
                              int64_t rows, int64_t cols, float *y, hipStream_t s);

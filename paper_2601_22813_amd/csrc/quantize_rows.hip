@@ -411,20 +411,8 @@ int rows_wpr(int64_t R, int64_t C)
     return waves % 4 == 0 ? 4 : waves % 2 == 0 ? 2 : 1;
 }
 
-// Rows of a quantizer's wave: a quad, whose rows share a scale-rounding draw call, or one where quads leave the GPU's 1024
-// vector units short of waves, each of which then works its four rows off one after the other.  Whole calls, us, quads : rows
-// (`waves`: those that quads make):
-//   64 waves     256 x  256 f32 RTN 8.6 : 7.6, 4/6 9.7 : 7.9, SR 10.6 : 8.2, MS-EDEN 11.0 : 9.0, post hoc 9.9 : 7.8
-//   256 waves   1024 x 1024 bf16 RTN 8.5 : 7.6, 4/6 9.7 : 8.1, SR 10.7 : 8.3, MS-EDEN 10.9 : 9.1, post hoc 10.4 : 8.4
-//   512 waves   2048 x 1024 bf16 RTN 9.3 : 8.5, MS-EDEN 11.7 : 10.3, post hoc 10.5 : 9.2; f32 RTN 10.1 : 10.2
-//   1024 waves  2048 x 2048 bf16 RTN 10.8 : 11.3, MS-EDEN 13.0 : 14.0, post hoc 11.0 : 11.3; f32 12.1 : 12.8, 15.2 : 15.0
-//   2048 waves  4096 x 2048 f32 RTN 18.1 : 20.0, bf16 post hoc 13.7 : 14.5
-// 4/6 has twice the arithmetic per row and gains a little longer (forward passes, both tensors' waves: 1280 26.8 : 25.2, 2048 31.8 : 31.4,
-// 4096 46.2 : 46.1).
-int rows_per_wave(int64_t R, int64_t C, int mode)
-{
-    return (R + 3) / 4 * rows_waves(C) < (mode == QII_RTN_46 ? 2048 : 1024) ? 1 : 4;
-}
+// blocks side by side on a row
+int64_t rows_gy(int64_t C, int wpr) { return ((C / 16 + 7) / 8 + 8 * wpr - 1) / (8 * wpr); }
 
 // The abs-max passes: as many as the row needs, at most 4, but 2 where fours would leave some beyond the end of 5 waves or
 // more (2 : 4, quantizer as above: 8192 x 4112 bf16 RTN 32.7 : 35.2, 8192 x 5632 bf16 MS-EDEN 46.1 : 47.1, f32 SR 78.0 : 80.0; one
@@ -434,9 +422,6 @@ int absmax_wpr(int64_t C)
     const int waves = rows_waves(C);
     return waves >= 5 && waves % 4 != 0 ? 2 : waves >= 3 ? 4 : waves;
 }
-
-// blocks side by side on a row
-int64_t rows_gy(int64_t C, int wpr) { return ((C / 16 + 7) / 8 + 8 * wpr - 1) / (8 * wpr); }
 
 // one wave per `rows` rows (4, or 1: rows_per_wave) x 1024 columns; max_block_rows > 0 caps the number of blocks below one
 // another (the abs-max pass then strides over the rest)
@@ -471,6 +456,30 @@ RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
 }  // namespace
 
 // (a row of the source and of every output is addressed through a 32-bit buffer descriptor)
+// Rows of a quantizer's wave: a quad, whose rows share a scale-rounding draw call, or one where quads leave the GPU's 1024
+// vector units short of waves, each of which then works its four rows off one after the other.  Whole calls, us, quads : rows
+// (`waves`: those that quads make):
+//   64 waves     256 x  256 f32 RTN 8.6 : 7.6, 4/6 9.7 : 7.9, SR 10.6 : 8.2, MS-EDEN 11.0 : 9.0, post hoc 9.9 : 7.8
+//   256 waves   1024 x 1024 bf16 RTN 8.5 : 7.6, 4/6 9.7 : 8.1, SR 10.7 : 8.3, MS-EDEN 10.9 : 9.1, post hoc 10.4 : 8.4
+//   512 waves   2048 x 1024 bf16 RTN 9.3 : 8.5, MS-EDEN 11.7 : 10.3, post hoc 10.5 : 9.2; f32 RTN 10.1 : 10.2
+//   1024 waves  2048 x 2048 bf16 RTN 10.8 : 11.3, MS-EDEN 13.0 : 14.0, post hoc 11.0 : 11.3; f32 12.1 : 12.8, 15.2 : 15.0
+//   2048 waves  4096 x 2048 f32 RTN 18.1 : 20.0, bf16 post hoc 13.7 : 14.5
+// 4/6 has twice the arithmetic per row and gains a little longer (forward passes, both tensors' waves: 1280 26.8 : 25.2,
+// 2048 31.8 : 31.4, 4096 46.2 : 46.1).  The post hoc scheme's heavy pass gains less long (no abs-max pass before it leaves the tensor
+// in cache, and its blocks each leave a word for the scales pass), and what counts are the waves launched, with those beyond
+// the row's end (rows of three waves go in fours).  bf16, by launched waves:
+//   680 511 x 2304 10.2 : 9.6, 768 3071 x 1024 10.5 : 10.0, 852 851 x 2304 10.3 : 10.5, 896 3583 x 1024 10.6 : 10.8,
+//   1192 1191 x 2560 12.0 : 12.5 (where blocks of single rows are too many for a word each)
+int rows_per_wave(int64_t R, int64_t C, int mode)
+{
+    const int64_t quads = (R + 3) / 4;
+    if (mode == QII_MS_EDEN_PH) {
+        const int wpr = rows_wpr(R, C);
+        return quads * rows_gy(C, wpr) * wpr < 840 ? 1 : 4;
+    }
+    return quads * rows_waves(C) < (mode == QII_RTN_46 ? 2048 : 1024) ? 1 : 4;
+}
+
 bool rows_kernels_apply(const Source &src, int64_t R, int64_t C)
 {
     return !src.transpose && (src.kind == kSrcBF16 || src.kind == kSrcF32) && C <= ((int64_t)1 << 28) &&

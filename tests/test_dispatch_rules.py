@@ -32,6 +32,23 @@ def test_the_faster_abs_max_pass_along_columns(libqii, rows, cols):
     assert bool(libqii.lib().qii_absmax_takes_tiles(rows, cols)) == (tiles < columns)
 
 
+# whole post hoc calls along the rows of a bf16 matrix, us: a wave per row, a wave per four rows
+ROWS_US = {
+    (1023, 1024): (8.15, 10.19), (2559, 1024): (9.86, 10.42), (3071, 1024): (10.01, 10.52), (3583, 1024): (10.83, 10.63),
+    (4799, 1024): (12.55, 12.15), (1535, 2048): (9.94, 10.52), (1999, 2048): (10.89, 10.59), (339, 2304): (8.73, 10.14), (679, 2304): (9.86, 10.35),
+    (1191, 2304): (12.57, 11.91), (1331, 2304): (12.59, 11.93), (679, 2560): (9.89, 10.36), (851, 2560): (10.59, 10.41), (1023, 2560): (10.81, 10.55),
+    (1331, 2560): (12.57, 12.06), (679, 3072): (9.89, 10.30), (1023, 3072): (10.67, 10.50), (1331, 3072): (12.79, 12.05), (767, 4096): (9.94, 10.57),
+    (895, 4096): (10.80, 10.57), (611, 5120): (10.04, 10.57), (715, 5120): (10.69, 10.58), (511, 6144): (10.03, 10.53), (663, 6144): (10.88, 10.64),
+    (435, 7168): (9.89, 10.53), (567, 7168): (10.82, 10.66), (383, 8192): (9.93, 10.55), (447, 8192): (10.79, 10.59),
+}
+
+
+@pytest.mark.parametrize("rows,cols", ROWS_US)
+def test_the_faster_wave_of_the_post_hoc_quantizer(libqii, rows, cols):
+    one, four = ROWS_US[rows, cols]
+    assert libqii.lib().qii_rows_per_wave(rows, cols, libqii.MS_EDEN_PH) == (1 if one < four else 4)
+
+
 MAIN, NO_WORKSPACE, T64, T128, T128_WIDE = range(5)
 
 

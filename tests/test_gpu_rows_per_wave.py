@@ -29,6 +29,7 @@ def quantize(x, mode, rht, amax=None):
     (1, 16, 0), (6, 1040, 0), (511, 80, 0), (512, 128, 0), (513, 128, 0), (63, 1024, 0), (255, 272, 0),     # the first six: measured by each block
     (1021, 1024, 0), (4097, 1024, 0), (1023, 2064, 0), (4099, 1040, 0), (301, 4112, 0), (205, 5648, 0), (1025, 4096, 0),
     (1, 128, 128), (1021, 1024, 128), (4097, 1024, 128), (515, 1152, 128), (205, 5120, 128), (1026, 5632, 128), (131, 7168, 128),
+    (3356, 1024, 128), (3357, 1024, 128), (836, 2304, 128), (837, 2304, 128),      # the line of the post hoc scheme
 ])
 @pytest.mark.parametrize("f32", [False, True])
 def test_rows_on_both_sides_of_the_rules(oracle, R, C, rht, f32):
