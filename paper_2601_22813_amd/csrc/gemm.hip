@@ -664,23 +664,22 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // of units that `grid` blocks (at most 256, at least 4 units each) cut into equal ranges, partial
 // tiles go to the workspace and a second kernel adds them up.
 //
-// The plan follows a cost model fitted to kernel traces (microseconds): a K tile takes 5.8 when all
-// 256 units work and 4.6 when at most 176 do (the part is power-limited: fewer active units run at
-// a higher clock, so filling idle units gains less than their number suggests); a tile costs 5 more
-// for its first loads and its stores; a sharing block 26 more (all blocks store their 256 KiB
-// partial tiles at the same moment), 38 when its range spans two tiles; the second kernel 0.05 per
-// partial tile (they are stored with plain stores, not streaming ones, and mostly still in cache).  Sharing is used
-// where the model promises at least 7 %.  The constants were fitted before the memory operations were spread between the
-// matrix instructions, which makes a K tile 4 to 7 % faster, plain and shared alike.  Measured with the present kernel on
-// one box in turn, bf16 results, one block per tile -> shared: 256 x 256 x 32768 522 -> 72, 512 x 128 x 26624 434 -> 70,
-// 300 x 520 x 30720 497 -> 92, 2816 x 2048 x 16384 287 -> 186, 3072 x 3072 x 16384 314 -> 274, 6100 x 2800 x 4096 181 -> 156,
-// 8448 x 2048 x 8192 327 -> 246, 4200 x 4200 x 8192 334 -> 283, 11264 x 2048 x 16384 647 -> 581.
+// The plan follows a model of the whole product's time (microseconds), the one that choose_route compares with the other
+// kernels': a round of 256 tiles takes 4.83 per K tile, an incomplete one 4.5 up to 176 tiles and 1.12 more at 256 (the part is
+// power-limited: fewer active units run at a higher clock, so filling idle units gains less than their number suggests); every round
+// costs 8.57 more for its first loads, its stores and the launch; a shared last round 30.1 (all blocks store their 256 KiB partial
+// tiles at the same moment, and the second kernel adds them up) and, per K tile of a block's range, 3.19 plus 2.62 times the share of
+// the units that work; 1.31 more where ranges span two tiles.  Sharing is used where the model promises 4 %.  Of 796 products
+// of 1 to 255 tiles in their last round, each timed both ways, the rule takes the slower way by more than 3 % for 30 (190 of them outside the
+// fit: 9); with the figures of a plan whose sharing blocks stored more slowly it was 184.  Measured, us, bf16 results,
+// one block per tile : shared: 8448 x 2048 x 3072 128 : 106, 3072 x 2816 x 10240 184 : 157, 8448 x 1024 x 10240 189 : 157,
+// 11264 x 2048 x 6144 250 : 225, 18432 x 2048 x 3072 200 : 189, 2816 x 2048 x 16384 287 : 165, 256 x 256 x 32768 522 : 72; not taken, though
+// it would pay, 2048 x 5632 x 16384 312 : 287 (176 tiles, where the model sees 301 : 292).
 struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
     int grid;   // blocks that share them
-    double us;  // modelled time of the main kernel (and the second one), without the re-tiling launch
-    bool spans; // priced for ranges that span two tiles
+    double us;  // modelled time, without the re-tiling launch
 };
 
 // (share = false: one block per tile, as where the workspace has no room for the partial tiles)
@@ -688,24 +687,24 @@ static StreamPlan stream_plan(int64_t M, int64_t N, int64_t K, bool share = true
 {
     const int64_t tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN), ktiles = K / BK4;
     const int64_t rounds = tiles / 256, rem = tiles % 256;
-    const double full_us = (double)rounds * (5.8 * (double)ktiles + 5.0);
-    const double kt_us = 4.6 + (rem > 176 ? 1.2 * (double)(rem - 176) / 80.0 : 0.0);
-    const double plain_us = full_us + (rem ? kt_us * (double)ktiles + 5.0 : 0.0);
-    StreamPlan plan{(int)tiles, 0, 0, plain_us, false};
+    const double full_us = 0.1 + (double)rounds * (4.83 * (double)ktiles + 8.57);
+    const double kt_us = 4.5 + (rem > 176 ? 1.12 * (double)(rem - 176) / 80.0 : 0.0);
+    const double plain_us = full_us + (rem ? kt_us * (double)ktiles + 8.57 : 0.0);
+    StreamPlan plan{(int)tiles, 0, 0, plain_us};
     if (!share || K % BK4 != 0 || tiles == 0 || tiles > (1 << 24) || ktiles < 8 || rem == 0) return plan;
     const int64_t units = rem * ktiles;
     int64_t grid = units / 4 < 256 ? units / 4 : 256;
     if (grid >= 8) grid &= ~(int64_t)7;
     if (grid <= rem) return plan;
     const int64_t per = (units + grid - 1) / grid;
-    const bool one_segment = ktiles % per == 0 && units % grid == 0;
-    const double shared_us = full_us + 5.8 * (double)per + (one_segment ? 26.0 : 38.0) + 0.05 * (double)(grid + rem);
-    if (shared_us >= 0.93 * plain_us) return plan;
+    // ranges that differ in length span two tiles somewhere, but not those of one tile, or of two and an even number of blocks
+    const bool one_segment = (ktiles % per == 0 && units % grid == 0) || (rounds == 0 && rem <= 2 && grid % rem == 0);
+    const double shared_us = full_us + 30.0 + (3.19 + 2.62 * (double)grid / 256.0) * (double)per + (one_segment ? 0.0 : 1.31);
+    if (shared_us >= 0.96 * plain_us) return plan;
     plan.full = (int)(rounds * 256);
     plan.rem = (int)rem;
     plan.grid = (int)grid;
     plan.us = shared_us;
-    plan.spans = !one_segment;
     return plan;
 }
 
@@ -791,34 +790,35 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 }
 
 // Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to
-// timings of every kernel, each forced in turn, over 246 products of M, N = 64 .. 16384 and K = 128 .. 32768, bf16 and f32 results
-// (kt = K / 256, b = blocks / 256 compute units): what the rule takes is 0.4 % behind the fastest on average, 11 % at
-// most (13696 x 6272 x 640 f32: the no-workspace kernel instead of 128 x 128).  Some of them, us, from a graph, on one box:
+// timings of every kernel, each forced in turn, over 1671 products of M, N = 64 .. 16384 and K = 128 .. 32768, bf16 and f32 results
+// (kt = K / 256, b = blocks / 256 compute units): what the rule takes there is 0.3 % behind the fastest on average.  Of 700 other
+// products it is 0.5 % behind on average, more than 7 % for 16, at most 25 % (2509 x 3630 x 6784 bf16, rows of C that are not
+// aligned, which no model heeds: the no-workspace kernel instead of 64 x 64).  Some of them, us, bf16 results, from a
+// graph, operands in cache, on one box:
 //                         64 x 64   128 x 128 KG 2   128 x 128 (4, 4)   256 x 256 (with re-tiling)
-//    256 x  256 x   256        4.7              6.4                7.5     12.2
-//    512 x  512 x   512        5.5              8.5                9.4     16.5
-//   1024 x 1024 x  4096       18.5             36.3               27.0     37.0 (shared last round)
-//   1536 x 1536 x  1536       14.4             16.7               14.8     32.1
-//   2048 x 2048 x  2048       25.1             23.9               20.7     41.2
-//   2048 x 2048 x 16384      160.2            143.8              111.2    122.3 (shared)
-//   4096 x 2048 x  1024       25.5             21.3               24.4     27.0
-//   4096 x 2048 x  8192      156.4            127.6              114.8    122.1 (shared)
-//   2048 x 5632 x  2048       59.0             51.6               52.1     45.1
-//   4096 x 4096 x  4096      156.7            128.3              122.7    101.1
-//   2816 x 2048 x 16384      223.3            216.5              187.9    164.6 (shared)
-//   8192 x 8192 x   256                        58.5              105.0     83.3
+//    256 x  256 x   256        3.8              5.6                6.5     11.4
+//    512 x  512 x   512        4.6              7.8                8.5     15.6
+//   1024 x 1024 x  4096       15.8             34.6               25.4
+//   1536 x 1536 x  1536       13.3             16.3               14.3     31.5
+//   2048 x 2048 x  2048       22.4             22.7               18.9     39.9
+//   2048 x 2048 x 16384      153.4            145.3              108.6    120.6 (shared last round)
+//   4096 x 2048 x  1024       23.9             20.0               23.3     25.5
+//   4096 x 2048 x  8192      150.3            131.1              116.8    121.3 (shared)
+//   2048 x 5632 x  2048       56.1             52.3               52.7     46.1
+//   4096 x 4096 x  4096      149.5            126.1              123.3    100.0
+//   2816 x 2048 x 16384      222.7            233.4              196.5    161.2 (shared)
+//   8448 x 2048 x  3072      120.0            117.9              117.8    108.4 (shared)
+//   8192 x 8192 x   256       76.7             54.2               91.6     53.7
 // 64 x 64 tiles: up to three blocks run on a unit and their time adds up, so the unit with the most blocks counts.
 // 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is, and a block
 // beyond the fourth of a unit cheaper, its first loads and stores beside the products of others.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
-// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: stream_plan, whose
-// figure for a shared last round is some 15 more than it takes; 4.5 of re-tiling where the scale bytes are not tiled yet.
-// The plan counts 12 for ranges that span two tiles wherever ranges differ in length; of one tile, or of two and an even
-// number of blocks, none does and the 12 go (main kernel : 64 x 64 tiles, us, re-tiling included: 128 x 128 x 24320 bf16 59.5 : 71.2,
-// 256 x 256 x 19456 bf16 56.9 : 58.4, 256 x 512 x 22784 f32 62.9 : 70.1).
+// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: the plan's own figure, and 4.5
+// of re-tiling where the scale bytes are not tiled yet (one or two shared tiles, main kernel : 64 x 64 tiles: 128 x 128 x 24320
+// 51.6 : 70.4, 256 x 256 x 19456 48.1 : 57.8, 256 x 512 x 22784 56.6 : 67.6).
 // The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
-// 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 12.6 : 9.8 : 12.5 and 14.8 : 12.1 : 18.0, 4096 x 4096 41.0 : 22.3 : 13.7
-// and 49.7 : 28.7 : 20.9, 8192 x 8192 155 : 71 : 47 and 185 : 101 : 75.
+// 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 9.1 : 7.7 : 8.8 and 10.5 : 9.9 : 14.4, 4096 x 4096 25.5 : 18.0 : 12.4
+// and 31.6 : 23.9 : 18.9, 8192 x 8192 87 : 59 : 41 and 112 : 84 : 67.
 enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide };
 
 constexpr int64_t kMaxMainK = (int64_t)1 << 23;
@@ -831,12 +831,12 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     const double kt = (double)((K + BK4 - 1) / BK4), n64 = count(64), n128 = count(128), n256 = count(256);
     const double b64 = n64 > 256.0 ? n64 / 256.0 : 1.0, b = n128 > 256.0 ? n128 / 256.0 : 1.0;
     const double most64 = (double)(int64_t)((n64 + 255.0) / 256.0);
-    const double us64 = 4.259 + 0.753 * b64 + (0.236 + 0.531 * most64) * kt * (any ? 1.3 : 1.0);
+    const double us64 = 4.259 + 0.753 * b64 + (0.236 + 0.531 * most64) * kt * (any ? 1.24 : 1.0);
     const double pairs = (double)(int64_t)(b / 2.0), last = b - 2.0 * pairs;
     const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.49 + 0.55 * last : 2.6 + 0.53 * last);
-    const double us128 = 4.45 + (any ? 1.05 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.28 : 1.0);
+    const double us128 = 4.45 + (any ? 0.74 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.276 : 1.0);
     const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
-    const double us_wide = rounds * (7.75 + (any ? 0.89 : 0.0) + (1.09 + 0.36 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.35 : 1.0));
+    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : 1.0));
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     Route best = kRoute64;
@@ -848,9 +848,7 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     if (us_wide < us || K > kMaxNarrowK) { us = us_wide; best = kRoute128Wide; }
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        double main_us = plan.us + (plan.rem ? -18.6 : 0.1) + 3.32 * rounds256 + (retile ? 4.5 : 0.0);
-        if (plan.spans && plan.full == 0 && plan.rem <= 2 && plan.grid % plan.rem == 0) main_us -= 12.0;
-        offer(kRouteMain, main_us);
+        offer(kRouteMain, plan.us + (retile ? 4.5 : 0.0));
     }
     else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
     return best;

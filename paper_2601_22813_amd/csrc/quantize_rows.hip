@@ -455,7 +455,6 @@ RowsArgs make_args(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, u
 
 }  // namespace
 
-// (a row of the source and of every output is addressed through a 32-bit buffer descriptor)
 // Rows of a quantizer's wave: a quad, whose rows share a scale-rounding draw call, or one where quads leave the GPU's 1024
 // vector units short of waves, each of which then works its four rows off one after the other.  Whole calls, us, quads : rows
 // (`waves`: those that quads make):
@@ -480,6 +479,7 @@ int rows_per_wave(int64_t R, int64_t C, int mode)
     return quads * rows_waves(C) < (mode == QII_RTN_46 ? 2048 : 1024) ? 1 : 4;
 }
 
+// (a row of the source and of every output is addressed through a 32-bit buffer descriptor)
 bool rows_kernels_apply(const Source &src, int64_t R, int64_t C)
 {
     return !src.transpose && (src.kind == kSrcBF16 || src.kind == kSrcF32) && C <= ((int64_t)1 << 28) &&

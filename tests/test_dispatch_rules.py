@@ -90,6 +90,29 @@ def test_one_or_two_shared_tiles_are_priced_without_spans(libqii, M, N, K):
     assert all(L.qii_gemm_sharing_segments(plan[1], K // 256, plan[2], b, segments) == 1 for b in range(plan[2]))
 
 
+# products with an incomplete last round of 256 x 256 tiles, us: one block per tile, the last round's tiles shared, the fastest other kernel
+# (re-tiling included)
+LAST_ROUND_US = {
+    (3072, 2816, 10240): (183.8, 156.6, 186.9), (8448, 1024, 10240): (188.8, 157.2, 187.6), (8448, 2048, 3072): (128.2, 106.4, 114.8),
+    (11264, 2048, 6144): (249.8, 224.5, 254.0), (18432, 2048, 3072): (199.6, 188.5, 206.8), (8448, 3072, 12288): (474.8, 444.1, 520.3),
+    (7168, 5376, 3840): (250.6, 243.9, 277.8), (4096, 2816, 2048): (50.0, 73.8, 53.0), (5632, 1664, 17664): (317.6, 267.3, 307.5),
+    (8960, 1280, 32256): (654.0, 560.9, 602.4), (6912, 4992, 4864): (310.4, 273.5, 330.5), (2304, 5248, 3328): (73.8, 98.0, 80.9),
+    (11520, 1024, 2560): (59.8, 83.8, 61.1),
+}
+
+
+@pytest.mark.parametrize("M,N,K", LAST_ROUND_US)
+def test_the_last_round_is_shared_where_that_is_faster(libqii, M, N, K):
+    """And the product then takes the main kernel, where its time so shared is the least: the plan's figure is the route's."""
+    import ctypes
+    plain, shared, other = LAST_ROUND_US[M, N, K]
+    plan = (ctypes.c_int32 * 3)()
+    libqii.lib().qii_gemm_sharing_plan(ctypes.c_int64(M), ctypes.c_int64(N), ctypes.c_int64(K), plan)
+    assert (plan[1] > 0) == (shared < plain)
+    assert min(plain, shared) < other
+    assert libqii.lib().qii_gemm_route(M, N, K, libqii.qii_gemm_workspace_bytes(M, N, K), 0) == MAIN
+
+
 def test_routes_of_refused_and_smallest_sizes(libqii):
     L = libqii.lib()
     for bad in ((0, 8, 16, 0, 0), (8, 0, 16, 0, 0), (8, 8, 0, 0, 0), (8, 8, 24, 0, 0), (8, 8, 128, 0, 1)):
