@@ -337,26 +337,9 @@ __device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_
     return b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
 }
 
-template <int kTensors>
-struct ScalesLaunch {
-    ScalesArgs a[kTensors];
-    int end[kTensors];   // tensor i's blocks end here
-};
-
-template <int kTensors>
-__global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTensors> l)
+__device__ __forceinline__ void scales_block(const ScalesArgs a, int64_t block)
 {
     __shared__ float wave_m[4];
-    const int id = (int)blockIdx.x;
-    ScalesArgs a = l.a[0];
-    int begin = 0;
-#pragma unroll
-    for (int i = 0; i + 1 < kTensors; ++i)
-        if (id >= l.end[i]) {   // uniform
-            a = l.a[i + 1];
-            begin = l.end[i];
-        }
-    const int64_t block = id - begin;
     float amax = 0.0f;
     for (int i = threadIdx.x; i < a.n_amax; i += 256) amax = fmaxf(amax, a.amax[(int64_t)i * a.stride]);
     amax = wave_max(amax);
@@ -405,6 +388,37 @@ __global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTenso
                 if (g0 + j < G) a.scales[row * G + g0 + j] = (uint8_t)e4m3_sr(a.tbuf[row * G + g0 + j] / x32, draw[j][it]);
         }
     }
+}
+
+template <int kTensors>
+struct ScalesLaunch {
+    ScalesArgs a[kTensors];
+    int end[kTensors];   // tensor i's blocks end here
+};
+
+template <int kTensors>
+__global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTensors> l)
+{
+    const int id = (int)blockIdx.x;
+    ScalesArgs a = l.a[0];
+    int begin = 0;
+#pragma unroll
+    for (int i = 0; i + 1 < kTensors; ++i)
+        if (id >= l.end[i]) {   // uniform
+            a = l.a[i + 1];
+            begin = l.end[i];
+        }
+    scales_block(a, id - begin);
+}
+
+// (two tensors: as parameters of their own both are loaded at once and chosen by value, where the form above chooses an
+// address first: 0.1 us of a small pair's call)
+__global__ __launch_bounds__(256) void posthoc_scales2_kernel(ScalesArgs a0, ScalesArgs a1, int n0)
+{
+    const bool first = (int)blockIdx.x < n0;   // uniform
+    ScalesArgs a = a0;
+    if (!first) a = a1;
+    scales_block(a, (int64_t)blockIdx.x - (first ? 0 : n0));
 }
 
 __global__ void dequantize_kernel(const uint8_t *codes, const uint8_t *scales, const float *ts,
@@ -535,7 +549,8 @@ static hipError_t launch_scales(const PosthocScales *p, int count, hipStream_t s
         l.end[i] = (int)blocks;
     }
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(posthoc_scales_kernel<kTensors>, dim3((unsigned)blocks), dim3(256), 0, s, l);
+    if constexpr (kTensors == 2) hipLaunchKernelGGL(posthoc_scales2_kernel, dim3((unsigned)blocks), dim3(256), 0, s, l.a[0], l.a[1], l.end[0]);
+    else hipLaunchKernelGGL(posthoc_scales_kernel<kTensors>, dim3((unsigned)blocks), dim3(256), 0, s, l);
     return hipGetLastError();
 }
 

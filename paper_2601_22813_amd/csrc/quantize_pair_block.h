@@ -61,7 +61,7 @@ constexpr int kPairImage = 128 * 256;   // LDS bytes of the tile
 
 // tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it)
 template <int kMode, bool kMayTile = false>
-__device__ __forceinline__ void pair_block(const PairArgs &a, int block, uint8_t *tile)
+__device__ __forceinline__ void pair_block(const PairArgs a, int block, uint8_t *tile)
 {
     __shared__ float inv_r[128], inv_c[128];
     __shared__ float wave_m[2][4];
