@@ -104,9 +104,12 @@ template <bool kBf16Out, int NT>
 constexpr int staging_pitch() { return 32 * NT * (kBf16Out ? 2 : 4) + 16; }
 
 // `rows` staged rows whose places in C are aligned for one entry only, or (kEach = 2, bf16) for two: consecutive lanes store
-// consecutive entries, the reads of eight rows not waiting for the stores of those before.
+// consecutive entries, the reads of eight rows not waiting for the stores of those before.  A column is checked once, a row
+// only beside the last ones, and the maximum taken only where it is wanted (uniform): with all three at each store, bf16
+// 9420 x 2177 x 256 took 30.7 us instead of 27.5, f32 922 x 12753 x 256 22.4 instead of 21.3.
 template <bool kBf16Out, int NT, int kEach, int kRows>
-__device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *out, int64_t rb, int live_rows, int live_cols, int lane, float &cmax)
+__device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *out, int64_t rb, int live_rows, int live_cols, int lane, bool want_max,
+                                              float &cmax)
 {
     constexpr int esz = kBf16Out ? 2 : 4, cols = 32 * NT, pitch = staging_pitch<kBf16Out, NT>(), kAtOnce = 8;
     constexpr int lanes = cols / kEach < 64 ? cols / kEach : 64, rows_at_once = 64 / lanes;
@@ -117,8 +120,10 @@ __device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *ou
         const int col = c0 + lane % lanes * kEach;
         const uint8_t *src = staged + rl * pitch + col * esz;
         uint8_t *dst = out + rl * rb + col * esz;
+        if (col >= live_cols) continue;
+        const bool both = kEach == 2 && col + 1 < live_cols;
 #pragma unroll 1
-        for (int r0 = 0; r0 < kRows; r0 += kAtOnce * rows_at_once) {
+        for (int r0 = 0; r0 < kRows && r0 < live_rows; r0 += kAtOnce * rows_at_once) {
             uint32_t v[kAtOnce];
 #pragma unroll
             for (int i = 0; i < kAtOnce; ++i) {
@@ -128,13 +133,18 @@ __device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *ou
 #pragma unroll
             for (int i = 0; i < kAtOnce; ++i) {
                 const int row = r0 + i * rows_at_once;
+                if (row + rl >= live_rows) continue;
                 uint8_t *d = dst + row * rb;
-                if (row + rl >= live_rows || col >= live_cols) continue;
-                if (esz * kEach == 4 && (kEach == 1 || col + 1 < live_cols)) *reinterpret_cast<uint32_t *>(d) = v[i];
+                if (esz * kEach == 4 && (kEach == 1 || both)) *reinterpret_cast<uint32_t *>(d) = v[i];
                 else *reinterpret_cast<uint16_t *>(d) = (uint16_t)v[i];
-                cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v[i] << 16 : v[i])));
-                if (kEach == 2 && col + 1 < live_cols) cmax = fmaxf(cmax, fabsf(u2f(v[i] & 0xFFFF0000u)));
             }
+            if (want_max)
+#pragma unroll
+                for (int i = 0; i < kAtOnce; ++i) {
+                    if (r0 + i * rows_at_once + rl >= live_rows) continue;
+                    cmax = fmaxf(cmax, fabsf(u2f(kBf16Out ? v[i] << 16 : v[i])));
+                    if (both) cmax = fmaxf(cmax, fabsf(u2f(v[i] & 0xFFFF0000u)));
+                }
         }
     }
 }
@@ -229,8 +239,8 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_
                             put_entry(32 * (g + b) + lane, col, area + ((band0 + b) * 32 + lane) * pitch + col * esz);
         } else {
             const uint8_t *group = area + band0 * kBand;
-            if (kBf16Out && pairs) store_entries<kBf16Out, NT, 2, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, cmax);   // uniform
-            else store_entries<kBf16Out, NT, 1, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, cmax);
+            if (kBf16Out && pairs) store_entries<kBf16Out, NT, 2, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, amax_out != nullptr, cmax);   // uniform
+            else store_entries<kBf16Out, NT, 1, 32 * kGroup>(group, row_out, rb, live_rows - 32 * g, live_cols, lane, amax_out != nullptr, cmax);
         }
         wave_lds_fence();   // the reads come before the writes of a group that takes the same room
     }
