@@ -53,8 +53,8 @@ __device__ __forceinline__ uint32_t scale_pair(uint32_t two_bytes, int which)
     return (b << 7) | (b << 23);
 }
 
-// The epilogue of a wave's 128 x 128 tile: two bands at a time (bf16) or one (f32), room for two groups, so that a
-// group's stores leave while the next one is converted.  (The caller guarantees that nobody reads the stages any more.)
+// The epilogue of a wave's 128 x 128 tile in the main kernel: two bands at a time (bf16) or one (f32), room for two groups, so
+// that a group's stores leave while the next one is converted.  (The caller guarantees that nobody reads the stages any more.)
 template <bool kBf16Out, bool kStreaming>
 __device__ __forceinline__ void store_wave_tile(const floatx16 (&acc)[4][4], uint8_t *smem, float ts, void *Cout, int64_t ldc, int64_t M,
                                                 int64_t N, int64_t row0, int64_t col0, int wave, int lane, uint32_t *amax_out)
@@ -78,8 +78,12 @@ __device__ __forceinline__ void store_wave_tile(const floatx16 (&acc)[4][4], uin
 //    LDS tile, then stored as 16-byte pieces of full rows.
 constexpr int kStages = 3;
 constexpr int kOffA = 0, kOffB = 16384, kOffAs = 32768, kOffBs = 34816, kStage2Bytes = 36864;
-constexpr int kSmem2 = 144 * 1024;   // three stages are 108 KiB; the epilogue's staging areas take up to 136
-static_assert(kStages * kStage2Bytes <= kSmem2, "stages fit");
+// epilogue: one band of staged rows per wave, room for two in f32 where stores do not pause
+template <bool kBf16Out, bool kPaced>
+struct Smem2 {
+    static constexpr int kRoom = kBf16Out || kPaced ? 1 : 2, kArea = kRoom * 32 * staging_pitch<kBf16Out, 4>();
+    static constexpr int kBytes = kStages * kStage2Bytes > 4 * kArea ? kStages * kStage2Bytes : 4 * kArea;   // 108 or 132 KiB
+};
 
 struct RawFrag {
     uint4 a[4], b[4];
@@ -153,7 +157,7 @@ __device__ __forceinline__ void mma_slice(floatx16 (&acc)[4][4], const RawFrag &
     }
 }
 
-template <bool kBf16Out>
+template <bool kBf16Out, bool kPaced>
 __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restrict__ a_codes,
                                                          const uint8_t *__restrict__ a_scales,
                                                          const float *__restrict__ a_ts,
@@ -216,7 +220,9 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v2(const uint8_t *__restri
         st_cur = st_next;
     }
 
-    store_wave_tile<kBf16Out, true>(acc, smem, ts_a * ts_b, Cout, ldc, M, N, m0 + wm * 128, n0 + wn * 128, wave, lane, amax_out);
+    using S = Smem2<kBf16Out, kPaced>;
+    store_tile<kBf16Out, true, 4, 4, 1, S::kRoom, kPaced>(acc, smem + wave * S::kArea, ts_a * ts_b, Cout, ldc, M, N, m0 + wm * 128, n0 + wn * 128, lane,
+                                                          amax_out);
 }
 
 
@@ -884,6 +890,18 @@ static SmallTile small_tile(Route route, int64_t K)
     return route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : route == kRoute64 ? kTile64 : kTile128;
 }
 
+template <bool kBf16Out, bool kPaced>
+static hipError_t launch_no_workspace(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int64_t ldc, int tiles_m, int tiles_n, uint32_t *amax_out,
+                                      hipStream_t s)
+{
+    constexpr int lds = Smem2<kBf16Out, kPaced>::kBytes;
+    const hipError_t e = allow_dynamic_lds<gemm_kernel_v2<kBf16Out, kPaced>>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemm_kernel_v2<kBf16Out, kPaced>), dim3((unsigned)(tiles_m * tiles_n)), dim3(256), lds, s, A.codes, A.scales, A.tensor_scale,
+                       B.codes, B.scales, B.tensor_scale, A.rows, B.rows, A.cols, C, ldc, tiles_m, tiles_n, amax_out);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is_bf16, int64_t ldc,
                        float *amax_c, void *ws, size_t ws_bytes, hipStream_t s, int pretiled)
 {
@@ -916,16 +934,15 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
                          : launch_main_kernel<false>(A, a_tiled, B, b_tiled, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, plan, partial, s);
     }
     if (route == kRouteNoWorkspace && !pretiled) {
-        const dim3 grid((unsigned)(tiles_m * tiles_n)), block(256);
-        const hipError_t e = c_is_bf16 ? allow_dynamic_lds<gemm_kernel_v2<true>>(kSmem2) : allow_dynamic_lds<gemm_kernel_v2<false>>(kSmem2);
-        if (e != hipSuccess) return e;
-        if (c_is_bf16)
-            hipLaunchKernelGGL(gemm_kernel_v2<true>, grid, block, kSmem2, s, A.codes, A.scales, A.tensor_scale,
-                               B.codes, B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n, amax_out);
-        else
-            hipLaunchKernelGGL(gemm_kernel_v2<false>, grid, block, kSmem2, s, A.codes, A.scales, A.tensor_scale,
-                               B.codes, B.scales, B.tensor_scale, M, N, K, C, ldc, (int)tiles_m, (int)tiles_n, amax_out);
-        return hipGetLastError();
+        if (c_is_bf16) return launch_no_workspace<true, false>(A, B, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, s);
+        // A round that fills the GPU just once stores all of its f32 results in one go, and reaches more of the memory's rate
+        // when the stores come evenly: with pauses between them.  us, without : with: 256 blocks 4096 x 4096 x 384 24.0 : 23.6, 4096 x
+        // 4096 x 128 17.5 : 17.1, 240 blocks 3840 x 4096 x 384 22.9 : 22.7, 224 blocks 3584 x 4096 x 384 21.8 : 21.4; but 208 blocks
+        // 3328 x 4096 x 128 14.9 : 14.9, 192 blocks 14.1 : 14.9, and with several rounds, where others multiply
+        // meanwhile, 8192 x 8192 x 128 57 : 60.
+        return tiles_m * tiles_n >= 224 && tiles_m * tiles_n <= 256
+                   ? launch_no_workspace<false, true>(A, B, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, s)
+                   : launch_no_workspace<false, false>(A, B, C, ldc, (int)tiles_m, (int)tiles_n, amax_out, s);
     }
     // an operand that is tiled only (bits 0, 1) is read tiled, any other row-major
     const SmallGemm one = {&A, &B, (pretiled & 1) != 0, (pretiled & 2) != 0, C, c_is_bf16, ldc, amax_out};

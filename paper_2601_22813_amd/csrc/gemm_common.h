@@ -99,7 +99,8 @@ __device__ __forceinline__ void wave_lds_fence()
 // A tile that lies inside C with 16-byte aligned rows takes the loop without checks; where the rows are aligned only the
 // pieces that N cuts go entry by entry; other rows: consecutive lanes store consecutive entries (store_entries).
 // kStreaming: C is written once and not read again here, so the stores are non-temporal (false: a partial tile that
-// the next kernel reads back).  All threads of the block must call it if amax_out is given.
+// the next kernel reads back).  kPaced: a pause before each store of a whole tile.  All threads of the block must call it if
+// amax_out is given.
 template <bool kBf16Out, int NT>
 constexpr int staging_pitch() { return 32 * NT * (kBf16Out ? 2 : 4) + 16; }
 
@@ -149,7 +150,7 @@ __device__ __forceinline__ void store_entries(const uint8_t *staged, uint8_t *ou
     }
 }
 
-template <bool kBf16Out, bool kStreaming, int MT, int NT, int kGroup, int kRoom>
+template <bool kBf16Out, bool kStreaming, int MT, int NT, int kGroup, int kRoom, bool kPaced = false>
 __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_t *area, float ts, void *Cout, int64_t ldc, int64_t M,
                                            int64_t N, int64_t row0, int64_t col0, int lane, uint32_t *amax_out)
 {
@@ -208,14 +209,17 @@ __device__ __forceinline__ void store_tile(const floatx16 (&acc)[MT][NT], uint8_
         uint8_t *row_out = out + 32 * g * rb;   // (uniform)
         if (whole) {   // uniform
             const uint32_t voff = (uint32_t)row_l * (uint32_t)rb + (uint32_t)piece * 16u;
-            constexpr int kAtOnce = kPasses < 8 ? kPasses : 8;
+            constexpr int kMost = kPaced ? 2 : 8, kAtOnce = kPasses < kMost ? kPasses : kMost;
 #pragma unroll
             for (int p0 = 0; p0 < kPasses; p0 += kAtOnce) {
                 u32x4 v[kAtOnce];
 #pragma unroll
                 for (int p = 0; p < kAtOnce; ++p) v[p] = *reinterpret_cast<const u32x4 *>(src + (p0 + p) * rows_per_pass * pitch);
 #pragma unroll
-                for (int p = 0; p < kAtOnce; ++p) put(row_out + (p0 + p) * rows_per_pass * rb + voff, v[p]);
+                for (int p = 0; p < kAtOnce; ++p) {
+                    if (kPaced) __builtin_amdgcn_s_sleep(3);   // (192 cycles)
+                    put(row_out + (p0 + p) * rows_per_pass * rb + voff, v[p]);
+                }
                 if (amax_out)   // uniform
 #pragma unroll
                     for (int p = 0; p < kAtOnce; ++p) fold(v[p]);
