@@ -120,3 +120,10 @@ def test_routes_of_refused_and_smallest_sizes(libqii):
     assert L.qii_gemm_route(1, 1, 16, 0, 0) == T64
     # beyond 2^23 columns the main kernel's 32-bit offsets do not reach
     assert L.qii_gemm_route(512, 512, (1 << 23) + 256, 1 << 40, 0) != MAIN
+    # nor those of the 64 x 64 and two-group 128 x 128 kernels beyond 2^25
+    for M, N in ((1, 1), (64, 64), (512, 512), (2048, 2048)):
+        assert L.qii_gemm_route(M, N, 1 << 25, 0, 0) in (T64, T128, T128_WIDE, NO_WORKSPACE)
+        for K in ((1 << 25) + 16, (1 << 25) + 128, (1 << 25) + 256, 1 << 28):
+            for ws in (0, 1 << 40):
+                assert L.qii_gemm_route(M, N, K, ws, 0) in (T128_WIDE, NO_WORKSPACE)
+    assert L.qii_gemm_route(64, 64, 1 << 25, 0, 0) == T64

@@ -51,9 +51,8 @@ MAIN, T64, T128, T128_WIDE = 0, 2, 3, 4
 ])
 @pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
 def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, mode):
-    ph = mode == qii.MS_EDEN_PH
-    for (M, K), route in zip(((T, d_out), (d_out, T)), routes):
-        assert qii.lib().qii_gemm_route(M, d_in, K, qii.qii_gemm_workspace_bytes(M, d_in, K), int(ph and K % 256 == 0)) == route
+    for (M, K), route in zip(((T, d_out), (d_out, T)), routes):   # (both schemes hand over tiled scale bytes)
+        assert qii.lib().qii_gemm_route(M, d_in, K, qii.qii_gemm_workspace_bytes(M, d_in, K), int(K % 256 == 0)) == route
     Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=7)
     oXq, oWq = oracle.linear_fwd(Xb, Wb)
     Eq, WTq, ETq, XTq = oracle.linear_bwd_operands(Eb, oXq, oWq, 10, mode)
@@ -81,8 +80,10 @@ def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, m
 @pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
 @pytest.mark.parametrize("place", ["apart", "misaligned", "dX in dY", "dW in dY", "dX beside dW"])
 def test_where_the_results_lie_makes_no_difference(T, d_in, d_out, mode, place):
-    """The four quantizations of a pass run in one launch, whose buffers of W and X the results' memory takes; results that are
-    misaligned for it, or share bytes with the gradient that the launch reads, get the launches one after the other.  The same bits."""
+    """The four quantizations of a pass run in one launch, whose buffers of W and X (post hoc scheme) the results' memory takes; results
+    that are misaligned for it, or share bytes with the gradient that the launch reads, get the launches one after the other.  The
+    same bits.  Algorithm 1 has no such buffers and looks at no place: its reference is the same gradient in f32, whose quantizations
+    always take launches of their own and leave row-major scale bytes (the kernels of the products are the same either way)."""
     n_e, n_x, n_w = T * d_out, T * d_in, d_out * d_in
     if (place == "dX in dY" and n_x > n_e) or (place == "dW in dY" and n_w > n_e):
         pytest.skip("the result is larger than the gradient")
@@ -103,7 +104,13 @@ def test_where_the_results_lie_makes_no_difference(T, d_in, d_out, mode, place):
         return torch.full((n + 16,), float("nan"), dtype=torch.bfloat16, device="cuda")[off:off + n].view(shape)
 
     print(f"backward T={T} {d_in}->{d_out} mode {mode} {place}", flush=True)
-    eX, eW = run(buf(n_e, (T, d_out)), buf(n_x, (T, d_in), 1), buf(n_w, (d_out, d_in), 1))
+    if mode == qii.MS_EDEN:
+        for M, K in ((T, d_out), (d_out, T)):
+            size = qii.qii_gemm_workspace_bytes(M, d_in, K)
+            assert qii.lib().qii_gemm_route(M, d_in, K, size, int(K % 256 == 0)) == qii.lib().qii_gemm_route(M, d_in, K, size, 0)
+        eX, eW = run(torch.empty((T, d_out), device="cuda"), buf(n_x, (T, d_in), 1), buf(n_w, (d_out, d_in), 1))
+    else:
+        eX, eW = run(buf(n_e, (T, d_out)), buf(n_x, (T, d_in), 1), buf(n_w, (d_out, d_in), 1))
     E, dX, dW = buf(n_e, (T, d_out)), buf(n_x, (T, d_in)), buf(n_w, (d_out, d_in))
     if place == "misaligned":
         dW = buf(n_w, (d_out, d_in), 3)
