@@ -246,8 +246,10 @@ qii_status qii_linear_bwd(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq_save
 /* The same backward pass with the scheme of its four quantizers chosen by the caller:
  * QII_MS_EDEN (as qii_linear_bwd: an abs-max pass and a quantize pass per tensor) or
  * QII_MS_EDEN_PH (Sec. 7: one heavy pass and a scales-only pass per tensor).  Workspace:
- * qii_linear_bwd_mode_workspace_bytes.  Other modes are rejected.  Until the products write them, dX and dW
- * may hold intermediate values of the pass (they then lie outside everything that the pass reads).  */
+ * qii_linear_bwd_mode_workspace_bytes.  Other modes are rejected.
+ * With QII_MS_EDEN_PH the memory of dX and dW may serve as scratch from the pass's first launch on: what they held before
+ * is gone then, and nothing else may read or write them until the pass is done.  Results that share bytes with dY or
+ * with a saved operand, or that are not 16-byte aligned, are as valid as others but take more launches.  */
 qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq_saved,
                                const qii_nvfp4 *Wq_saved, uint64_t seed, qii_mode mode, void *dX,
                                void *dW, qii_dtype g_dt, void *ws, size_t ws_bytes, void *stream);

@@ -215,7 +215,8 @@ qii_status requantize_saved(const qii_nvfp4 *in, int transpose, qii_mode mode, i
 size_t posthoc_region_bytes(int64_t T, int64_t d_in, int64_t d_out, qii_mode mode)
 {
     if (mode != QII_MS_EDEN_PH) return 4 * kSlot;
-    // Q(E) and Q(E^T) are produced together and need a buffer each; the two re-quantizations reuse the first
+    // Q(E) and Q(E^T) are produced together and need a buffer each.  The re-quantizations of W and X take theirs from the results'
+    // memory; where they cannot (qii_linear_bwd_mode) they run later and reuse this one, for which it may have to be larger
     const size_t e_bytes = 2 * align_up((size_t)(T * (d_out / 16)) * 4);
     int64_t groups = d_in * d_out / 16;
     if (d_in * T / 16 > groups) groups = d_in * T / 16;

@@ -241,7 +241,8 @@ __device__ __forceinline__ float measure_tensor(const RowsArgs &a, float *wave_m
     return m;
 }
 
-// One wave = one quad of rows x 1024 columns, one block = 4 such pieces; the grid covers the tensor.
+// One wave = a quad of rows, or one row of a small tensor (kRows), x 1024 columns; one block = 4 such pieces (a measuring block
+// has 12 waves more, without rows); the grid covers the tensor.
 // Blocks are short-lived on purpose: many independent blocks that start and finish at different
 // times keep the memory traffic of the chip smooth, where long-lived waves marching in step (a
 // grid-stride loop with prefetch was measured) load and compute in bursts and ran 10 % slower.
