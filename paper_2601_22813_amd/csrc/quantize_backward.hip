@@ -21,14 +21,14 @@ __global__ __launch_bounds__(512) void quantize_backward_kernel(PairArgs e, Requ
     extern __shared__ __align__(16) uint8_t lds[];   // kChunks images of 32 KiB, the first of them a block's tile of E
     const int block = (int)blockIdx.x;               // (branches on it are uniform)
     if (block < n_e) {
-        pair_block<kMode, true>(e, block, lds);
+        pair_block<kMode, true, const PairArgs &>(e, block, lds);
         return;
     }
     if (kChunks == 1 && threadIdx.x >= 256) return;   // (a wave that has ended takes no part in barriers)
     const bool first = block < n_e + n_w;
     RequantArgs a = w;
     if (!first) a = x;
-    requant_block<kMode, true, kChunks, true>(a, block - n_e - (first ? 0 : n_w), lds);
+    requant_block<kMode, true, kChunks, true, const RequantArgs &>(a, block - n_e - (first ? 0 : n_w), lds);
 }
 
 template <int kMode, int kChunks>

@@ -59,9 +59,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region(const void *base, int64
 // 46.1 -> 43.2, 69.4 -> 65.3.)
 constexpr int kPairImage = 128 * 256;   // LDS bytes of the tile
 
-// tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it)
-template <int kMode, bool kMayTile = false>
-__device__ __forceinline__ void pair_block(const PairArgs a, int block, uint8_t *tile)
+// tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it).  Args: by value, or by reference
+// in a kernel that holds other arguments too (the addresses are then formed otherwise: 0.1 us of a small pair's call by reference,
+// but 1 to 2 % of a backward pass by value)
+template <int kMode, bool kMayTile = false, class Args = const PairArgs>
+__device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
 {
     __shared__ float inv_r[128], inv_c[128];
     __shared__ float wave_m[2][4];

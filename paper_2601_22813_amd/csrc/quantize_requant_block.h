@@ -159,9 +159,9 @@ __device__ __forceinline__ void finish_groups(const RequantArgs &a, float v[2][3
     }
 }
 
-// 256 kChunks threads; image: kChunks * kImage bytes of LDS; kMayTile: heeds ksn
-template <int kMode, bool kRht, int kChunks, bool kMayTile = false>
-__device__ __forceinline__ void requant_block(const RequantArgs a, int block, uint8_t *image)
+// 256 kChunks threads; image: kChunks * kImage bytes of LDS; kMayTile: heeds ksn; Args: as for pair_block
+template <int kMode, bool kRht, int kChunks, bool kMayTile = false, class Args = const RequantArgs>
+__device__ __forceinline__ void requant_block(Args a, int block, uint8_t *image)
 {
     __shared__ float inv_tab[128], wave_m[4 * kChunks];
     const int lane = threadIdx.x & 63, q = lane & 3;
