@@ -18,6 +18,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
          "-fno-fast-math", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wno-unused-command-line-argument"]
 
+# Loops begin on a 64-byte line: the K loop of the small-tile GEMM kernels is some 200 instructions, most of 8 bytes, and where it began
+# 4 bytes off (by accident of the code before it) a K tile took 3 to 4 % longer: 128 x 128 x 7680 25.0 us, aligned 24.2.
+EXTRA = {"gemm_small.hip": ["-falign-loops=64"]}
+
 
 def _stale() -> bool:
     if not os.path.exists(LIB):
@@ -34,7 +38,7 @@ def build(force: bool = True, verbose: bool = False) -> str:
     procs = []
     for src in SOURCES:
         obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = ["hipcc", *FLAGS, *EXTRA.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
@@ -60,7 +64,7 @@ def build_sanitized(out_dir: str) -> str:
     procs, objs = [], []
     for src in SOURCES:
         obj = os.path.join(out_dir, src.replace(".hip", ".san.o"))
-        cmd = ["hipcc", *FLAGS, *san, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = ["hipcc", *FLAGS, *EXTRA.get(src, []), *san, "-c", os.path.join(CSRC, src), "-o", obj]
         procs.append((src, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
         objs.append(obj)
     for src, p in procs:
