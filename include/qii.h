@@ -348,6 +348,9 @@ int qii_absmax_takes_tiles(int64_t rows, int64_t cols);
  *   two K groups, 4 of 128 x 128 in four; -1 for sizes the GEMM refuses.  tiled != 0 (K a multiple of 256): both operands'
  *   scale bytes are already in the tiled layout, as in the layer passes.                                            */
 int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
+/* qii_linear_bwd_gemm_route: the kernel (numbers as for qii_gemm_route) whose one launch computes both dX and dW of a backward pass;
+ *   -1: each takes its own, as qii_gemm_route says, in a launch of its own.  tiled as there, where the inner dimension allows it.  */
+int qii_linear_bwd_gemm_route(int64_t T, int64_t d_in, int64_t d_out, size_t ws_bytes, int tiled);
 /* qii_rows_per_wave: rows that a wave of the quantizer along rows takes for a contiguous rows x cols matrix (4, or 1 where
  *   the matrix is small); -1 for sizes that it refuses.                                      */
 int qii_rows_per_wave(int64_t rows, int64_t cols, qii_mode mode);

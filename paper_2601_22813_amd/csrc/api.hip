@@ -847,6 +847,13 @@ int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
     return M <= 0 || N <= 0 || K <= 0 || K % 16 != 0 || (tiled && K % 256 != 0) ? -1 : qii::gemm_route(M, N, K, ws_bytes, tiled);
 }
 
+int qii_linear_bwd_gemm_route(int64_t T, int64_t d_in, int64_t d_out, size_t ws_bytes, int tiled)
+{
+    if (T <= 0 || d_in <= 0 || d_out <= 0 || T % 128 != 0 || d_out % 128 != 0 || d_in % 16 != 0) return -1;
+    const int64_t M[2] = {T, d_out}, N[2] = {d_in, d_in}, K[2] = {d_out, T};
+    return qii::gemm_pair_route(M, N, K, ws_bytes, tiled);
+}
+
 int qii_absmax_takes_tiles(int64_t rows, int64_t cols)
 {
     return rows > 0 && cols > 0 && rows % 128 == 0 && cols % 128 == 0 && qii::absmax_tiles_pay(rows, cols);

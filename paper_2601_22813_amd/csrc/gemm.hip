@@ -9,7 +9,7 @@
 // v_mfma_f32_32x32x16_f16; every product and the f32 accumulation are those of the
 // dequantized operands.  The two tensor scales are applied once in the epilogue.
 //
-// Three families of kernels share this scheme (choose_route picks one): gemm_kernel_v4, the main one
+// Three families of kernels share this scheme (price_routes picks one): gemm_kernel_v4, the main one
 // (K a multiple of 256, scale bytes re-tiled into a workspace, LDS-direct loads, explicit
 // software pipeline); gemm_kernel_v2 (K a multiple of 128, no workspace); the small-tile kernels
 // of gemm_small.hip (any K that is a multiple of 16, NVFP4's own rule, no workspace).
@@ -19,6 +19,7 @@
 // one scale group per lane: lanes 0..31 supply k 0..31 of a 64-element K slice and
 // lanes 32..63 supply k 32..63, four MFMAs walk the four dwords of a lane's 16 bytes
 // (the order of k inside the contraction is free as long as A and B agree).
+#include <math.h>
 #include <utility>
 
 #include "gemm_common.h"
@@ -670,7 +671,7 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // of units that `grid` blocks (at most 256, at least 4 units each) cut into equal ranges, partial
 // tiles go to the workspace and a second kernel adds them up.
 //
-// The plan follows a model of the whole product's time (microseconds), the one that choose_route compares with the other
+// The plan follows a model of the whole product's time (microseconds), the one that price_routes compares with the other
 // kernels': a round of 256 tiles takes 4.83 per K tile, an incomplete one 4.5 up to 176 tiles and 1.12 more at 256 (the part is
 // power-limited: fewer active units run at a higher clock, so filling idle units gains less than their number suggests); every round
 // costs 8.57 more for its first loads, its stores and the launch; a shared last round 30.1 (all blocks store their 256 KiB partial
@@ -829,8 +830,13 @@ enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide }
 
 constexpr int64_t kMaxMainK = (int64_t)1 << 23;
 
+struct Prices {
+    double us[5];   // by Route; HUGE_VAL: cannot run
+    Route best;
+};
+
 // main_ws: bytes of workspace that the main kernel can use; 0: it cannot run
-static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile)
+static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
     const bool any = K % BK4 != 0;
@@ -845,28 +851,22 @@ static Route choose_route(int64_t M, int64_t N, int64_t K, size_t main_ws, bool 
     const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : 1.0));
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
-    Route best = kRoute64;
-    double us = us64;
-    auto offer = [&](Route r, double t) {
-        if (t < us) { us = t; best = r; }
-    };
-    offer(kRoute128, us128);
-    if (us_wide < us || K > kMaxNarrowK) { us = us_wide; best = kRoute128Wide; }
-    if (main_ws) {
-        const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        offer(kRouteMain, plan.us + (retile ? 4.5 : 0.0));
-    }
-    else if (K % 128 == 0) offer(kRouteNoWorkspace, us_v2);
-    return best;
+    const bool narrow = K <= kMaxNarrowK;
+    Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide};
+    if (main_ws) p.us[kRouteMain] = plan_that_fits(M, N, K, main_ws).us + (retile ? 4.5 : 0.0);
+    else if (K % 128 == 0) p.us[kRouteNoWorkspace] = us_v2;
+    for (const Route r : {kRoute128, kRoute128Wide, kRouteMain, kRouteNoWorkspace})
+        if (p.us[r] < p.us[p.best]) p.best = r;
+    return p;
 }
 
 bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
 {
-    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && choose_route(M, N, K, gemm_workspace_bytes(M, N, K), false) == kRouteMain;
+    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && price_routes(M, N, K, gemm_workspace_bytes(M, N, K), false).best == kRouteMain;
 }
 
-// whether the main kernel can run, and the route, for operands and a workspace as launch_gemm has them
-static Route route_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, size_t ws_bytes, int pretiled)
+// whether the main kernel can run, and the prices, for operands and a workspace as launch_gemm has them
+static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, size_t ws_bytes, int pretiled)
 {
     const int64_t M = A.rows, N = B.rows, K = A.cols;
     // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
@@ -875,19 +875,52 @@ static Route route_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, si
     // (K: offsets within a tile's rows stay below 2^31)
     const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= scales_workspace_bytes(M, N, K) &&
                          (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
-    return choose_route(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10));
+    return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10));
+}
+
+static Prices test_prices(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
+{
+    const qii_nvfp4 a = {nullptr, nullptr, nullptr, M, K}, b = {nullptr, nullptr, nullptr, N, K};
+    // (a stand-in address: the route looks at its alignment)
+    return prices_of(a, b, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
 }
 
 int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
 {
-    const qii_nvfp4 a = {nullptr, nullptr, nullptr, M, K}, b = {nullptr, nullptr, nullptr, N, K};
-    // (a stand-in address: the route looks at its alignment)
-    return (int)route_of(a, b, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
+    return (int)test_prices(M, N, K, ws_bytes, tiled).best;
 }
 
 static SmallTile small_tile(Route route, int64_t K)
 {
     return route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : route == kRoute64 ? kTile64 : kTile128;
+}
+
+// Whether two products whose operands are both ready take one launch of a small-tile kernel: where their modelled times in that
+// kernel, less what a launch of its own costs the second (the launch itself, and units that idle at the end of one and at the
+// beginning of the other), are below those of the products' own routes.  Returns that kernel, else kRouteMain.  The three
+// savings are fitted to 200 backward passes of T, d_in, d_out = 128 .. 8192, each with two launches and with one of each kernel; of 260
+// others the choice is 0.7 % of the pass behind the fastest on average (3.2 % where products shared a launch only if both took the
+// kernel alone), at most 28 %.  Whole passes, us, two launches : one: 64 x 64 tiles 128 x 2432 -> 1408 post hoc 31.1 : 24.2, 1280 x
+// 512 -> 4864 64.3 : 52.3, 3840 x 1280 -> 1024 f32 gradient 86.2 : 80.6; 128 x 128 in two groups 1920 x 6144 -> 1408 128.9 :
+// 105.8, 640 x 4992 -> 896 50.8 : 39.4; in four 6912 x 640 -> 3840 129.1 : 112.1; but 6656 x 6912 -> 256 115.6 : 135.0, 4992 x 5616 -> 128
+// 83.0 : 96.4.
+static Route shared_route(const Prices &a, const Prices &b)
+{
+    constexpr double kSaved[5] = {0.0, 0.0, 9.6, 11.7, 12.0};
+    Route best = kRouteMain;
+    double us = a.us[a.best] + b.us[b.best];
+    for (const Route r : {kRoute64, kRoute128, kRoute128Wide}) {
+        const double t = a.us[r] + b.us[r] - kSaved[r];
+        if (t < us) { us = t; best = r; }
+    }
+    return best;
+}
+
+int gemm_pair_route(const int64_t M[2], const int64_t N[2], const int64_t K[2], size_t ws_bytes, int tiled)
+{
+    if ((K[0] % BK4 != 0) != (K[1] % BK4 != 0)) return -1;
+    const Route r = shared_route(test_prices(M[0], N[0], K[0], ws_bytes, tiled && K[0] % BK4 == 0), test_prices(M[1], N[1], K[1], ws_bytes, tiled && K[1] % BK4 == 0));
+    return r == kRouteMain ? -1 : (int)r;
 }
 
 template <bool kBf16Out, bool kPaced>
@@ -914,7 +947,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     }
     if (M == 0 || N == 0) return hipSuccess;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    const Route route = route_of(A, B, ws, ws_bytes, pretiled);
+    const Route route = prices_of(A, B, ws, ws_bytes, pretiled).best;
     uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
     uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
     if (route == kRouteMain) {
@@ -951,17 +984,16 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
 
 hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_bytes, hipStream_t s)
 {
-    Route r[2];
+    Prices p[2];
     SmallGemm two[2];
-    bool small = true;
-    for (int i = 0; i < 2; ++i) {
-        if (c[i].A->rows == 0 || c[i].B->rows == 0 || (c[i].pretiled && c[i].A->cols % BK4 != 0)) { small = false; break; }
-        r[i] = route_of(*c[i].A, *c[i].B, ws, ws_bytes, c[i].pretiled);
-        small = small && r[i] != kRouteMain && !(r[i] == kRouteNoWorkspace && !c[i].pretiled);
+    bool can_share = (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0);
+    for (int i = 0; i < 2 && can_share; ++i) {
+        if (c[i].A->rows == 0 || c[i].B->rows == 0 || (c[i].pretiled && c[i].A->cols % BK4 != 0)) { can_share = false; break; }
+        p[i] = prices_of(*c[i].A, *c[i].B, ws, ws_bytes, c[i].pretiled);
         two[i] = SmallGemm{c[i].A, c[i].B, (c[i].pretiled & 1) != 0, (c[i].pretiled & 2) != 0, c[i].C, c_is_bf16, c[i].ldc, nullptr};
     }
-    if (small && small_tile(r[0], c[0].A->cols) == small_tile(r[1], c[1].A->cols) && (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0))
-        return launch_gemm_small(two, 2, small_tile(r[0], c[0].A->cols), s);
+    const Route shared = can_share ? shared_route(p[0], p[1]) : kRouteMain;
+    if (shared != kRouteMain) return launch_gemm_small(two, 2, shared == kRoute64 ? kTile64 : shared == kRoute128 ? kTile128 : kTile128Wide, s);
     for (int i = 0; i < 2; ++i) {
         const hipError_t e = launch_gemm(*c[i].A, *c[i].B, c[i].C, c_is_bf16, c[i].ldc, nullptr, ws, ws_bytes, s, c[i].pretiled);
         if (e != hipSuccess) return e;

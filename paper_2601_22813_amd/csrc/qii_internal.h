@@ -178,7 +178,7 @@ struct SmallGemm {
     uint32_t *amax_out;
 };
 hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipStream_t s);
-// two products whose operands are both ready: in one launch when they take the same small-tile kernel, else one
+// two products whose operands are both ready: in one launch of a small-tile kernel where that is the faster way, else one
 // launch_gemm after the other (arguments as there, no maxima)
 struct GemmCall {
     const qii_nvfp4 *A, *B;
@@ -197,6 +197,7 @@ int gemm_sharing_segments(int rem, int ktotal, int grid, int block_id, int32_t *
 void gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t out[2]);
 // the kernel that launch_gemm would run: see qii_gemm_route
 int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
+int gemm_pair_route(const int64_t M[2], const int64_t N[2], const int64_t K[2], size_t ws_bytes, int tiled);
 
 // sweeps of the hardware conversions and short division sequences against their value-space
 // rules; counts[0..7] (device) receive the numbers of mismatches (selftest.hip)

@@ -90,6 +90,36 @@ def test_one_or_two_shared_tiles_are_priced_without_spans(libqii, M, N, K):
     assert all(L.qii_gemm_sharing_segments(plan[1], K // 256, plan[2], b, segments) == 1 for b in range(plan[2]))
 
 
+# whole backward passes T x d_in -> d_out in bf16, us: dX and dW in a launch each, both in one launch of 64 x 64 tiles, of 128 x 128 tiles in
+# two and in four K groups
+PASS_US = {
+    (896, 256, 384): (31.86, 26.69, 32.56, 32.93), (128, 304, 128): (28.56, 23.73, 26.65, 27.79), (512, 512, 256): (28.07, 24.35, 27.42, 28.46),
+    (128, 2432, 1408): (31.06, 24.23, 31.57, 30.13), (128, 2048, 3968): (56.59, 48.40, 68.50, 59.84), (1280, 512, 4864): (64.29, 52.29, 72.92, 61.94),
+    (896, 1280, 4480): (79.51, 64.96, 78.14, 71.06), (1280, 7552, 2304): (149.26, 155.40, 136.43, 148.79), (896, 3072, 2176): (75.61, 69.47, 64.02, 73.67),
+    (1920, 6144, 1408): (128.89, 121.71, 105.75, 118.24), (512, 6528, 512): (46.41, 43.42, 40.05, 47.27), (640, 4992, 896): (50.75, 43.28, 39.39, 45.66),
+    (6912, 640, 3840): (129.08, 124.61, 123.78, 112.09), (2688, 5792, 640): (81.03, 91.66, 89.86, 88.78), (6656, 6912, 256): (115.57, 134.98, 144.82, 144.61),
+    (5120, 3968, 512): (82.69, 90.89, 111.24, 97.96), (4992, 5616, 128): (83.01, 96.38, 103.96, 110.89), (6912, 3840, 256): (79.18, 91.88, 103.58, 102.64),
+}
+
+
+@pytest.mark.parametrize("T,d_in,d_out", PASS_US)
+def test_dx_and_dw_share_a_launch_where_that_is_faster(libqii, T, d_in, d_out):
+    size = max(libqii.qii_gemm_workspace_bytes(T, d_in, d_out), libqii.qii_gemm_workspace_bytes(d_out, d_in, T))
+    ways = dict(zip((-1, T64, T128, T128_WIDE), PASS_US[T, d_in, d_out]))
+    assert libqii.lib().qii_linear_bwd_gemm_route(T, d_in, d_out, size, 1) == min(ways, key=ways.get)
+
+
+def test_products_of_different_routes_share_a_launch(libqii):
+    """dX alone is faster in 128 x 128 tiles, dW in 64 x 64 ones; with a launch each the pass took 86.2 us, with one 80.6."""
+    L = libqii.lib()
+    T, d_in, d_out = 3840, 1280, 1024
+    dx, dw = libqii.qii_gemm_workspace_bytes(T, d_in, d_out), libqii.qii_gemm_workspace_bytes(d_out, d_in, T)
+    assert (L.qii_gemm_route(T, d_in, d_out, dx, 0), L.qii_gemm_route(d_out, d_in, T, dw, 0)) == (T128, T64)
+    assert L.qii_linear_bwd_gemm_route(T, d_in, d_out, max(dx, dw), 0) == T64
+    for bad in ((0, 16, 128), (128, 0, 128), (128, 16, 0), (64, 16, 128), (128, 16, 64), (128, 8, 128)):
+        assert L.qii_linear_bwd_gemm_route(*bad, 1 << 30, 0) == -1
+
+
 # products with an incomplete last round of 256 x 256 tiles, us: one block per tile, the last round's tiles shared, the fastest other kernel
 # (re-tiling included)
 LAST_ROUND_US = {

@@ -48,6 +48,7 @@ MAIN, T64, T128, T128_WIDE = 0, 2, 3, 4
     (1280, 4112, 1280, (T128, T128)),              # 128 x 128 tiles in two K groups, five K tiles
     (384, 16400, 384, (T128, T128)),               # K no multiple of 256; W and X re-quantized by blocks of two chunks, three chunks each
     (2048, 2048, 5632, (T128_WIDE, MAIN)),         # dX and dW by different kernels, so in two launches
+    (3840, 1280, 1024, (T128, T64)),               # different kernels alone, one launch of 64 x 64 tiles together
 ])
 @pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
 def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, mode):
