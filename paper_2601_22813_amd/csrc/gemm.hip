@@ -331,40 +331,64 @@ __device__ __forceinline__ void issue_tile_loads(std::integer_sequence<int, I...
 // destination registers, and the matching wait "produces" them for the code that follows.
 struct RawFrag4 {
     u32x4 a[4], b[4];       // 32 codes (16 bytes) of K for 4 row blocks of A and of B
-    uint32_t sa[4], sb[4];  // their two scale bytes
+};
+
+// the 16 scale bytes that each of a lane's 8 rows has for a whole K tile: one 16-byte read per row and tile (a read of the
+// lane's two bytes per row and slice is 64 LDS reads a tile instead of 40)
+struct TileScales {
+    u32x4 a[4], b[4];
+};
+
+// a slice's two scales per row, as two f16 numbers (scale_halves)
+struct SliceScales {
+    uint32_t a[4], b[4];
 };
 
 struct FragAddr {
     uint32_t a, b, sa, sb;  // LDS byte addresses of this lane's row 0 pieces in stage 0
     uint32_t xo[4];         // swizzled 16-byte slot of K slice j, times 16
+    uint32_t sel;           // selector of this lane's two bytes among a slice's four
 };
 
 // LDS addresses of one slice's reads
 struct ReadAddr {
-    uint32_t a, b, sa, sb;
+    uint32_t a, b;
 };
 
 template <int J>
 __device__ __forceinline__ ReadAddr read_addr(const FragAddr &fa, uint32_t stage_off)
 {
-    return ReadAddr{fa.a + fa.xo[J] + stage_off, fa.b + fa.xo[J] + stage_off, fa.sa + stage_off, fa.sb + stage_off};
+    return ReadAddr{fa.a + fa.xo[J] + stage_off, fa.b + fa.xo[J] + stage_off};
 }
 
-// read I (0..15) of K slice J: rows 32 T (codes 32 * 128 bytes apart, re-tiled scales 32 * 16 bytes apart), T = I / 4
-template <int J, int I>
+// read I (0..7) of a K slice's codes: rows 32 T (32 * 128 bytes apart), T = I / 2
+template <int I>
 __device__ __forceinline__ void frag_read_one(RawFrag4 &f, const ReadAddr &r)
 {
-    constexpr int T = I >> 2;
-    if constexpr ((I & 3) == 0) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[T]) : "v"(r.a), "n"(T * 4096));
-    else if constexpr ((I & 3) == 1) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(r.b), "n"(T * 4096));
-    else if constexpr ((I & 3) == 2) asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sa[T]) : "v"(r.sa), "n"(T * 512 + 4 * J));
-    else asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sb[T]) : "v"(r.sb), "n"(T * 512 + 4 * J));
+    constexpr int T = I >> 1;
+    if constexpr ((I & 1) == 0) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[T]) : "v"(r.a), "n"(T * 4096));
+    else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(r.b), "n"(T * 4096));
 }
 
-template <int J, int... I>
+// read I (0..7) of a K tile's scale bytes (rows 32 * 16 bytes apart)
+template <int I>
+__device__ __forceinline__ void scale_read_one(TileScales &f, const FragAddr &fa, uint32_t stage_off)
+{
+    constexpr int T = I >> 1;
+    if constexpr ((I & 1) == 0) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.a[T]) : "v"(fa.sa + stage_off), "n"(T * 512));
+    else asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(fa.sb + stage_off), "n"(T * 512));
+}
+
+template <int... I>
 __device__ __forceinline__ void frag_read_issue(std::integer_sequence<int, I...>, RawFrag4 &f, const ReadAddr &r)
 {
-    (frag_read_one<J, I>(f, r), ...);
+    (frag_read_one<I>(f, r), ...);
+}
+
+template <int... I>
+__device__ __forceinline__ void scale_read_issue(std::integer_sequence<int, I...>, TileScales &f, const FragAddr &fa, uint32_t stage_off)
+{
+    (scale_read_one<I>(f, fa, stage_off), ...);
 }
 
 // all outstanding LDS reads have landed; ties the registers of f to the wait
@@ -372,75 +396,97 @@ __device__ __forceinline__ void frag_read_wait(RawFrag4 &f)
 {
     asm volatile("s_waitcnt lgkmcnt(0)"
                  : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]),
-                   "+v"(f.b[2]), "+v"(f.b[3]), "+v"(f.sa[0]), "+v"(f.sa[1]), "+v"(f.sa[2]), "+v"(f.sa[3]),
-                   "+v"(f.sb[0]), "+v"(f.sb[1]), "+v"(f.sb[2]), "+v"(f.sb[3]));
+                   "+v"(f.b[2]), "+v"(f.b[3]));
+}
+
+__device__ __forceinline__ void frag_read_wait(RawFrag4 &f, TileScales &s)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]),
+                   "+v"(f.b[2]), "+v"(f.b[3]), "+v"(s.a[0]), "+v"(s.a[1]), "+v"(s.a[2]), "+v"(s.a[3]),
+                   "+v"(s.b[0]), "+v"(s.b[1]), "+v"(s.b[2]), "+v"(s.b[3]));
 }
 
 struct Frags {
     half8_t a[4], b[4];
 };
 
-// chunk I (0..15) of the dequantization of dword D of raw fragments f into nx: fragment I/2
-// (0..3 = A, 4..7 = B), half I%2.  The first chunk that touches a fragment of a freshly read
-// slice (dword 0, half 0) first turns its two scale bytes into the two-f16 form, in place.
-template <int I, int D>
-__device__ __forceinline__ void dequant_chunk(Frags &nx, RawFrag4 &f)
+// chunk I (0..15) of the dequantization of dword D of slice J's raw fragments f into nx: fragment I/2
+// (0..3 = A, 4..7 = B), half I%2.  The first chunk that touches a fragment of a new slice (dword 0, half 0) first puts the
+// lane's two scale bytes of that slice into the two-f16 form.
+template <int I, int D, int J>
+__device__ __forceinline__ void dequant_chunk(Frags &nx, const RawFrag4 &f, const TileScales &ts, SliceScales &ss, uint32_t sel)
 {
     constexpr int t = (I >> 1) & 3, h = I & 1;
     if (I < 8) {
-        if (D == 0 && h == 0) f.sa[t] = scale_halves(f.sa[t]);
-        dequant_half<h, (D >> 1)>(nx.a[t], f.a[t][D], f.sa[t]);
+        if (D == 0 && h == 0) ss.a[t] = scale_halves(ts.a[t][J], sel);
+        dequant_half<h, (D >> 1)>(nx.a[t], f.a[t][D], ss.a[t]);
     } else {
-        if (D == 0 && h == 0) f.sb[t] = scale_halves(f.sb[t]);
-        dequant_half<h, (D >> 1)>(nx.b[t], f.b[t][D], f.sb[t]);
+        if (D == 0 && h == 0) ss.b[t] = scale_halves(ts.b[t][J], sel);
+        dequant_half<h, (D >> 1)>(nx.b[t], f.b[t][D], ss.b[t]);
     }
 }
 
+template <int J, int... I>
+__device__ __forceinline__ void dequant_all(std::integer_sequence<int, I...>, Frags &nx, const RawFrag4 &f, const TileScales &ts, SliceScales &ss, uint32_t sel)
+{
+    (dequant_chunk<I, 0, J>(nx, f, ts, ss, sel), ...);
+}
+
 // One step = 16 matrix instructions on the fragments in cu, with the fragments of the next
-// step (dword D of f) dequantized into nx in between, one chunk per matrix instruction, and the memory
+// step (dword D of slice J, raw in f) dequantized into nx in between, one chunk per matrix instruction, and the memory
 // operations side(I) spread over the step; the scheduling barriers keep that order, so the conversions and
 // the issue of the memory operations run in the shadow of the matrix pipe.  (A K tile's 18 loads, with their
 // address arithmetic, and 64 LDS reads used to be issued in blocks between the steps, with the matrix pipe idle:
 // 16384 x 2048 x 8192 441 -> 412 us, 32768 x 16384 x 2048 1820 -> 1743, 8192^3 827 -> 797 on one box.)
-struct NoSide {
-    template <int I>
-    __device__ __forceinline__ void at() const {}
-};
-
-template <int D, class Side>
-__device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, RawFrag4 &f, const Side &side)
+template <int D, int J, class Side>
+__device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, const RawFrag4 &f, const TileScales &ts, SliceScales &ss,
+                                         uint32_t sel, const Side &side)
 {
 #define QII_MMA(I)                                                                                          \
     acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[(I) & 3], cu.a[(I) >> 2],          \
                                                                     acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
     side.template at<I>();                                                                                  \
-    dequant_chunk<I, D>(nx, f);                                                                             \
+    dequant_chunk<I, D, J>(nx, f, ts, ss, sel);                                                             \
     __builtin_amdgcn_sched_barrier(0)
     QII_MMA(0); QII_MMA(1); QII_MMA(2); QII_MMA(3); QII_MMA(4); QII_MMA(5); QII_MMA(6); QII_MMA(7);
     QII_MMA(8); QII_MMA(9); QII_MMA(10); QII_MMA(11); QII_MMA(12); QII_MMA(13); QII_MMA(14); QII_MMA(15);
 #undef QII_MMA
 }
 
-// the 16 reads of K slice J into g, one per matrix instruction
-template <int J>
-struct ReadSide {
-    RawFrag4 &g;
-    const ReadAddr r;
-    template <int I>
-    __device__ __forceinline__ void at() const { frag_read_one<J, I>(g, r); }
-};
+// The memory operations of a K tile go out one at a time: a load every 3 matrix instructions from the tile's first on, a fragment
+// read every 4, a read of scale bytes every 4.  (The address unit takes 16 cycles for a load of 1 KiB, so the four waves' loads after
+// every matrix instruction, 32 cycles, waited for one another and the matrix pipe with them.  A load, a read every 1 and 1, 64 reads a
+// tile -> 3 and 4, 40 reads: 16384 x 8192 x 2048 400.6 -> 385.4 us, 8192^3 734 -> 714; loads every 2, 4, 6, 8: 387, 388, 387, 389 and 715 to 716.)
+constexpr int kLoadEvery = 3, kReadEvery = 4, kScaleEvery = 4;
 
-// loads kFirst + I of K tile kt (those below 18), one per matrix instruction
-template <int kFirst>
-struct LoadSide {
-    uint8_t *stage;
+// step Q (0..15) of a tile: the next tile's loads, and the reads of the slice whose registers are free
+template <int Q>
+struct TileSide {
+    uint8_t *load_stage;
     const TileSource &a, &b;
     const TileDescriptors &d;
     int kt, wave;
+    RawFrag4 &fe, &fo;
+    TileScales &ts;
+    const FragAddr &fa;
+    uint32_t nxt_off;
+    const ReadAddr r[4];   // of the slices 2, 3 of this tile, 0, 1 of the next; r[3] in steps 0 to 2: slice 1 of this one
     template <int I>
     __device__ __forceinline__ void at() const
     {
-        if constexpr (kFirst + I < 18) issue_tile_load<kFirst + I>(stage, a, b, d, kt, wave);
+        constexpr int n = 16 * Q + I;
+        if constexpr (n % kLoadEvery == 0 && n / kLoadEvery < 18) issue_tile_load<n / kLoadEvery>(load_stage, a, b, d, kt, wave);
+        // reads r[g] begin in step 3 + 4 g, one matrix instruction after a load; they must be out before step 7 + 4 g
+        constexpr int g = n >= 240 || n < 48 ? 3 : (n - 48) / 64, rel = (n < 48 ? n + 16 : n - 48 - 64 * g) - 1;
+        static_assert(1 + 7 * kReadEvery < 64 && 17 * kLoadEvery < 176 && 194 + 7 * kScaleEvery < 240, "before their waits");
+        if constexpr (rel >= 0 && rel % kReadEvery == 0 && rel / kReadEvery < 8) {
+            constexpr int i = rel / kReadEvery;
+            if constexpr ((g & 1) == 0) frag_read_one<i>(fe, r[g]);
+            else frag_read_one<i>(fo, r[g]);
+        }
+        constexpr int s = n - 194;   // (after the step that turns slice 3's scale bytes into numbers)
+        if constexpr (s >= 0 && s % kScaleEvery == 0 && s / kScaleEvery < 8) scale_read_one<s / kScaleEvery>(ts, fa, nxt_off);
     }
 };
 
@@ -511,15 +557,17 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
         fa.a = lds0 + kOff4A + (wm * 128 + li) * 128;
         fa.b = lds0 + kOff4B + (wn * 128 + li) * 128;
-        fa.sa = lds0 + kOff4As + (wm * 128 + li) * 16 + 2 * kb;
-        fa.sb = lds0 + kOff4Bs + (wn * 128 + li) * 16 + 2 * kb;
+        fa.sa = lds0 + kOff4As + (wm * 128 + li) * 16;
+        fa.sb = lds0 + kOff4Bs + (wn * 128 + li) * 16;
 #pragma unroll
         for (int j = 0; j < 4; ++j) fa.xo[j] = (uint32_t)(((2 * j + kb) ^ (li & 7)) * 16);
+        fa.sel = kb ? kScalesHigh : kScalesLow;
     }
 
     const TileSource src_a = tile_source(a_codes, a_tiled, m0, M, K), src_b = tile_source(b_codes, b_tiled, n0, N, K);
     const std::make_integer_sequence<int, 18> all_loads;
-    const std::make_integer_sequence<int, 16> all_reads;
+    const std::make_integer_sequence<int, 8> all_reads;
+    const std::make_integer_sequence<int, (14 / kReadEvery + 1 < 8 ? 14 / kReadEvery + 1 : 8)> first_reads;   // those of step 15
     issue_tile_loads(all_loads, smem, src_a, src_b, kt0, wave);
     // in the shadow of these loads: the tensor scales (not when the epilogue needs them) and the accumulators' zeros (the
     // compiler would put their 256 writes behind the barrier, 0.5 us of a tile)
@@ -539,8 +587,8 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     // Pipeline over K, in steps of 16 columns of K per lane half (4 steps = one 64-wide slice,
     // 4 slices = one tile).  While step n multiplies, the fragments of step n+1 are dequantized;
     // the raw fragments of slice g live in fe (g even) or fo (g odd) and are re-filled with
-    // slice g+2 at the start of step (g, 3), once the last conversion of slice g is done, a
-    // full slice ahead of their first use.  The hand-over between the two LDS stages sits at
+    // slice g+2 from step (g, 3) on, once the last conversion of slice g is done; the scale bytes of the next tile are
+    // read once slice 3's are numbers.  The hand-over between the two LDS stages sits at
     // step (2, 3) of a tile: this wave's last read of the current stage (slice 3) has landed,
     // so after the barrier tile kt+1, whose loads went out in slice 0 of this tile, is complete in the other
     // stage and the current stage can take tile kt+2.  (Loads in slice 0, not a slice earlier behind the barrier: two
@@ -548,50 +596,50 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     // 4096 x 4096 x 512 20.35 -> 20.09 us, 4096 x 4096 x 1024 31.05 -> 30.78, 8192 x 8192 x 512 72.2 -> 71.3, 2816 x 2048 x
     // 16384 162.9 -> 162.1, one box in turn.)
     RawFrag4 fe, fo;
+    TileScales ts;
+    SliceScales ss;
     Frags x, y;
-    frag_read_issue<0>(all_reads, fe, read_addr<0>(fa, 0));
-    frag_read_issue<1>(all_reads, fo, read_addr<1>(fa, 0));
-    frag_read_wait(fe);   // (waits for both)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        fe.sa[t] = scale_halves(fe.sa[t]);
-        fe.sb[t] = scale_halves(fe.sb[t]);
-        dequant_half<0, 0>(x.a[t], fe.a[t][0], fe.sa[t]);
-        dequant_half<1, 0>(x.a[t], fe.a[t][0], fe.sa[t]);
-        dequant_half<0, 0>(x.b[t], fe.b[t][0], fe.sb[t]);
-        dequant_half<1, 0>(x.b[t], fe.b[t][0], fe.sb[t]);
-    }
+    frag_read_issue(all_reads, fe, read_addr<0>(fa, 0));
+    scale_read_issue(all_reads, ts, fa, 0);
+    frag_read_wait(fe, ts);
+    dequant_all<0>(std::make_integer_sequence<int, 16>(), x, fe, ts, ss, fa.sel);
+    frag_read_issue(first_reads, fo, read_addr<1>(fa, 0));
     for (int kt = 0; kt < ktiles; ++kt) {
         const uint32_t cur_off = (kt & 1) * kStage4Bytes, nxt_off = ((kt + 1) & 1) * kStage4Bytes;
-        const NoSide none;
         const TileDescriptors d = descriptors(src_a, src_b, kt + 1 < ktiles);
+        uint8_t *const load_stage = smem + nxt_off;
+        const int ld = kt0 + kt + 1;
+        const ReadAddr r1 = read_addr<1>(fa, cur_off), r2 = read_addr<2>(fa, cur_off), r3 = read_addr<3>(fa, cur_off), n0r = read_addr<0>(fa, nxt_off), n1r = read_addr<1>(fa, nxt_off);
+#define QII_STEP(Q, D, J, CU, NX, F, R3) \
+        mma_step<D, J>(acc, CU, NX, F, ts, ss, fa.sel, TileSide<Q>{load_stage, src_a, src_b, d, ld, wave, fe, fo, ts, fa, nxt_off, {r2, r3, n0r, R3}})
         // slice 0 (raw: fe)
-        mma_step<1>(acc, x, y, fe, LoadSide<0>{smem + nxt_off, src_a, src_b, d, kt0 + kt + 1, wave});
-        mma_step<2>(acc, y, x, fe, LoadSide<16>{smem + nxt_off, src_a, src_b, d, kt0 + kt + 1, wave});
-        mma_step<3>(acc, x, y, fe, none);
+        QII_STEP(0, 1, 0, x, y, fe, r1);
+        QII_STEP(1, 2, 0, y, x, fe, r1);
+        QII_STEP(2, 3, 0, x, y, fe, r1);
         frag_read_wait(fo);
-        mma_step<0>(acc, y, x, fo, ReadSide<2>{fe, read_addr<2>(fa, cur_off)});
+        QII_STEP(3, 0, 1, y, x, fo, n1r);
         // slice 1 (raw: fo)
-        mma_step<1>(acc, x, y, fo, none);
-        mma_step<2>(acc, y, x, fo, none);
-        mma_step<3>(acc, x, y, fo, none);
+        QII_STEP(4, 1, 1, x, y, fo, n1r);
+        QII_STEP(5, 2, 1, y, x, fo, n1r);
+        QII_STEP(6, 3, 1, x, y, fo, n1r);
         frag_read_wait(fe);
-        mma_step<0>(acc, y, x, fe, ReadSide<3>{fo, read_addr<3>(fa, cur_off)});
+        QII_STEP(7, 0, 2, y, x, fe, n1r);
         // slice 2 (raw: fe)
-        mma_step<1>(acc, x, y, fe, none);
-        mma_step<2>(acc, y, x, fe, none);
-        mma_step<3>(acc, x, y, fe, none);
+        QII_STEP(8, 1, 2, x, y, fe, n1r);
+        QII_STEP(9, 2, 2, y, x, fe, n1r);
+        QII_STEP(10, 3, 2, x, y, fe, n1r);
         frag_read_wait(fo);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        // (after the last tile the reads of slices 0 and 1 fetch a stale stage; the values are never used)
-        mma_step<0>(acc, y, x, fo, ReadSide<0>{fe, read_addr<0>(fa, nxt_off)});
+        // (after the last tile the reads fetch a stale stage; the values are never used)
+        QII_STEP(11, 0, 3, y, x, fo, n1r);
         // slice 3 (raw: fo)
-        mma_step<1>(acc, x, y, fo, none);
-        mma_step<2>(acc, y, x, fo, none);
-        mma_step<3>(acc, x, y, fo, none);
-        frag_read_wait(fe);
-        mma_step<0>(acc, y, x, fe, ReadSide<1>{fo, read_addr<1>(fa, nxt_off)});
+        QII_STEP(12, 1, 3, x, y, fo, n1r);
+        QII_STEP(13, 2, 3, y, x, fo, n1r);
+        QII_STEP(14, 3, 3, x, y, fo, n1r);
+        frag_read_wait(fe, ts);
+        QII_STEP(15, 0, 0, y, x, fe, n1r);
+#undef QII_STEP
     }
     // the last read block is still in flight: its registers and the stages are reused below
     frag_read_wait(fo);

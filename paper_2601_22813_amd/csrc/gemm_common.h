@@ -56,9 +56,10 @@ __device__ __forceinline__ void emit_tile_max(float cmax, uint32_t *amax_out)
 // The two scale bytes of a lane's 32 elements of K, as two f16 numbers in one register: byte b in
 // f16 position (b << 7) is e4m3 * 2^-8, subnormals included.  v_perm_b32 spreads the bytes to the
 // two halves, one shift moves them to f16 position.
-__device__ __forceinline__ uint32_t scale_halves(uint32_t two_bytes)
+constexpr uint32_t kScalesLow = 0x0C010C00u, kScalesHigh = 0x0C030C02u;   // of the two in the low or the high half of a word
+__device__ __forceinline__ uint32_t scale_halves(uint32_t bytes, uint32_t selector = kScalesLow)
 {
-    return __builtin_amdgcn_perm(0u, two_bytes, 0x0C010C00u) << 7;
+    return __builtin_amdgcn_perm(0u, bytes, selector) << 7;
 }
 
 // half of one fragment (4 of its 8 values): two conversions and two packed multiplies by the f16
