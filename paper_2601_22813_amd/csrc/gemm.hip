@@ -269,21 +269,28 @@ __global__ void retile_scales_kernel(const uint8_t *__restrict__ a_scales, uint8
 struct TileSource {
     uint8_t *codes_base, *scales_base;
     int codes_bytes, scales_bytes;
-    uint32_t voff, row32;   // row32: bytes of 32 rows
 };
+
+// what a lane adds to them: the offset of its piece in row t / 8, the bytes of 32 rows, the offset of its row's scale bytes
+struct LaneOffsets {
+    uint32_t voff, row32, scales;
+};
+
+__device__ __forceinline__ LaneOffsets lane_offsets(int64_t K, int t)
+{
+    const int64_t pitch = K / 2;
+    // the piece is chosen so that the LDS image is swizzled (rows of a thread differ by multiples of 32)
+    return LaneOffsets{(uint32_t)((t >> 3) * pitch) + 16u * (uint32_t)((t & 7) ^ ((t >> 3) & 7)), (uint32_t)(32 * pitch), (uint32_t)t * 16u};
+}
 
 __device__ __forceinline__ TileSource tile_source(const uint8_t *codes, const uint8_t *tiled, int64_t row0, int64_t rows_total, int64_t K)
 {
     const int64_t left = rows_total - row0, rows = left < BM ? left : BM, pitch = K / 2;
-    const int t = threadIdx.x;
     TileSource o;
     o.codes_base = const_cast<uint8_t *>(codes) + row0 * pitch;
     o.scales_base = const_cast<uint8_t *>(tiled) + (row0 >> 8) * (K * 16);
     o.codes_bytes = (int)(rows * pitch);
     o.scales_bytes = (int)(K * 16);
-    // the piece is chosen so that the LDS image is swizzled (rows of a thread differ by multiples of 32)
-    o.voff = (uint32_t)((t >> 3) * pitch) + 16u * (uint32_t)((t & 7) ^ ((t >> 3) & 7));
-    o.row32 = (uint32_t)(32 * pitch);
     return o;
 }
 
@@ -302,25 +309,23 @@ __device__ __forceinline__ TileDescriptors descriptors(const TileSource &a, cons
 // load I of the 18 that a thread issues per K tile: 8 code pieces of A, 8 of B, the scales of A and of B.  (The row
 // part sits in the vector offset, which the descriptor's bounds check covers; the scalar offset stays inside a row.)
 template <int I>
-__device__ __forceinline__ void issue_tile_load(uint8_t *stage, const TileSource &a, const TileSource &b, const TileDescriptors &d, int kt, int wave)
+__device__ __forceinline__ void issue_tile_load(uint8_t *stage, const LaneOffsets &l, const TileDescriptors &d, int kt, int wave)
 {
     typedef __attribute__((address_space(3))) void *lds_ptr;
     if constexpr (I < 16) {
         constexpr int p = I & 7;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(I < 8 ? d.ac : d.bc, (lds_ptr)(stage + (I < 8 ? kOff4A : kOff4B) + (p * 256 + wave * 64) * 16), 16,
-                                                 I < 8 ? a.voff + p * a.row32 : b.voff + p * b.row32, kt * (BK4 / 2), 0, 0);
+                                                 l.voff + p * l.row32, kt * (BK4 / 2), 0, 0);
     } else {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(I == 16 ? d.as : d.bs, (lds_ptr)(stage + (I == 16 ? kOff4As : kOff4Bs) + (wave * 64) * 16), 16,
-                                                 threadIdx.x * 16u, kt * 4096, 0, 0);
+                                                 l.scales, kt * 4096, 0, 0);
     }
 }
 
 template <int... I>
-__device__ __forceinline__ void issue_tile_loads(std::integer_sequence<int, I...>, uint8_t *stage, const TileSource &a, const TileSource &b,
-                                                 int kt, int wave)
+__device__ __forceinline__ void issue_tile_loads(std::integer_sequence<int, I...>, uint8_t *stage, const LaneOffsets &l, const TileDescriptors &d, int kt, int wave)
 {
-    const TileDescriptors d = descriptors(a, b, true);
-    (issue_tile_load<I>(stage, a, b, d, kt, wave), ...);
+    (issue_tile_load<I>(stage, l, d, kt, wave), ...);
 }
 
 // ---- fragment pipeline of the main kernel -------------------------------------------------
@@ -349,6 +354,30 @@ struct FragAddr {
     uint32_t xo[4];         // swizzled 16-byte slot of K slice j, times 16
     uint32_t sel;           // selector of this lane's two bytes among a slice's four
 };
+
+__device__ __forceinline__ uint32_t lds_address(uint8_t *smem) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem; }
+
+__device__ __forceinline__ FragAddr frag_addr(uint8_t *smem, int wm, int wn, int li, int kb)
+{
+    FragAddr fa;
+    const uint32_t lds0 = lds_address(smem);
+    fa.a = lds0 + kOff4A + (wm * 128 + li) * 128;
+    fa.b = lds0 + kOff4B + (wn * 128 + li) * 128;
+    fa.sa = lds0 + kOff4As + (wm * 128 + li) * 16;
+    fa.sb = lds0 + kOff4Bs + (wn * 128 + li) * 16;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fa.xo[j] = (uint32_t)(((2 * j + kb) ^ (li & 7)) * 16);
+    fa.sel = kb ? kScalesHigh : kScalesLow;
+    return fa;
+}
+
+// s_barrier alone: every wait that it needs is written out (a fence may wait for stores as well)
+__device__ __forceinline__ void block_barrier()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
 // LDS addresses of one slice's reads
 struct ReadAddr {
@@ -439,13 +468,14 @@ __device__ __forceinline__ void dequant_all(std::integer_sequence<int, I...>, Fr
 // the issue of the memory operations run in the shadow of the matrix pipe.  (A K tile's 18 loads, with their
 // address arithmetic, and 64 LDS reads used to be issued in blocks between the steps, with the matrix pipe idle:
 // 16384 x 2048 x 8192 441 -> 412 us, 32768 x 16384 x 2048 1820 -> 1743, 8192^3 827 -> 797 on one box.)
-template <int D, int J, class Side>
+// kNew: the tile's first step, which begins the sums.
+template <int D, int J, bool kNew = false, class Side>
 __device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, const RawFrag4 &f, const TileScales &ts, SliceScales &ss,
                                          uint32_t sel, const Side &side)
 {
 #define QII_MMA(I)                                                                                          \
     acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[(I) & 3], cu.a[(I) >> 2],          \
-                                                                    acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
+                                                                    kNew ? floatx16{} : acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
     side.template at<I>();                                                                                  \
     dequant_chunk<I, D, J>(nx, f, ts, ss, sel);                                                             \
     __builtin_amdgcn_sched_barrier(0)
@@ -460,11 +490,11 @@ __device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu,
 // tile -> 3 and 4, 40 reads: 16384 x 8192 x 2048 400.6 -> 385.4 us, 8192^3 734 -> 714; loads every 2, 4, 6, 8: 387, 388, 387, 389 and 715 to 716.)
 constexpr int kLoadEvery = 3, kReadEvery = 4, kScaleEvery = 4;
 
-// step Q (0..15) of a tile: the next tile's loads, and the reads of the slice whose registers are free
-template <int Q>
+// step Q (0..15) of a tile: a later tile's loads from matrix instruction kLoadFrom on, and the reads of the slice whose registers are free
+template <int Q, int kLoadFrom>
 struct TileSide {
     uint8_t *load_stage;
-    const TileSource &a, &b;
+    const LaneOffsets &lanes;
     const TileDescriptors &d;
     int kt, wave;
     RawFrag4 &fe, &fo;
@@ -476,10 +506,11 @@ struct TileSide {
     __device__ __forceinline__ void at() const
     {
         constexpr int n = 16 * Q + I;
-        if constexpr (n % kLoadEvery == 0 && n / kLoadEvery < 18) issue_tile_load<n / kLoadEvery>(load_stage, a, b, d, kt, wave);
+        constexpr int l = n - kLoadFrom;
+        if constexpr (l >= 0 && l % kLoadEvery == 0 && l / kLoadEvery < 18) issue_tile_load<l / kLoadEvery>(load_stage, lanes, d, kt, wave);
         // reads r[g] begin in step 3 + 4 g, one matrix instruction after a load; they must be out before step 7 + 4 g
         constexpr int g = n >= 240 || n < 48 ? 3 : (n - 48) / 64, rel = (n < 48 ? n + 16 : n - 48 - 64 * g) - 1;
-        static_assert(1 + 7 * kReadEvery < 64 && 17 * kLoadEvery < 176 && 194 + 7 * kScaleEvery < 240, "before their waits");
+        static_assert(1 + 7 * kReadEvery < 64 && 17 * kLoadEvery < 80 && 194 + 7 * kScaleEvery < 240, "before their waits");
         if constexpr (rel >= 0 && rel % kReadEvery == 0 && rel / kReadEvery < 8) {
             constexpr int i = rel / kReadEvery;
             if constexpr ((g & 1) == 0) frag_read_one<i>(fe, r[g]);
@@ -552,23 +583,13 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    FragAddr fa;
-    {
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
-        fa.a = lds0 + kOff4A + (wm * 128 + li) * 128;
-        fa.b = lds0 + kOff4B + (wn * 128 + li) * 128;
-        fa.sa = lds0 + kOff4As + (wm * 128 + li) * 16;
-        fa.sb = lds0 + kOff4Bs + (wn * 128 + li) * 16;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) fa.xo[j] = (uint32_t)(((2 * j + kb) ^ (li & 7)) * 16);
-        fa.sel = kb ? kScalesHigh : kScalesLow;
-    }
-
+    const FragAddr fa = frag_addr(smem, wm, wn, li, kb);
     const TileSource src_a = tile_source(a_codes, a_tiled, m0, M, K), src_b = tile_source(b_codes, b_tiled, n0, N, K);
     const std::make_integer_sequence<int, 18> all_loads;
     const std::make_integer_sequence<int, 8> all_reads;
     const std::make_integer_sequence<int, (14 / kReadEvery + 1 < 8 ? 14 / kReadEvery + 1 : 8)> first_reads;   // those of step 15
-    issue_tile_loads(all_loads, smem, src_a, src_b, kt0, wave);
+    const LaneOffsets lanes = lane_offsets(K, threadIdx.x);
+    issue_tile_loads(all_loads, smem, lanes, descriptors(src_a, src_b, true), kt0, wave);
     // in the shadow of these loads: the tensor scales (not when the epilogue needs them) and the accumulators' zeros (the
     // compiler would put their 256 writes behind the barrier, 0.5 us of a tile)
     __builtin_amdgcn_sched_barrier(0);
@@ -611,7 +632,7 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
         const int ld = kt0 + kt + 1;
         const ReadAddr r1 = read_addr<1>(fa, cur_off), r2 = read_addr<2>(fa, cur_off), r3 = read_addr<3>(fa, cur_off), n0r = read_addr<0>(fa, nxt_off), n1r = read_addr<1>(fa, nxt_off);
 #define QII_STEP(Q, D, J, CU, NX, F, R3) \
-        mma_step<D, J>(acc, CU, NX, F, ts, ss, fa.sel, TileSide<Q>{load_stage, src_a, src_b, d, ld, wave, fe, fo, ts, fa, nxt_off, {r2, r3, n0r, R3}})
+        mma_step<D, J>(acc, CU, NX, F, ts, ss, fa.sel, TileSide<Q, 0>{load_stage, lanes, d, ld, wave, fe, fo, ts, fa, nxt_off, {r2, r3, n0r, R3}})
         // slice 0 (raw: fe)
         QII_STEP(0, 1, 0, x, y, fe, r1);
         QII_STEP(1, 2, 0, y, x, fe, r1);
@@ -653,6 +674,257 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     u += ktiles;
     if (u >= u_end) break;
     __syncthreads();   // every wave is done with its staging tile before the next segment's loads land in LDS
+    }
+}
+
+// The epilogue of a block that goes on to another tile: both LDS stages stay with the loads of the K tiles to come, so a wave's
+// 128 x 128 entries pass through 4 KiB of their own, 128 bytes of 32 rows at a time (64 columns of bf16, 32 of f32), and leave as
+// whole 128-byte lines.  While a round's reads are under way the next round's entries are converted.  LDS operations of a wave run in
+// order, so its writes need no wait for the reads before them; they are inline assembly like the fragment reads, because the compiler
+// would let them wait for the loads.  16-byte piece s of row r is at slot s ^ (r % 8): neither side has bank conflicts.
+// What lies beyond C is dropped by the descriptor.  (Straight from the accumulators, 32 bytes of a row at a time: 2.2 us longer for a tile, and with non-temporal stores 17 to 46.)
+// maximum over a wave by lane exchanges that need no lane number (one more register kept through the loop)
+__device__ __forceinline__ float wave_max_in_registers(float m)
+{
+    m = fmaxf(m, dpp_f<kDppXor1>(m));
+    m = fmaxf(m, dpp_f<kDppXor2>(m));
+    m = fmaxf(m, dpp_f<kDppHalfMirror>(m));
+    m = fmaxf(m, dpp_f<kDppRor8>(m));
+    const auto x = __builtin_amdgcn_permlane16_swap(f2u(m), f2u(m), false, false);
+    m = fmaxf(u2f(x[0]), u2f(x[1]));
+    const auto y = __builtin_amdgcn_permlane32_swap(f2u(m), f2u(m), false, false);
+    return fmaxf(u2f(y[0]), u2f(y[1]));
+}
+
+constexpr int kStoreArea = 4096;   // LDS bytes per wave
+
+template <bool kBf16Out, bool kMax>
+__device__ __forceinline__ void store_rounds(const floatx16 (&acc)[4][4], float ts, __amdgpu_buffer_rsrc_t out, uint32_t rb, int live_cols, int lane,
+                                             uint32_t area, float &cmax)
+{
+    constexpr int esz = kBf16Out ? 2 : 4, kParts = kBf16Out ? 2 : 4, kRounds = 4 * kParts, kCols = 128 / esz, kTiles = kCols / 32;
+    const int li = lane & 31, kb = lane >> 5, row = lane >> 3, piece = lane & 7;
+    const uint32_t put = area + (uint32_t)(li * 128 + (kBf16Out ? (li & 7) * 16 + 8 * kb : ((li & 7) ^ kb) * 16)), get = area + (uint32_t)(row * 128 + ((piece ^ row) * 16));
+    uint32_t voff = (uint32_t)row * rb + (uint32_t)piece * 16u;
+    u32x4 v[4];
+    uint32_t w[16];   // a round's entries: 16 of f32, 32 of bf16
+#pragma unroll
+    for (int r = 0; r <= kRounds; ++r) {
+        if (r < kRounds) {
+#pragma unroll
+            for (int t = 0; t < kTiles; ++t) {
+                const floatx16 &a = acc[r / kParts][(r % kParts) * kTiles + t];
+                float e[16];
+#pragma unroll
+                for (int k = 0; k < 16; ++k) e[k] = a[k] * ts;
+                if (kMax)
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) cmax = fmaxf(cmax, fabsf(e[k]));
+                if (kBf16Out) {
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) w[8 * t + k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(float2_t{e[2 * k], e[2 * k + 1]}, bf16x2_t));
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) w[k] = f2u(e[k]);
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (r > 0) {   // round r - 1 has come back
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+            const int col = ((r - 1) % kParts) * kCols;
+            const bool on = col + (piece + 1) * (16 / esz) <= live_cols;
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                __builtin_amdgcn_raw_buffer_store_b128(v[p], out, on ? voff + (uint32_t)(8 * p) * rb + (uint32_t)(col * esz) : 0x80000000u, 0, 2 /* nt */);
+            if ((r - 1) % kParts == kParts - 1) voff += 32u * rb;
+        }
+        if (r < kRounds) {
+            if (kBf16Out) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k)   // slot 4 t + q
+                    asm volatile("ds_write_b64 %0, %1" ::"v"(put ^ (uint32_t)(16 * k)), "v"(u32x2{w[2 * k], w[2 * k + 1]}));
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)   // slot 2 q + kb
+                    asm volatile("ds_write_b128 %0, %1" ::"v"(put ^ (uint32_t)(32 * k)), "v"(u32x4{w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]}));
+            }
+            asm volatile("ds_read_b128 %0, %1" : "=v"(v[0]) : "v"(get));
+            asm volatile("ds_read_b128 %0, %1 offset:1024" : "=v"(v[1]) : "v"(get));
+            asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(v[2]) : "v"(get));
+            asm volatile("ds_read_b128 %0, %1 offset:3072" : "=v"(v[3]) : "v"(get));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+__device__ __forceinline__ void zero_tile(floatx16 (&acc)[4][4])
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            uint32_t w = 0u;
+            asm volatile("" : "+v"(w));   // (or all sixteen are one, copied)
+            const half8_t z = __builtin_bit_cast(half8_t, u32x4{w, w, w, w});
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(z, z, floatx16{}, 0, 0, 0);
+        }
+}
+
+// whether a block may take several tiles: three rounds of them (with two, forward 16384 x 2048 -> 2048 128.6 : 128.2 us, but backward with f32
+// gradients 315 to 320 : 319 to 327), C's rows on 128-byte lines and made of whole 16-byte pieces (a round of
+// the epilogue that covers two lines in part writes both to memory twice: 8448 x 4104 x 512 bf16 62.8 us instead of 46), a wave's tile within
+// 32-bit offsets
+static bool blocks_take_tiles(int64_t tiles, const void *C, int64_t ldc, int64_t N, int c_is_bf16)
+{
+    const int64_t esz = c_is_bf16 ? 2 : 4;
+    return tiles >= 768 && ((reinterpret_cast<uintptr_t>(C) | (uintptr_t)(ldc * esz)) & 127) == 0 && N * esz % 16 == 0 && ldc * esz < (1 << 24);
+}
+
+// The main kernel where blocks_take_tiles: a block takes the tiles at launch
+// positions blockIdx.x, + gridDim.x, ..., and their K tiles are one sequence to its pipeline.  The loads of the K tile after the
+// next go out behind the barrier that frees their stage, whichever tile it belongs to, so that a tile begins with its first fragments
+// in registers; what is left between two tiles is the epilogue, without its stores' time.  us, a block per tile : this: bf16 32768 x
+// 16384 x 2048 1499 : 1460, 16384 x 8192 x 2048 385 : 374, 16384 x 8192 x 512 138 : 127, f32 16384 x 8192 x 1024 258 : 238, 16384 x
+// 8192 x 256 123 : 123; long K hides the ends of a tile anyway (8192^3 684 : 685); with one round there is nothing to go on to, and
+// the second K tile's loads come first: 4096 x 4096 x 512 19.7 : 20.5.
+template <bool kBf16Out, bool kMax>
+__global__ __launch_bounds__(256, 1) void gemm_kernel_tiles(const uint8_t *__restrict__ a_codes, const uint8_t *__restrict__ a_tiled,
+                                                            const float *__restrict__ a_ts, const uint8_t *__restrict__ b_codes,
+                                                            const uint8_t *__restrict__ b_tiled, const float *__restrict__ b_ts, int64_t M,
+                                                            int64_t N, int64_t K, void *__restrict__ Cout, int64_t ldc, int tiles_m,
+                                                            int tiles_n, int count, uint32_t *amax_out)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    const int li = lane & 31, kb = lane >> 5;
+    FragAddr fa = frag_addr(smem, wm, wn, li, kb);
+    const int ktiles = (int)(K / BK4);
+
+    // what the next loads take: K tile next_kt of the tile at next_pos (nothing behind the block's last tile)
+    int pos = (int)blockIdx.x, next_pos = pos, next_kt = 0;
+    LaneOffsets lanes = lane_offsets(K, threadIdx.x);
+    TileDescriptors d;
+    auto aim = [&]() {
+        const bool on = next_pos < count;
+        int64_t m0, n0;
+        tile_origin(on ? next_pos : pos, tiles_m, tiles_n, m0, n0);
+        d = descriptors(tile_source(a_codes, a_tiled, m0, M, K), tile_source(b_codes, b_tiled, n0, N, K), on);
+    };
+    auto advance = [&]() {
+        if (++next_kt == ktiles) {
+            next_kt = 0;
+            next_pos += (int)gridDim.x;
+            aim();
+        }
+    };
+    const std::make_integer_sequence<int, 18> all_loads;
+    const std::make_integer_sequence<int, 8> all_reads;
+    const std::make_integer_sequence<int, (14 / kReadEvery + 1 < 8 ? 14 / kReadEvery + 1 : 8)> first_reads;   // those of step 15
+    aim();
+    issue_tile_loads(all_loads, smem, lanes, d, 0, wave);
+    advance();
+    issue_tile_loads(all_loads, smem + kStage4Bytes, lanes, d, next_kt, wave);
+    advance();
+    __builtin_amdgcn_sched_barrier(0);
+    const float ts = u2f((uint32_t)__builtin_amdgcn_readfirstlane((int)f2u((*a_ts) * (*b_ts))));
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
+    block_barrier();
+
+    floatx16 acc[4][4];
+    RawFrag4 fe, fo;
+    TileScales sc;
+    SliceScales ss;
+    Frags x, y;
+    frag_read_issue(all_reads, fe, read_addr<0>(fa, 0));
+    scale_read_issue(all_reads, sc, fa, 0);
+    frag_read_wait(fe, sc);
+    dequant_all<0>(std::make_integer_sequence<int, 16>(), x, fe, sc, ss, fa.sel);
+    frag_read_issue(first_reads, fo, read_addr<1>(fa, 0));
+    uint32_t cmax = 0u;     // (uniform: the wave's largest |entry|; non-negative numbers order like their bits)
+    uint32_t cur_off = 0;
+    for (;;) {
+        int kt = 0;
+        zero_tile(acc);
+        for (;;) {
+            const uint32_t nxt_off = kStage4Bytes - cur_off;
+            uint8_t *const load_stage = smem + cur_off;
+            const ReadAddr r1 = read_addr<1>(fa, cur_off), r2 = read_addr<2>(fa, cur_off), r3 = read_addr<3>(fa, cur_off), n0r = read_addr<0>(fa, nxt_off), n1r = read_addr<1>(fa, nxt_off);
+#define QII_SIDE(Q, R3) TileSide<Q, 176>{load_stage, lanes, d, next_kt, wave, fe, fo, sc, fa, nxt_off, {r2, r3, n0r, R3}}
+#define QII_STEP(Q, D, J, CU, NX, F, R3) mma_step<D, J>(acc, CU, NX, F, sc, ss, fa.sel, QII_SIDE(Q, R3))
+            // slice 0 (raw: fe)
+            QII_STEP(0, 1, 0, x, y, fe, r1);
+            QII_STEP(1, 2, 0, y, x, fe, r1);
+            QII_STEP(2, 3, 0, x, y, fe, r1);
+            frag_read_wait(fo);
+            QII_STEP(3, 0, 1, y, x, fo, n1r);
+            // slice 1 (raw: fo)
+            QII_STEP(4, 1, 1, x, y, fo, n1r);
+            QII_STEP(5, 2, 1, y, x, fo, n1r);
+            QII_STEP(6, 3, 1, x, y, fo, n1r);
+            frag_read_wait(fe);
+            QII_STEP(7, 0, 2, y, x, fe, n1r);
+            // slice 2 (raw: fe)
+            QII_STEP(8, 1, 2, x, y, fe, n1r);
+            QII_STEP(9, 2, 2, y, x, fe, n1r);
+            QII_STEP(10, 3, 2, x, y, fe, n1r);
+            frag_read_wait(fo);
+            // the next K tile has landed.  (This waits for a finished tile's stores too; a count that leaves them out is 1 % slower.)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            block_barrier();
+            QII_STEP(11, 0, 3, y, x, fo, n1r);
+            // slice 3 (raw: fo)
+            QII_STEP(12, 1, 3, x, y, fo, n1r);
+            QII_STEP(13, 2, 3, y, x, fo, n1r);
+            QII_STEP(14, 3, 3, x, y, fo, n1r);
+            frag_read_wait(fe, sc);
+            QII_STEP(15, 0, 0, y, x, fe, n1r);
+#undef QII_STEP
+#undef QII_SIDE
+            advance();
+            cur_off = nxt_off;
+            if (++kt == ktiles) break;
+        }
+        frag_read_wait(fo);   // (no read is in flight while the epilogue needs registers)
+        int64_t m0, n0;
+        tile_origin(pos, tiles_m, tiles_n, m0, n0);
+        const int64_t row0 = m0 + wm * 128, col0 = n0 + wn * 128, rows = M - row0, cols = N - col0;
+        const int live_rows = rows < 128 ? (int)rows : 128, live_cols = cols < 128 ? (int)cols : 128;   // (may be negative)
+        constexpr int esz = kBf16Out ? 2 : 4;
+        const uint32_t rb = (uint32_t)ldc * esz;
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<uint8_t *>(Cout) + (row0 * ldc + col0) * esz, 0,
+            live_rows > 0 && live_cols > 0 ? (live_rows - 1) * (int)rb + live_cols * esz : 0, 0x00020000);
+        // (The thread's number is formed here, volatile, and the loop's offsets again behind the epilogue: kept, they take each other's
+        // registers, and a reload from scratch memory waits for the loads and stores before it.)
+        int t;
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(t));
+        float tile_max = 0.0f;
+        store_rounds<kBf16Out, kMax>(acc, ts, out, rb, live_cols, t, lds_address(smem) + 2 * kStage4Bytes + (uint32_t)wave * kStoreArea, tile_max);
+        if (kMax) {
+            const uint32_t bits = (uint32_t)__builtin_amdgcn_readfirstlane((int)f2u(wave_max_in_registers(tile_max)));
+            cmax = bits > cmax ? bits : cmax;
+        }
+        pos += (int)gridDim.x;
+        if (pos >= count) break;
+        lanes = lane_offsets(K, wave * 64 + t);
+        fa = frag_addr(smem, wm, wn, t & 31, t >> 5);
+        frag_read_issue(first_reads, fo, read_addr<1>(fa, cur_off));   // (again: its registers were the epilogue's)
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (no load is on its way to LDS when the block ends)
+    if (kMax) {
+        // rounding is monotone: the largest stored value is the rounded largest one
+        uint32_t *const waves = reinterpret_cast<uint32_t *>(smem);   // (every load has landed, every read is done)
+        block_barrier();
+        if (threadIdx.x % 64 == 0) waves[wave] = cmax;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const uint32_t a = waves[0] > waves[1] ? waves[0] : waves[1], b = waves[2] > waves[3] ? waves[2] : waves[3], m = a > b ? a : b;
+            max_to_global(u2f(kBf16Out ? f32_to_bf16_bits(u2f(m)) << 16 : m), amax_out);
+        }
     }
 }
 
@@ -829,7 +1101,18 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
     if (e != hipSuccess) return e;
     e = allow_dynamic_lds<gemm_kernel_v4<kBf16Out, true>>(kSmem4);
     if (e != hipSuccess) return e;
-    if (plan.full > 0)
+    if (blocks_take_tiles(plan.full, C, ldc, N, kBf16Out)) {
+        constexpr int kLds = kSmem4 + 4 * kStoreArea;   // all of a compute unit's 160 KiB
+        auto launch = [&](auto kernel, hipError_t ready) {
+            if (ready == hipSuccess)
+                hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.full < 256 ? plan.full : 256)), dim3(256), kLds, s, A.codes, a_tiled, A.tensor_scale,
+                                   B.codes, b_tiled, B.tensor_scale, M, N, K, C, ldc, tiles_m, tiles_n, plan.full, amax_out);
+            return ready;
+        };
+        e = amax_out ? launch(gemm_kernel_tiles<kBf16Out, true>, allow_dynamic_lds<gemm_kernel_tiles<kBf16Out, true>>(kLds))
+                     : launch(gemm_kernel_tiles<kBf16Out, false>, allow_dynamic_lds<gemm_kernel_tiles<kBf16Out, false>>(kLds));
+        if (e != hipSuccess) return e;
+    } else if (plan.full > 0)
         hipLaunchKernelGGL((gemm_kernel_v4<kBf16Out, false>), dim3((unsigned)plan.full), dim3(256), kSmem4, s, A.codes, a_tiled,
                            A.tensor_scale, B.codes, b_tiled, B.tensor_scale, M, N, K, C, ldc, tiles_m, tiles_n, amax_out, 0, 0,
                            partial);
@@ -883,8 +1166,11 @@ struct Prices {
     Route best;
 };
 
-// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run
-static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile)
+// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run.  Blocks that take several tiles: a round's bf16 stores leave beside
+// the next round's products, 3.3 us less a round than the plan has it (8192 x 6144 x 256 37.9 us, where 128 x 128 tiles take 42.3; 8192 x 8192
+// x 256 48.9 : 56.3, 16384 x 8192 x 256 84.5 : 111); f32 results take all of a round's figure at short K (memory: 16384 x 8192 x 256 118.8 us for
+// 537 MB).
+static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile, const void *C, int64_t ldc, int c_is_bf16)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
     const bool any = K % BK4 != 0;
@@ -901,20 +1187,24 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     const bool narrow = K <= kMaxNarrowK;
     Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide};
-    if (main_ws) p.us[kRouteMain] = plan_that_fits(M, N, K, main_ws).us + (retile ? 4.5 : 0.0);
-    else if (K % 128 == 0) p.us[kRouteNoWorkspace] = us_v2;
+    if (main_ws) {
+        const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
+        p.us[kRouteMain] = plan.us + (retile ? 4.5 : 0.0) - (c_is_bf16 && blocks_take_tiles(plan.full, C, ldc, N, 1) ? 3.3 * (double)(plan.full / 256) : 0.0);
+    }
+    if (!main_ws && K % 128 == 0) p.us[kRouteNoWorkspace] = us_v2;
     for (const Route r : {kRoute128, kRoute128Wide, kRouteMain, kRouteNoWorkspace})
         if (p.us[r] < p.us[p.best]) p.best = r;
     return p;
 }
 
-bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K)
+bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K, const void *C, int64_t ldc, int c_is_bf16)
 {
-    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 && price_routes(M, N, K, gemm_workspace_bytes(M, N, K), false).best == kRouteMain;
+    return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 &&
+           price_routes(M, N, K, gemm_workspace_bytes(M, N, K), false, C, ldc, c_is_bf16).best == kRouteMain;
 }
 
 // whether the main kernel can run, and the prices, for operands and a workspace as launch_gemm has them
-static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, size_t ws_bytes, int pretiled)
+static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, int64_t ldc, int c_is_bf16, const void *ws, size_t ws_bytes, int pretiled)
 {
     const int64_t M = A.rows, N = B.rows, K = A.cols;
     // (the re-tiling kernel reads the row-major scale bytes 16 at a time)
@@ -923,14 +1213,14 @@ static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *ws, 
     // (K: offsets within a tile's rows stay below 2^31)
     const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= scales_workspace_bytes(M, N, K) &&
                          (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
-    return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10));
+    return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10), C, ldc, c_is_bf16);
 }
 
 static Prices test_prices(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
 {
     const qii_nvfp4 a = {nullptr, nullptr, nullptr, M, K}, b = {nullptr, nullptr, nullptr, N, K};
-    // (a stand-in address: the route looks at its alignment)
-    return prices_of(a, b, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
+    // (stand-in addresses: the route looks at their alignment; bf16 results without gaps between the rows)
+    return prices_of(a, b, reinterpret_cast<const void *>(256), N, 1, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
 }
 
 int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
@@ -995,7 +1285,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
     }
     if (M == 0 || N == 0) return hipSuccess;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-    const Route route = prices_of(A, B, ws, ws_bytes, pretiled).best;
+    const Route route = prices_of(A, B, C, ldc, c_is_bf16, ws, ws_bytes, pretiled).best;
     uint8_t *a_ws = reinterpret_cast<uint8_t *>(ws);
     uint8_t *b_ws = a_ws + (M + 255) / 256 * 256 * (K / 16);
     if (route == kRouteMain) {
@@ -1037,7 +1327,7 @@ hipError_t launch_gemm2(const GemmCall c[2], int c_is_bf16, void *ws, size_t ws_
     bool can_share = (c[0].A->cols % BK4 != 0) == (c[1].A->cols % BK4 != 0);
     for (int i = 0; i < 2 && can_share; ++i) {
         if (c[i].A->rows == 0 || c[i].B->rows == 0 || (c[i].pretiled && c[i].A->cols % BK4 != 0)) { can_share = false; break; }
-        p[i] = prices_of(*c[i].A, *c[i].B, ws, ws_bytes, c[i].pretiled);
+        p[i] = prices_of(*c[i].A, *c[i].B, c[i].C, c[i].ldc, c_is_bf16, ws, ws_bytes, c[i].pretiled);
         two[i] = SmallGemm{c[i].A, c[i].B, (c[i].pretiled & 1) != 0, (c[i].pretiled & 2) != 0, c[i].C, c_is_bf16, c[i].ldc, nullptr};
     }
     const Route shared = can_share ? shared_route(p[0], p[1]) : kRouteMain;

@@ -16,6 +16,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 // Launch position -> tile coordinates.  XCD-aware order: consecutive block ids land on different XCDs (8
 // of them, each with its own L2), so every XCD gets a contiguous run of tiles; within the run, tiles are

@@ -164,7 +164,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
 
 // whether launch_gemm, given a workspace and tiled scale bytes, would run the main kernel: only then is
 // it worth a quantizer's while to write the tiled copy
-bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K);
+bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K, const void *C, int64_t ldc, int c_is_bf16);
 // products by the small-tile kernels (gemm_small.hip), one or two in one launch (with one result type, and K a
 // multiple of 256 in both or in neither): any K; each operand's scale bytes row-major or, K a multiple of 256, tiled
 enum SmallTile { kTile64, kTile128, kTile128Wide };

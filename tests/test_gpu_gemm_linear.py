@@ -367,3 +367,43 @@ def test_forward_pass_hands_its_abs_max_to_the_next_layer(oracle):
         assert_nv_equal(Wq2, oWq2, f"second layer's saved weight, mode {mode}")
         ref, absum = oracle.gemm(oXq2, oWq2, with_abs=True)
         check(bf16_to_f64(Y2), ref, absum, True)
+
+
+@pytest.mark.parametrize("M,N,K", [(12288, 4096, 256), (12288, 4096, 512), (12200, 4032, 512), (12800, 4064, 1280)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_gemm_blocks_that_take_several_tiles(M, N, K, dtype):
+    """Three rounds of 256 x 256 tiles and a little more, whole and cut by M and N, one, two and five K tiles: against the products of the
+    dequantized operands in binary64; the same bits as the kernel with a block per tile, which takes C with unaligned rows (the sums
+    run in the same order; K = 256 takes another kernel there), nothing beyond N, and the emitted maximum is that of the
+    stored values."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    a, b = (qii.NVFP4Tensor.empty(r, K) for r in (M, N))
+    f64 = []
+    for t in (a, b):
+        qii.qii_quantize_nvfp4(torch.randn((t.rows, K), device="cuda", generator=g), False, qii.RTN, 0, 0, 0, None, t, ws(256))
+        d = torch.empty((t.rows, K), device="cuda")
+        qii.qii_dequantize_nvfp4(t, d)
+        f64.append(d.double())
+    w = ws(qii.qii_gemm_workspace_bytes(M, N, K))
+    assert qii.lib().qii_gemm_route(M, N, K, w.numel(), 0) == 0
+    line = 64 if dtype == torch.bfloat16 else 32
+    ld = (N + line) // line * line
+    odd, whole = (torch.full((M, n), -3.0, dtype=dtype, device="cuda") for n in (N + 1, ld))
+    top = torch.zeros(1, device="cuda")
+    qii.qii_gemm_nvfp4(a, b, odd, w)
+    whole_only = None
+    for _ in range(3):
+        whole.fill_(-3.0)
+        qii.qii_gemm_nvfp4_amax(a, b, whole, top, w)
+        torch.cuda.synchronize()
+        assert K == 256 or torch.equal(whole[:, :N], odd[:, :N])
+        assert bool((whole[:, N:] == -3.0).all())
+        assert top.item() == whole[:, :N].float().abs().max().item()
+        assert whole_only is None or torch.equal(whole, whole_only)
+        whole_only = whole.clone()
+    whole.fill_(-3.0)
+    qii.qii_gemm_nvfp4(a, b, whole, w)
+    assert torch.equal(whole, whole_only)
+    ref, absum = f64[0] @ f64[1].t(), f64[0].abs() @ f64[1].abs().t()
+    tol = 1e-5 * absum + (2.0 ** -8 * ref.abs() if dtype == torch.bfloat16 else 0.0)   # (as `check`)
+    assert bool(((whole[:, :N].double() - ref).abs() <= tol).all())
