@@ -138,18 +138,25 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
             if (kMode == QII_MS_EDEN_PH) {
                 float gmax;
                 const float tt = posthoc_group16(v, packed, gmax);
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kMayTile ? 0 : 2 /* nt */);
                 a.r.tbuf[(row0 + r) * G + col0 / 16 + L.blk] = tt;
                 m_r = fmaxf(m_r, gmax);
                 continue;
             }
             uint32_t b = quantize_group16<QII_MS_EDEN, -1, true>(v, tcr, draw[it], a.r.seed_sr, row0 + r, tx * 8 + L.blk, packed, inv_r);
             if (zero) { packed[0] = 0u; packed[1] = 0u; b = 0u; }
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kMayTile ? 0 : 2 /* nt */);
             const uint2 sc = gather_scale_bytes(b, L.blk);
             __builtin_amdgcn_raw_buffer_store_b64(u32x2{sc.x, sc.y}, rs, L.blk == 0 ? (uint32_t)(r * spitch) : kNoStore, 0, 0);
         }
     }
+
+    // (the kernel of a backward pass leaves its codes to the products that follow at once: ordinary stores, 512 x 512 -> 512 17.5 us, with
+    // non-temporal ones 17.8; alone non-temporal ones are the faster: 8192 x 8192 post hoc 80.0 -> 78.6, 16384 x 2048 46.3 -> 44.4, Algorithm 1 117.4 -> 116.5)
+    auto put_codes = [](uint8_t *dst, const uint32_t c[4]) {
+        if (kMayTile) *reinterpret_cast<uint4 *>(dst) = make_uint4(c[0], c[1], c[2], c[3]);
+        else store_codes16(dst, c[0], c[1], c[2], c[3]);
+    };
 
     // ---- column part: Q(x^T).  The tile is chunk `ty` of the columns' 128-chunks; wave w takes the
     // tile's columns 32 w .. 32 w + 31, a lane quad two of them, lane q of the quad rows 32 q .. 32 q + 31
@@ -185,7 +192,7 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
                     tt[h] = posthoc_group16(v[e] + 16 * h, codes + 2 * h, gmax);
                     m_c = fmaxf(m_c, gmax);
                 }
-                *reinterpret_cast<uint4 *>(a.c.codes + (j0 + e) * cpitch + chunk * 64 + 16 * q) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
+                put_codes(a.c.codes + (j0 + e) * cpitch + chunk * 64 + 16 * q, codes);
                 *reinterpret_cast<float2 *>(a.c.tbuf + (j0 + e) * G + chunk * 8 + 2 * q) = make_float2(tt[0], tt[1]);
                 continue;
             }
@@ -198,7 +205,7 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
             }
             if (zero) { codes[0] = codes[1] = codes[2] = codes[3] = 0u; sc = 0u; }
             const uint2 s8 = gather_quad_scales(sc, q);
-            *reinterpret_cast<uint4 *>(a.c.codes + (j0 + e) * cpitch + chunk * 64 + 16 * q) = make_uint4(codes[0], codes[1], codes[2], codes[3]);
+            put_codes(a.c.codes + (j0 + e) * cpitch + chunk * 64 + 16 * q, codes);
             if (q == 0) *reinterpret_cast<uint2 *>(kMayTile && a.c.ksn ? tiled_scales(a.c.scales, a.c.ksn, j0 + e, chunk) : a.c.scales + (j0 + e) * G + chunk * 8) = s8;
         }
     }
