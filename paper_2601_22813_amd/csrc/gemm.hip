@@ -1151,7 +1151,8 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 // 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is, and a block
 // beyond the fourth of a unit cheaper, its first loads and stores beside the products of others.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
-// work (power).  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: the plan's own figure, and 4.5
+// work (power).  (Fitted with operands staged through registers and the main kernel's memory operations bunched: the factors 0.935 and 0.97 are what
+// the present kernels take of that, 2048 x 2048 x 16384 105 -> 98 us, 8192^3 730 -> 709.)  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: the plan's own figure, and 4.5
 // of re-tiling where the scale bytes are not tiled yet (one or two shared tiles, main kernel : 64 x 64 tiles: 128 x 128 x 24320
 // 51.6 : 70.4, 256 x 256 x 19456 48.1 : 57.8, 256 x 512 x 22784 56.6 : 67.6).
 // The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
@@ -1182,14 +1183,14 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.49 + 0.55 * last : 2.6 + 0.53 * last);
     const double us128 = 4.45 + (any ? 0.74 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.276 : 1.0);
     const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
-    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : 1.0));
+    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : 0.935));
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     const bool narrow = K <= kMaxNarrowK;
     Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide};
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        p.us[kRouteMain] = plan.us + (retile ? 4.5 : 0.0) - (c_is_bf16 && blocks_take_tiles(plan.full, C, ldc, N, 1) ? 3.3 * (double)(plan.full / 256) : 0.0);
+        p.us[kRouteMain] = 0.97 * plan.us + (retile ? 4.5 : 0.0) - (c_is_bf16 && blocks_take_tiles(plan.full, C, ldc, N, 1) ? 3.3 * (double)(plan.full / 256) : 0.0);
     }
     if (!main_ws && K % 128 == 0) p.us[kRouteNoWorkspace] = us_v2;
     for (const Route r : {kRoute128, kRoute128Wide, kRouteMain, kRouteNoWorkspace})

@@ -13,10 +13,12 @@
 //                         or one wave of 128 x 128 (4, 4) per group, 4 groups (one block per unit);
 //   64 x 64 block tile:   one wave of 64 x 64 (2, 2) per group, 4 groups.
 //
-// Operands are staged through registers (global -> VGPR -> LDS): a tile is small enough for that (at
-// most 36 registers), the next tile's loads then stay in flight for a whole tile's time, and a ragged K
+// Operands are staged through registers (global -> VGPR -> LDS) but for the 4 x 4 form at K a multiple of 256 (gemm_wide_kernel): a tile is
+// small enough for that (at most 36 registers), the next tile's loads then stay in flight for a whole tile's time, and a ragged K
 // needs no padding of the operands: codes and scales beyond K are staged as zeros.  The scale bytes are
 // read row-major or in the tiled layout, whichever the operand has: no re-tiling launch, no workspace.
+#include <utility>
+
 #include "gemm_common.h"
 #include "gemm_reduce.h"
 #include "gemm_tail.h"
@@ -377,7 +379,7 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
     // fragments are in registers by then: all reads of this tile's stage are done, and the first slice of
     // the next tile is read while the rest is multiplied.
     const int ktiles = (int)((g.K + BK - 1) / BK);
-    const int partial = kAnyK ? ktiles - 1 : -1;   // the tile that K cuts
+    const int partial = kAnyK && g.K % BK != 0 ? ktiles - 1 : -1;   // the tile that K cuts
     float ts_a, ts_b;
     auto tensor_scales = [&]() {   // requested behind the first loads, not before them and not when the epilogue needs them
         __builtin_amdgcn_sched_barrier(0);
@@ -501,6 +503,242 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
     }
 }
 
+// ---- the 4 x 4 form for K a multiple of 256 -------------------------------------------------------
+// As the main kernel: codes and scale bytes go straight from memory to LDS (no staging registers, no LDS writes), four stages of
+// a K tile, and the fragment reads are inline assembly with their own waits (the compiler would let them wait for the loads).  A wave has
+// its slice of the next K tile in registers before it multiplies the last step of this one, so the barrier that shows the next tile
+// frees this tile's stage too: the loads of tile kt + 4 follow it, one every 5 matrix instructions, the 16 reads of tile kt + 1 one every
+// 2 (1 to 3 and 3 to 7 are all the same).  us, operands staged through registers : this: 1024 x 4096 x 4096 32.3 : 30.1, 2048 x 2048 x 5632 41.3 :
+// 39.0, 2048 x 2048 x 16384 f32 105.1 : 98.2, 2048^3 19.1 : 18.3, 1500 x 2000 x 1024 12.2 : 11.7, 2048 x 2048 x 256 6.8 : 6.8, 2040 x 1999 x 768
+// f32 13.7 : 13.7.  A K tile then takes 1.44 us where the main kernel takes 1.34 for as many matrix instructions: half the
+// tile has twice the operand bytes for each.
+constexpr int kWideStages = 4;
+constexpr int64_t kMaxWideK = (int64_t)1 << 23;
+constexpr int kLoadEvery = 5, kReadEvery = 2;
+
+struct WideRaw {
+    u32x4 a[4], b[4];
+    uint32_t sa[4], sb[4];   // two scale bytes each
+};
+
+// LDS addresses of a lane's reads of one stage: A's bands in the order the reduction asks for, B's one after the other
+struct WideAddr {
+    uint32_t a[4], sa[4], b, sb;
+};
+
+template <int I>
+__device__ __forceinline__ void wide_read_one(WideRaw &f, const WideAddr &r)
+{
+    constexpr int T = I >> 2;
+    if constexpr ((I & 3) == 0) asm volatile("ds_read_b128 %0, %1" : "=v"(f.a[T]) : "v"(r.a[T]));
+    else if constexpr ((I & 3) == 1) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f.b[T]) : "v"(r.b), "n"(T * 4096));
+    else if constexpr ((I & 3) == 2) asm volatile("ds_read_u16 %0, %1" : "=v"(f.sa[T]) : "v"(r.sa[T]));
+    else asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(f.sb[T]) : "v"(r.sb), "n"(T * 512));
+}
+
+template <int... I>
+__device__ __forceinline__ void wide_read_all(std::integer_sequence<int, I...>, WideRaw &f, const WideAddr &r)
+{
+    (wide_read_one<I>(f, r), ...);
+}
+
+__device__ __forceinline__ void wide_read_wait(WideRaw &f)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]), "+v"(f.b[2]), "+v"(f.b[3]),
+                   "+v"(f.sa[0]), "+v"(f.sa[1]), "+v"(f.sa[2]), "+v"(f.sa[3]), "+v"(f.sb[0]), "+v"(f.sb[1]), "+v"(f.sb[2]), "+v"(f.sb[3]));
+}
+
+// what a wave loads from: buffer descriptors over the block's rows of A and B and over the scale bytes of the wave's 64 rows (rows beyond the
+// matrix, and K tiles beyond the last, read as zeros), and a lane's offsets
+struct WideSource {
+    uint8_t *a, *b, *s;
+    int a_bytes, b_bytes, s_bytes, kt_stride;
+    uint32_t codes, row32, scales;
+};
+
+__device__ __forceinline__ WideSource wide_source(const SmallArgs &g, int64_t m0, int64_t n0, int wave, int t)
+{
+    const int64_t pitch = g.K / 2, rows_a = g.M - m0 < 128 ? g.M - m0 : 128, rows_b = g.N - n0 < 128 ? g.N - n0 : 128;
+    WideSource w;
+    w.a = const_cast<uint8_t *>(g.a_codes) + m0 * pitch;
+    w.b = const_cast<uint8_t *>(g.b_codes) + n0 * pitch;
+    w.a_bytes = (int)(rows_a * pitch);
+    w.b_bytes = (int)(rows_b * pitch);
+    // (the piece is chosen so that the LDS image is swizzled; rows of a thread differ by multiples of 32)
+    w.codes = (uint32_t)((t >> 3) * pitch) + 16u * (uint32_t)((t & 7) ^ ((t >> 3) & 7));
+    w.row32 = (uint32_t)(32 * pitch);
+    const bool of_a = wave < 2;   // uniform: waves 0, 1 take the scale bytes of A's rows, 2, 3 of B's
+    const ScaleView v = of_a ? g.as : g.bs;
+    const int64_t row0 = (of_a ? m0 : n0) + 64 * (wave & 1), left = (of_a ? g.M : g.N) - row0, rows = left < 64 ? left : 64;
+    w.s = const_cast<uint8_t *>(scale_row(v, row0));
+    // (tiled: a K tile's rows lie side by side, and there is room for 256 of them)
+    w.s_bytes = rows <= 0 ? 0 : v.tiled ? (int)((g.K / BK - 1) * 4096 + rows * 16) : (int)(rows * v.row_pitch);
+    w.scales = (uint32_t)((t & 63) * (v.tiled ? 16 : (int)v.row_pitch));
+    w.kt_stride = (int)v.kt_stride;
+    return w;
+}
+
+// load I (0..8) of K tile kt: four passes of 32 rows of A's codes, four of B's, the scale bytes
+template <int I>
+__device__ __forceinline__ void wide_load_one(uint8_t *stage, const WideSource &w, int kt, int ktiles, int wave)
+{
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const bool on = kt < ktiles;   // uniform
+    if constexpr (I < 8) {
+        constexpr int p = I & 3;
+        const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(I < 4 ? w.a : w.b, 0, on ? (I < 4 ? w.a_bytes : w.b_bytes) : 0, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(d, (lds_ptr)(stage + (I < 4 ? 0 : 16384) + p * 4096 + wave * 1024), 16, w.codes + p * w.row32, kt * 128, 0, 0);
+    } else {
+        const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc(w.s, 0, on ? w.s_bytes : 0, 0x00020000);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(d, (lds_ptr)(stage + 32768 + wave * 1024), 16, w.scales, kt * w.kt_stride, 0, 0);
+    }
+}
+
+template <int... I>
+__device__ __forceinline__ void wide_load_all(std::integer_sequence<int, I...>, uint8_t *stage, const WideSource &w, int kt, int ktiles, int wave)
+{
+    (wide_load_one<I>(stage, w, kt, ktiles, wave), ...);
+}
+
+// step Q (0..3) of a K tile: the reads of the next one, the loads of the fourth after it
+template <int Q>
+struct WideSide {
+    uint8_t *load_stage;
+    const WideSource &w;
+    int kt, ktiles, wave;
+    WideRaw &fn;
+    const WideAddr &r;
+    template <int I>
+    __device__ __forceinline__ void at() const
+    {
+        constexpr int n = 16 * Q + I;
+        static_assert(16 * kReadEvery <= 48 && 3 + 8 * kLoadEvery < 64, "reads before step 3, loads within the tile");
+        if constexpr (n % kReadEvery == kReadEvery - 1 && n / kReadEvery < 16) wide_read_one<n / kReadEvery>(fn, r);
+        if constexpr (n % kLoadEvery == kLoadEvery / 2 && n / kLoadEvery < 9) wide_load_one<n / kLoadEvery>(load_stage, w, kt, ktiles, wave);
+    }
+};
+
+template <int I, int D>
+__device__ __forceinline__ void wide_dequant(half8_t (&na)[4], half8_t (&nb)[4], WideRaw &f)
+{
+    constexpr int t = (I >> 1) & 3, h = I & 1;
+    if (I < 8) {
+        if (D == 0 && h == 0) f.sa[t] = scale_halves(f.sa[t]);
+        dequant_half<h, (D >> 1)>(na[t], f.a[t][D], f.sa[t]);
+    } else {
+        if (D == 0 && h == 0) f.sb[t] = scale_halves(f.sb[t]);
+        dequant_half<h, (D >> 1)>(nb[t], f.b[t][D], f.sb[t]);
+    }
+}
+
+template <int... I>
+__device__ __forceinline__ void wide_dequant_all(std::integer_sequence<int, I...>, half8_t (&na)[4], half8_t (&nb)[4], WideRaw &f)
+{
+    (wide_dequant<I, 0>(na, nb, f), ...);
+}
+
+struct WideFrags {
+    half8_t a[4], b[4];
+};
+
+template <int D, class Side, int... I>
+__device__ __forceinline__ void wide_step(std::integer_sequence<int, I...>, floatx16 (&acc)[16], const WideFrags &cu, WideFrags &nx, WideRaw &f, const Side &side)
+{
+    ((acc[I] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[I & 3], cu.a[I >> 2], acc[I], 0, 0, 0), side.template at<I>(),
+      wide_dequant<I, D>(nx.a, nx.b, f), __builtin_amdgcn_sched_barrier(0)), ...);
+}
+
+template <bool kBf16Out>
+__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(SmallArgs g0, SmallArgs g1, int n0_blocks)
+{
+    using G = Geo<4, 4, 1, 4>;
+    const bool first = (int)blockIdx.x < n0_blocks;   // uniform
+    SmallArgs g = g0;
+    if (!first) g = g1;
+    extern __shared__ __align__(16) uint8_t smem[];
+    const int t = threadIdx.x, lane = t & 63;
+    const int kg = __builtin_amdgcn_readfirstlane(t >> 6);   // (a group of waves is one wave)
+    const int li = lane & 31, kb = lane >> 5;
+    int tm, tn;
+    tile_coords((int)blockIdx.x - (first ? 0 : n0_blocks), g.tiles_m, g.tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * G::BM, n0 = (int64_t)tn * G::BN;
+    const int ktiles = (int)(g.K / BK);
+    const WideSource src = wide_source(g, m0, n0, kg, t);
+    const std::make_integer_sequence<int, 9> all_loads;
+    const std::make_integer_sequence<int, 16> all_reads, all_steps;
+    wide_load_all(all_loads, smem, src, 0, ktiles, kg);
+    wide_load_all(all_loads, smem + G::kStage, src, 1, ktiles, kg);
+    __builtin_amdgcn_sched_barrier(0);
+    const float ts_a = *g.a_ts, ts_b = *g.b_ts;
+    floatx16 acc[16];   // tile (i ^ row_flip, j ^ col_flip) of the wave at 4 i + j
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[u][r] = 0.0f;
+        asm volatile("" : "+a"(acc[u]));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const uint32_t codes = (uint32_t)(li * 128 + ((2 * kg + kb) ^ (li & 7)) * 16), scales = (uint32_t)(32768 + li * 16 + 4 * kg + 2 * kb);
+    const uint32_t flip = (uint32_t)G::row_flip(kg);   // (uniform)
+    auto addresses = [&](int tile) {
+        const uint32_t stage = lds0 + (uint32_t)(tile & (kWideStages - 1)) * G::kStage;
+        WideAddr r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r.a[i] = codes + (stage + ((uint32_t)i ^ flip) * 4096u);
+            r.sa[i] = scales + (stage + ((uint32_t)i ^ flip) * 512u);
+        }
+        r.b = codes + (stage + 16384u);
+        r.sb = scales + (stage + 2048u);
+        return r;
+    };
+    auto barrier = [&]() {   // (s_barrier alone: the waits are written out)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    asm volatile("s_waitcnt vmcnt(9)" ::: "memory");   // tile 0; tile 1 may be under way
+    barrier();
+    WideRaw f0, f1;
+    WideFrags x, y;
+    wide_read_all(all_reads, f0, addresses(0));
+    wide_load_all(all_loads, smem + 2 * G::kStage, src, 2, ktiles, kg);
+    wide_load_all(all_loads, smem + 3 * G::kStage, src, 3, ktiles, kg);
+    wide_read_wait(f0);
+    wide_dequant_all(all_steps, x.a, x.b, f0);
+    // one tile: fc holds its raw slice, x its first fragments; fn takes the next tile's slice (after the last: zeros, never multiplied)
+    auto one_tile = [&](int kt, WideRaw &fc, WideRaw &fn) {
+        asm volatile("s_waitcnt vmcnt(18)" ::: "memory");   // tile kt + 1, behind it those of tiles kt + 2 and kt + 3
+        barrier();
+        const WideAddr r = addresses(kt + 1);
+        uint8_t *const load_stage = smem + (kt & (kWideStages - 1)) * G::kStage;
+        wide_step<1>(all_steps, acc, x, y, fc, WideSide<0>{load_stage, src, kt + kWideStages, ktiles, kg, fn, r});
+        wide_step<2>(all_steps, acc, y, x, fc, WideSide<1>{load_stage, src, kt + kWideStages, ktiles, kg, fn, r});
+        wide_step<3>(all_steps, acc, x, y, fc, WideSide<2>{load_stage, src, kt + kWideStages, ktiles, kg, fn, r});
+        wide_read_wait(fn);
+        wide_step<0>(all_steps, acc, y, x, fn, WideSide<3>{load_stage, src, kt + kWideStages, ktiles, kg, fn, r});
+    };
+    // (an odd tile first: a way out in the middle of the loop makes the compiler spill the accumulators)
+    int kt = 0;
+    if (ktiles & 1) {
+        one_tile(0, f0, f1);
+        f0 = f1;
+        kt = 1;
+    }
+    for (; kt < ktiles; kt += 2) {
+        one_tile(kt, f0, f1);
+        one_tile(kt + 1, f1, f0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the reduction overlays the stages
+    __syncthreads();
+    floatx16 sum[G::kUnits / G::KG];
+    uint8_t *const area = reduce_groups<G::WM, G::KG, G::kArea>(acc, sum, smem, kg, 0, lane);
+    finish<kBf16Out, G>(sum, area, ts_a * ts_b, g, m0 + kg * 32, n0, lane);
+}
+
 template <auto kKernel>
 hipError_t launch_kernel(int blocks, int threads, int lds, const SmallArgs *g, int count, hipStream_t s)
 {
@@ -519,6 +757,15 @@ hipError_t launch(SmallArgs *g, int count, hipStream_t s)
         g[i].tiles_n = (int)((g[i].N + G::BN - 1) / G::BN);
         blocks += g[i].tiles_m * g[i].tiles_n;
     }
+    if constexpr (G::MT == 4) {
+        constexpr int lds = kWideStages * G::kStage > G::kLds ? kWideStages * G::kStage : G::kLds;
+        bool direct = g[0].K % BK == 0;
+        for (int i = 0; i < count; ++i)   // (offsets below 2^31, 16-byte pieces of scale bytes where they are row-major)
+            direct = direct && g[i].K <= kMaxWideK && ((reinterpret_cast<uintptr_t>(g[i].as.s) | reinterpret_cast<uintptr_t>(g[i].bs.s)) & 15) == 0;
+        // (the form for any K otherwise: it takes whole tiles as well)
+        return direct ? launch_kernel<gemm_wide_kernel<kBf16Out>>(blocks, G::kThreads, lds, g, count, s)
+                      : launch_kernel<gemm_small_kernel<kBf16Out, G, true>>(blocks, G::kThreads, G::kLds, g, count, s);
+    } else
     return g[0].K % BK != 0 ? launch_kernel<gemm_small_kernel<kBf16Out, G, true>>(blocks, G::kThreads, G::kLds, g, count, s)
                             : launch_kernel<gemm_small_kernel<kBf16Out, G, false>>(blocks, G::kThreads, G::kLds, g, count, s);
 }

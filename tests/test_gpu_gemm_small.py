@@ -141,3 +141,21 @@ def test_a_ragged_k_costs_little_more(M, N, K, most):
         us.append(median_us(lambda: qii.qii_gemm_nvfp4(A, B, C, None)))
     print(f"gemm {M}x{N}x{K}: {us[0]:.1f} us, with whole K tiles {us[1]:.1f}", flush=True)
     assert us[0] <= most * us[1]
+
+
+@pytest.mark.parametrize("M,N,K", [(2040, 1990, 768), (2040, 1990, 1024), (1921, 1929, 1280)])
+def test_wide_tiles_with_fewer_k_tiles_than_stages_and_more(oracle, M, N, K):
+    """128 x 128 tiles of four 4 x 4 waves whose operands go straight to LDS, in four stages: three, four and five K tiles, ragged edges.
+    Scale bytes that begin 8 bytes off take the form that stages operands through registers: the same sums in the same
+    order, so the same bits."""
+    check_product(oracle, M, N, K, True, T128_WIDE)
+    rng = np.random.default_rng(K)
+    A, B = nv_to_dev(operand(oracle, rng, M, K)), nv_to_dev(operand(oracle, rng, N, K))
+    assert (A.scales.data_ptr() | B.scales.data_ptr()) % 16 == 0
+    room = torch.zeros(N * K // 16 + 8, dtype=torch.uint8, device="cuda")
+    off = room[8:].view(N, K // 16)
+    off.copy_(B.scales)
+    C, D = (torch.empty((M, N), device="cuda") for _ in range(2))
+    qii.qii_gemm_nvfp4(A, B, C, None)
+    qii.qii_gemm_nvfp4(A, qii.NVFP4Tensor(B.codes, off, B.tensor_scale, N, K), D, None)
+    assert torch.equal(C, D)
