@@ -745,7 +745,7 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     const bool together = shared && (at_once || !ph || 4 * kRegion + tw + tx <= posthoc_region_bytes(T, d_in, d_out, mode));
     int words_q[2] = {0, 0};
     if (ph && together)
-        for (int i = 0; i < 2; ++i) words_q[i] = qii::requant_blocks(Rq, Cq, 2, i);
+        for (int i = 0; i < 2; ++i) words_q[i] = at_once ? qii::backward_requant_blocks(Rq[i], Cq[i]) : qii::requant_blocks(Rq, Cq, 2, i);
     const bool words_ok = words_q[0] > 0 && words_q[0] <= qii::kMaxBlockWords && words_q[1] > 0 && words_q[1] <= qii::kMaxBlockWords;
     if (!words_ok) words_q[0] = words_q[1] = 0;
     const bool words_e = ph && pair_e && (T / 128) * (d_out / 128) <= qii::kMaxBlockWords;

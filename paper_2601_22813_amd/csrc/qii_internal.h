@@ -152,6 +152,7 @@ hipError_t launch_quantize_requant(const QuantizeArgs *a, int count, hipStream_t
 // Q(E), Q(E^T) and the re-quantizations q of W and X in one launch (pair_kernel_applies to E, requant_kernels_apply to
 // both, all in one mode, the arguments as for the two launches; quantize_backward.hip)
 hipError_t launch_quantize_backward(const PairQuantizeArgs &e, const QuantizeArgs q[2], hipStream_t s);
+int backward_requant_blocks(int64_t R, int64_t C);   // its blocks for an R x C re-quantization (post hoc scheme)
 // ws (nullable): gemm_workspace_bytes(M, N, K) bytes, 16-byte aligned, for the re-tiled scale
 // bytes of the fast kernel; without it a slower kernel reads the row-major scales directly
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);

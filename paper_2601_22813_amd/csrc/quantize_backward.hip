@@ -15,8 +15,12 @@
 namespace qii {
 namespace {
 
+// Registers for three blocks per compute unit in the post hoc scheme, 80 (85 without a bound, two blocks: one spilled register more than
+// pays for itself), and images of one chunk, which leave the LDS for three.  Kernel 16384 x 2048 -> 8192 172.5 -> 157.6 us, 2048 x 2048 -> 5632 29.1 ->
+// 27.6; passes 892 -> 884, 118.1 -> 116.2, 4096 x 4096 -> 4096 234.3 -> 232.9.  (Either alone gains nothing; 55 registers, one column at a
+// time, and four blocks lose what they gain.)  Algorithm 1's 94 registers would spill 22.
 template <int kMode, int kChunks>
-__global__ __launch_bounds__(512) void quantize_backward_kernel(PairArgs e, RequantArgs w, RequantArgs x, int n_e, int n_w)
+__global__ __launch_bounds__(512, kMode == QII_MS_EDEN_PH ? 6 : 4) void quantize_backward_kernel(PairArgs e, RequantArgs w, RequantArgs x, int n_e, int n_w)
 {
     extern __shared__ __align__(16) uint8_t lds[];   // kChunks images of 32 KiB, the first of them a block's tile of E
     const int block = (int)blockIdx.x;               // (branches on it are uniform)
@@ -47,13 +51,14 @@ hipError_t launch(const PairArgs &e, const QuantizeArgs q[2], hipStream_t s)
 
 static_assert(kPairImage <= kImage, "a tile of E takes one image");
 
+int backward_requant_blocks(int64_t R, int64_t C) { return (int)tiles_of(R, C, 1); }
+
 hipError_t launch_quantize_backward(const PairQuantizeArgs &e, const QuantizeArgs q[2], hipStream_t s)
 {
     const int64_t R[2] = {q[0].R, q[1].R}, C[2] = {q[0].C, q[1].C};
     const PairArgs p = pair_args(e);
-    if (chunks_per_block(R, C, 2) == 2)
-        return e.mode == QII_MS_EDEN_PH ? launch<QII_MS_EDEN_PH, 2>(p, q, s) : launch<QII_MS_EDEN, 2>(p, q, s);
-    return e.mode == QII_MS_EDEN_PH ? launch<QII_MS_EDEN_PH, 1>(p, q, s) : launch<QII_MS_EDEN, 1>(p, q, s);
+    if (e.mode == QII_MS_EDEN_PH) return launch<QII_MS_EDEN_PH, 1>(p, q, s);
+    return chunks_per_block(R, C, 2) == 2 ? launch<QII_MS_EDEN, 2>(p, q, s) : launch<QII_MS_EDEN, 1>(p, q, s);
 }
 
 }  // namespace qii
