@@ -11,6 +11,8 @@
 //   reverse order so that "xor 7" pairs blocks that differ in index bit 2.
 //   An octet processes 4 consecutive rows of the same chunk, which lets one
 //   Philox4x32 call feed the four scale roundings of a lane.
+#include <type_traits>
+
 #include "qii_device.h"
 #include "qii_internal.h"
 #include "quantize_core.h"
@@ -308,6 +310,8 @@ struct ScalesArgs {
     int64_t tiled_ksn;          // != 0 (G a multiple of 16): K tiles of the layout the main GEMM kernel reads
 };
 
+typedef uint32_t quad_t __attribute__((ext_vector_type(4)));
+
 // four scale bytes of one row
 __device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_t draw[4][4], int it, float x32, float rd, bool in_range)
 {
@@ -341,7 +345,21 @@ __device__ __forceinline__ void scales_block(const ScalesArgs a, int64_t block)
 {
     __shared__ float wave_m[4];
     float amax = 0.0f;
-    for (int i = threadIdx.x; i < a.n_amax; i += 256) amax = fmaxf(amax, a.amax[(int64_t)i * a.stride]);
+    if (a.stride == 1) {   // uniform: one word per block of the heavy pass (16-byte aligned; what lies beyond the last reads as zero)
+        const __amdgpu_buffer_rsrc_t words = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(a.amax), 0, a.n_amax * 4, 0x00020000);
+        auto fold = [&](auto count) {
+            constexpr int kLoads = decltype(count)::value;
+            quad_t w[kLoads];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(words, (uint32_t)(i * 4096) + threadIdx.x * 16u, 0, 0);
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i) amax = fmaxf(fmaxf(fmaxf(amax, u2f(w[i][0])), fmaxf(u2f(w[i][1]), u2f(w[i][2]))), u2f(w[i][3]));
+        };
+        if (a.n_amax <= 1024) fold(std::integral_constant<int, 1>());   // uniform
+        else fold(std::integral_constant<int, kMaxBlockWords / 1024>());
+    } else {
+        for (int i = threadIdx.x; i < a.n_amax; i += 256) amax = fmaxf(amax, a.amax[(int64_t)i * a.stride]);
+    }
     amax = wave_max(amax);
     if ((threadIdx.x & 63) == 0) wave_m[threadIdx.x >> 6] = amax;
     __syncthreads();

@@ -27,3 +27,29 @@ def test_pair_equals_separate_calls(rows, cols, mode):
         for a, b in zip(pair, alone):
             assert torch.equal(a.codes, b.codes) and torch.equal(a.scales, b.scales)
             assert torch.equal(a.tensor_scale, b.tensor_scale)
+
+
+@pytest.mark.parametrize("rows,cols", [(4096, 4096), (4096, 4224), (8192, 8064), (8192, 8192), (8192, 8320)])
+def test_every_block_word_counts(rows, cols):
+    """1024 blocks of the heavy pass (one load of the scales pass holds their words), 1056, 4032, 4096 (as many words as the region has) and
+    4160 (the spread running maximum): an outlier in the first, a middle and the last tile sets the maximum, the
+    same as a call that is given it, along the rows, the columns and both; the workspace holds no zeros before."""
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = (0.1 * torch.randn((rows, cols), device="cuda", generator=g)).bfloat16()
+    for tile in ((0, 0), (rows // 256, cols // 256), (rows // 128 - 1, cols // 128 - 1)):
+        y = x.clone()
+        y[tile[0] * 128 + 77, tile[1] * 128 + 99] = 400.0
+        pair = qii.NVFP4Tensor.empty(rows, cols), qii.NVFP4Tensor.empty(cols, rows)
+        w = ws(qii.qii_quantize_pair_workspace_bytes(rows, cols, qii.MS_EDEN_PH))
+        w.fill_(0x7E)
+        qii.qii_quantize_pair_nvfp4(y, qii.MS_EDEN_PH, 11, 12, 13, 14, *pair, w)
+        for transpose, seed, both in ((False, 11, pair[0]), (True, 13, pair[1])):
+            top = torch.empty(1, device="cuda")
+            qii.qii_absmax(y, transpose, 128, seed, top)
+            alone, given = (qii.NVFP4Tensor.empty(both.rows, both.cols) for _ in range(2))
+            size = ws(qii.qii_quantize_posthoc_workspace_bytes(both.rows, both.cols))
+            size.fill_(0x7E)
+            qii.qii_quantize_nvfp4(y, transpose, qii.MS_EDEN_PH, 128, seed, seed + 1, None, alone, size)
+            qii.qii_quantize_nvfp4(y, transpose, qii.MS_EDEN_PH, 128, seed, seed + 1, top, given, size)
+            for t in (alone, both):
+                assert torch.equal(t.codes, given.codes) and torch.equal(t.scales, given.scales) and torch.equal(t.tensor_scale, given.tensor_scale)
