@@ -12,19 +12,18 @@ __global__ __launch_bounds__(512) void quantize_pair_kernel(PairArgs a)
     pair_block<kMode>(a, (int)blockIdx.x, tile);
 }
 
-// Abs-max of a rotated matrix along its columns, and along its rows as well (kRows), from one read.  The result words take one
-// atomic per block, and such atomics on one address are resolved one after the other (about 10 ns each), so the pass
-// runs as few blocks; to keep the memory busy all the same a block is 16 waves (12 for both orientations, whose
-// registers allow no more): groups of four waves, each group with an LDS image of its own (as above), that
+// Abs-max of a rotated matrix along its columns.  The result word takes one atomic per block, and such atomics on one
+// address are resolved one after the other (about 10 ns each), so the pass runs as few blocks; to keep the memory busy
+// all the same a block is 16 waves: groups of four waves, each group with an LDS image of its own (as above), that
 // stride over the 128 x 128 tiles with the next tile's loads in flight.  Up to 512 tiles a block is one
 // group and one tile: small tensors need every compute unit.
 // 8192 x 8192 along the columns: 39 -> 30 us against a pass whose two waves per SIMD loaded 4 bytes
 // per lane and row.
-template <bool kRows, int kGroups>
+template <int kGroups>
 __global__ __launch_bounds__(256 * kGroups) void absmax_tiles_kernel(PairArgs a, int tiles)
 {
     extern __shared__ __align__(16) uint8_t images[];
-    __shared__ float wave_m[2][4 * kGroups];
+    __shared__ float wave_m[4 * kGroups];
     const int t = threadIdx.x & 255, lane = t & 63;
     const int wave16 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave16 & 3, group = wave16 >> 2;
     uint8_t *tile = images + group * (128 * 256);
@@ -40,7 +39,7 @@ __global__ __launch_bounds__(256 * kGroups) void absmax_tiles_kernel(PairArgs a,
         for (int i = 0; i < 8; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (int)(i * 16 * a.ld * 2), 0);
     };
     load(id);
-    float m_r = 0.0f, m_c = 0.0f;
+    float m = 0.0f;
     const int rounds = (tiles + stride - 1) / stride;   // the same for every group: the barriers are the block's
     for (int k = 0; k < rounds; ++k) {
 #pragma unroll
@@ -51,22 +50,6 @@ __global__ __launch_bounds__(256 * kGroups) void absmax_tiles_kernel(PairArgs a,
         __syncthreads();
         id += stride;
         if (k + 1 < rounds) load(id);
-        if (kRows) {
-            const OctetLane L = octet_lane(lane, a.r.sign);
-            uint32_t mask[8];
-            make_masks<true>(L.sign16, mask);
-            const int quad = 8 * wave + (lane >> 3);
-#pragma unroll
-            for (int it = 0; it < 4; ++it) {
-                const uint8_t *src = tile + (4 * quad + it) * 256 + ((L.blk ^ wave) * 32);
-                const u32x4 q0 = *reinterpret_cast<const u32x4 *>(src), q1 = *reinterpret_cast<const u32x4 *>(src + 16);
-                const uint32_t w8[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
-                float v[16];
-                unpack_bf16x16<true>(w8, v, mask);
-                rht128_lane<false>(v, L);
-                m_r = fmaxf(m_r, group_absmax(v));
-            }
-        }
         {
             const int q = lane & 3, jp = lane >> 2;
             const uint8_t *src = tile + (32 * q) * 256 + 4 * ((16 * wave + jp) ^ (8 * q));
@@ -80,31 +63,119 @@ __global__ __launch_bounds__(256 * kGroups) void absmax_tiles_kernel(PairArgs a,
                     v[i] = u2f((e == 0 ? raw << 16 : raw & 0xFFFF0000u) ^ flip);
                 }
                 fwht128_quad<false>(v, q);
-                m_c = fmaxf(m_c, fmaxf(group_absmax(v), group_absmax(v + 16)));
+                m = fmaxf(m, fmaxf(group_absmax(v), group_absmax(v + 16)));
             }
         }
         __syncthreads();   // the images are free again
     }
-    m_r = wave_max(__builtin_fmaf(m_r, kInvSqrt128, 0.0f));   // the scaling the rotation left out
-    m_c = wave_max(__builtin_fmaf(m_c, kInvSqrt128, 0.0f));
-    if (lane == 0) { wave_m[0][wave16] = m_r; wave_m[1][wave16] = m_c; }
+    m = wave_max(__builtin_fmaf(m, kInvSqrt128, 0.0f));   // the scaling the rotation left out
+    if (lane == 0) wave_m[wave16] = m;
     __syncthreads();
-    if (threadIdx.x == 1 || (kRows && threadIdx.x == 0)) {
-        float m = 0.0f;
+    if (threadIdx.x == 0) {
 #pragma unroll
-        for (int i = 0; i < 4 * kGroups; ++i) m = fmaxf(m, wave_m[threadIdx.x][i]);
-        max_to_global(m, threadIdx.x == 0 ? a.r.amax_out : a.c.amax_out);
+        for (int i = 1; i < 4 * kGroups; ++i) m = fmaxf(m, wave_m[i]);
+        max_to_global(m, a.c.amax_out);
     }
 }
 
-template <bool kRows, int kGroups>
-hipError_t launch_absmax(const PairArgs &a, int tiles, hipStream_t s)
+// Abs-max along the rows and the columns from one read: blocks as in the quantizer (waves 0..3 take the rows, 4..7 the columns).
+// The result words take one atomic per block, and such atomics on one address are resolved one after the other (about 10 ns
+// each), so the pass runs as few blocks as fill the chip: they stride over the tiles, the next tile's loads in flight and two
+// LDS images in turn (one barrier a tile: a wave that fills an image has passed the barrier that the last readers of that image
+// reach after their reads).  Instruction issue and the waits between a tile's steps bound it.  Before, groups of four waves did
+// the rows and then the columns of a tile, 12 waves a block between common barriers.  Whole MS-EDEN pair calls, us, before :
+// now: 8192 x 8192 115.7 : 101.8, 16384 x 2048 64.0 : 58.6, 4096 x 4096 42.3 : 32.3, 4096 x 2560 31.5 : 26.6, 2048 x 2176
+// 23.6 : 21.3, 1024 x 1024 17.2 : 16.6; one image 115.5, 59.4, 33.4, 26.6, 21.4, 17.1 where these took 113.3, 58.6, 32.8,
+// 26.6, 21.3, 17.1; three blocks per unit of 80 registers, one column at a time, no faster (4096 x 4096 34.2).
+constexpr int kAbsmaxPairBlocks = 512;   // two per compute unit
+
+__global__ __launch_bounds__(512, 4) void absmax_pair_kernel(PairArgs a, int tiles)
+{
+    extern __shared__ __align__(16) uint8_t images[];
+    __shared__ float wave_m[8];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave_id = __builtin_amdgcn_readfirstlane(t >> 6), wave = wave_id & 3;
+    const bool take_rows = wave_id < 4;   // (wave-uniform)
+    u32x4 w[4];
+    const uint32_t voff = (uint32_t)(((t >> 4) * a.ld + (t & 15) * 8) * 2);
+    auto load = [&](int n) {
+        const int ty = n / a.tiles_x, tx = n - ty * a.tiles_x;
+        const __amdgpu_buffer_rsrc_t src = region(a.x + (int64_t)ty * 128 * a.ld + (int64_t)tx * 128, (127 * a.ld + 128) * 2);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = __builtin_amdgcn_raw_buffer_load_b128(src, voff, (int)(i * 32 * a.ld * 2), 0);
+    };
+    int id = (int)blockIdx.x;
+    load(id);
+    const OctetLane L = octet_lane(lane, a.r.sign);
+    const int q = lane & 3, jp = lane >> 2;
+    const uint32_t sign_word = q == 0 ? a.c.sign[0] : q == 1 ? a.c.sign[1] : q == 2 ? a.c.sign[2] : a.c.sign[3];
+    float m = 0.0f;
+    for (int k = 0; id < tiles; ++k) {   // uniform
+        uint8_t *tile = images + (k & 1) * kPairImage;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = (t >> 4) + 32 * i, p = (t & 15) ^ (2 * (r >> 5));
+            *reinterpret_cast<u32x4 *>(tile + r * 256 + p * 16) = w[i];
+        }
+        id += (int)gridDim.x;
+        if (id < tiles) load(id);
+        __syncthreads();
+        if (take_rows) {
+            uint32_t mask[8], sign16 = L.sign16;
+            asm("" : "+v"(sign16));
+            make_masks<true>(sign16, mask);
+            const int quad = 8 * wave + (lane >> 3);
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const uint8_t *src = tile + (4 * quad + it) * 256 + ((L.blk ^ wave) * 32);
+                const u32x4 q0 = *reinterpret_cast<const u32x4 *>(src), q1 = *reinterpret_cast<const u32x4 *>(src + 16);
+                const uint32_t w8[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
+                float v[16];
+                unpack_bf16x16<true>(w8, v, mask);
+                rht128_lane<false>(v, L);
+                m = fmaxf(m, group_absmax(v));
+            }
+        } else {
+            const uint8_t *src = tile + (32 * q) * 256 + 4 * ((16 * wave + jp) ^ (8 * q));
+            uint32_t sw = sign_word;
+            asm("" : "+v"(sw));   // (the 32 sign masks are formed again for each tile: kept, they would take 32 registers)
+            float v[2][32];
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {
+                const uint32_t raw = *reinterpret_cast<const uint32_t *>(src + i * 256), flip = ((sw >> i) & 1u) << 31;
+                v[0][i] = u2f((raw << 16) ^ flip);
+                v[1][i] = u2f((raw & 0xFFFF0000u) ^ flip);
+            }
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                fwht128_quad<false>(v[e], q);
+                m = fmaxf(m, fmaxf(group_absmax(v[e]), group_absmax(v[e] + 16)));
+            }
+        }
+    }
+    m = wave_max(__builtin_fmaf(m, kInvSqrt128, 0.0f));   // the scaling the rotation left out
+    if (lane == 0) wave_m[wave_id] = m;
+    __syncthreads();
+    if (t < 2) max_to_global(fmaxf(fmaxf(wave_m[4 * t], wave_m[4 * t + 1]), fmaxf(wave_m[4 * t + 2], wave_m[4 * t + 3])), t == 0 ? a.r.amax_out : a.c.amax_out);
+}
+
+hipError_t launch_absmax_pair(const PairArgs &a, int tiles, hipStream_t s)
+{
+    const int lds = (tiles > kAbsmaxPairBlocks ? 2 : 1) * kPairImage;
+    const hipError_t e = allow_dynamic_lds<absmax_pair_kernel>(2 * kPairImage);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(absmax_pair_kernel, dim3((unsigned)(tiles < kAbsmaxPairBlocks ? tiles : kAbsmaxPairBlocks)), dim3(512), lds, s, a, tiles);
+    return hipGetLastError();
+}
+
+template <int kGroups>
+hipError_t launch_absmax_columns(const PairArgs &a, int tiles, hipStream_t s)
 {
     constexpr int lds = kGroups * 128 * 256, most = kGroups == 1 ? 512 : 256;
-    const hipError_t e = allow_dynamic_lds<absmax_tiles_kernel<kRows, kGroups>>(lds);
+    const hipError_t e = allow_dynamic_lds<absmax_tiles_kernel<kGroups>>(lds);
     if (e != hipSuccess) return e;
     const int blocks = (tiles + kGroups - 1) / kGroups;
-    hipLaunchKernelGGL((absmax_tiles_kernel<kRows, kGroups>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(256 * kGroups), lds, s, a, tiles);
+    hipLaunchKernelGGL((absmax_tiles_kernel<kGroups>), dim3((unsigned)(blocks < most ? blocks : most)), dim3(256 * kGroups), lds, s, a, tiles);
     return hipGetLastError();
 }
 
@@ -166,8 +237,8 @@ hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, ui
     a.r.amax_out = reinterpret_cast<uint32_t *>(amax_r);
     a.c.amax_out = reinterpret_cast<uint32_t *>(amax_c);
     const int tiles = (int)((rows / 128) * (cols / 128));
-    if (tiles <= 512) return amax_r ? launch_absmax<true, 1>(a, tiles, s) : launch_absmax<false, 1>(a, tiles, s);
-    return amax_r ? launch_absmax<true, 3>(a, tiles, s) : launch_absmax<false, 4>(a, tiles, s);
+    if (amax_r) return launch_absmax_pair(a, tiles, s);
+    return tiles <= 512 ? launch_absmax_columns<1>(a, tiles, s) : launch_absmax_columns<4>(a, tiles, s);
 }
 
 }  // namespace qii

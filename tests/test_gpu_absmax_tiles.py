@@ -1,5 +1,5 @@
 """Rotated abs-max by 128 x 128 tiles (along the columns, and along both orientations for Algorithm 1's pair): bit for
-bit the oracle's maximum where the tile kernel can go wrong: one tile, fewer tiles than a block has wave groups, a
+bit the oracle's maximum where the tile kernels can go wrong: one tile, fewer tiles than a block has wave groups, a
 tile count that leaves some groups without a tile in the last of two rounds (4480 x 5248; at 1280 x 6656 and 4224 x 4352
 qii_absmax takes the columns kernel), a leading dimension beyond the row whose extra columns are huge, and a maximum that
 sits in the last tile."""
@@ -30,3 +30,25 @@ def test_rotated_abs_max_by_tiles(oracle, rows, cols):
     qii.qii_quantize_pair_nvfp4(full, qii.MS_EDEN, 91, 92, 93, 94, out_r, out_c, ws(qii.qii_quantize_pair_workspace_bytes(rows, cols, qii.MS_EDEN)))
     assert_nv_equal(out_r, oracle.quantize(x, qii.MS_EDEN, seed_rht=91, seed_sr=92), "rows")
     assert_nv_equal(out_c, oracle.quantize(x, qii.MS_EDEN, transpose=True, seed_rht=93, seed_sr=94), "columns")
+
+
+@pytest.mark.parametrize("rows,cols", [(4096, 2048), (3456, 2432), (3200, 5248)])
+@pytest.mark.parametrize("where", ["first", "block 0's second", "last"])
+def test_both_maxima_of_a_pair(rows, cols, where):
+    """512 tiles (one a block), 513 (one block has a second one) and 1025 (two or three each, the two LDS images in turn):
+    Algorithm 1's pair equals the two separate quantizations, whose maxima come from other kernels; one tile holds the maximum."""
+    tiles_x = cols // 128
+    tile = {"first": 0, "last": rows // 128 * tiles_x - 1}.get(where, 512)
+    if tile >= rows // 128 * tiles_x:
+        return
+    x = synth.normal_bf16((rows, cols), 1.0, rows + cols)
+    r, c = tile // tiles_x * 128, tile % tiles_x * 128
+    x[r:r + 128, c:c + 128] = synth.normal_bf16((128, 128), 50.0, 3)
+    x = to_dev(x)
+    out_r, out_c = qii.NVFP4Tensor.empty(rows, cols), qii.NVFP4Tensor.empty(cols, rows)
+    qii.qii_quantize_pair_nvfp4(x, qii.MS_EDEN, 91, 92, 93, 94, out_r, out_c, ws(qii.qii_quantize_pair_workspace_bytes(rows, cols, qii.MS_EDEN)))
+    for out, transpose, rht, sr in ((out_r, False, 91, 92), (out_c, True, 93, 94)):
+        one = qii.NVFP4Tensor.empty(out.rows, out.cols)
+        qii.qii_quantize_nvfp4(x, transpose, qii.MS_EDEN, 128, rht, sr, None, one, ws(qii.qii_quantize_workspace_bytes()))
+        assert torch.equal(out.tensor_scale, one.tensor_scale)
+        assert torch.equal(out.scales, one.scales) and torch.equal(out.codes, one.codes)
