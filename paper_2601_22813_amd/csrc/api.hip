@@ -156,17 +156,13 @@ qii_status quantize_source(const qii::Source &src, int64_t R, int64_t C, qii_mod
         if (e != hipSuccess) return hip_fail(e, "quantize");
         return QII_OK;
     }
-    // a re-quantization of few blocks leaves a word per block and needs no clearing launch
-    const int words = amax_in ? 0 : qii::requant_amax_words(src, R, C);
-    if (words) {
-        hipError_t e = qii::launch_absmax_requant(&src, &R, &C, rht_group == 128, &seed_rht, &amax_slot, 1, s, words);
-        if (e != hipSuccess) return hip_fail(e, "absmax");
-        a.amax = amax_slot;
-    } else if (!amax_in) {
+    // the abs-max pass over a small tensor leaves a word per block and needs no clearing launch
+    const int words = amax_in ? 0 : qii::absmax_words(src, R, C, rht_group == 128);
+    if (!amax_in) {
         hipError_t e = hipSuccess;
-        if (!slot_zeroed) e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_slot), 0u, 1, 1, s);
+        if (!slot_zeroed && !words) e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(amax_slot), 0u, 1, 1, s);
         if (e != hipSuccess) return hip_fail(e, "fill");
-        e = qii::launch_absmax(src, R, C, rht_group == 128, seed_rht, amax_slot, s);
+        e = qii::launch_absmax(src, R, C, rht_group == 128, seed_rht, amax_slot, s, words);
         if (e != hipSuccess) return hip_fail(e, "absmax");
         a.amax = amax_slot;
     }
@@ -308,17 +304,14 @@ qii_status quantize_pair(const qii::Source &src, int64_t rows, int64_t cols, qii
     if ((tiled_r || tiled_c) && !ph) return fail(QII_INVALID_ARG, "tiled scales are written by the post hoc scheme only");
     hipError_t e = hipSuccess;
     const int64_t blocks = (rows / 128) * (cols / 128);
-    const int words = ph && blocks <= qii::kMaxBlockWords ? (int)blocks : 0;   // one word per block: nothing to clear
-    if (!slots_zeroed && !words) {
-        e = ph ? qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s)
-               : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, 1, 1, s);
-        if (e != hipSuccess) return hip_fail(e, "fill");
-        e = ph ? qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_c), 0u, (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s)
-               : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_c), 0u, 1, 1, s);
+    const int words = !ph ? qii::absmax_tiles_words(rows, cols, true) : blocks <= qii::kMaxBlockWords ? (int)blocks : 0;   // one word per block: nothing to clear
+    if (!slots_zeroed && !words) {   // (the two areas are then neighbours: one launch clears both)
+        e = ph ? qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, 2 * (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s)
+               : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slot_r), 0u, 2, (int)(kSlot / 4), s);
         if (e != hipSuccess) return hip_fail(e, "fill");
     }
     if (!ph) {   // Algorithm 1 needs both rotated maxima before any scale: one read for both, then one for both outputs
-        e = qii::launch_absmax_tiles(src, rows, cols, seed_rht_r, slot_r, seed_rht_c, slot_c, s);
+        e = qii::launch_absmax_tiles(src, rows, cols, seed_rht_r, slot_r, seed_rht_c, slot_c, s, words);
         if (e != hipSuccess) return hip_fail(e, "absmax");
     }
     const qii::PairQuantizeArgs p = pair_arguments(src, rows, cols, mode, seed_rht_r, seed_sr_r, seed_rht_c, seed_sr_c, out_r, out_c, slot_r,
@@ -751,8 +744,12 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
     const bool words_e = ph && pair_e && (T / 128) * (d_out / 128) <= qii::kMaxBlockWords;
     // (the post hoc scheme spreads each running maximum over 64 words, 256 bytes apart, where its blocks are too
     // many for a word each: the four regions are contiguous, so one launch clears all 256 words)
+    // (Algorithm 1: a word per block where every tensor's abs-max blocks are few enough for their slot)
+    const int am_e = !ph && at_once ? qii::absmax_tiles_words(T, d_out, true) : 0;
+    const int am_q[2] = {am_e ? qii::requant_blocks(Rq, Cq, 2, 0) : 0, am_e ? qii::requant_blocks(Rq, Cq, 2, 1) : 0};
+    const bool am_words = am_e > 0 && am_q[0] <= qii::kSlotWords && am_q[1] <= qii::kSlotWords;
     hipError_t e = hipSuccess;
-    if (!ph) e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4, slot_words, s);
+    if (!ph) e = am_words ? hipSuccess : qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4, slot_words, s);
     else if (!words_ok || !words_e)
         e = qii::launch_fill_u32(reinterpret_cast<uint32_t *>(slots), 0u, 4 * (int)qii::kAmaxSpread, (int)qii::kAmaxStrideWords, s);
     if (e != hipSuccess) return hip_fail(e, "fill");
@@ -774,10 +771,10 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
         }
         if (!ph) {
             if (at_once) {
-                e = qii::launch_absmax_tiles(se, T, d_out, sd[0], slots, sd[1], slots + 2 * slot_words, s);
+                e = qii::launch_absmax_tiles(se, T, d_out, sd[0], slots, sd[1], slots + 2 * slot_words, s, am_words ? am_e : 0);
                 if (e != hipSuccess) return hip_fail(e, "absmax");
             }
-            e = qii::launch_absmax_requant(sq, Rq, Cq, 1, rht, slot_q, 2, s);
+            e = qii::launch_absmax_requant(sq, Rq, Cq, 1, rht, slot_q, 2, s, am_words);
             if (e != hipSuccess) return hip_fail(e, "absmax");
         }
         qii::QuantizeArgs q[2] = {};
@@ -787,10 +784,10 @@ qii_status qii_linear_bwd_mode(const void *dY, qii_dtype dt, const qii_nvfp4 *Xq
             q[i].amax = ph ? nullptr : slot_q[i];
             q[i].codes = out[i]->codes; q[i].scales = out[i]->scales; q[i].tensor_scale = out[i]->tensor_scale;
             q[i].tbuf = tb[i]; q[i].amax_accum = ph ? reinterpret_cast<uint32_t *>(slot_q[i]) : nullptr;
-            q[i].amax_words = words_q[i];
+            q[i].amax_words = am_words ? am_q[i] : words_q[i];
             q[i].tiled = !ph && (i == 0 ? tile_dx : tile_dw);   // (not set unless at_once)
         }
-        const int e_words = words_e ? (int)((T / 128) * (d_out / 128)) : 0;
+        const int e_words = words_e ? (int)((T / 128) * (d_out / 128)) : am_words ? am_e : 0;
         if (at_once)
             e = qii::launch_quantize_backward(pair_arguments(se, T, d_out, mode, sd[0], sd[2], sd[1], sd[4], &Eq, &ETq, slots, slots + 2 * slot_words,
                                                              tbuf, tbuf2, e_words, !ph && tile_dx, !ph && tile_dw), q, s);

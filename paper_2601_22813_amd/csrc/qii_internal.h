@@ -56,7 +56,7 @@ struct QuantizeArgs {
     float *tbuf;
     uint32_t *amax_accum;
     int amax_words = 0;      // != 0: one word per block at amax_accum instead (posthoc_words, requant_blocks); in the other
-                             // modes: words at amax whose maximum is the tensor's (requant_amax_words)
+                             // modes: words at amax whose maximum is the tensor's (absmax_words)
     // a second copy of the scale bytes in the main GEMM kernel's tiled layout (nullable; only where
     // rows_kernels_apply, no rotation, C a multiple of 256; room for R rounded up to 256 rows)
     uint8_t *scales_tiled = nullptr;
@@ -71,7 +71,7 @@ struct PairQuantizeArgs {
     Source src;
     int64_t rows, cols;
     int mode;
-    int amax_words;          // QII_MS_EDEN_PH: one word per block ((rows / 128) (cols / 128) of them) per side
+    int amax_words;          // QII_MS_EDEN_PH: one word per block ((rows / 128) (cols / 128) of them) per side; QII_MS_EDEN: words at amax, or 0
     struct Side {
         uint64_t seed_rht, seed_sr;
         const float *amax;
@@ -88,13 +88,17 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s);
 
 bool absmax_tiles_pay(int64_t rows, int64_t cols);
 hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, uint64_t seed_rht_r, float *amax_r, uint64_t seed_rht_c,
-                               float *amax_c, hipStream_t s);
+                               float *amax_c, hipStream_t s, int words = 0);
+int absmax_tiles_words(int64_t rows, int64_t cols, bool both);
 
 // p[i * stride_words] = v for i < count (count <= 256); a kernel, not a memset node, so that the
 // calls can be captured in a HIP graph
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int count, int stride_words, hipStream_t s);
 hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
-                         float *amax /* must hold 0 */, hipStream_t s);
+                         float *amax /* must hold 0, or words (absmax_words) words to write */, hipStream_t s, int words = 0);
+// One word per block of the abs-max pass over a small tensor, in the 256-byte slot: nothing to clear first (a launch of its own,
+// about 2.4 us of a call), 0 where the blocks would be too many or too few for the tensor's size
+int absmax_words(const Source &src, int64_t R, int64_t C, int rht);
 hipError_t launch_rht(const Source &src, int64_t R, int64_t C, uint64_t seed_rht, float *y,
                       float *amax /* nullable, must hold 0 */, hipStream_t s);
 hipError_t launch_quantize(const QuantizeArgs &a, hipStream_t s);
@@ -124,7 +128,8 @@ hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const 
 // tuned kernels for dense sources quantized along their rows (quantize_rows.hip)
 bool rows_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
-                              float *amax, hipStream_t s);
+                              float *amax, hipStream_t s, int words);
+int absmax_rows_words(int64_t R, int64_t C);
 hipError_t launch_quantize_rows(const QuantizeArgs &a, hipStream_t s);
 // a small tensor (no rotation; amax not needed) whose blocks measure it themselves
 bool measures_itself(const QuantizeArgs &q);
@@ -137,13 +142,14 @@ hipError_t launch_forward_quantize(const QuantizeArgs q[2], float *words, hipStr
 // tuned kernels for dense sources quantized along their columns (quantize_cols.hip)
 bool cols_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_cols(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
-                              float *amax, hipStream_t s);
+                              float *amax, hipStream_t s, int words);
+int absmax_cols_words(int64_t R, int64_t C);
 hipError_t launch_quantize_cols(const QuantizeArgs &a, hipStream_t s);
 // a saved NVFP4 tensor quantized along its columns (quantize_requant.hip)
 bool requant_kernels_apply(const Source &src, int64_t R, int64_t C);
 // (one or two tensors in one launch, quantized in the same mode; requant_blocks: blocks of tensor i of such a launch)
 int requant_blocks(const int64_t *R, const int64_t *C, int count, int i);
-// words: one word per block at amax (one tensor, requant_amax_words of them), else one word that must hold 0
+// words: one word per block at amax (requant_blocks of them, at most kSlotWords), else one word that must hold 0
 hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int64_t *C, int rht, const uint64_t *seed_rht,
                                  float *const *amax, int count, hipStream_t s, int words = 0);
 // words that the blocks of the abs-max pass over one such tensor leave: at most 64 (a 256-byte slot), else 0

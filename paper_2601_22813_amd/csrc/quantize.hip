@@ -485,17 +485,36 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int count, int stride_words,
     return hipGetLastError();
 }
 
+// a rotated transposed matrix that the tile kernels take: R columns, C rows
+static Source untransposed(Source src)
+{
+    src.transpose = 0;
+    return src;
+}
+
+static bool tiles_measure_columns(const Source &src, int64_t R, int64_t C, int rht)
+{
+    return rht && src.transpose && pair_kernel_applies(untransposed(src), C, R);
+}
+
+int absmax_words(const Source &src, int64_t R, int64_t C, int rht)
+{
+    if (R == 0 || C == 0) return 0;
+    if (rows_kernels_apply(src, R, C)) return absmax_rows_words(R, C);
+    if (tiles_measure_columns(src, R, C, rht)) return absmax_tiles_words(C, R, false);
+    if (requant_kernels_apply(src, R, C)) return requant_amax_words(src, R, C);
+    return cols_kernels_apply(src, R, C) ? absmax_cols_words(R, C) : 0;
+}
+
 hipError_t launch_absmax(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
-                         float *amax, hipStream_t s)
+                         float *amax, hipStream_t s, int words)
 {
     if (R == 0 || C == 0) return hipSuccess;
-    if (rows_kernels_apply(src, R, C)) return launch_absmax_rows(src, R, C, rht, seed_rht, amax, s);
-    Source plain = src;   // a rotated transposed matrix that the tile kernels take: R columns, C rows
-    plain.transpose = 0;
-    if (rht && src.transpose && pair_kernel_applies(plain, C, R) && absmax_tiles_pay(C, R))
-        return launch_absmax_tiles(plain, C, R, 0, nullptr, seed_rht, amax, s);
-    if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(&src, &R, &C, rht, &seed_rht, &amax, 1, s);
-    if (cols_kernels_apply(src, R, C)) return launch_absmax_cols(src, R, C, rht, seed_rht, amax, s);
+    if (rows_kernels_apply(src, R, C)) return launch_absmax_rows(src, R, C, rht, seed_rht, amax, s, words);
+    if (tiles_measure_columns(src, R, C, rht) && (words || absmax_tiles_pay(C, R)))
+        return launch_absmax_tiles(untransposed(src), C, R, 0, nullptr, seed_rht, amax, s, words);
+    if (requant_kernels_apply(src, R, C)) return launch_absmax_requant(&src, &R, &C, rht, &seed_rht, &amax, 1, s, words);
+    if (cols_kernels_apply(src, R, C)) return launch_absmax_cols(src, R, C, rht, seed_rht, amax, s, words);
     const dim3 grid((unsigned)grid_for(R, C, 256)), block(256);
     return with_loader(src, [&](auto load) {
         using L = decltype(load);

@@ -19,13 +19,13 @@ namespace {
 // pays for itself), and images of one chunk, which leave the LDS for three.  Kernel 16384 x 2048 -> 8192 172.5 -> 157.6 us, 2048 x 2048 -> 5632 29.1 ->
 // 27.6; passes 892 -> 884, 118.1 -> 116.2, 4096 x 4096 -> 4096 234.3 -> 232.9.  (Either alone gains nothing; 55 registers, one column at a
 // time, and four blocks lose what they gain.)  Algorithm 1's 94 registers would spill 22.
-template <int kMode, int kChunks>
+template <int kMode, int kChunks, bool kWords>
 __global__ __launch_bounds__(512, kMode == QII_MS_EDEN_PH ? 6 : 4) void quantize_backward_kernel(PairArgs e, RequantArgs w, RequantArgs x, int n_e, int n_w)
 {
     extern __shared__ __align__(16) uint8_t lds[];   // kChunks images of 32 KiB, the first of them a block's tile of E
     const int block = (int)blockIdx.x;               // (branches on it are uniform)
     if (block < n_e) {
-        pair_block<kMode, true, const PairArgs &>(e, block, lds);
+        pair_block<kMode, true, kWords, const PairArgs &>(e, block, lds);
         return;
     }
     if (kChunks == 1 && threadIdx.x >= 256) return;   // (a wave that has ended takes no part in barriers)
@@ -35,14 +35,14 @@ __global__ __launch_bounds__(512, kMode == QII_MS_EDEN_PH ? 6 : 4) void quantize
     requant_block<kMode, true, kChunks, true, const RequantArgs &>(a, block - n_e - (first ? 0 : n_w), lds);
 }
 
-template <int kMode, int kChunks>
+template <int kMode, int kChunks, bool kWords>
 hipError_t launch(const PairArgs &e, const QuantizeArgs q[2], hipStream_t s)
 {
-    const hipError_t err = allow_dynamic_lds<quantize_backward_kernel<kMode, kChunks>>(kChunks * kImage);
+    const hipError_t err = allow_dynamic_lds<quantize_backward_kernel<kMode, kChunks, kWords>>(kChunks * kImage);
     if (err != hipSuccess) return err;
     const RequantArgs w = requant_args(q[0], kChunks), x = requant_args(q[1], kChunks);
     const int n_e = (int)((e.rows / 128) * (e.cols / 128));
-    hipLaunchKernelGGL((quantize_backward_kernel<kMode, kChunks>), dim3((unsigned)(n_e + w.tiles + x.tiles)), dim3(512), kChunks * kImage, s,
+    hipLaunchKernelGGL((quantize_backward_kernel<kMode, kChunks, kWords>), dim3((unsigned)(n_e + w.tiles + x.tiles)), dim3(512), kChunks * kImage, s,
                        e, w, x, n_e, w.tiles);
     return hipGetLastError();
 }
@@ -57,8 +57,9 @@ hipError_t launch_quantize_backward(const PairQuantizeArgs &e, const QuantizeArg
 {
     const int64_t R[2] = {q[0].R, q[1].R}, C[2] = {q[0].C, q[1].C};
     const PairArgs p = pair_args(e);
-    if (e.mode == QII_MS_EDEN_PH) return launch<QII_MS_EDEN_PH, 1>(p, q, s);
-    return chunks_per_block(R, C, 2) == 2 ? launch<QII_MS_EDEN, 2>(p, q, s) : launch<QII_MS_EDEN, 1>(p, q, s);
+    if (e.mode == QII_MS_EDEN_PH) return launch<QII_MS_EDEN_PH, 1, false>(p, q, s);
+    if (chunks_per_block(R, C, 2) == 2) return p.words ? hipErrorInvalidValue : launch<QII_MS_EDEN, 2, false>(p, q, s);   // (words: small tensors only)
+    return p.words ? launch<QII_MS_EDEN, 1, true>(p, q, s) : launch<QII_MS_EDEN, 1, false>(p, q, s);
 }
 
 }  // namespace qii

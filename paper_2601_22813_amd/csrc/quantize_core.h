@@ -244,6 +244,22 @@ __device__ __forceinline__ float wave_max(float m)
     return m;
 }
 
+// The tensor maximum that an abs-max pass left: one word (words == 0), or one per block of that pass, at most kSlotWords.
+// slot_word before a block's own loads (loads return in order), slot_max where the maximum is needed; all lanes call both.
+constexpr int kSlotWords = 64;   // a 256-byte slot
+
+__device__ __forceinline__ float slot_word(const float *amax, int words)
+{
+    if (words == 0) return 0.0f;   // uniform
+    const int lane = threadIdx.x & 63;
+    return amax[lane < words ? lane : words - 1];
+}
+
+__device__ __forceinline__ float slot_max(const float *amax, int words, float word)
+{
+    return words ? u2f(__builtin_amdgcn_readfirstlane(f2u(wave_max(word)))) : *amax;   // uniform
+}
+
 // The heavy pass of the post hoc scheme folds block maxima into a running maximum.  A device-wide
 // atomic on one address costs about 10 ns however many compute units issue it (the eight L2 caches
 // of the chip are not coherent with one another, so such atomics are resolved on the memory side

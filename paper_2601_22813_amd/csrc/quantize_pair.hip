@@ -5,11 +5,11 @@
 namespace qii {
 namespace {
 
-template <int kMode>
+template <int kMode, bool kWords>
 __global__ __launch_bounds__(512) void quantize_pair_kernel(PairArgs a)
 {
     __shared__ __align__(16) uint8_t tile[kPairImage];
-    pair_block<kMode>(a, (int)blockIdx.x, tile);
+    pair_block<kMode, false, kWords>(a, (int)blockIdx.x, tile);
 }
 
 // Abs-max of a rotated matrix along its columns.  The result word takes one atomic per block, and such atomics on one
@@ -74,7 +74,8 @@ __global__ __launch_bounds__(256 * kGroups) void absmax_tiles_kernel(PairArgs a,
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int i = 1; i < 4 * kGroups; ++i) m = fmaxf(m, wave_m[i]);
-        max_to_global(m, a.c.amax_out);
+        if (a.words) a.c.amax_out[blockIdx.x] = f2u(m);
+        else max_to_global(m, a.c.amax_out);
     }
 }
 
@@ -156,7 +157,12 @@ __global__ __launch_bounds__(512, 4) void absmax_pair_kernel(PairArgs a, int til
     m = wave_max(__builtin_fmaf(m, kInvSqrt128, 0.0f));   // the scaling the rotation left out
     if (lane == 0) wave_m[wave_id] = m;
     __syncthreads();
-    if (t < 2) max_to_global(fmaxf(fmaxf(wave_m[4 * t], wave_m[4 * t + 1]), fmaxf(wave_m[4 * t + 2], wave_m[4 * t + 3])), t == 0 ? a.r.amax_out : a.c.amax_out);
+    if (t < 2) {
+        m = fmaxf(fmaxf(wave_m[4 * t], wave_m[4 * t + 1]), fmaxf(wave_m[4 * t + 2], wave_m[4 * t + 3]));
+        uint32_t *out = t == 0 ? a.r.amax_out : a.c.amax_out;
+        if (a.words) out[blockIdx.x] = f2u(m);
+        else max_to_global(m, out);
+    }
 }
 
 hipError_t launch_absmax_pair(const PairArgs &a, int tiles, hipStream_t s)
@@ -194,8 +200,9 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
 {
     const PairArgs a = pair_args(p);
     const dim3 grid((unsigned)((p.rows / 128) * (p.cols / 128))), block(512);
-    if (p.mode == QII_MS_EDEN_PH) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN_PH>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN>), grid, block, 0, s, a);
+    if (p.mode == QII_MS_EDEN_PH) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN_PH, false>), grid, block, 0, s, a);
+    else if (a.words) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN, false>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -213,21 +220,36 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
 //  2048 tiles                                     4096 x 8192 (local) 41.1 : 37.5
 //  2112 and 2176 tiles  8448 x 4096 52.8 : 49.1  2176 x 16384 (local) 42.8 : 44.6
 //  2560 tiles 10240 x 4096 61.0 : 52.9            5120 x 8192 (local) 47.5 : 45.2
+static bool columns_local(int64_t rows, int64_t cols) { return ((rows + 511) / 512) % 8 == 0 || (cols + 31) / 32 % 256 == 0; }
+
 bool absmax_tiles_pay(int64_t rows, int64_t cols)
 {
     const int64_t tiles = (rows / 128) * (cols / 128);
     if (tiles <= 128) return true;
-    const bool local = ((rows + 511) / 512) % 8 == 0 || (cols + 31) / 32 % 256 == 0;
-    if (!local) return tiles >= 1280;
+    if (!columns_local(rows, cols)) return tiles >= 1280;
     return (tiles > 1792 && tiles <= 2048) || tiles >= 2560;
 }
 
-// max |rotated| along the columns and, amax_r not null, along the rows of a matrix that pair_kernel_applies to; the
-// words must hold 0
+// A word per block, at most kSlotWords blocks, and no clearing launch.  Both orientations: a tile a block.  Along the columns alone a
+// block has one, two or four groups and a tile each.  Whole MS-EDEN calls, us, clearing and atomics (the form above) : words: both 128 x 128
+// 15.5 : 11.9, 1024 x 1024 16.0 : 12.9; columns 1024 x 1024 12.9 : 11.2, 2048 x 1024 13.5 : 12.5, 2048 x 2048 16.7 : 15.3, but 512 x 8192
+// (local) 14.8 : 14.9; 128 tiles in blocks of four groups 13.6 : 14.0.
+int absmax_tiles_words(int64_t rows, int64_t cols, bool both)
+{
+    const int64_t tiles = (rows / 128) * (cols / 128);
+    if (both) return tiles <= kSlotWords ? (int)tiles : 0;
+    if (tiles > 4 * kSlotWords || (tiles > 2 * kSlotWords && columns_local(rows, cols))) return 0;
+    const int64_t groups = tiles <= kSlotWords ? 1 : tiles <= 2 * kSlotWords ? 2 : 4;
+    return (int)((tiles + groups - 1) / groups);
+}
+
+// max |rotated| along the columns and, amax_r not null, along the rows of a matrix that pair_kernel_applies to; words:
+// absmax_tiles_words of them at each, else (words == 0) one word that must hold 0
 hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, uint64_t seed_rht_r, float *amax_r, uint64_t seed_rht_c,
-                               float *amax_c, hipStream_t s)
+                               float *amax_c, hipStream_t s, int words)
 {
     PairArgs a = {};
+    a.words = words;
     a.x = reinterpret_cast<const uint16_t *>(src.x);
     a.ld = src.ld; a.rows = rows; a.cols = cols;
     a.tiles_x = (int)(cols / 128);
@@ -238,7 +260,8 @@ hipError_t launch_absmax_tiles(const Source &src, int64_t rows, int64_t cols, ui
     a.c.amax_out = reinterpret_cast<uint32_t *>(amax_c);
     const int tiles = (int)((rows / 128) * (cols / 128));
     if (amax_r) return launch_absmax_pair(a, tiles, s);
-    return tiles <= 512 ? launch_absmax_columns<1>(a, tiles, s) : launch_absmax_columns<4>(a, tiles, s);
+    if (tiles <= (words ? kSlotWords : 512)) return launch_absmax_columns<1>(a, tiles, s);
+    return words && tiles <= 2 * kSlotWords ? launch_absmax_columns<2>(a, tiles, s) : launch_absmax_columns<4>(a, tiles, s);
 }
 
 }  // namespace qii

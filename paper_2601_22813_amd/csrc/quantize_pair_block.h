@@ -42,7 +42,7 @@ struct PairArgs {
     int64_t ld;            // elements
     int64_t rows, cols;    // of x; both multiples of 128
     int tiles_x;           // tiles along a row of x
-    int words;             // the maxima go to one word per block
+    int words;             // QII_MS_EDEN_PH: the maxima go to one word per block; QII_MS_EDEN and abs-max pass: see slot_max
     PairSide r, c;         // r: Q(x), rows x cols;  c: Q(x^T), cols x rows
 };
 
@@ -59,10 +59,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region(const void *base, int64
 // 46.1 -> 43.2, 69.4 -> 65.3.)
 constexpr int kPairImage = 128 * 256;   // LDS bytes of the tile
 
-// tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it).  Args: by value, or by reference
+// tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it); kWords: Algorithm 1's maxima are those
+// of a.words words each (as a run-time question 0.7 % of a backward pass).  Args: by value, or by reference
 // in a kernel that holds other arguments too (the addresses are then formed otherwise: 0.1 us of a small pair's call by reference,
 // but 1 to 2 % of a backward pass by value)
-template <int kMode, bool kMayTile = false, class Args = const PairArgs>
+template <int kMode, bool kMayTile = false, bool kWords = false, class Args = const PairArgs>
 __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
 {
     __shared__ float inv_r[128], inv_c[128];
@@ -72,6 +73,9 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
     const bool take_rows = wave_id < 4;   // (wave-uniform)
     const int ty = block / a.tiles_x, tx = block - ty * a.tiles_x;
     const int64_t row0 = (int64_t)ty * 128, col0 = (int64_t)tx * 128;
+
+    const int words = kMode == QII_MS_EDEN && kWords ? a.words : 0;
+    const float word_r = slot_word(a.r.amax, words), word_c = slot_word(a.c.amax, words);
 
     // ---- the tile's loads first: 4 pieces of 16 bytes per thread, 16 threads per row
     u32x4 w[4];
@@ -85,8 +89,8 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
     // ---- tensor constants and reciprocal tables of the two sides while the loads are in flight
     TensorConsts tcr = TensorConsts{}, tcc = TensorConsts{};
     if (kMode == QII_MS_EDEN) {
-        tcr = tensor_consts(QII_MS_EDEN, *a.r.amax);
-        tcc = tensor_consts(QII_MS_EDEN, *a.c.amax);
+        tcr = tensor_consts(QII_MS_EDEN, slot_max(a.r.amax, words, word_r));
+        tcc = tensor_consts(QII_MS_EDEN, slot_max(a.c.amax, words, word_c));
         if (block == 0 && t == 0) {
             *a.r.tensor_scale = tcr.x32;
             *a.c.tensor_scale = tcc.x32;

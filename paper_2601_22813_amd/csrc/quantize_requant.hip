@@ -90,7 +90,7 @@ int requant_amax_words(const Source &src, int64_t R, int64_t C)
 {
     if (!requant_kernels_apply(src, R, C)) return 0;
     const int n = requant_blocks(&R, &C, 1, 0);
-    return n <= 64 ? n : 0;
+    return n <= kSlotWords ? n : 0;
 }
 
 int requant_blocks(const int64_t *R, const int64_t *C, int count, int i)
@@ -107,7 +107,7 @@ hipError_t launch_absmax_requant(const Source *src, const int64_t *R, const int6
     for (int i = 0; i < count; ++i) {
         a[i] = make_args(src[i], R[i], C[i], seed_rht[i], 0, ch);
         a[i].amax_out = reinterpret_cast<uint32_t *>(amax[i]);
-        a[i].words = words;
+        a[i].words = words ? a[i].tiles : 0;
         all += a[i].tiles;
     }
     // at most 512 blocks, shared out by size

@@ -1,0 +1,70 @@
+"""Algorithm 1 and the other one-pass modes on small tensors: the blocks of the abs-max pass leave a word each in a 256-byte slot
+that nobody clears.  The largest entry in the first, a middle and the last tile, in a workspace of exactly that slot which held NaN before, gives
+what a call gives that is told the maximum: at one block, where 64 words are just enough and where they no longer are (clearing and
+atomics again), for each kernel that measures (rows; columns by tiles of one, two and four groups to a block; columns by
+32-column blocks), and for both orientations of a pair."""
+import pytest
+import torch
+
+from paper_2601_22813_amd import binding as qii
+
+pytestmark = pytest.mark.gpu
+
+
+def nan_slots(n):
+    """n slots of 256 bytes that hold NaN, and a guard behind them."""
+    return torch.full((256 * n + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+
+
+def spiked(rows, cols, dtype, r, c):
+    g = torch.Generator(device="cuda").manual_seed(rows + cols)
+    x = 0.1 * torch.randn((rows, cols), device="cuda", generator=g)
+    x[r, c] = 400.0
+    return x.to(dtype)
+
+
+def places(rows, cols):
+    return (0, 0), (rows // 2, cols // 2), (rows - 1, cols - 1)
+
+
+def same(a, b):
+    assert torch.equal(a.tensor_scale, b.tensor_scale) and torch.equal(a.scales, b.scales) and torch.equal(a.codes, b.codes)
+
+
+@pytest.mark.parametrize("rows,cols,transpose,mode,rht,dtype", [
+    (1, 128, False, qii.MS_EDEN, 128, torch.bfloat16), (1021, 1024, False, qii.MS_EDEN, 128, torch.bfloat16),
+    (1040, 1024, False, qii.SR, 128, torch.float32), (2048, 2048, False, qii.MS_EDEN, 128, torch.bfloat16),
+    (2049, 2048, False, qii.MS_EDEN, 128, torch.bfloat16), (67, 9216, False, qii.SR, 128, torch.float32),
+    (2000, 1552, False, qii.RTN_46, 0, torch.float32), (1000, 1552, False, qii.RTN, 0, torch.bfloat16),
+    (128, 128, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1024, True, qii.MS_EDEN, 128, torch.bfloat16),
+    (640, 1664, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 2048, True, qii.SR, 128, torch.bfloat16),
+    (384, 5504, True, qii.MS_EDEN, 128, torch.bfloat16), (2048, 2048, True, qii.MS_EDEN, 128, torch.bfloat16),
+    (512, 8192, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1000, True, qii.SR, 128, torch.float32),
+    (1024, 1024, True, qii.MS_EDEN, 128, torch.float32), (1024, 1026, True, qii.MS_EDEN, 128, torch.float32),
+    (1920, 520, True, qii.RTN, 0, torch.bfloat16)])
+def test_words_of_one_tensor(rows, cols, transpose, mode, rht, dtype):
+    R, C = (cols, rows) if transpose else (rows, cols)
+    for r, c in places(rows, cols):
+        x = spiked(rows, cols, dtype, r, c)
+        out, given = qii.NVFP4Tensor.empty(R, C), qii.NVFP4Tensor.empty(R, C)
+        w, top = nan_slots(1), torch.empty(1, device="cuda")
+        qii.qii_quantize_nvfp4(x, transpose, mode, rht, 21, 22, None, out, w[:256])
+        qii.qii_absmax(x, transpose, rht, 21, top)
+        qii.qii_quantize_nvfp4(x, transpose, mode, rht, 21, 22, top, given, None)
+        same(out, given)
+        assert bool((w[256:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("rows,cols", [(128, 128), (1024, 1024), (640, 1664), (2048, 4096)])
+def test_words_of_a_pair(rows, cols):
+    for r, c in places(rows, cols):
+        x = spiked(rows, cols, torch.bfloat16, r, c)
+        pair = qii.NVFP4Tensor.empty(rows, cols), qii.NVFP4Tensor.empty(cols, rows)
+        w = nan_slots(2)
+        qii.qii_quantize_pair_nvfp4(x, qii.MS_EDEN, 21, 22, 23, 24, *pair, w[:512])
+        for out, transpose, seed in ((pair[0], False, 21), (pair[1], True, 23)):
+            given, top = qii.NVFP4Tensor.empty(out.rows, out.cols), torch.empty(1, device="cuda")
+            qii.qii_absmax(x, transpose, 128, seed, top)
+            qii.qii_quantize_nvfp4(x, transpose, qii.MS_EDEN, 128, seed, seed + 1, top, given, None)
+            same(out, given)
+        assert bool((w[512:] == 0xFF).all())
