@@ -296,7 +296,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(Loader load, int64_t R, i
 // Second pass of the post hoc scheme (Sec. 7): scales only.  x^FP32 = max|x| / (s * 256); the
 // byte of group (row, g) is SR_E4M3(t / x^FP32) with the 20-bit draw of (seed, row, g), the one
 // Algorithm 1 uses.  One thread takes 4 rows x 4 groups: four Philox calls (a call serves the
-// four rows of one group) and, when whole, one 16-byte load and one 4-byte store per row.  The vector unit
+// four rows of one group) and, when whole, one 16-byte load and one 4-byte store per row; or (kOneGroup) 4 rows x 1 group, and
+// four neighbouring lanes exchange their bytes and store 4 of a row each.  The vector unit
 // bounds it (the Philox calls above all).  The divisions take the short exact sequence, and the roundings the
 // form without subnormals, wherever a whole wave's operands allow.  Up to four tensors in one launch (the backward
 // pass's, quantize_backward.hip); a launch for one has its arguments at a fixed place, with no scalar load that waits for another.
@@ -312,8 +313,8 @@ struct ScalesArgs {
 
 typedef uint32_t quad_t __attribute__((ext_vector_type(4)));
 
-// four scale bytes of one row
-__device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_t draw[4][4], int it, float x32, float rd, bool in_range)
+// four scale bytes
+__device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_t draw[4], float x32, float rd, bool in_range)
 {
     float u[4];
     bool odd = !in_range;
@@ -330,17 +331,28 @@ __device__ __forceinline__ uint32_t scale_bytes4(const float t[4], const uint32_
     bool small = false;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const uint32_t bn = ((f2u(u[j]) + draw[j][it]) >> 20) - 960u;
+        const uint32_t bn = ((f2u(u[j]) + draw[j]) >> 20) - 960u;
         b[j] = bn > 0x7Eu ? 0x7Eu : bn;
         small = small || !(u[j] >= 0x1p-6f);
     }
     if (__builtin_amdgcn_ballot_w64(small) != 0ull) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) b[j] = e4m3_sr(u[j], draw[j][it]);
+        for (int j = 0; j < 4; ++j) b[j] = e4m3_sr(u[j], draw[j]);
     }
     return b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24);
 }
 
+// byte l of the four lanes' words, in the order of the lanes (l: the lane's place in its four)
+__device__ __forceinline__ uint32_t transpose_bytes4(uint32_t w, int l)
+{
+    const uint32_t p = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w, kDppXor1, 0xF, 0xF, true);
+    const uint32_t x = __builtin_amdgcn_perm(p, w, (l & 1) ? 0x03070105u : 0x06020400u);
+    const uint32_t q = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kDppXor2, 0xF, 0xF, true);
+    return __builtin_amdgcn_perm(q, x, (l & 2) ? 0x03020706u : 0x05040100u);
+}
+
+// kOneGroup: see launch_posthoc_scales
+template <bool kOneGroup>
 __device__ __forceinline__ void scales_block(const ScalesArgs a, int64_t block)
 {
     __shared__ float wave_m[4];
@@ -370,6 +382,28 @@ __device__ __forceinline__ void scales_block(const ScalesArgs a, int64_t block)
     const bool in_range = x32 > 0x1p-60f && x32 < 0x1p60f;
     const int64_t idx = block * 256 + threadIdx.x, G = a.G;
     if (idx == 0) *a.tensor_scale = x32;
+    uint8_t *const scales = a.scales;
+    auto place = [&](int64_t row, int64_t g0) {
+        return a.tiled_ksn ? scales + (((row >> 8) * a.tiled_ksn + (g0 >> 4)) * 256 + (row & 255)) * 16 + (g0 & 15) : scales + row * G + g0;
+    };
+    if (kOneGroup) {   // (G a multiple of 4: four neighbouring lanes have four neighbouring groups of the same rows)
+        const int64_t total = ((a.R + 3) / 4) * G;
+        const bool live = idx < total;
+        const uint32_t quad = live ? (uint32_t)idx / (uint32_t)G : 0u, g = live ? (uint32_t)idx - quad * (uint32_t)G : 0u;
+        float t[4];
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int64_t row = (int64_t)quad * 4 + it;
+            t[it] = live && row < a.R ? a.tbuf[row * G + g] : 0.0f;
+        }
+        const U4 w = philox_seeded(a.seed_sr, g, quad, 0, kStreamScale);
+        const uint32_t draw[4] = {w.x >> 12, w.y >> 12, w.z >> 12, w.w >> 12};
+        const int l = threadIdx.x & 3;
+        const uint32_t b = transpose_bytes4(scale_bytes4(t, draw, x32, rd, in_range), l);   // (all lanes)
+        const int64_t row = (int64_t)quad * 4 + l;
+        if (live && row < a.R) *reinterpret_cast<uint32_t *>(place(row, g & ~3u)) = b;
+        return;
+    }
     const int64_t gq = (G + 3) / 4;
     const int64_t total = ((a.R + 3) / 4) * gq;
     const bool live = idx < total;
@@ -396,10 +430,9 @@ __device__ __forceinline__ void scales_block(const ScalesArgs a, int64_t block)
         const bool ok = live && row < a.R;
         if (whole) {
             const float tt[4] = {t[it].x, t[it].y, t[it].z, t[it].w};
-            const uint32_t b = scale_bytes4(tt, draw, it, x32, rd, in_range);   // (all lanes: it votes)
-            uint8_t *dst = a.tiled_ksn ? a.scales + (((row >> 8) * a.tiled_ksn + (g0 >> 4)) * 256 + (row & 255)) * 16 + (g0 & 15)
-                                       : a.scales + row * G + g0;
-            if (ok) *reinterpret_cast<uint32_t *>(dst) = b;
+            const uint32_t d[4] = {draw[0][it], draw[1][it], draw[2][it], draw[3][it]};
+            const uint32_t b = scale_bytes4(tt, d, x32, rd, in_range);   // (all lanes: it votes)
+            if (ok) *reinterpret_cast<uint32_t *>(place(row, g0)) = b;
         } else if (ok) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -414,7 +447,7 @@ struct ScalesLaunch {
     int end[kTensors];   // tensor i's blocks end here
 };
 
-template <int kTensors>
+template <int kTensors, bool kOneGroup>
 __global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTensors> l)
 {
     const int id = (int)blockIdx.x;
@@ -426,17 +459,18 @@ __global__ __launch_bounds__(256) void posthoc_scales_kernel(ScalesLaunch<kTenso
             a = l.a[i + 1];
             begin = l.end[i];
         }
-    scales_block(a, id - begin);
+    scales_block<kOneGroup>(a, id - begin);
 }
 
 // (two tensors: as parameters of their own both are loaded at once and chosen by value, where the form above chooses an
 // address first: 0.1 us of a small pair's call)
+template <bool kOneGroup>
 __global__ __launch_bounds__(256) void posthoc_scales2_kernel(ScalesArgs a0, ScalesArgs a1, int n0)
 {
     const bool first = (int)blockIdx.x < n0;   // uniform
     ScalesArgs a = a0;
     if (!first) a = a1;
-    scales_block(a, (int64_t)blockIdx.x - (first ? 0 : n0));
+    scales_block<kOneGroup>(a, (int64_t)blockIdx.x - (first ? 0 : n0));
 }
 
 __global__ void dequantize_kernel(const uint8_t *codes, const uint8_t *scales, const float *ts,
@@ -569,7 +603,7 @@ int posthoc_words(const Source &src, int64_t R, int64_t C)
     return n <= kMaxBlockWords ? (int)n : 0;
 }
 
-template <int kTensors>
+template <int kTensors, bool kOneGroup>
 static hipError_t launch_scales(const PosthocScales *p, int count, hipStream_t s)
 {
     ScalesLaunch<kTensors> l = {};
@@ -581,19 +615,37 @@ static hipError_t launch_scales(const PosthocScales *p, int count, hipStream_t s
             l.a[i] = ScalesArgs{p[i].tbuf, p[i].amax, p[i].words ? p[i].words : p[i].supplied ? 1 : (int)kAmaxSpread,
                                 p[i].words ? 1 : (int)kAmaxStrideWords, p[i].R, G, p[i].seed_sr, p[i].scales, p[i].tensor_scale,
                                 p[i].tiled ? p[i].C / 256 : (int64_t)0};
-            blocks += (((p[i].R + 3) / 4) * ((G + 3) / 4) + 255) / 256;
+            blocks += (((p[i].R + 3) / 4) * (kOneGroup ? G : (G + 3) / 4) + 255) / 256;
         }
         l.end[i] = (int)blocks;
     }
     if (blocks == 0) return hipSuccess;
-    if constexpr (kTensors == 2) hipLaunchKernelGGL(posthoc_scales2_kernel, dim3((unsigned)blocks), dim3(256), 0, s, l.a[0], l.a[1], l.end[0]);
-    else hipLaunchKernelGGL(posthoc_scales_kernel<kTensors>, dim3((unsigned)blocks), dim3(256), 0, s, l);
+    if constexpr (kTensors == 2) hipLaunchKernelGGL(posthoc_scales2_kernel<kOneGroup>, dim3((unsigned)blocks), dim3(256), 0, s, l.a[0], l.a[1], l.end[0]);
+    else hipLaunchKernelGGL((posthoc_scales_kernel<kTensors, kOneGroup>), dim3((unsigned)blocks), dim3(256), 0, s, l);
     return hipGetLastError();
 }
 
+template <bool kOneGroup>
+static hipError_t launch_scales_of(const PosthocScales *p, int count, hipStream_t s)
+{
+    return count == 1 ? launch_scales<1, kOneGroup>(p, count, s) : count == 2 ? launch_scales<2, kOneGroup>(p, count, s) : launch_scales<4, kOneGroup>(p, count, s);
+}
+
+// Four rows x one group a thread: up to 2 M groups in all, where threads are few and the four groups of the other form one after the other
+// are most of the pass; beyond, every block's own read of the maximum words and its divisions cost more than that.  Whole calls, us, four
+// groups : one: 512 x 512 -> 512 backward 18.4 : 17.1, 1024 x 1024 -> 1024 22.5 : 21.0; pair 512 x 512 11.7 : 10.3, 4096 x 2048 17.1 :
+// 15.9, 4096 x 4096 (2 M groups) 24.4 : 23.8, 4096 x 6144 32.0 : 32.9; along rows 2048 x 2048 11.2 : 9.5, 8192 x 4096 (2 M) 25.2 :
+// 25.0, 6144 x 8192 35.6 : 36.6, 8192 x 8192 45.3 : 47.1.
 hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t s)
 {
-    return count == 1 ? launch_scales<1>(p, count, s) : count == 2 ? launch_scales<2>(p, count, s) : launch_scales<4>(p, count, s);
+    bool one = true;
+    int64_t groups = 0;
+    for (int i = 0; i < count; ++i) {
+        one = one && p[i].C % 64 == 0;   // (groups in fours)
+        groups += (p[i].R + 3) / 4 * 4 * (p[i].C / 16);
+    }
+    if (one && groups <= (int64_t)2 << 20) return launch_scales_of<true>(p, count, s);
+    return launch_scales_of<false>(p, count, s);
 }
 
 hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const float *ts,

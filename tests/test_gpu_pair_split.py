@@ -8,7 +8,7 @@ import torch
 from paper_2601_22813_amd import binding as qii
 from paper_2601_22813_amd import synth
 
-from gpu_util import to_dev, ws
+from gpu_util import assert_nv_equal, to_dev, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -53,3 +53,26 @@ def test_every_block_word_counts(rows, cols):
             qii.qii_quantize_nvfp4(y, transpose, qii.MS_EDEN_PH, 128, seed, seed + 1, top, given, size)
             for t in (alone, both):
                 assert torch.equal(t.codes, given.codes) and torch.equal(t.scales, given.scales) and torch.equal(t.tensor_scale, given.tensor_scale)
+
+
+@pytest.mark.parametrize("rows,cols,rht", [(1, 128, 128), (2, 64, 0), (3, 128, 128), (6, 192, 0), (5, 48, 0), (1001, 1024, 128), (4096, 8192, 128), (4100, 8192, 128)])
+def test_scale_bytes_by_one_group_and_by_four(oracle, rows, cols, rht):
+    """Post hoc scheme: a thread of the scales pass takes four rows of one group (groups a multiple of four, up to 2 M of them: 4096 x 8192) or of
+    four groups (48 columns, 4100 x 8192); rows that are no multiple of four, and fewer than four."""
+    x = synth.student_t_bf16((rows, cols), 3, 0.1, seed=rows + cols)
+    out = qii.NVFP4Tensor.empty(rows, cols)
+    w = ws(qii.qii_quantize_posthoc_workspace_bytes(rows, cols))
+    w.fill_(0x7E)
+    qii.qii_quantize_nvfp4(to_dev(x), False, qii.MS_EDEN_PH, rht, 31, 32, None, out, w)
+    if rows * cols > 1 << 22:   # the oracle on a part: the scale bytes of the last rows depend on the tensor's maximum only
+        tail = rows // 4 * 4 - 8
+        top = torch.empty(1, device="cuda")
+        qii.qii_absmax(to_dev(x), False, rht, 31, top)
+        given = qii.NVFP4Tensor.empty(rows, cols)
+        qii.qii_quantize_nvfp4(to_dev(x), False, qii.MS_EDEN_PH, rht, 31, 32, top, given, w)
+        part = qii.NVFP4Tensor.empty(tail, cols)   # (2 M groups and more less two rows of threads: the other form or the same)
+        qii.qii_quantize_nvfp4(to_dev(x[:tail]), False, qii.MS_EDEN_PH, rht, 31, 32, top, part, w)
+        assert torch.equal(out.scales, given.scales) and torch.equal(out.tensor_scale, given.tensor_scale)
+        assert torch.equal(out.scales[:tail], part.scales) and torch.equal(out.codes[:tail], part.codes)
+        return
+    assert_nv_equal(out, oracle.quantize(x, qii.MS_EDEN_PH, rht_group=rht, seed_rht=31, seed_sr=32), "rows")
