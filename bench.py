@@ -617,7 +617,7 @@ def main() -> int:
                     "the kernel runs within 10 % of its own loads and stores without arithmetic (profiles/microbench_summary.txt)",
         },
         "roofline_gemm": {
-            "kernel": f"gemm_kernel_v4<bf16 out> M={T} N={d_out} K={d_in} (incl. the scale re-tiling launch)",
+            "kernel": f"gemm_kernel_tiles<bf16 out> M={T} N={d_out} K={d_in} (incl. the scale re-tiling launch)",
             "bound": "mfma", "achieved": round(gemm_tflops, 1), "peak": MFMA_F16_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": round(gemm_tflops / MFMA_F16_PEAK_TFLOPS, 4),
         },
