@@ -11,7 +11,7 @@
 //
 // Three families of kernels share this scheme (price_routes picks one): gemm_kernel_v4, the main one
 // (K a multiple of 256, scale bytes re-tiled into a workspace, LDS-direct loads, explicit
-// software pipeline); gemm_kernel_v2 (K a multiple of 128, no workspace); the small-tile kernels
+// software pipeline), and gemm_kernel_tiles, whose blocks take several of its tiles; gemm_kernel_v2 (K a multiple of 128, no workspace); the small-tile kernels
 // of gemm_small.hip (any K that is a multiple of 16, NVFP4's own rule, no workspace).
 //
 // Tiling of the two kernels here: 256 x 256 block tile, K tile 128 or 256, 4 waves (2 x 2) each owning 128 x 128 =
