@@ -118,7 +118,7 @@ struct PosthocScales {
 };
 hipError_t launch_posthoc_scales(const PosthocScales *p, int count, hipStream_t s);
 // number of blocks of the heavy pass that launch_quantize would run for this source, when it can leave one
-// word per block (at most 1024 of them, 4 KiB); else 0
+// word per block (at most kMaxBlockWords, 16 KiB); else 0
 int posthoc_words(const Source &src, int64_t R, int64_t C);
 int rows_blocks(int64_t R, int64_t C);
 int rows_per_wave(int64_t R, int64_t C, int mode);   // 4, or 1 where the tensor is small
