@@ -623,7 +623,7 @@ qii_status qii_linear_fwd_amax(const void *X, const void *W, qii_dtype dt, int64
     // When the GEMM will take its main kernel the two quantizers also write their scale bytes straight
     // into the GEMM workspace in that kernel's tiled layout: no re-tiling launch.
     uint8_t *gws = p + kForwardWords;
-    const bool tile = qii::gemm_reads_tiled_scales(T, d_out, d_in, Y, d_out, y_dt == QII_BF16) && qii::rows_kernels_apply(sx, T, d_in) && qii::rows_kernels_apply(sw, d_out, d_in);
+    const bool tile = qii::gemm_reads_tiled_scales(*Xq, *Wq, Y, d_out, y_dt == QII_BF16) && qii::rows_kernels_apply(sx, T, d_in) && qii::rows_kernels_apply(sw, d_out, d_in);
     uint8_t *x_tiled = tile ? gws : nullptr, *w_tiled = tile ? gws + (T + 255) / 256 * 256 * (d_in / 16) : nullptr;
     if (qii::forward_quantize_applies(sx, T, sw, d_out, d_in)) {
         qii::QuantizeArgs q[2] = {};

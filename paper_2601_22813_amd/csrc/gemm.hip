@@ -1167,11 +1167,11 @@ struct Prices {
     Route best;
 };
 
-// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run.  Blocks that take several tiles: a round's bf16 stores leave beside
+// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run.  direct: gemm_wide_applies.  Blocks that take several tiles: a round's bf16 stores leave beside
 // the next round's products, 3.3 us less a round than the plan has it (8192 x 6144 x 256 37.9 us, where 128 x 128 tiles take 42.3; 8192 x 8192
 // x 256 48.9 : 56.3, 16384 x 8192 x 256 84.5 : 111); f32 results take all of a round's figure at short K (memory: 16384 x 8192 x 256 118.8 us for
 // 537 MB).
-static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile, const void *C, int64_t ldc, int c_is_bf16)
+static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile, bool direct, const void *C, int64_t ldc, int c_is_bf16)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
     const bool any = K % BK4 != 0;
@@ -1183,7 +1183,7 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.49 + 0.55 * last : 2.6 + 0.53 * last);
     const double us128 = 4.45 + (any ? 0.74 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.276 : 1.0);
     const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
-    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : 0.935));
+    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : direct ? 0.935 : 1.0));
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     const bool narrow = K <= kMaxNarrowK;
@@ -1198,10 +1198,11 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     return p;
 }
 
-bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K, const void *C, int64_t ldc, int c_is_bf16)
+bool gemm_reads_tiled_scales(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, int64_t ldc, int c_is_bf16)
 {
+    const int64_t M = A.rows, N = B.rows, K = A.cols;
     return K % BK4 == 0 && K <= kMaxMainK && M > 0 && N > 0 &&
-           price_routes(M, N, K, gemm_workspace_bytes(M, N, K), false, C, ldc, c_is_bf16).best == kRouteMain;
+           price_routes(M, N, K, gemm_workspace_bytes(M, N, K), false, gemm_wide_applies(A, B), C, ldc, c_is_bf16).best == kRouteMain;
 }
 
 // whether the main kernel can run, and the prices, for operands and a workspace as launch_gemm has them
@@ -1214,7 +1215,7 @@ static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, i
     // (K: offsets within a tile's rows stay below 2^31)
     const bool main_ok = K % BK4 == 0 && K <= kMaxMainK && ws && ws_bytes >= scales_workspace_bytes(M, N, K) &&
                          (reinterpret_cast<uintptr_t>(ws) & 15) == 0 && a_ok && b_ok;
-    return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10), C, ldc, c_is_bf16);
+    return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10), gemm_wide_applies(A, B), C, ldc, c_is_bf16);
 }
 
 static Prices test_prices(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)

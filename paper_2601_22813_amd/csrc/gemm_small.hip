@@ -13,7 +13,7 @@
 //                         or one wave of 128 x 128 (4, 4) per group, 4 groups (one block per unit);
 //   64 x 64 block tile:   one wave of 64 x 64 (2, 2) per group, 4 groups.
 //
-// Operands are staged through registers (global -> VGPR -> LDS) but for the 4 x 4 form at K a multiple of 256 (gemm_wide_kernel): a tile is
+// Operands are staged through registers (global -> VGPR -> LDS) but for the 4 x 4 form where gemm_wide_applies (gemm_wide_kernel): a tile is
 // small enough for that (at most 36 registers), the next tile's loads then stay in flight for a whole tile's time, and a ragged K
 // needs no padding of the operands: codes and scales beyond K are staged as zeros.  The scale bytes are
 // read row-major or in the tiled layout, whichever the operand has: no re-tiling launch, no workspace.
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
     // fragments are in registers by then: all reads of this tile's stage are done, and the first slice of
     // the next tile is read while the rest is multiplied.
     const int ktiles = (int)((g.K + BK - 1) / BK);
-    const int partial = kAnyK && g.K % BK != 0 ? ktiles - 1 : -1;   // the tile that K cuts
+    const int partial = kAnyK ? ktiles - 1 : -1;   // the tile that K cuts
     float ts_a, ts_b;
     auto tensor_scales = [&]() {   // requested behind the first loads, not before them and not when the epilogue needs them
         __builtin_amdgcn_sched_barrier(0);
@@ -748,8 +748,9 @@ hipError_t launch_kernel(int blocks, int threads, int lds, const SmallArgs *g, i
     return hipGetLastError();
 }
 
+// direct: gemm_wide_applies to every product
 template <bool kBf16Out, class G>
-hipError_t launch(SmallArgs *g, int count, hipStream_t s)
+hipError_t launch(SmallArgs *g, int count, bool direct, hipStream_t s)
 {
     int blocks = 0;
     for (int i = 0; i < count; ++i) {
@@ -759,13 +760,8 @@ hipError_t launch(SmallArgs *g, int count, hipStream_t s)
     }
     if constexpr (G::MT == 4) {
         constexpr int lds = kWideStages * G::kStage > G::kLds ? kWideStages * G::kStage : G::kLds;
-        bool direct = g[0].K % BK == 0;
-        for (int i = 0; i < count; ++i)   // (offsets below 2^31, 16-byte pieces of scale bytes where they are row-major)
-            direct = direct && g[i].K <= kMaxWideK && ((reinterpret_cast<uintptr_t>(g[i].as.s) | reinterpret_cast<uintptr_t>(g[i].bs.s)) & 15) == 0;
-        // (the form for any K otherwise: it takes whole tiles as well)
-        return direct ? launch_kernel<gemm_wide_kernel<kBf16Out>>(blocks, G::kThreads, lds, g, count, s)
-                      : launch_kernel<gemm_small_kernel<kBf16Out, G, true>>(blocks, G::kThreads, G::kLds, g, count, s);
-    } else
+        if (direct) return launch_kernel<gemm_wide_kernel<kBf16Out>>(blocks, G::kThreads, lds, g, count, s);
+    }
     return g[0].K % BK != 0 ? launch_kernel<gemm_small_kernel<kBf16Out, G, true>>(blocks, G::kThreads, G::kLds, g, count, s)
                             : launch_kernel<gemm_small_kernel<kBf16Out, G, false>>(blocks, G::kThreads, G::kLds, g, count, s);
 }
@@ -777,9 +773,18 @@ ScaleView view(const qii_nvfp4 &t, bool tiled)
 
 }  // namespace
 
+// Whether the 4 x 4 form takes a product's operands straight to LDS: whole K tiles, offsets below 2^31, and scale bytes that can be
+// loaded 16 at a time, which row-major ones that begin 8 bytes off cannot: those are staged through registers like the codes, us, staged :
+// for any K : straight: 2048 x 2048 x 2048 20.2 : 21.8 : 19.1, 1024 x 4096 x 4096 33.0 : 34.7 : 31.3, 2048 x 2048 x 16384 110 : 115 : 104.
+bool gemm_wide_applies(const qii_nvfp4 &A, const qii_nvfp4 &B)
+{
+    return A.cols % BK == 0 && A.cols <= kMaxWideK && ((reinterpret_cast<uintptr_t>(A.scales) | reinterpret_cast<uintptr_t>(B.scales)) & 15) == 0;
+}
+
 hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipStream_t s)
 {
     SmallArgs g[2];
+    bool direct = true;
     for (int i = 0; i < count; ++i) {
         const qii_nvfp4 &A = *c[i].A, &B = *c[i].B;
         if ((A.cols % BK != 0) != (c[0].A->cols % BK != 0) || c[i].c_is_bf16 != c[0].c_is_bf16 ||
@@ -790,11 +795,12 @@ hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipS
         g[i].a_ts = A.tensor_scale; g[i].b_ts = B.tensor_scale;
         g[i].M = A.rows; g[i].N = B.rows; g[i].K = A.cols;
         g[i].C = c[i].C; g[i].ldc = c[i].ldc; g[i].amax_out = c[i].amax_out;
+        direct = direct && gemm_wide_applies(A, B);
     }
     const int bf = c[0].c_is_bf16;
-    if (tile == kTile64) return bf ? launch<true, Geo<2, 2, 1, 4>>(g, count, s) : launch<false, Geo<2, 2, 1, 4>>(g, count, s);
-    if (tile == kTile128Wide) return bf ? launch<true, Geo<4, 4, 1, 4>>(g, count, s) : launch<false, Geo<4, 4, 1, 4>>(g, count, s);
-    return bf ? launch<true, Geo<2, 4, 2, 2>>(g, count, s) : launch<false, Geo<2, 4, 2, 2>>(g, count, s);
+    if (tile == kTile64) return bf ? launch<true, Geo<2, 2, 1, 4>>(g, count, direct, s) : launch<false, Geo<2, 2, 1, 4>>(g, count, direct, s);
+    if (tile == kTile128Wide) return bf ? launch<true, Geo<4, 4, 1, 4>>(g, count, direct, s) : launch<false, Geo<4, 4, 1, 4>>(g, count, direct, s);
+    return bf ? launch<true, Geo<2, 4, 2, 2>>(g, count, direct, s) : launch<false, Geo<2, 4, 2, 2>>(g, count, direct, s);
 }
 
 }  // namespace qii

@@ -171,7 +171,7 @@ hipError_t launch_gemm(const qii_nvfp4 &A, const qii_nvfp4 &B, void *C, int c_is
 
 // whether launch_gemm, given a workspace and tiled scale bytes, would run the main kernel: only then is
 // it worth a quantizer's while to write the tiled copy
-bool gemm_reads_tiled_scales(int64_t M, int64_t N, int64_t K, const void *C, int64_t ldc, int c_is_bf16);
+bool gemm_reads_tiled_scales(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, int64_t ldc, int c_is_bf16);
 // products by the small-tile kernels (gemm_small.hip), one or two in one launch (with one result type, and K a
 // multiple of 256 in both or in neither): any K; each operand's scale bytes row-major or, K a multiple of 256, tiled
 enum SmallTile { kTile64, kTile128, kTile128Wide };
@@ -185,6 +185,7 @@ struct SmallGemm {
     uint32_t *amax_out;
 };
 hipError_t launch_gemm_small(const SmallGemm *c, int count, SmallTile tile, hipStream_t s);
+bool gemm_wide_applies(const qii_nvfp4 &A, const qii_nvfp4 &B);   // whether kTile128Wide takes its operands straight to LDS
 // two products whose operands are both ready: in one launch of a small-tile kernel where that is the faster way, else one
 // launch_gemm after the other (arguments as there, no maxima)
 struct GemmCall {
