@@ -340,9 +340,13 @@ int qii_gemm_sharing_segments(int rem, int ktotal, int grid, int block_id, int32
 void qii_gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t out[2]);
 
 /* Test aids for rules that pick a kernel (host computations, no device work).
- * qii_absmax_takes_tiles: whether max |rotated x| along the columns of a contiguous bf16 matrix x of
- *   rows x cols, both multiples of 128, is measured by 128 x 128 tiles.                     */
+ * qii_absmax_takes_tiles: whether qii_absmax measures max |rotated x| along the columns of a contiguous bf16 matrix x of
+ *   rows x cols, both multiples of 128, by 128 x 128 tiles; so does a quantizer call whose blocks leave no words (below).  */
 int qii_absmax_takes_tiles(int64_t rows, int64_t cols);
+/* qii_absmax_words: words that the abs-max pass of a quantizer call (modes other than the post hoc scheme, no maximum given, arguments as
+ *   there) leaves on a contiguous matrix, one per block; 0: one word, cleared by a launch of its own.  Rotated along the columns of a
+ *   bf16 matrix whose sides are multiples of 128, the blocks that leave words take 128 x 128 tiles.  -1 for sizes that it refuses.  */
+int qii_absmax_words(qii_dtype dt, int64_t rows, int64_t cols, int transpose, int rht_group);
 /* qii_gemm_route: the kernel that a GEMM of M x N x K takes when its workspace has ws_bytes (0: none given): 0 the
  *   256 x 256 kernel that uses the workspace, 1 the 256 x 256 kernel without one, 2 tiles of 64 x 64, 3 of 128 x 128 in
  *   two K groups, 4 of 128 x 128 in four; -1 for sizes the GEMM refuses.  tiled != 0 (K a multiple of 256): both operands'

@@ -28,7 +28,7 @@ EXPORTS = [
     "qii_quantize_nvfp4_noalloc", "qii_gemm_nvfp4_amax", "qii_linear_fwd_amax",
     "qii_quantize_pair_nvfp4", "qii_quantize_pair_workspace_bytes",
     "qii_gemm_sharing_plan", "qii_gemm_sharing_segments", "qii_gemm_sharing_tile_slots",
-    "qii_absmax_takes_tiles", "qii_gemm_route", "qii_rows_per_wave",
+    "qii_absmax_takes_tiles", "qii_absmax_words", "qii_gemm_route", "qii_rows_per_wave",
     "qii_linear_bwd_gemm_route",
 ]
 
@@ -99,6 +99,8 @@ def lib() -> ctypes.CDLL:
         L.qii_gemm_route.restype = c.c_int
         L.qii_absmax_takes_tiles.argtypes = [i64, i64]
         L.qii_absmax_takes_tiles.restype = c.c_int
+        L.qii_absmax_words.argtypes = [c.c_int, i64, i64, c.c_int, c.c_int]
+        L.qii_absmax_words.restype = c.c_int
         L.qii_linear_bwd_gemm_route.argtypes = [i64, i64, i64, sz, c.c_int]
         L.qii_linear_bwd_gemm_route.restype = c.c_int
         L.qii_rows_per_wave.argtypes = [i64, i64, c.c_int]

@@ -856,6 +856,16 @@ int qii_absmax_takes_tiles(int64_t rows, int64_t cols)
     return rows > 0 && cols > 0 && rows % 128 == 0 && cols % 128 == 0 && qii::absmax_tiles_pay(rows, cols);
 }
 
+int qii_absmax_words(qii_dtype dt, int64_t rows, int64_t cols, int transpose, int rht_group)
+{
+    qii::Source src;
+    int64_t R, C;
+    const void *x = reinterpret_cast<const void *>(256);   // (a stand-in address: the kernels' rules look at its alignment)
+    const int64_t piece = dt == QII_F32 ? 4 : 8, ld = transpose ? cols : (cols + piece - 1) / piece * piece;
+    if (rows <= 0 || cols <= 0 || dense_source(x, dt, rows, cols, ld, transpose, rht_group, &src, &R, &C) != QII_OK) return -1;
+    return qii::absmax_words(src, R, C, rht_group == 128);
+}
+
 int qii_rows_per_wave(int64_t rows, int64_t cols, qii_mode mode)
 {
     return rows <= 0 || cols <= 0 || cols % 16 != 0 ? -1 : qii::rows_per_wave(rows, cols, (int)mode);

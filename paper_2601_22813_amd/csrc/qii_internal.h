@@ -129,7 +129,7 @@ hipError_t launch_dequantize(const uint8_t *codes, const uint8_t *scales, const 
 bool rows_kernels_apply(const Source &src, int64_t R, int64_t C);
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,
                               float *amax, hipStream_t s, int words);
-int absmax_rows_words(int64_t R, int64_t C);
+int absmax_rows_words(const Source &src, int64_t R, int64_t C, int rht);
 hipError_t launch_quantize_rows(const QuantizeArgs &a, hipStream_t s);
 // a small tensor (no rotation; amax not needed) whose blocks measure it themselves
 bool measures_itself(const QuantizeArgs &q);

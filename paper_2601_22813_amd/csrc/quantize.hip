@@ -534,7 +534,7 @@ static bool tiles_measure_columns(const Source &src, int64_t R, int64_t C, int r
 int absmax_words(const Source &src, int64_t R, int64_t C, int rht)
 {
     if (R == 0 || C == 0) return 0;
-    if (rows_kernels_apply(src, R, C)) return absmax_rows_words(R, C);
+    if (rows_kernels_apply(src, R, C)) return absmax_rows_words(src, R, C, rht);
     if (tiles_measure_columns(src, R, C, rht)) return absmax_tiles_words(C, R, false);
     if (requant_kernels_apply(src, R, C)) return requant_amax_words(src, R, C);
     return cols_kernels_apply(src, R, C) ? absmax_cols_words(R, C) : 0;

@@ -532,13 +532,26 @@ static dim3 absmax_rows_grid(int64_t R, int64_t C, int words)
     return rows_grid(R, C, wpr, most > 0 ? most : 1);
 }
 
-// A word per block, at most kSlotWords blocks, and no clearing launch: up to 4 M elements, where the few blocks' longer way through the
-// tensor still costs less.  Whole calls, us, clearing and atomics : words: MS-EDEN bf16 1024 x 1024 12.1 : 9.5, 512 x 4096 12.2 :
-// 9.5, 2048 x 2048 13.2 : 13.0, 4096 x 1024 13.6 : 13.0, 300 x 8192 12.3 : 11.4; SR f32 2048 x 2048 16.0 : 15.2; RTN 2000 x 2048 12.5 : 10.5.
-int absmax_rows_words(int64_t R, int64_t C)
+// A word per block, at most kSlotWords blocks, and no clearing launch, where the few blocks' longer way through the tensor costs less:
+// what counts are the rounds, row quads that a wave takes one after the other, whose loads and rotation wait for one another (narrow
+// rows fill their waves with as many quads as wide ones).  Whole calls, us, clearing and atomics : words, medians over 3500 tensors of up to 4 M
+// elements.  Rotated, by rounds: 1 9.0 : 7.3, 2 10.1 : 9.0, 3 11.5 : 11.2, 4 in 56 blocks and more 13.4 : 13.3, in fewer 12.6 : 13.0, 5 15.4 :
+// 15.9, 6 17.0 : 18.4; 20480 x 128 bf16 MS-EDEN 22.4 : 37.7, 16384 x 256 f32 20.0 : 31.2.  (f32 rows of 7 or 15 waves: four or eight blocks side by
+// side, so that the idle waves of the last are all on the same dies: the fourth round costs 1.3 more.)  Unrotated bf16: 4 10.5 : 8.3, 8 14.4 : 11.6,
+// 14 19.0 : 18.3, 21 20.6 : 21.3, 24 23.2 : 25.7; f32, whose bytes count as well: 5 and 6 up to 8 MiB 13.4 : 10.5, above 13.1 : 12.2, 7 to 10 up to 8 MiB
+// 14.5 : 12.4, above 13.5 : 13.9, 13 up to 2 MiB 16.6 : 15.8, above 15.6 : 17.7.
+int absmax_rows_words(const Source &src, int64_t R, int64_t C, int rht)
 {
-    if (R * C > (int64_t)4 << 20 || rows_gy(C, absmax_wpr(C)) > kSlotWords) return 0;
-    return (int)absmax_rows_grid(R, C, 1).x;
+    const int wpr = absmax_wpr(C);
+    const int64_t gy = rows_gy(C, wpr), elements = R * C;
+    if (elements > (int64_t)4 << 20 || gy > kSlotWords) return 0;
+    const int64_t block_rows = rows_grid(R, C, wpr, 0).x / gy, most = kSlotWords / gy, rounds = (block_rows + most - 1) / most;
+    const int blocks = (int)absmax_rows_grid(R, C, 1).x;
+    const bool bf16 = src.kind == kSrcBF16;
+    const bool pays = rht    ? rounds <= 3 || (rounds == 4 && blocks >= 56 && (bf16 || rows_waves(C) % 8 != 7))
+                      : bf16 ? rounds <= 19
+                             : rounds <= 6 || (rounds <= 10 && elements <= (int64_t)2 << 20) || (rounds <= 13 && elements <= (int64_t)1 << 19);
+    return pays ? blocks : 0;
 }
 
 hipError_t launch_absmax_rows(const Source &src, int64_t R, int64_t C, int rht, uint64_t seed_rht,

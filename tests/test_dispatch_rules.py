@@ -32,6 +32,30 @@ def test_the_faster_abs_max_pass_along_columns(libqii, rows, cols):
     assert bool(libqii.lib().qii_absmax_takes_tiles(rows, cols)) == (tiles < columns)
 
 
+# whole quantizer calls that measure their tensor, us: one maximum, cleared by a launch and kept by atomics; a word per block.  f32 or
+# not, rows, cols, along the columns or not, rotation
+F32, BF16 = 0, 1
+WORDS_US = {   # (MS-EDEN or SR with the rotation, RTN, 4/6 or SR without)
+    # along the rows: the row quads that a wave takes one after the other decide, not the elements
+    (BF16, 32382, 128, 0, 128): (29.93, 57.03), (BF16, 20480, 128, 0, 128): (22.43, 37.70), (F32, 16384, 256, 0, 128): (19.96, 31.25),
+    (BF16, 10239, 256, 0, 128): (21.46, 26.57), (F32, 7038, 384, 0, 128): (15.33, 17.85), (BF16, 4685, 768, 0, 128): (17.26, 18.22),
+    (BF16, 510, 5376, 0, 128): (12.56, 12.89), (BF16, 512, 7040, 0, 128): (12.72, 12.41), (BF16, 184, 13056, 0, 128): (12.04, 11.91),
+    (F32, 381, 9600, 0, 128): (13.98, 13.37), (BF16, 640, 1664, 0, 128): (9.48, 8.70), (F32, 126, 640, 0, 128): (8.78, 7.28),
+    (BF16, 31439, 16, 0, 0): (16.98, 20.81), (BF16, 25389, 48, 0, 0): (17.17, 18.69), (F32, 28064, 96, 0, 0): (21.36, 29.30),
+    (F32, 13967, 80, 0, 0): (19.54, 21.97), (BF16, 12445, 256, 0, 0): (16.82, 16.22), (BF16, 7902, 144, 0, 0): (14.48, 11.65),
+    (F32, 245, 14464, 0, 128): (11.17, 13.03), (F32, 10357, 32, 0, 0): (16.51, 14.73), (BF16, 16510, 144, 0, 0): (19.29, 18.23), (F32, 12663, 32, 0, 0): (14.99, 13.87),
+    (F32, 7549, 16, 0, 0): (12.93, 10.43), (F32, 5598, 192, 0, 0): (12.58, 10.20),
+}
+
+
+@pytest.mark.parametrize("call", WORDS_US)
+def test_blocks_leave_words_where_that_is_faster(libqii, call):
+    clearing, words = WORDS_US[call]
+    n = libqii.lib().qii_absmax_words(*call)
+    assert 0 <= n <= 64
+    assert (n > 0) == (words < clearing)
+
+
 # whole post hoc calls along the rows of a bf16 matrix, us: a wave per row, a wave per four rows
 ROWS_US = {
     (1023, 1024): (8.15, 10.19), (2559, 1024): (9.86, 10.42), (3071, 1024): (10.01, 10.52), (3583, 1024): (10.83, 10.63),

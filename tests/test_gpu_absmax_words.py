@@ -35,6 +35,11 @@ def same(a, b):
     (1, 128, False, qii.MS_EDEN, 128, torch.bfloat16), (1021, 1024, False, qii.MS_EDEN, 128, torch.bfloat16),
     (1040, 1024, False, qii.SR, 128, torch.float32), (2048, 2048, False, qii.MS_EDEN, 128, torch.bfloat16),
     (2049, 2048, False, qii.MS_EDEN, 128, torch.bfloat16), (67, 9216, False, qii.SR, 128, torch.float32),
+    # a wave's rounds at the lines of the rule: rotated 3, 4 in few blocks, 4 in 64, 5; unrotated bf16 19, 20; f32 6, 7 above 8 MiB, 10, 11 below it
+    (3072, 128, False, qii.MS_EDEN, 128, torch.bfloat16), (3080, 128, False, qii.SR, 128, torch.float32), (4096, 128, False, qii.MS_EDEN, 128, torch.float32),
+    (4100, 128, False, qii.MS_EDEN, 128, torch.bfloat16), (19456, 64, False, qii.RTN, 0, torch.bfloat16), (19460, 64, False, qii.RTN_46, 0, torch.bfloat16),
+    (6144, 512, False, qii.RTN, 0, torch.float32), (6148, 512, False, qii.SR, 0, torch.float32),
+    (10240, 128, False, qii.RTN, 0, torch.float32), (10244, 128, False, qii.RTN, 0, torch.float32),
     (2000, 1552, False, qii.RTN_46, 0, torch.float32), (1000, 1552, False, qii.RTN, 0, torch.bfloat16),
     (128, 128, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1024, True, qii.MS_EDEN, 128, torch.bfloat16),
     (640, 1664, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 2048, True, qii.SR, 128, torch.bfloat16),
