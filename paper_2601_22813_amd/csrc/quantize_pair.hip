@@ -233,12 +233,16 @@ bool absmax_tiles_pay(int64_t rows, int64_t cols)
 // A word per block, at most kSlotWords blocks, and no clearing launch.  Both orientations: a tile a block.  Along the columns alone a
 // block has one, two or four groups and a tile each.  Whole MS-EDEN calls, us, clearing and atomics (the form above) : words: both 128 x 128
 // 15.5 : 11.9, 1024 x 1024 16.0 : 12.9; columns 1024 x 1024 12.9 : 11.2, 2048 x 1024 13.5 : 12.5, 2048 x 2048 16.7 : 15.3, but 512 x 8192
-// (local) 14.8 : 14.9; 128 tiles in blocks of four groups 13.6 : 14.0.
+// (local) 14.8 : 14.9; 128 tiles in blocks of four groups 13.6 : 14.0.  Beyond 128 tiles the columns kernel is the other way, in blocks of four
+// waves below one another: 635 shapes of 129 to 256 tiles, medians, columns kernel : words: one such block high 15.0 : 14.3, more and a whole last
+// one 14.1 : 13.3, three waves of the last at work 13.9 : 13.4; two of them 12.9 : 13.5, one 13.6 : 14.3 (5760 x 512 11.6 : 13.2).
 int absmax_tiles_words(int64_t rows, int64_t cols, bool both)
 {
     const int64_t tiles = (rows / 128) * (cols / 128);
     if (both) return tiles <= kSlotWords ? (int)tiles : 0;
-    if (tiles > 4 * kSlotWords || (tiles > 2 * kSlotWords && columns_local(rows, cols))) return 0;
+    if (tiles > 4 * kSlotWords) return 0;
+    const int64_t last = rows % 512;   // rows of the columns kernel's last block
+    if (tiles > 2 * kSlotWords && (columns_local(rows, cols) || (rows > 512 && (last == 128 || last == 256)))) return 0;
     const int64_t groups = tiles <= kSlotWords ? 1 : tiles <= 2 * kSlotWords ? 2 : 4;
     return (int)((tiles + groups - 1) / groups);
 }

@@ -45,6 +45,12 @@ WORDS_US = {   # (MS-EDEN or SR with the rotation, RTN, 4/6 or SR without)
     (F32, 13967, 80, 0, 0): (19.54, 21.97), (BF16, 12445, 256, 0, 0): (16.82, 16.22), (BF16, 7902, 144, 0, 0): (14.48, 11.65),
     (F32, 245, 14464, 0, 128): (11.17, 13.03), (F32, 10357, 32, 0, 0): (16.51, 14.73), (BF16, 16510, 144, 0, 0): (19.29, 18.23), (F32, 12663, 32, 0, 0): (14.99, 13.87),
     (F32, 7549, 16, 0, 0): (12.93, 10.43), (F32, 5598, 192, 0, 0): (12.58, 10.20),
+    # along the columns of bf16 matrices that the 128 x 128 tiles take
+    (BF16, 5760, 512, 1, 128): (11.56, 13.17), (BF16, 4352, 896, 1, 128): (12.58, 13.89), (BF16, 1664, 1408, 1, 128): (13.13, 14.32),
+    (BF16, 18560, 128, 1, 128): (11.60, 13.00), (BF16, 9984, 384, 1, 128): (13.72, 14.70), (BF16, 256, 16000, 1, 128): (14.98, 14.72),
+    (BF16, 384, 5760, 1, 128): (14.32, 14.03), (BF16, 2048, 2048, 1, 128): (14.31, 13.32), (BF16, 1408, 2816, 1, 128): (19.11, 17.77),
+    (BF16, 13184, 256, 1, 128): (15.31, 14.51), (BF16, 1536, 2304, 1, 128): (15.61, 14.58), (BF16, 14848, 256, 1, 128): (14.26, 13.42),
+    (BF16, 7936, 128, 1, 128): (13.30, 11.51), (BF16, 640, 2944, 1, 128): (12.38, 11.30),
 }
 
 

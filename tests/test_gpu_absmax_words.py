@@ -44,7 +44,8 @@ def same(a, b):
     (128, 128, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1024, True, qii.MS_EDEN, 128, torch.bfloat16),
     (640, 1664, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 2048, True, qii.SR, 128, torch.bfloat16),
     (384, 5504, True, qii.MS_EDEN, 128, torch.bfloat16), (2048, 2048, True, qii.MS_EDEN, 128, torch.bfloat16),
-    (512, 8192, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1000, True, qii.SR, 128, torch.float32),
+    (512, 8192, True, qii.MS_EDEN, 128, torch.bfloat16), (1536, 2304, True, qii.SR, 128, torch.bfloat16),
+    (1664, 1664, True, qii.MS_EDEN, 128, torch.bfloat16), (1792, 1280, True, qii.MS_EDEN, 128, torch.bfloat16), (1408, 1664, True, qii.MS_EDEN, 128, torch.bfloat16), (1024, 1000, True, qii.SR, 128, torch.float32),
     (1024, 1024, True, qii.MS_EDEN, 128, torch.float32), (1024, 1026, True, qii.MS_EDEN, 128, torch.float32),
     (1920, 520, True, qii.RTN, 0, torch.bfloat16)])
 def test_words_of_one_tensor(rows, cols, transpose, mode, rht, dtype):
