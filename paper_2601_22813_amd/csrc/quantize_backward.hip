@@ -25,7 +25,7 @@ __global__ __launch_bounds__(512, kMode == QII_MS_EDEN_PH ? 6 : 4) void quantize
     extern __shared__ __align__(16) uint8_t lds[];   // kChunks images of 32 KiB, the first of them a block's tile of E
     const int block = (int)blockIdx.x;               // (branches on it are uniform)
     if (block < n_e) {
-        pair_block<kMode, true, kWords, const PairArgs &>(e, block, lds);
+        pair_block<kMode, true, kWords, false, const PairArgs &>(e, block, lds);   // (512 x 512 -> 512 17.5 us, with non-temporal stores 17.8)
         return;
     }
     if (kChunks == 1 && threadIdx.x >= 256) return;   // (a wave that has ended takes no part in barriers)

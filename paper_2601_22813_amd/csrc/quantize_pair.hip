@@ -5,11 +5,11 @@
 namespace qii {
 namespace {
 
-template <int kMode, bool kWords>
+template <int kMode, bool kWords, bool kStream>
 __global__ __launch_bounds__(512) void quantize_pair_kernel(PairArgs a)
 {
     __shared__ __align__(16) uint8_t tile[kPairImage];
-    pair_block<kMode, false, kWords>(a, (int)blockIdx.x, tile);
+    pair_block<kMode, false, kWords, kStream>(a, (int)blockIdx.x, tile);
 }
 
 // Abs-max of a rotated matrix along its columns.  The result word takes one atomic per block, and such atomics on one
@@ -196,13 +196,29 @@ bool pair_kernel_applies(const Source &src, int64_t rows, int64_t cols)
            cols <= ((int64_t)1 << 23) && rows <= ((int64_t)1 << 23) && (rows / 128) * (cols / 128) < ((int64_t)1 << 31);
 }
 
+// Non-temporal stores of the codes get out of the loads' way, but a product that follows finds the codes in the caches only after
+// ordinary ones.  us, ordinary : non-temporal, post hoc scheme (Algorithm 1 alike), the call alone, and with a product of each orientation behind it:
+//    512 x  512  9.8 :  9.8   19.1 : 19.7       1024 x 1024 10.1 : 10.1   23.1 : 23.3       1024 x 2048 10.3 : 10.3   28.4 : 28.3
+//   1536 x 1536 10.8 : 10.8   40.1 : 39.6       2048 x 4096 16.8 : 16.3   84.8 : 84.7       4096 x 4096 27.0 : 26.3    147 : 149
+//   16384 x 2048 43.2 : 42.2   251 : 252        8192 x 8192 75.9 : 74.9    450 : 452
+// From 2 M elements the call gains 1 to 3 %, and the three together lose at most 1 %, about as much; below there is nothing to gain.
+constexpr int kStreamTiles = 128;
+static_assert(kSlotWords < kStreamTiles, "a pair whose blocks leave words has fewer tiles");
+
 hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
 {
     const PairArgs a = pair_args(p);
-    const dim3 grid((unsigned)((p.rows / 128) * (p.cols / 128))), block(512);
-    if (p.mode == QII_MS_EDEN_PH) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN_PH, false>), grid, block, 0, s, a);
-    else if (a.words) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN, false>), grid, block, 0, s, a);
+    const int tiles = (int)((p.rows / 128) * (p.cols / 128));
+    const dim3 grid((unsigned)tiles), block(512);
+#define QII_PAIR(MODE, WORDS)                                                                                               \
+    do {                                                                                                                   \
+        if (tiles >= kStreamTiles) hipLaunchKernelGGL((quantize_pair_kernel<MODE, WORDS, true>), grid, block, 0, s, a);     \
+        else hipLaunchKernelGGL((quantize_pair_kernel<MODE, WORDS, false>), grid, block, 0, s, a);                          \
+    } while (0)
+    if (p.mode == QII_MS_EDEN_PH) QII_PAIR(QII_MS_EDEN_PH, false);
+    else if (a.words) hipLaunchKernelGGL((quantize_pair_kernel<QII_MS_EDEN, true, false>), grid, block, 0, s, a);   // (small tensors only)
+    else QII_PAIR(QII_MS_EDEN, false);
+#undef QII_PAIR
     return hipGetLastError();
 }
 

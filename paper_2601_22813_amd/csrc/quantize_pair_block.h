@@ -60,10 +60,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t region(const void *base, int64
 constexpr int kPairImage = 128 * 256;   // LDS bytes of the tile
 
 // tile: kPairImage bytes of LDS; kMayTile: heeds ksn (false costs nothing where nobody asks for it); kWords: Algorithm 1's maxima are those
-// of a.words words each (as a run-time question 0.7 % of a backward pass).  Args: by value, or by reference
+// of a.words words each (as a run-time question 0.7 % of a backward pass); kStream: the codes leave by non-temporal stores
+// (launch_quantize_pair).  Args: by value, or by reference
 // in a kernel that holds other arguments too (the addresses are then formed otherwise: 0.1 us of a small pair's call by reference,
 // but 1 to 2 % of a backward pass by value)
-template <int kMode, bool kMayTile = false, bool kWords = false, class Args = const PairArgs>
+template <int kMode, bool kMayTile, bool kWords, bool kStream, class Args = const PairArgs>
 __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
 {
     __shared__ float inv_r[128], inv_c[128];
@@ -142,24 +143,22 @@ __device__ __forceinline__ void pair_block(Args a, int block, uint8_t *tile)
             if (kMode == QII_MS_EDEN_PH) {
                 float gmax;
                 const float tt = posthoc_group16(v, packed, gmax);
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kMayTile ? 0 : 2 /* nt */);
+                __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kStream ? 2 /* nt */ : 0);
                 a.r.tbuf[(row0 + r) * G + col0 / 16 + L.blk] = tt;
                 m_r = fmaxf(m_r, gmax);
                 continue;
             }
             uint32_t b = quantize_group16<QII_MS_EDEN, -1, true>(v, tcr, draw[it], a.r.seed_sr, row0 + r, tx * 8 + L.blk, packed, inv_r);
             if (zero) { packed[0] = 0u; packed[1] = 0u; b = 0u; }
-            __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kMayTile ? 0 : 2 /* nt */);
+            __builtin_amdgcn_raw_buffer_store_b64(u32x2{packed[0], packed[1]}, rc, vc, 0, kStream ? 2 /* nt */ : 0);
             const uint2 sc = gather_scale_bytes(b, L.blk);
             __builtin_amdgcn_raw_buffer_store_b64(u32x2{sc.x, sc.y}, rs, L.blk == 0 ? (uint32_t)(r * spitch) : kNoStore, 0, 0);
         }
     }
 
-    // (the kernel of a backward pass leaves its codes to the products that follow at once: ordinary stores, 512 x 512 -> 512 17.5 us, with
-    // non-temporal ones 17.8; alone non-temporal ones are the faster: 8192 x 8192 post hoc 80.0 -> 78.6, 16384 x 2048 46.3 -> 44.4, Algorithm 1 117.4 -> 116.5)
     auto put_codes = [](uint8_t *dst, const uint32_t c[4]) {
-        if (kMayTile) *reinterpret_cast<uint4 *>(dst) = make_uint4(c[0], c[1], c[2], c[3]);
-        else store_codes16(dst, c[0], c[1], c[2], c[3]);
+        if (kStream) store_codes16(dst, c[0], c[1], c[2], c[3]);
+        else *reinterpret_cast<uint4 *>(dst) = make_uint4(c[0], c[1], c[2], c[3]);
     };
 
     // ---- column part: Q(x^T).  The tile is chunk `ty` of the columns' 128-chunks; wave w takes the
