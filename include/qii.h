@@ -350,10 +350,18 @@ int qii_absmax_words(qii_dtype dt, int64_t rows, int64_t cols, int transpose, in
 /* qii_gemm_route: the kernel that a GEMM of M x N x K takes when its workspace has ws_bytes (0: none given): 0 the
  *   256 x 256 kernel that uses the workspace, 1 the 256 x 256 kernel without one, 2 tiles of 64 x 64, 3 of 128 x 128 in
  *   two K groups, 4 of 128 x 128 in four; -1 for sizes the GEMM refuses.  tiled != 0 (K a multiple of 256): both operands'
- *   scale bytes are already in the tiled layout, as in the layer passes.                                            */
+ *   scale bytes are already in the tiled layout, as in the layer passes.  The route also looks at the type, the address and the
+ *   row length of C and at the alignment of the scale bytes: this is the answer for bf16 results without gaps between the
+ *   rows, C on a 128-byte line and scale bytes aligned to 16.                                                             */
 int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
+/* qii_gemm_call_route: the same for a call of qii_gemm_nvfp4 with these arguments, of which it looks at types, sizes and
+ *   addresses only; 5 where the 256 x 256 kernel that uses the workspace runs with blocks that take several tiles.
+ *   tiled != 0 (K a multiple of 256): the workspace holds both operands' scale bytes already, as in a forward pass.      */
+int qii_gemm_call_route(const qii_nvfp4 *A, const qii_nvfp4 *B, const void *C, qii_dtype c_dt, int64_t ldc, const void *ws, size_t ws_bytes,
+                        int tiled);
 /* qii_linear_bwd_gemm_route: the kernel (numbers as for qii_gemm_route) whose one launch computes both dX and dW of a backward pass;
- *   -1: each takes its own, as qii_gemm_route says, in a launch of its own.  tiled as there, where the inner dimension allows it.  */
+ *   -1: each takes its own, as qii_gemm_route says, in a launch of its own.  tiled as there, where the inner dimension allows it; bf16
+ *   gradients on 128-byte lines.                                                                                        */
 int qii_linear_bwd_gemm_route(int64_t T, int64_t d_in, int64_t d_out, size_t ws_bytes, int tiled);
 /* qii_rows_per_wave: rows that a wave of the quantizer along rows takes for a contiguous rows x cols matrix (4, or 1 where
  *   the matrix is small); -1 for sizes that it refuses.                                      */

@@ -28,7 +28,7 @@ EXPORTS = [
     "qii_quantize_nvfp4_noalloc", "qii_gemm_nvfp4_amax", "qii_linear_fwd_amax",
     "qii_quantize_pair_nvfp4", "qii_quantize_pair_workspace_bytes",
     "qii_gemm_sharing_plan", "qii_gemm_sharing_segments", "qii_gemm_sharing_tile_slots",
-    "qii_absmax_takes_tiles", "qii_absmax_words", "qii_gemm_route", "qii_rows_per_wave",
+    "qii_absmax_takes_tiles", "qii_absmax_words", "qii_gemm_route", "qii_gemm_call_route", "qii_rows_per_wave",
     "qii_linear_bwd_gemm_route",
 ]
 
@@ -97,6 +97,8 @@ def lib() -> ctypes.CDLL:
             getattr(L, name).restype = sz
         L.qii_gemm_route.argtypes = [i64, i64, i64, sz, c.c_int]
         L.qii_gemm_route.restype = c.c_int
+        L.qii_gemm_call_route.argtypes = [nv, nv, vp, c.c_int, i64, vp, sz, c.c_int]
+        L.qii_gemm_call_route.restype = c.c_int
         L.qii_absmax_takes_tiles.argtypes = [i64, i64]
         L.qii_absmax_takes_tiles.restype = c.c_int
         L.qii_absmax_words.argtypes = [c.c_int, i64, i64, c.c_int, c.c_int]
@@ -300,6 +302,13 @@ def qii_gemm_nvfp4(A: NVFP4Tensor, B: NVFP4Tensor, C: torch.Tensor, ws: torch.Te
     sa, sb = A.c_struct(), B.c_struct()
     _check(lib().qii_gemm_nvfp4(ctypes.byref(sa), ctypes.byref(sb), C.data_ptr(), _dt(C), C.stride(0),
                                 _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream()))
+
+
+def qii_gemm_call_route(A: NVFP4Tensor, B: NVFP4Tensor, C: torch.Tensor, ws: torch.Tensor | None = None, tiled: bool = False) -> int:
+    """The kernel that qii_gemm_nvfp4 takes for these arguments (a test aid; nothing runs)."""
+    sa, sb = A.c_struct(), B.c_struct()
+    return int(lib().qii_gemm_call_route(ctypes.byref(sa), ctypes.byref(sb), C.data_ptr(), _dt(C), C.stride(0), _ptr(ws),
+                                         0 if ws is None else ws.numel() * ws.element_size(), int(tiled)))
 
 
 INEXACT_FP8, INEXACT_FP4_POW2 = 0, 1

@@ -844,6 +844,12 @@ int qii_gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
     return M <= 0 || N <= 0 || K <= 0 || K % 16 != 0 || (tiled && K % 256 != 0) ? -1 : qii::gemm_route(M, N, K, ws_bytes, tiled);
 }
 
+int qii_gemm_call_route(const qii_nvfp4 *A, const qii_nvfp4 *B, const void *C, qii_dtype c_dt, int64_t ldc, const void *ws, size_t ws_bytes, int tiled)
+{
+    if (check_gemm_args(A, B, C, c_dt, ldc) != QII_OK || A->rows * B->rows == 0 || (tiled && A->cols % 256 != 0)) return -1;
+    return qii::gemm_call_route(*A, *B, C, c_dt == QII_BF16, ldc, ws, ws_bytes, tiled ? 12 : 0);
+}
+
 int qii_linear_bwd_gemm_route(int64_t T, int64_t d_in, int64_t d_out, size_t ws_bytes, int tiled)
 {
     if (T <= 0 || d_in <= 0 || d_out <= 0 || T % 128 != 0 || d_out % 128 != 0 || d_in % 16 != 0) return -1;

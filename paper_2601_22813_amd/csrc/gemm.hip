@@ -1159,6 +1159,7 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
 // 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 9.1 : 7.7 : 8.8 and 10.5 : 9.9 : 14.4, 4096 x 4096 25.5 : 18.0 : 12.4
 // and 31.6 : 23.9 : 18.9, 8192 x 8192 87 : 59 : 41 and 112 : 84 : 67.
 enum Route { kRouteMain, kRouteNoWorkspace, kRoute64, kRoute128, kRoute128Wide };
+constexpr int kRouteMainTiles = 5;   // (gemm_call_route)
 
 constexpr int64_t kMaxMainK = (int64_t)1 << 23;
 
@@ -1218,10 +1219,18 @@ static Prices prices_of(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, i
     return price_routes(M, N, K, main_ok ? ws_bytes : 0, !(pretiled & 5) || !(pretiled & 10), gemm_wide_applies(A, B), C, ldc, c_is_bf16);
 }
 
+// test aid (host only): the kernel that launch_gemm takes, or kRouteMainTiles for the main kernel in the form whose blocks take several tiles
+int gemm_call_route(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, int c_is_bf16, int64_t ldc, const void *ws, size_t ws_bytes, int pretiled)
+{
+    const Route best = prices_of(A, B, C, ldc, c_is_bf16, ws, ws_bytes, pretiled).best;
+    const bool several = best == kRouteMain && blocks_take_tiles(plan_that_fits(A.rows, B.rows, A.cols, ws_bytes).full, C, ldc, B.rows, c_is_bf16);
+    return several ? kRouteMainTiles : (int)best;
+}
+
 static Prices test_prices(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled)
 {
     const qii_nvfp4 a = {nullptr, nullptr, nullptr, M, K}, b = {nullptr, nullptr, nullptr, N, K};
-    // (stand-in addresses: the route looks at their alignment; bf16 results without gaps between the rows)
+    // (stand-in addresses, 16-byte aligned scale bytes and a C on a 128-byte line; bf16 results without gaps between the rows)
     return prices_of(a, b, reinterpret_cast<const void *>(256), N, 1, ws_bytes ? reinterpret_cast<const void *>(256) : nullptr, ws_bytes, tiled ? 3 : 0);
 }
 

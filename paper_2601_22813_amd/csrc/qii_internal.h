@@ -204,6 +204,7 @@ void gemm_sharing_plan(int64_t M, int64_t N, int64_t K, int32_t plan[3]);
 int gemm_sharing_segments(int rem, int ktotal, int grid, int block_id, int32_t *out);
 void gemm_sharing_tile_slots(int rem, int ktotal, int grid, int lt, int32_t out[2]);
 // the kernel that launch_gemm would run: see qii_gemm_route
+int gemm_call_route(const qii_nvfp4 &A, const qii_nvfp4 &B, const void *C, int c_is_bf16, int64_t ldc, const void *ws, size_t ws_bytes, int pretiled);
 int gemm_route(int64_t M, int64_t N, int64_t K, size_t ws_bytes, int tiled);
 int gemm_pair_route(const int64_t M[2], const int64_t N[2], const int64_t K[2], size_t ws_bytes, int tiled);
 

@@ -173,6 +173,39 @@ def test_the_last_round_is_shared_where_that_is_faster(libqii, M, N, K):
     assert libqii.lib().qii_gemm_route(M, N, K, libqii.qii_gemm_workspace_bytes(M, N, K), 0) == MAIN
 
 
+MAIN_TILES = 5
+
+
+def call_route(libqii, M, N, K, c_dt, ldc, c=1 << 20, a_scales=1 << 21, ws=1 << 22, tiled=0):
+    """qii_gemm_call_route for operands at made-up addresses."""
+    import ctypes
+    A, B = (libqii._NVFP4(1 << 23, s, 1 << 24, r, K) for r, s in ((M, a_scales), (N, 1 << 21)))
+    size = libqii.qii_gemm_workspace_bytes(M, N, K) if ws else 0
+    return libqii.lib().qii_gemm_call_route(ctypes.byref(A), ctypes.byref(B), c, c_dt, ldc, ws, size, tiled)
+
+
+def test_the_route_of_a_call_heeds_its_result_and_its_scale_bytes(libqii):
+    """Blocks take several tiles from three rounds of tiles on, where C's rows lie on 128-byte lines and are whole 16-byte pieces."""
+    M, N, K = 16384, 8192, 2048
+    assert libqii.lib().qii_gemm_route(M, N, K, libqii.qii_gemm_workspace_bytes(M, N, K), 0) == MAIN
+    for dt in (BF16, F32):
+        line = 64 if dt == BF16 else 32
+        assert call_route(libqii, M, N, K, dt, N) == MAIN_TILES
+        assert call_route(libqii, M, N - line // 8, K, dt, N) == MAIN_TILES
+        assert call_route(libqii, M, N - line // 8, K, dt, N - line // 8) == MAIN       # rows off the lines
+        assert call_route(libqii, M, N - 1, K, dt, N) == MAIN                           # a piece cut
+        assert call_route(libqii, M, N, K, dt, N, c=(1 << 20) + 16) == MAIN             # C off the lines
+        assert call_route(libqii, 2048, N, K, dt, N) == MAIN                            # one round
+    # without a workspace, or with scale bytes that the re-tiling kernel cannot load, the main kernel is out of the question
+    assert call_route(libqii, M, N, K, BF16, N, ws=None) == call_route(libqii, M, N, K, BF16, N, a_scales=(1 << 21) + 8) == T128
+    assert call_route(libqii, M, N, K, BF16, N, a_scales=(1 << 21) + 8, tiled=1) == MAIN_TILES
+    for bad in ((0, N, K), (M, 0, K), (M, N, 24)):
+        assert call_route(libqii, *bad, BF16, N, ws=None) == -1
+    assert call_route(libqii, M, N, K, 7, N) == call_route(libqii, M, N, K, BF16, N - 1) == call_route(libqii, M, N, 128, BF16, N, tiled=1) == -1
+    # the routes differ by the type of the result alone
+    assert call_route(libqii, 16384, 8192, 256, BF16, 8192) == MAIN_TILES and call_route(libqii, 16384, 8192, 256, F32, 8192) == T128
+
+
 def test_routes_of_refused_and_smallest_sizes(libqii):
     L = libqii.lib()
     for bad in ((0, 8, 16, 0, 0), (8, 0, 16, 0, 0), (8, 8, 0, 0, 0), (8, 8, 24, 0, 0), (8, 8, 128, 0, 1)):
