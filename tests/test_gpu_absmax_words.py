@@ -8,6 +8,8 @@ import torch
 
 from paper_2601_22813_amd import binding as qii
 
+from gpu_util import ws
+
 pytestmark = pytest.mark.gpu
 
 
@@ -74,3 +76,24 @@ def test_words_of_a_pair(rows, cols):
             qii.qii_quantize_nvfp4(x, transpose, qii.MS_EDEN, 128, seed, seed + 1, top, given, None)
             same(out, given)
         assert bool((w[512:] == 0xFF).all())
+
+
+@pytest.mark.parametrize("T,d_in,d_out", [(640, 1248, 5376), (1408, 768, 256)])
+def test_slots_that_one_launch_has_cleared_take_one_word(T, d_in, d_out):
+    """A backward pass with an f32 gradient clears all four slots at once: its quantizers have no launch to save, and their abs-max
+    passes run as many blocks as are fastest.  What lies behind the first word of each dense tensor's slot stays as it was."""
+    assert qii.lib().qii_absmax_words(qii.F32, T, d_out, 0, 128) > 1   # (a call of its own would leave as many)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    saved = []
+    for rows in (T, d_out):
+        saved.append(qii.NVFP4Tensor.empty(rows, d_in))
+        qii.qii_quantize_nvfp4(torch.randn((rows, d_in), device="cuda", generator=g), False, qii.RTN, 0, 0, 0, None, saved[-1], ws(256))
+    dX, dW = torch.empty((T, d_in), device="cuda"), torch.empty((d_out, d_in), device="cuda")
+    w = ws(qii.qii_linear_bwd_mode_workspace_bytes(T, d_in, d_out, qii.MS_EDEN))
+    w.fill_(0x7F)
+    qii.qii_linear_bwd_mode(torch.randn((T, d_out), device="cuda", generator=g), *saved, 5, qii.MS_EDEN, dX, dW, w)
+    for slot in (0, 2):   # along the rows and along the columns of the gradient
+        maximum = w[256 * slot:256 * slot + 4].view(torch.float32).item()
+        assert 3.0 < maximum < 8.0
+        assert bool((w[256 * slot + 4:256 * slot + 256] == 0x7F).all())
+    assert torch.isfinite(dX).all() and torch.isfinite(dW).all()
