@@ -996,12 +996,12 @@ __global__ __launch_bounds__(256) void streamk_fixup_kernel(const float *__restr
 // power-limited: fewer active units run at a higher clock, so filling idle units gains less than their number suggests); every round
 // costs 8.57 more for its first loads, its stores and the launch; a shared last round 30.1 (all blocks store their 256 KiB partial
 // tiles at the same moment, and the second kernel adds them up) and, per K tile of a block's range, 3.19 plus 2.62 times the share of
-// the units that work; 1.31 more where ranges span two tiles.  Sharing is used where the model promises 4 %.  Of 796 products
-// of 1 to 255 tiles in their last round, each timed both ways, the rule takes the slower way by more than 3 % for 30 (190 of them outside the
-// fit: 9); with the figures of a plan whose sharing blocks stored more slowly it was 184.  Measured, us, bf16 results,
-// one block per tile : shared: 8448 x 2048 x 3072 128 : 106, 3072 x 2816 x 10240 184 : 157, 8448 x 1024 x 10240 189 : 157,
-// 11264 x 2048 x 6144 250 : 225, 18432 x 2048 x 3072 200 : 189, 2816 x 2048 x 16384 287 : 165, 256 x 256 x 32768 522 : 72; not taken, though
-// it would pay, 2048 x 5632 x 16384 312 : 287 (176 tiles, where the model sees 301 : 292).
+// the units that work; 1.31 more where ranges span two tiles.  Sharing is used where the model promises 4 %.  Of 3274
+// products that can share, each timed both ways on the present kernel (the model is that of one about 3 % slower), the rule takes the slower way by more
+// than 3 % for 93, 9 of them among the 1498 for which this kernel is within 5 % of the fastest.  Measured, us, bf16 results,
+// one block per tile : shared: 8448 x 2048 x 3072 122 : 105, 3072 x 2816 x 10240 183 : 154, 8448 x 1024 x 10240 188 : 157,
+// 11264 x 2048 x 6144 245 : 223, 18432 x 2048 x 3072 196 : 189, 2816 x 2048 x 16384 273 : 157, 256 x 256 x 32768 475 : 60; not taken, though
+// it would pay, 2048 x 5632 x 16384 313 : 288 (176 tiles, where the model sees 301 : 292).
 struct StreamPlan {
     int full;   // launch positions run one block per tile
     int rem;    // positions after them whose tiles are shared (0: none)
@@ -1127,34 +1127,38 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
     return hipGetLastError();
 }
 
-// Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to
-// timings of every kernel, each forced in turn, over 1671 products of M, N = 64 .. 16384 and K = 128 .. 32768, bf16 and f32 results
-// (kt = K / 256, b = blocks / 256 compute units): what the rule takes there is 0.3 % behind the fastest on average.  Of 700 other
-// products it is 0.5 % behind on average, more than 7 % for 16, at most 25 % (2509 x 3630 x 6784 bf16, rows of C that are not
-// aligned, which no model heeds: the no-workspace kernel instead of 64 x 64).  Some of them, us, bf16 results, from a
+// Which kernel a product takes: the one whose modelled time (microseconds) is least.  The models are fitted to timings of every kernel, each
+// forced in turn (kt = K / 256, b = blocks / 256 compute units): those of the kernels for a ragged K, of 64 x 64 tiles and of 128 x 128 tiles in two
+// K groups over 1671 products of M, N = 64 .. 16384 and K = 128 .. 32768, bf16 and f32 results; those of the main kernel and of 128 x 128 tiles in four K
+// groups, both for whole K tiles, over 7200 products (1800 of them of at least 180 tiles of 256 x 256).  What the rule takes of these is 0.37 %
+// behind the fastest on average, more than 7 % for 128, at most 30 % (13440 x 1016 x 512 f32; rows of C that are not aligned, which no model
+// heeds, and K of one or two tiles are the worst); with scale bytes that are tiled already 0.42 %, 178 and 25 %.  Some of them, us, bf16 results, from a
 // graph, operands in cache, on one box:
 //                         64 x 64   128 x 128 KG 2   128 x 128 (4, 4)   256 x 256 (with re-tiling)
-//    256 x  256 x   256        3.8              5.6                6.5     11.4
-//    512 x  512 x   512        4.6              7.8                8.5     15.6
-//   1024 x 1024 x  4096       15.8             34.6               25.4
-//   1536 x 1536 x  1536       13.3             16.3               14.3     31.5
-//   2048 x 2048 x  2048       22.4             22.7               18.9     39.9
-//   2048 x 2048 x 16384      153.4            145.3              108.6    120.6 (shared last round)
-//   4096 x 2048 x  1024       23.9             20.0               23.3     25.5
-//   4096 x 2048 x  8192      150.3            131.1              116.8    121.3 (shared)
-//   2048 x 5632 x  2048       56.1             52.3               52.7     46.1
-//   4096 x 4096 x  4096      149.5            126.1              123.3    100.0
-//   2816 x 2048 x 16384      222.7            233.4              196.5    161.2 (shared)
-//   8448 x 2048 x  3072      120.0            117.9              117.8    108.4 (shared)
-//   8192 x 8192 x   256       76.7             54.2               91.6     53.7
+//    256 x  256 x   256        3.9             5.7                7.4       11.1
+//    512 x  512 x   512        4.6             7.8                8.5       14.8
+//   1024 x 1024 x  4096       16.9            35.9               24.1       41.4 (shared last round)
+//   1536 x 1536 x  1536       13.7            16.7               13.8       30.0
+//   2048 x 2048 x  2048       23.3            22.8               18.7       38.6
+//   2048 x 2048 x 16384      162.3           156.3              102.9      117.6 (shared last round)
+//   4096 x 2048 x  1024       23.8            19.5               23.2       26.5
+//   4096 x 2048 x  8192      152.5           130.2              107.3      116.8 (shared last round)
+//   2048 x 5632 x  2048       56.8            51.9               51.7       46.6
+//   4096 x 4096 x  4096      154.5           130.7              117.8       96.0
+//   2816 x 2048 x 16384      220.7           236.5              177.5      156.8 (shared last round)
+//   8448 x 2048 x  3072      124.3           118.7              112.2      104.4 (shared last round)
+//   8192 x 8192 x   256       81.1            57.0              108.8       48.3
 // 64 x 64 tiles: up to three blocks run on a unit and their time adds up, so the unit with the most blocks counts.
 // 128 x 128 with two K groups: two blocks per unit, so rounds of 512, the last one cheaper the emptier it is, and a block
 // beyond the fourth of a unit cheaper, its first loads and stores beside the products of others.
 // 128 x 128 with a 4 x 4 wave tile: one block per unit, rounds of 256; a K tile costs less while few units
-// work (power).  (Fitted with operands staged through registers and the main kernel's memory operations bunched: the factors 0.935 and 0.97 are what
-// the present kernels take of that, 2048 x 2048 x 16384 105 -> 98 us, 8192^3 730 -> 709.)  K not a multiple of 256 costs these kernels half-width operand loads.  256 x 256: the plan's own figure, and 4.5
-// of re-tiling where the scale bytes are not tiled yet (one or two shared tiles, main kernel : 64 x 64 tiles: 128 x 128 x 24320
-// 51.6 : 70.4, 256 x 256 x 19456 48.1 : 57.8, 256 x 512 x 22784 56.6 : 67.6).
+// work (power); three forms (wide_block_us): K not a multiple of 256 costs it, like the two others, half-width operand loads.  256 x 256: the plan's
+// figure, which is that of a slower kernel and about 3 % too long for the present ones, and 4.5 of re-tiling where the scale bytes are not tiled yet (one or
+// two shared tiles, main kernel : 64 x 64 tiles: 128 x 128 x 24320 51.6 : 70.4, 256 x 256 x 19456 48.1 : 57.8, 256 x 512 x 22784 56.6 : 67.6); for f32 results
+// 1.7 more a round (their stores), and where blocks take several tiles, whose stores leave beside the next tile's products, 4.3 less a round with
+// bf16 results and 1.1 less with f32 ones of two K tiles and more (main kernel : 128 x 128 tiles: bf16 8192 x 6144 x 256 37.9 : 42.3, 16384 x 8192 x 256
+// 84.5 : 111; f32 27648 x 7936 x 512 forward pass 268 : 317; but without that form, 14848 x 3008 x 512 68.1 : 64.8; f32 and one K tile is memory's time, and the
+// one's depends on where C lies, 14592 x 5120 x 256 forward pass 84 to 93 : 84).
 // The no-workspace kernel has 128-wide K tiles, so K an odd multiple of 128 costs it no half tile; at K = 128 and
 // 384, 64 x 64 : 128 x 128 : it: 2048 x 2048 9.1 : 7.7 : 8.8 and 10.5 : 9.9 : 14.4, 4096 x 4096 25.5 : 18.0 : 12.4
 // and 31.6 : 23.9 : 18.9, 8192 x 8192 87 : 59 : 41 and 112 : 84 : 67.
@@ -1166,12 +1170,18 @@ constexpr int64_t kMaxMainK = (int64_t)1 << 23;
 struct Prices {
     double us[5];   // by Route; HUGE_VAL: cannot run
     Route best;
+    double blocks128, ktiles;   // of 128 x 128 tiles
+    bool ragged, direct;        // K no multiple of 256; gemm_wide_applies
 };
 
-// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run.  direct: gemm_wide_applies.  Blocks that take several tiles: a round's bf16 stores leave beside
-// the next round's products, 3.3 us less a round than the plan has it (8192 x 6144 x 256 37.9 us, where 128 x 128 tiles take 42.3; 8192 x 8192
-// x 256 48.9 : 56.3, 16384 x 8192 x 256 84.5 : 111); f32 results take all of a round's figure at short K (memory: 16384 x 8192 x 256 118.8 us for
-// 537 MB).
+// a block of the 4 x 4 form of 128 x 128 tiles, `blocks` of which run: one per unit
+static double wide_block_us(double blocks, double ktiles, bool ragged, bool direct)
+{
+    const double busy = blocks < 256.0 ? blocks / 256.0 : 1.0;
+    return ragged ? 8.78 + (1.63 + 0.262 * busy) * ktiles : direct ? 8.22 + (1.164 + 0.179 * busy) * ktiles : 7.93 + (1.244 + 0.2 * busy) * ktiles;
+}
+
+// main_ws: bytes of workspace that the main kernel can use; 0: it cannot run.  direct: gemm_wide_applies.
 static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool retile, bool direct, const void *C, int64_t ldc, int c_is_bf16)
 {
     auto count = [&](int64_t tile) { return (double)((M + tile - 1) / tile) * (double)((N + tile - 1) / tile); };
@@ -1183,15 +1193,16 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     const double pairs = (double)(int64_t)(b / 2.0), last = b - 2.0 * pairs;
     const double slope = 3.65 * pairs + (last <= 0.0 ? 0.0 : last <= 1.0 ? 1.49 + 0.55 * last : 2.6 + 0.53 * last);
     const double us128 = 4.45 + (any ? 0.74 : 0.0) + 1.7 * b - 0.79 * (b > 4.0 ? b - 4.0 : 0.0) + slope * kt * (any ? 1.276 : 1.0);
-    const double rounds = (double)(int64_t)((n128 + 255.0) / 256.0);
-    const double us_wide = rounds * (7.93 + (any ? 0.85 : 0.0) + (1.244 + 0.2 * (n128 < 256.0 ? n128 / 256.0 : 1.0)) * kt * (any ? 1.31 : direct ? 0.935 : 1.0));
+    const double us_wide = (double)(int64_t)((n128 + 255.0) / 256.0) * wide_block_us(n128, kt, any, direct);
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     const bool narrow = K <= kMaxNarrowK;
-    Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide};
+    Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide, n128, kt, any, direct};
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
-        p.us[kRouteMain] = 0.97 * plan.us + (retile ? 4.5 : 0.0) - (c_is_bf16 && blocks_take_tiles(plan.full, C, ldc, N, 1) ? 3.3 * (double)(plan.full / 256) : 0.0);
+        const bool several = blocks_take_tiles(plan.full, C, ldc, N, c_is_bf16);
+        const double round_us = c_is_bf16 ? (several ? -4.3 : 0.0) : several && K > BK4 ? -1.1 : 1.7;
+        p.us[kRouteMain] = (plan.rem ? 0.981 : 0.97) * plan.us + (retile ? 4.5 : 0.0) + round_us * (double)(plan.full / 256);
     }
     if (!main_ws && K % 128 == 0) p.us[kRouteNoWorkspace] = us_v2;
     for (const Route r : {kRoute128, kRoute128Wide, kRouteMain, kRouteNoWorkspace})
@@ -1244,22 +1255,32 @@ static SmallTile small_tile(Route route, int64_t K)
     return route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : route == kRoute64 ? kTile64 : kTile128;
 }
 
+// Both products in one launch of the 4 x 4 form, a's blocks first, K whole K tiles: the units share the work evenly but for the last blocks (0.4 of
+// one of b's as fitted; a round counted for each product, as with a launch each, has units idle twice).
+static double wide_pair_us(const Prices &a, const Prices &b)
+{
+    const double blocks = a.blocks128 + b.blocks128;
+    const bool direct = a.direct && b.direct;
+    const double us_a = wide_block_us(blocks, a.ktiles, false, direct), us_b = wide_block_us(blocks, b.ktiles, false, direct);
+    const double even = (a.blocks128 * us_a + b.blocks128 * us_b) / 256.0 + (blocks > 256.0 ? 0.4 * us_b : 0.0), longest = us_a > us_b ? us_a : us_b;
+    return even > longest ? even : longest;
+}
+
 // Whether two products whose operands are both ready take one launch of a small-tile kernel: where their modelled times in that
 // kernel, less what a launch of its own costs the second (the launch itself, and units that idle at the end of one and at the
-// beginning of the other), are below those of the products' own routes.  Returns that kernel, else kRouteMain.  The three
-// savings are fitted to 200 backward passes of T, d_in, d_out = 128 .. 8192, each with two launches and with one of each kernel; of 260
-// others the choice is 0.7 % of the pass behind the fastest on average (3.2 % where products shared a launch only if both took the
-// kernel alone), at most 28 %.  Whole passes, us, two launches : one: 64 x 64 tiles 128 x 2432 -> 1408 post hoc 31.1 : 24.2, 1280 x
-// 512 -> 4864 64.3 : 52.3, 3840 x 1280 -> 1024 f32 gradient 86.2 : 80.6; 128 x 128 in two groups 1920 x 6144 -> 1408 128.9 :
-// 105.8, 640 x 4992 -> 896 50.8 : 39.4; in four 6912 x 640 -> 3840 129.1 : 112.1; but 6656 x 6912 -> 256 115.6 : 135.0, 4992 x 5616 -> 128
-// 83.0 : 96.4.
+// beginning of the other), are below those of the products' own routes.  Returns that kernel, else kRouteMain.  The
+// savings are fitted to 2000 backward passes of T, d_in, d_out = 128 .. 12288, each with two launches and with one of each kernel; the choice there is 0.8 %
+// of the pass behind the fastest on average, at most 27 %.  Whole passes, us, two launches : one: 64 x 64 tiles 128 x 2432 -> 1408 post
+// hoc 31.1 : 24.2, 1280 x 512 -> 4864 64.3 : 52.3, 3840 x 1280 -> 1024 f32 gradient 86.2 : 80.6; 128 x 128 in two groups 1920 x 6144 -> 1408 128.9 :
+// 105.8, 640 x 4992 -> 896 50.8 : 39.4; in four 9728 x 256 -> 4352 128.0 : 102.3, 6144 x 1536 -> 4608 197 : 182; but 6656 x 6912 -> 256 115.6 : 135.0,
+// 4992 x 5616 -> 128 83.0 : 96.4.
 static Route shared_route(const Prices &a, const Prices &b)
 {
-    constexpr double kSaved[5] = {0.0, 0.0, 9.6, 11.7, 12.0};
+    constexpr double kSaved[5] = {0.0, 0.0, 10.0, 12.0, 12.0};
     Route best = kRouteMain;
     double us = a.us[a.best] + b.us[b.best];
     for (const Route r : {kRoute64, kRoute128, kRoute128Wide}) {
-        const double t = a.us[r] + b.us[r] - kSaved[r];
+        const double t = r == kRoute128Wide && !a.ragged ? wide_pair_us(a, b) : a.us[r] + b.us[r] - kSaved[r];
         if (t < us) { us = t; best = r; }
     }
     return best;

@@ -129,6 +129,10 @@ PASS_US = {
     (1920, 6144, 1408): (128.89, 121.71, 105.75, 118.24), (512, 6528, 512): (46.41, 43.42, 40.05, 47.27), (640, 4992, 896): (50.75, 43.28, 39.39, 45.66),
     (6912, 640, 3840): (129.08, 124.61, 123.78, 112.09), (2688, 5792, 640): (81.03, 91.66, 89.86, 88.78), (6656, 6912, 256): (115.57, 134.98, 144.82, 144.61),
     (5120, 3968, 512): (82.69, 90.89, 111.24, 97.96), (4992, 5616, 128): (83.01, 96.38, 103.96, 110.89), (6912, 3840, 256): (79.18, 91.88, 103.58, 102.64),
+    (1536, 1872, 768): (36.7, 33.6, 37.5, 39.6), (768, 2304, 1280): (35.1, 32.3, 33.2, 35.7),
+    # the four-group form, whose blocks of both products share the rounds
+    (2560, 512, 6656): (84.8, 74.8, 91.0, 69.1), (6144, 1536, 4608): (197.1, 226.3, 198.6, 182.4), (8192, 256, 7168): (140.7, 135.5, 138.8, 116.2),
+    (9728, 256, 4352): (128.0, 113.5, 132.0, 102.3), (3072, 624, 2816): (54.6, 50.4, 50.1, 44.0),
 }
 
 
@@ -203,7 +207,32 @@ def test_the_route_of_a_call_heeds_its_result_and_its_scale_bytes(libqii):
         assert call_route(libqii, *bad, BF16, N, ws=None) == -1
     assert call_route(libqii, M, N, K, 7, N) == call_route(libqii, M, N, K, BF16, N - 1) == call_route(libqii, M, N, 128, BF16, N, tiled=1) == -1
     # the routes differ by the type of the result alone
-    assert call_route(libqii, 16384, 8192, 256, BF16, 8192) == MAIN_TILES and call_route(libqii, 16384, 8192, 256, F32, 8192) == T128
+    assert call_route(libqii, 5376, 5376, 512, BF16, 5376) == MAIN and call_route(libqii, 5376, 5376, 512, F32, 5376) == T128
+
+
+# products, us: the main kernel (re-tiling included, the last round shared where the plan says so), tiles of 64 x 64, of 128 x 128 in two K
+# groups, in four
+ROUTE_US = {
+    # short K: 64 x 64 tiles, though the four-group form takes less per K tile than it did
+    (1856, 1664, 768, F32): (22.3, 9.5, 11.5, 11.3), (226, 11243, 768, BF16): (26.3, 10.5, 12.6, 12.3),
+    (4352, 512, 1024, F32): (24.1, 10.7, 13.1, 12.0), (256, 9216, 1024, F32): (24.3, 10.8, 13.3, 12.3), (1280, 2304, 768, BF16): (19.2, 9.3, 10.8, 10.5),
+    (768, 4096, 768, BF16): (19.3, 9.3, 10.8, 10.5), (576, 3648, 1024, F32): (27.0, 10.2, 13.2, 12.3),
+    # few tiles of long K: a shared round is not as much cheaper as a whole one
+    (6016, 256, 11520, F32): (62.7, 59.3, 98.8, 59.0), (450, 2419, 9216, F32): (51.4, 44.7, 76.4, 47.3),
+    # f32 results at short K: memory, whose time the main kernel's price has per round
+    (11584, 3776, 512, F32): (67.3, 76.9, 63.6, 99.5), (14848, 3008, 512, F32): (68.1, 76.5, 64.8, 104.5), (9216, 2368, 1536, F32): (78.2, 80.1, 72.9, 84.0),
+    (2376, 22776, 768, F32): (118.8, 123.6, 105.4, 150.6), (7320, 4872, 1280, F32): (114.6, 122.6, 100.8, 126.4),
+    # but not where its blocks take several tiles
+    (25344, 15616, 512, F32): (423.4, 736.3, 523.7, 808.6), (32768, 2560, 512, F32): (105.6, 149.4, 113.7, 181.7),
+}
+
+
+@pytest.mark.parametrize("M,N,K,c_dt", ROUTE_US)
+def test_the_fastest_kernel_of_a_product(libqii, M, N, K, c_dt):
+    """Within 3 %."""
+    us = dict(zip((MAIN, T64, T128, T128_WIDE), ROUTE_US[M, N, K, c_dt]))
+    us[MAIN_TILES] = us[MAIN]
+    assert us[call_route(libqii, M, N, K, c_dt, N)] <= 1.03 * min(us.values())
 
 
 def test_routes_of_refused_and_smallest_sizes(libqii):
