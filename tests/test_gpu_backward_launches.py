@@ -77,6 +77,34 @@ def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, m
             assert np.all(np.abs(bf16_to_f64(got)[ms, ns] - ref) <= tol)
 
 
+@pytest.mark.parametrize("T,d_in,d_out", [(512, 2176, 3584), (512, 2064, 3584)])
+@pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
+def test_backward_products_of_two_k_tiles(oracle, T, d_in, d_out, mode):
+    """Both products in one launch of 128 x 128 tiles in four K groups, one with K = 512: fewer K tiles than the kernel's four stages, and
+    fewer than its loads run ahead."""
+    size = max(qii.qii_gemm_workspace_bytes(T, d_in, d_out), qii.qii_gemm_workspace_bytes(d_out, d_in, T))
+    assert qii.lib().qii_linear_bwd_gemm_route(T, d_in, d_out, size, 1) == T128_WIDE
+    Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=8)
+    oXq, oWq = oracle.linear_fwd(Xb, Wb)
+    Eq, WTq, ETq, XTq = oracle.linear_bwd_operands(Eb, oXq, oWq, 11, mode)
+    E, Xq, Wq = to_dev(Eb), nv_to_dev(oXq), nv_to_dev(oWq)
+    rng = np.random.default_rng(T + d_in)
+    for dtype in (torch.float32, torch.bfloat16):
+        print(f"backward T={T} {d_in}->{d_out} mode {mode} {dtype}", flush=True)
+        dX, dW = (torch.full((r, d_in), float("nan"), dtype=dtype, device="cuda") for r in (T, d_out))
+        w = ws(qii.qii_linear_bwd_mode_workspace_bytes(T, d_in, d_out, mode))
+        w.fill_(0x7F)
+        qii.qii_linear_bwd_mode(E, Xq, Wq, 11, mode, dX, dW, w)
+        torch.cuda.synchronize()
+        for got, (a, b) in ((dX, (Eq, WTq)), (dW, (ETq, XTq))):
+            assert torch.isfinite(got).all()
+            ms = np.concatenate([rng.integers(0, a.rows, 6000), [0, 0, a.rows - 1, a.rows - 1]])
+            ns = np.concatenate([rng.integers(0, b.rows, 3000), rng.integers(b.rows - 100, b.rows, 3000), [0, b.rows - 1, 0, b.rows - 1]])
+            ref, absum = oracle.gemm_sampled(a, b, ms, ns)
+            tol = 1e-5 * absum + (2.0 ** -8 * np.abs(ref) if dtype == torch.bfloat16 else 0.0) + 1e-30
+            assert np.all(np.abs(bf16_to_f64(got)[ms, ns] - ref) <= tol)
+
+
 @pytest.mark.parametrize("T,d_in,d_out", [(128, 128, 128), (512, 512, 512), (384, 208, 256), (1024, 2048, 2048), (4096, 2048, 4096)])
 @pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
 @pytest.mark.parametrize("place", ["apart", "misaligned", "dX in dY", "dW in dY", "dX beside dW"])

@@ -369,13 +369,17 @@ def test_forward_pass_hands_its_abs_max_to_the_next_layer(oracle):
         check(bf16_to_f64(Y2), ref, absum, True)
 
 
-@pytest.mark.parametrize("M,N,K", [(12288, 4096, 256), (12288, 4096, 512), (12200, 4032, 512), (12800, 4064, 1280)])
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("M,N,K,dtype", [
+    (12288, 4096, 256, torch.bfloat16), (12288, 4096, 256, torch.float32), (12288, 4096, 512, torch.bfloat16), (12288, 4096, 512, torch.float32),
+    (12200, 4032, 512, torch.bfloat16), (12200, 4032, 512, torch.float32), (12800, 4064, 1280, torch.bfloat16), (12800, 4064, 1280, torch.float32),
+    # the last row and column of tiles end within their first waves' 128 rows and columns, and C's rows within a round of the epilogue (64 columns of
+    # bf16, 32 of f32), the last of them after a single row and a single 16-byte piece
+    (12388, 4200, 1280, torch.bfloat16), (12388, 4132, 1280, torch.float32), (12289, 4104, 1280, torch.bfloat16), (12289, 4100, 1280, torch.float32)])
 def test_gemm_blocks_that_take_several_tiles(M, N, K, dtype):
     """Three rounds of 256 x 256 tiles and a little more, whole and cut by M and N, one, two and five K tiles: against the products of the
-    dequantized operands in binary64; the same bits as the kernel with a block per tile, which takes C with unaligned rows (the sums
-    run in the same order; K = 256 takes another kernel there), nothing beyond N, and the emitted maximum is that of the
-    stored values."""
+    dequantized operands in binary64; the same bits as the kernel with a block per tile, where C with unaligned rows takes that (the sums
+    run in the same order), nothing beyond N, and the emitted maximum is that of the stored values, whatever the workspace held before
+    (scale bytes of 0xFF in the rows beyond M and N are NaN).  f32 results of a single K tile take another kernel."""
     g = torch.Generator(device="cuda").manual_seed(M + K)
     a, b = (qii.NVFP4Tensor.empty(r, K) for r in (M, N))
     f64 = []
@@ -385,18 +389,22 @@ def test_gemm_blocks_that_take_several_tiles(M, N, K, dtype):
         qii.qii_dequantize_nvfp4(t, d)
         f64.append(d.double())
     w = ws(qii.qii_gemm_workspace_bytes(M, N, K))
-    assert qii.lib().qii_gemm_route(M, N, K, w.numel(), 0) == 0
     line = 64 if dtype == torch.bfloat16 else 32
     ld = (N + line) // line * line
     odd, whole = (torch.full((M, n), -3.0, dtype=dtype, device="cuda") for n in (N + 1, ld))
     top = torch.zeros(1, device="cuda")
+    several, main = 5, 0   # the library's names (qii_gemm_call_route)
+    assert (qii.qii_gemm_call_route(a, b, whole, w) == several) == (dtype == torch.bfloat16 or K > 256)
+    same = qii.qii_gemm_call_route(a, b, odd, w) == main
+    assert same or K <= 512
     qii.qii_gemm_nvfp4(a, b, odd, w)
     whole_only = None
     for _ in range(3):
         whole.fill_(-3.0)
+        w.fill_(0xFF)
         qii.qii_gemm_nvfp4_amax(a, b, whole, top, w)
         torch.cuda.synchronize()
-        assert K == 256 or torch.equal(whole[:, :N], odd[:, :N])
+        assert not same or torch.equal(whole[:, :N], odd[:, :N])
         assert bool((whole[:, N:] == -3.0).all())
         assert top.item() == whole[:, :N].float().abs().max().item()
         assert whole_only is None or torch.equal(whole, whole_only)
