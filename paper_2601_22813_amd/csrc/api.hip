@@ -472,8 +472,8 @@ qii_status qii_quantize_nvfp4_noalloc(const void *x, qii_dtype dt, int64_t rows,
     void *base = nullptr;
     st = scratch_address(&base);
     if (st != QII_OK) return st;
-    // the slot is cleared by quantize_source (a fill kernel); the per-group buffer is written in
-    // full by the heavy pass before the scales pass reads it
+    // quantize_source clears the slot (a fill kernel) or has every word that is read written first; the per-group buffer is
+    // written in full by the heavy pass before the scales pass reads it
     float *slot = reinterpret_cast<float *>(base);
     float *tbuf = mode == QII_MS_EDEN_PH ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(base) + kRegion) : nullptr;
     return quantize_source(src, R, C, mode, rht_group, seed_rht, seed_sr, nullptr, out, slot, tbuf,

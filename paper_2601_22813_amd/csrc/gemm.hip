@@ -468,14 +468,13 @@ __device__ __forceinline__ void dequant_all(std::integer_sequence<int, I...>, Fr
 // the issue of the memory operations run in the shadow of the matrix pipe.  (A K tile's 18 loads, with their
 // address arithmetic, and 64 LDS reads used to be issued in blocks between the steps, with the matrix pipe idle:
 // 16384 x 2048 x 8192 441 -> 412 us, 32768 x 16384 x 2048 1820 -> 1743, 8192^3 827 -> 797 on one box.)
-// kNew: the tile's first step, which begins the sums.
-template <int D, int J, bool kNew = false, class Side>
+template <int D, int J, class Side>
 __device__ __forceinline__ void mma_step(floatx16 (&acc)[4][4], const Frags &cu, Frags &nx, const RawFrag4 &f, const TileScales &ts, SliceScales &ss,
                                          uint32_t sel, const Side &side)
 {
 #define QII_MMA(I)                                                                                          \
     acc[(I) >> 2][(I) & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cu.b[(I) & 3], cu.a[(I) >> 2],          \
-                                                                    kNew ? floatx16{} : acc[(I) >> 2][(I) & 3], 0, 0, 0);       \
+                                                                    acc[(I) >> 2][(I) & 3], 0, 0, 0);                            \
     side.template at<I>();                                                                                  \
     dequant_chunk<I, D, J>(nx, f, ts, ss, sel);                                                             \
     __builtin_amdgcn_sched_barrier(0)
@@ -677,12 +676,6 @@ __global__ __launch_bounds__(256, 1) void gemm_kernel_v4(const uint8_t *__restri
     }
 }
 
-// The epilogue of a block that goes on to another tile: both LDS stages stay with the loads of the K tiles to come, so a wave's
-// 128 x 128 entries pass through 4 KiB of their own, 128 bytes of 32 rows at a time (64 columns of bf16, 32 of f32), and leave as
-// whole 128-byte lines.  While a round's reads are under way the next round's entries are converted.  LDS operations of a wave run in
-// order, so its writes need no wait for the reads before them; they are inline assembly like the fragment reads, because the compiler
-// would let them wait for the loads.  16-byte piece s of row r is at slot s ^ (r % 8): neither side has bank conflicts.
-// What lies beyond C is dropped by the descriptor.  (Straight from the accumulators, 32 bytes of a row at a time: 2.2 us longer for a tile, and with non-temporal stores 17 to 46.)
 // maximum over a wave by lane exchanges that need no lane number (one more register kept through the loop)
 __device__ __forceinline__ float wave_max_in_registers(float m)
 {
@@ -696,6 +689,12 @@ __device__ __forceinline__ float wave_max_in_registers(float m)
     return fmaxf(u2f(y[0]), u2f(y[1]));
 }
 
+// The epilogue of a block that goes on to another tile: both LDS stages stay with the loads of the K tiles to come, so a wave's
+// 128 x 128 entries pass through 4 KiB of their own, 128 bytes of 32 rows at a time (64 columns of bf16, 32 of f32), and leave as
+// whole 128-byte lines.  While a round's reads are under way the next round's entries are converted.  LDS operations of a wave run in
+// order, so its writes need no wait for the reads before them; they are inline assembly like the fragment reads, because the compiler
+// would let them wait for the loads.  16-byte piece s of row r is at slot s ^ (r % 8): neither side has bank conflicts.
+// What lies beyond C is dropped by the descriptor.  (Straight from the accumulators, 32 bytes of a row at a time: 2.2 us longer for a tile, and with non-temporal stores 17 to 46.)
 constexpr int kStoreArea = 4096;   // LDS bytes per wave
 
 template <bool kBf16Out, bool kMax>
@@ -1105,7 +1104,7 @@ static hipError_t launch_main_kernel(const qii_nvfp4 &A, const uint8_t *a_tiled,
         constexpr int kLds = kSmem4 + 4 * kStoreArea;   // all of a compute unit's 160 KiB
         auto launch = [&](auto kernel, hipError_t ready) {
             if (ready == hipSuccess)
-                hipLaunchKernelGGL(kernel, dim3((unsigned)(plan.full < 256 ? plan.full : 256)), dim3(256), kLds, s, A.codes, a_tiled, A.tensor_scale,
+                hipLaunchKernelGGL(kernel, dim3(256), dim3(256), kLds, s, A.codes, a_tiled, A.tensor_scale,
                                    B.codes, b_tiled, B.tensor_scale, M, N, K, C, ldc, tiles_m, tiles_n, plan.full, amax_out);
             return ready;
         };

@@ -503,15 +503,17 @@ __global__ __launch_bounds__(G::kThreads, G::kBlocksPerUnit) void gemm_small_ker
     }
 }
 
-// ---- the 4 x 4 form for K a multiple of 256 -------------------------------------------------------
+// ---- the 4 x 4 form where gemm_wide_applies -------------------------------------------------------
 // As the main kernel: codes and scale bytes go straight from memory to LDS (no staging registers, no LDS writes), four stages of
 // a K tile, and the fragment reads are inline assembly with their own waits (the compiler would let them wait for the loads).  A wave has
 // its slice of the next K tile in registers before it multiplies the last step of this one, so the barrier that shows the next tile
 // frees this tile's stage too: the loads of tile kt + 4 follow it, one every 5 matrix instructions, the 16 reads of tile kt + 1 one every
 // 2 (1 to 3 and 3 to 7 are all the same).  us, operands staged through registers : this: 1024 x 4096 x 4096 32.3 : 30.1, 2048 x 2048 x 5632 41.3 :
 // 39.0, 2048 x 2048 x 16384 f32 105.1 : 98.2, 2048^3 19.1 : 18.3, 1500 x 2000 x 1024 12.2 : 11.7, 2048 x 2048 x 256 6.8 : 6.8, 2040 x 1999 x 768
-// f32 13.7 : 13.7.  A K tile then takes 1.44 us where the main kernel takes 1.34 for as many matrix instructions: half the
-// tile has twice the operand bytes for each.
+// f32 13.7 : 13.7.  A K tile then takes 1.44 to 1.53 us by the box's clock where the main kernel takes 1.34 for as many matrix instructions, which has half the
+// operand bytes and 10 LDS reads for each 64, where this has 16.  Copies of the kernel, us, as it is : without its loads behind the first four tiles :
+// without its LDS reads : without both: 1024 x 4096 x 4096 31.8 : 29.4 : 27.4 : 25.3, 2048 x 2048 x 16384 105.4 : 94.4 : 81.9 : 75.1, per K tile 1.53 : 1.35 : 1.14 :
+// 1.04 (without reads the operands do not change either, which draws less power).
 constexpr int kWideStages = 4;
 constexpr int64_t kMaxWideK = (int64_t)1 << 23;
 constexpr int kLoadEvery = 5, kReadEvery = 2;

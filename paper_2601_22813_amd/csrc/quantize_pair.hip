@@ -226,7 +226,8 @@ hipError_t launch_quantize_pair(const PairQuantizeArgs &p, hipStream_t s)
 // tiles (four a block, a block per unit), so a round with few tiles costs as much as a full one; below one round it has fewer
 // waves in flight than the other.  The other reads 64-byte pieces of a source row, and fetches a line twice unless
 // neighbouring column blocks run on one die (`local`: the number of its row blocks is a multiple of 8, or its stripe order
-// applies).  Whole MS-EDEN calls, us, columns kernel : tile kernel, on one box:
+// applies).  Whole MS-EDEN calls, us, columns kernel : tile kernel, both with a cleared word and atomics, on one box (a quantizer call whose blocks leave
+// words goes by absmax_tiles_words; this is the rule of the others and of qii_absmax):
 //   128 tiles  1024 x 2048 13.0 : 12.5            4096 x  512 (local) 13.0 : 12.5   128 x 16384 (local) 15.5 : 11.8
 //   256 tiles  2048 x 2048 14.6 : 15.7            4096 x 1024 (local) 14.5 : 14.2   512 x  8192 (local) 14.6 : 15.0
 //   512 tiles  4096 x 2048 (local) 17.0 : 18.8    1024 x 8192 (local) 17.3 : 17.5

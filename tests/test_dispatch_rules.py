@@ -13,8 +13,9 @@ def libqii():
     return binding
 
 
-# whole MS-EDEN calls along the columns of a bf16 matrix, us: abs-max by column blocks, by 128 x 128 tiles; shapes where the
-# two differ by more than their repeated runs do
+# whole MS-EDEN calls along the columns of a bf16 matrix, us: abs-max by column blocks, by 128 x 128 tiles, with one cleared word and atomics in
+# both, as qii_absmax measures (a quantizer call whose blocks leave words goes by WORDS_US); shapes where the two differ by more than their
+# repeated runs do
 ABSMAX_US = {
     (128, 8192): (12.7, 10.8), (1024, 2048): (13.0, 12.5), (4096, 512): (13.0, 12.5), (128, 16384): (15.5, 11.8),
     (3328, 1024): (12.8, 14.3), (2048, 2048): (14.6, 15.7), (896, 8192): (15.8, 17.9), (4096, 2048): (17.0, 18.8),
