@@ -31,7 +31,7 @@ struct RequantArgs {
     int64_t R, C;        // logical shape: R = stored columns (output rows), C = stored rows
     uint32_t sign[4];
     uint64_t seed_sr;
-    const float *amax;   // the tensor maximum (words == 0), or that of the `words` words the abs-max kernel's blocks left
+    const float *amax;   // the tensor maximum: see slot_max
     uint8_t *codes;
     uint8_t *scales;
     float *tensor_scale;
@@ -168,13 +168,13 @@ __device__ __forceinline__ void requant_block(Args a, int block, uint8_t *image)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t chunk0, col0;
     tile_origin<kChunks>(a, block, chunk0, col0);
+    const float word = kMode != QII_MS_EDEN_PH ? slot_word(a.amax, a.words) : 0.0f;
     RawTile raw;
     load_tile<kChunks>(raw, a, chunk0, col0);
     // (the heavy pass of the post hoc scheme knows no tensor maximum: tc stays unused there)
     TensorConsts tc = TensorConsts{};
     if (kMode != QII_MS_EDEN_PH) {
-        const float amax = a.words ? wave_max(lane < a.words ? a.amax[lane] : 0.0f) : *a.amax;   // uniform
-        tc = tensor_consts(kMode, amax);
+        tc = tensor_consts(kMode, slot_max(a.amax, a.words, word));
         if (block == 0 && threadIdx.x == 0) *a.tensor_scale = tc.x32;
         fill_inv_table(inv_tab, tc);
     }
