@@ -1169,7 +1169,7 @@ constexpr int64_t kMaxMainK = (int64_t)1 << 23;
 struct Prices {
     double us[5];   // by Route; HUGE_VAL: cannot run
     Route best;
-    double blocks128, ktiles;   // of 128 x 128 tiles
+    double blocks64, blocks128, ktiles;
     bool ragged, direct;        // K no multiple of 256; gemm_wide_applies
 };
 
@@ -1196,7 +1196,7 @@ static Prices price_routes(int64_t M, int64_t N, int64_t K, size_t main_ws, bool
     const double full = (double)(int64_t)(n256 / 256.0), rem = n256 - 256.0 * full, rounds256 = full + (rem > 0.0 ? 1.0 : 0.0);
     const double us_v2 = 1.04 * (3.0 + rounds256 * 6.7 + (7.5 * full + (rem > 176.0 ? 6.9 : rem > 0.0 ? 5.9 : 0.0)) * ((double)K / 256.0));
     const bool narrow = K <= kMaxNarrowK;
-    Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide, n128, kt, any, direct};
+    Prices p = {{HUGE_VAL, HUGE_VAL, narrow ? us64 : HUGE_VAL, narrow ? us128 : HUGE_VAL, us_wide}, narrow ? kRoute64 : kRoute128Wide, n64, n128, kt, any, direct};
     if (main_ws) {
         const StreamPlan plan = plan_that_fits(M, N, K, main_ws);
         const bool several = blocks_take_tiles(plan.full, C, ldc, N, c_is_bf16);
@@ -1254,32 +1254,38 @@ static SmallTile small_tile(Route route, int64_t K)
     return route == kRoute128Wide || K > kMaxNarrowK ? kTile128Wide : route == kRoute64 ? kTile64 : kTile128;
 }
 
-// Both products in one launch of the 4 x 4 form, a's blocks first, K whole K tiles: the units share the work evenly but for the last blocks (0.4 of
-// one of b's as fitted; a round counted for each product, as with a launch each, has units idle twice).
-static double wide_pair_us(const Prices &a, const Prices &b)
+// Both products in one launch of kernel r, a's blocks first: as long as all their work spread over the units and part of a last block's way from
+// where the others end, as b's blocks one behind a's work, or as one of a's blocks; whichever is the longest.  A block of 64 x 64 or of 128 x 128 tiles
+// in two K groups that shares its unit takes less of it (work) than it takes alone.  (The products' own prices are longer for a ragged K, by the last summand.)
+static double shared_us(const Prices &a, const Prices &b, Route r)
 {
-    const double blocks = a.blocks128 + b.blocks128;
-    const bool direct = a.direct && b.direct;
-    const double us_a = wide_block_us(blocks, a.ktiles, false, direct), us_b = wide_block_us(blocks, b.ktiles, false, direct);
-    const double even = (a.blocks128 * us_a + b.blocks128 * us_b) / 256.0 + (blocks > 256.0 ? 0.4 * us_b : 0.0), longest = us_a > us_b ? us_a : us_b;
-    return even > longest ? even : longest;
+    if (a.us[r] == HUGE_VAL || b.us[r] == HUGE_VAL) return HUGE_VAL;
+    const double na = r == kRoute64 ? a.blocks64 : a.blocks128, nb = r == kRoute64 ? b.blocks64 : b.blocks128;
+    auto work = [&](const Prices &p) {
+        return r == kRoute64    ? 0.99 + 0.59 * p.ktiles * (p.ragged ? 1.043 : 1.0)
+               : r == kRoute128 ? 1.8 + 1.9 * p.ktiles
+                                : wide_block_us(na + nb, p.ktiles, p.ragged, a.direct && b.direct);
+    };
+    auto alone = [&](const Prices &p) { return r == kRoute64 ? 0.9 * p.ktiles * (p.ragged ? 1.043 : 1.0) : r == kRoute128 ? 2.51 + 2.84 * p.ktiles : work(p); };
+    const double tail = r == kRoute64 ? 0.7 : r == kRoute128 ? 0.56 : 0.33, under_way = r == kRoute64 ? 0.0 : 128.0;
+    const double even = (na * work(a) + nb * work(b)) / 256.0 + (na + nb > 256.0 ? tail * alone(b) : 0.0);
+    const double behind = (na > under_way ? (na - under_way) * work(a) / 256.0 : 0.0) + alone(b);
+    const double longest = behind > alone(a) ? behind : alone(a);
+    return (even > longest ? even : longest) + (!a.ragged ? 0.0 : r == kRoute128Wide ? 7.1 : 10.0);
 }
 
-// Whether two products whose operands are both ready take one launch of a small-tile kernel: where their modelled times in that
-// kernel, less what a launch of its own costs the second (the launch itself, and units that idle at the end of one and at the
-// beginning of the other), are below those of the products' own routes.  Returns that kernel, else kRouteMain.  The
-// savings are fitted to 2000 backward passes of T, d_in, d_out = 128 .. 12288, each with two launches and with one of each kernel; the choice there is 0.8 %
-// of the pass behind the fastest on average, at most 27 %.  Whole passes, us, two launches : one: 64 x 64 tiles 128 x 2432 -> 1408 post
-// hoc 31.1 : 24.2, 1280 x 512 -> 4864 64.3 : 52.3, 3840 x 1280 -> 1024 f32 gradient 86.2 : 80.6; 128 x 128 in two groups 1920 x 6144 -> 1408 128.9 :
-// 105.8, 640 x 4992 -> 896 50.8 : 39.4; in four 9728 x 256 -> 4352 128.0 : 102.3, 6144 x 1536 -> 4608 197 : 182; but 6656 x 6912 -> 256 115.6 : 135.0,
-// 4992 x 5616 -> 128 83.0 : 96.4.
+// Whether two products whose operands are both ready take one launch of a small-tile kernel: where the modelled time of that launch is
+// below those of the products' own routes and what a launch of its own costs the second, 6.6 us.  Returns that kernel, else kRouteMain.  Fitted to 8273 backward
+// passes of T, d_in, d_out = 128 .. 16384, each with two launches and with one of each kernel; the choice is 0.31 % of the pass behind the fastest on average, more
+// than 5 % for 134, at most 16 % (the products' times in that kernel added up, less a constant each: 1.15 %, 724, 21 %).  Whole passes, us, two
+// launches : one of 64 x 64 tiles : of 128 x 128 in two groups : in four: T = 128, 1792 -> 14208 97.2 : 79.7 : 149 : 107, but 17920, 1280 -> 256 (dW's long blocks
+// last) 102 : 124 : 182 : 140; 256, 7344 -> 7936 152 : 151 : 129 : 168; 7040, 256 -> 6528 132 : 130 : 125 : 110.
 static Route shared_route(const Prices &a, const Prices &b)
 {
-    constexpr double kSaved[5] = {0.0, 0.0, 10.0, 12.0, 12.0};
     Route best = kRouteMain;
-    double us = a.us[a.best] + b.us[b.best];
+    double us = a.us[a.best] + b.us[b.best] + 6.6;
     for (const Route r : {kRoute64, kRoute128, kRoute128Wide}) {
-        const double t = r == kRoute128Wide && !a.ragged ? wide_pair_us(a, b) : a.us[r] + b.us[r] - kSaved[r];
+        const double t = shared_us(a, b, r);
         if (t < us) { us = t; best = r; }
     }
     return best;

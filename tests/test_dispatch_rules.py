@@ -134,6 +134,11 @@ PASS_US = {
     # the four-group form, whose blocks of both products share the rounds
     (2560, 512, 6656): (84.8, 74.8, 91.0, 69.1), (6144, 1536, 4608): (197.1, 226.3, 198.6, 182.4), (8192, 256, 7168): (140.7, 135.5, 138.8, 116.2),
     (9728, 256, 4352): (128.0, 113.5, 132.0, 102.3), (3072, 624, 2816): (54.6, 50.4, 50.1, 44.0),
+    # which product is long and which comes first decides as much as the sum: a long one behind many short blocks keeps few units busy at the end
+    (17920, 1280, 256): (102.1, 124.3, 181.7, 140.3), (14848, 1648, 512): (117.5, 138.2, 182.9, 149.2), (10240, 3328, 256): (113.0, 131.5, 155.3, 148.3),
+    (128, 1792, 14208): (97.2, 79.7, 149.0, 106.9), (384, 1296, 9856): (95.8, 80.8, 126.2, 99.7), (128, 2448, 12160): (101.3, 85.9, 137.1, 101.6),
+    (256, 7344, 7936): (151.5, 150.9, 129.1, 168.0), (128, 14592, 1152): (67.9, 69.3, 59.3, 72.3), (1920, 2816, 8064): (257.2, 258.1, 222.1, 235.7),
+    (7040, 256, 6528): (131.5, 130.0, 125.3, 109.6), (11136, 384, 7808): (285.9, 275.6, 267.8, 247.5), (3712, 512, 3968): (78.9, 73.7, 70.7, 63.9),
 }
 
 

@@ -80,10 +80,10 @@ def test_backward_products_of_the_larger_tiles(oracle, T, d_in, d_out, routes, m
 @pytest.mark.parametrize("T,d_in,d_out", [(512, 2176, 3584), (512, 2064, 3584)])
 @pytest.mark.parametrize("mode", [qii.MS_EDEN, qii.MS_EDEN_PH])
 def test_backward_products_of_two_k_tiles(oracle, T, d_in, d_out, mode):
-    """Both products in one launch of 128 x 128 tiles in four K groups, one with K = 512: fewer K tiles than the kernel's four stages, and
-    fewer than its loads run ahead."""
+    """Both products in one launch, one with K = 512: two K tiles.  (64 x 64 tiles: no product of fewer than three K tiles takes 128 x 128 tiles in
+    four K groups, whose loads run four ahead.)"""
     size = max(qii.qii_gemm_workspace_bytes(T, d_in, d_out), qii.qii_gemm_workspace_bytes(d_out, d_in, T))
-    assert qii.lib().qii_linear_bwd_gemm_route(T, d_in, d_out, size, 1) == T128_WIDE
+    assert qii.lib().qii_linear_bwd_gemm_route(T, d_in, d_out, size, 1) == T64
     Xb, Wb, Eb = synth.linear_layer_bf16(T, d_in, d_out, seed=8)
     oXq, oWq = oracle.linear_fwd(Xb, Wb)
     Eq, WTq, ETq, XTq = oracle.linear_bwd_operands(Eb, oXq, oWq, 11, mode)
